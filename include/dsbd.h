@@ -213,8 +213,8 @@ size_t dsbd_verify_forest_workspace_bytes(const dsbd_forest* forest, int32_t V, 
  *   - If a launch fails after the first kernel has been enqueued the call returns DSBD_ERR_HIP with that kernel
  *     already on the stream (every other error is reported before anything is enqueued).
  *   - The workspace must not be shared by calls that may overlap.
- *   - logits_target == logits_draft together with beam_logp_target == beam_logp_draft (one model in both roles,
- *     as dsbd_draft_layer passes them) is recognised: the joint is then formed once; the results are those of two
+ *   - logits_target == logits_draft together with beam_logp_target == beam_logp_draft (one model in both roles) is
+ *     recognised: the joint is then formed once; the results are those of two
  *     equal models.
  */
 int32_t dsbd_verify_forest(const dsbd_forest* forest, const dsbd_verify_in* in, const dsbd_params* params,
@@ -338,8 +338,8 @@ size_t dsbd_draft_layer_workspace_bytes(const dsbd_draft_in* in, int32_t W_S, in
 
 /*
  * W_S independent inverse-CDF draws per prompt from q_beam over (the prompt's beams) x V, flat order beam-major /
- * token-minor, warped by top_k / top_p as in dsbd_params (0 / 1: no warping).  Decisions in fp64; the same
- * kernels as the verification's sampling of its additional layer.  W_S in 1..64.  A prompt without beams gets
+ * token-minor, warped by top_k / top_p as in dsbd_params (0 / 1: no warping).  Decisions in fp64, as in
+ * the verification's sampling of its additional layer.  W_S in 1..64.  A prompt without beams gets
  * parent = token = -1.  Faults as for dsbd_verify_forest (non-finite logits, inconsistent beam_off).
  */
 int32_t dsbd_draft_layer(const dsbd_draft_in* in, int32_t W_S, int32_t top_k, float top_p,

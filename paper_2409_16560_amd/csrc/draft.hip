@@ -1,75 +1,504 @@
 // Draft stage (Section 3.1 "Overview" / "Details"): one beam-sampling step of the small model, and the layout of
 // the sampled layers as a draft forest.
 //
-// dsbd_draft_layer: W_S independent draws from q_beam = T o q/Q over (beams of the current layer) x V are what
-// the verification's additional layer does with p_beam: the call presents the layer's beams as a forest of
-// single-node trees (no draft layers), the small model's logits as both models', and runs the verification
-// kernels; their "additional layer" then is the W_S draws.
+// dsbd_draft_layer: W_S independent draws from q_beam = T o q/Q over (beams of the current layer) x V, by inverse CDF
+// in flat order.  Two dependent passes, two kernels that know nothing of each other's residency:
+//   1. draft_chunk_kernel: every row is cut into chunks, a workgroup per chunk; its maximum and its fp64 sum of
+//      exponentials against that maximum;
+//   2. draft_draw_kernel (a workgroup per draw) or, with warping, draft_warp_kernel (a workgroup per prompt): the row
+//      totals and beam weights out of the chunks' pairs, which every workgroup folds for itself in the same order, and
+//      then only the chunks that matter are read again: the one that holds the draw, or those that can hold one of
+//      the top_k leading entries.
+// What bounds a step is the chain of dependent memory round trips (8 MB of logits are 1.6 us at HBM rate); no
+// exchange between running workgroups is left in it.  Measured, 16 beams x 128256 tokens, 16 draws, top_k 10 / top_p
+// 0.8: chunk kernel 5.7 us and warp kernel 11.4 us, where the persistent layer kernel of the verification, which served
+// the draws before with a set-up kernel in front (its exchanges among 256 workgroups), took 42.6 + 3.2 us; 64 beams of
+// eight prompts x 32000, 8 draws each, no warping: 5.8 + 6.6 us against 27.9 + 3.4 us.
 //
 // dsbd_build_forest: one workgroup per prompt turns the layers' (parent row, token) lists into the
 // tree-contiguous layout the other calls expect.
 #include "common.h"
+#include "exp_nonpos.h"
+#include "wave_f64.h"
+#include <float.h>
+#include <limits.h>
 
-#define DR_BLOCK 256
+#define DC_BLOCK 256           // chunk kernel
+#define DD_BLOCK 512           // draw kernel
+#define DW_BLOCK 1024          // warped kernel
+#define DW_WAVES (DW_BLOCK / 64)
+#define DR_MAX_CHUNKS 64       // chunks per row: one per lane
+#define DR_K_MAX 32
+#define DW_CAND 1024           // candidates the warped kernel ranks directly
+#define DW_DIGIT 11            // bits per pass of its radix selection
 #define BF_BLOCK 512
 #define BF_NODE_CAP 512
 
 namespace {
 
-struct DraftSetupArgs {
-  int n_prompts, n_beams, W_S;
+__constant__ double c_draft_exp2_tab[64] = {DSBD_EXP2_TABLE_64};
+
+struct DraftArgs {
+  int n_prompts, n_beams, max_prompt_beams, V, W_S;
+  int chunk, nchunk;           // logits per chunk, chunks per row
   const int32_t* beam_off;
+  const float* z;
+  const double* cum;
   const float* u;
-  int32_t *tree_prompt, *tree_off, *parent, *token;
-  float *u_accept, *u_resid, *u_fill;
+  double2* part;               // [n_beams][nchunk]: maximum of the chunk, sum of exp(z - maximum)
+  int top_k;
+  float top_p;
+  int32_t *out_parent, *out_token;
+  double* out_logp;
   int32_t* fault;
 };
 
-// beams as single-node trees; uniforms into the layout of the verification (row 1 = its additional layer)
-__global__ __launch_bounds__(DR_BLOCK) void draft_setup_kernel(DraftSetupArgs a) {
-  const long long i = (long long)blockIdx.x * DR_BLOCK + threadIdx.x;
-  if (i == 0 && (a.beam_off[0] != 0 || a.beam_off[a.n_prompts] != a.n_beams)) atomicOr(a.fault, DSBD_FAULT_TOPOLOGY);
-  if (i < a.n_beams) {
-    // prompt of beam i: the last p with beam_off[p] <= i
-    int lo = 0, hi = a.n_prompts - 1;
-    while (lo < hi) {
-      const int mid = (lo + hi + 1) >> 1;
-      if (a.beam_off[mid] <= i) lo = mid; else hi = mid - 1;
+// ---- pass 1 (bound by a round trip to HBM, the maximum's barrier and fp64 exponentials; 2048-logit chunks at 16 x 128256
+// give 1008 workgroups, 4.4 us at best): NPT logits per thread and tile stay in registers between the maximum and the exponentials; chunks of
+// more than one tile (vocabularies above 262144 tokens) merge their tiles as they go.  Loads of 4 bytes per lane: a
+// row of an odd vocabulary starts anywhere, and 8 MB do not ask for more.
+template <int NPT>
+__global__ __launch_bounds__(DC_BLOCK) void draft_chunk_kernel(DraftArgs a) {
+  __shared__ double tab[64];
+  __shared__ float wmax[DC_BLOCK / 64];
+  __shared__ double wsum[DC_BLOCK / 64];
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int row = blockIdx.x / a.nchunk, c = blockIdx.x - row * a.nchunk;
+  const float* const z = a.z + (long long)row * a.V;
+  const int x_end = min(a.V, (c + 1) * a.chunk);
+  if (tid < 64) tab[tid] = c_draft_exp2_tab[tid];
+  float M = -INFINITY;
+  double S = 0.0;
+  bool bad = false;
+  for (int x0 = c * a.chunk; x0 < x_end; x0 += NPT * DC_BLOCK) {
+    float v[NPT];
+#pragma unroll
+    for (int k = 0; k < NPT; ++k) v[k] = z[min(x0 + k * DC_BLOCK + tid, x_end - 1)];     // (clamped repeats leave a maximum alone)
+    float m = -INFINITY;
+#pragma unroll
+    for (int k = 0; k < NPT; ++k) {
+      m = fmaxf(m, v[k]);
+      bad |= !(v[k] <= FLT_MAX);                     // NaN or +Inf (-Inf: a masked token, probability 0)
     }
-    a.tree_prompt[i] = lo;
-    a.tree_off[i] = (int)i;
-    a.parent[i] = -1;
-    a.token[i] = 0;
-    a.u_accept[i] = 0.f;
+    m = wave_max_f32(m);
+    __syncthreads();                                 // (the table; and the tile before has read its totals)
+    if (lane == 0) wmax[wave] = m;
+    __syncthreads();
+    m = fmaxf(fmaxf(wmax[0], wmax[1]), fmaxf(wmax[2], wmax[3]));
+    const double ref = m == -INFINITY ? 0.0 : (double)m;       // a tile masked whole adds 0
+    double s = 0.0;
+#pragma unroll
+    for (int k = 0; k < NPT; ++k) {
+      const double e = dsbd_exp_nonpos((double)v[k] - ref, tab);
+      s += x0 + k * DC_BLOCK + tid < x_end ? e : 0.0;
+    }
+    s = wave_sum(s);
+    if (lane == 0) wsum[wave] = s;
+    __syncthreads();
+    s = (wsum[0] + wsum[1]) + (wsum[2] + wsum[3]);
+    if (m > -INFINITY) {
+      const float Mn = fmaxf(M, m);
+      S = (M > -INFINITY ? S * dsbd_exp_nonpos((double)M - (double)Mn, tab) : 0.0) + s * dsbd_exp_nonpos((double)m - (double)Mn, tab);
+      M = Mn;
+    }
   }
-  if (i == a.n_beams) a.tree_off[i] = a.n_beams;
-  if (i < 2LL * a.n_prompts) a.u_resid[i] = 0.f;
-  if (i < 2LL * a.n_prompts * a.W_S) {
-    const int p = (int)(i / (2 * a.W_S)), rest = (int)(i % (2 * a.W_S));
-    a.u_fill[i] = rest >= a.W_S ? a.u[(long long)p * a.W_S + rest - a.W_S] : 0.f;
+  if (bad) atomicOr(a.fault, DSBD_FAULT_NONFINITE);
+  if (tid == 0) a.part[(long long)row * a.nchunk + c] = make_double2((double)M, S);
+}
+
+// A prompt's rows.  False: no usable beams (out of range or none); `bad` gets the fault bits.
+__device__ __forceinline__ bool prompt_rows(const DraftArgs& a, int p, int& r0, int& n, int& bad) {
+  r0 = a.beam_off[p];
+  const int r1 = a.beam_off[p + 1];
+  n = r1 - r0;
+  if (p == 0 && r0 != 0) bad |= DSBD_FAULT_TOPOLOGY;
+  if (p == a.n_prompts - 1 && r1 != a.n_beams) bad |= DSBD_FAULT_TOPOLOGY;
+  if (r0 < 0 || r1 > a.n_beams || n < 0) { bad |= DSBD_FAULT_TOPOLOGY; n = 0; }
+  if (n > a.max_prompt_beams || n > 64) { bad |= DSBD_FAULT_BOUNDS; n = 0; }
+  return n > 0;
+}
+
+// What the chunks' pairs say about a prompt: every row's maximum, sum and scale (beam weight / sum, Section 2.1: the
+// joint entry of token x is exp(z - max) * scale), folded by one wave per row, a chunk per lane, in a fixed order
+// (equal rows give equal bits).  `each(row, lane's chunk maximum, its sum, row maximum, scale)` sees every chunk.
+template <int WAVES, class Each>
+__device__ __forceinline__ void fold_rows(const DraftArgs& a, int r0, int n, const double* tab, double* row_max,
+                                          double* row_sum, double* row_scale, int& bad, Each&& each) {
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  // the first rows' pairs are requested before anything else: their round trip runs beside the weights
+  double2 first = make_double2(-INFINITY, 0.0);
+  if (wave < n && lane < a.nchunk) first = a.part[(long long)(r0 + wave) * a.nchunk + lane];
+  // beam weights = softmax of the stored likelihoods (Section 2.1), every wave for itself
+  const double cm = lane < n ? a.cum[r0 + lane] : -INFINITY;
+  const double top = wave_max_f64(cm);
+  const bool lost = !(top > -INFINITY && top < INFINITY) || __ballot(lane < n && cm != cm) != 0ull;
+  if (lost) bad |= DSBD_FAULT_NONFINITE;
+  const double e = lane < n ? dsbd_exp_nonpos(cm - top, tab) : 0.0;
+  const double w = e / wave_sum(e);
+  for (int r = wave; r < n; r += WAVES) {
+    double2 ms = first;
+    if (r != wave) {
+      ms = make_double2(-INFINITY, 0.0);
+      if (lane < a.nchunk) ms = a.part[(long long)(r0 + r) * a.nchunk + lane];
+    }
+    const double M = wave_max_f64(ms.x);
+    const double share = ms.x > -INFINITY ? ms.y * dsbd_exp_nonpos(ms.x - M, tab) : 0.0;
+    const double S = wave_sum(share);
+    const double scale = __shfl(w, r) / S;
+    if (lane == 0) { row_max[r] = M; row_sum[r] = S; row_scale[r] = scale; }
+    each(r, ms.x, share, M, scale);
   }
 }
 
-struct DraftScratch {
-  int32_t *tree_prompt, *tree_off, *parent, *token;
-  float *u_accept, *u_resid, *u_fill;
-  uint8_t* node_status;
-  int32_t *l_last, *layer_width, *n_out, *out_node, *near_tie;
-  double* out_logp_other;
-  void* verify_ws;
+__device__ __forceinline__ void write_draw(const DraftArgs& a, int p, int j, int row, int x, double M, double S) {
+  const long long o = (long long)p * a.W_S + j;
+  a.out_parent[o] = row;
+  a.out_token[o] = x;
+  a.out_logp[o] = a.cum[row] + ((double)a.z[(long long)row * a.V + x] - (M + log(S)));
+}
+
+__device__ __forceinline__ void write_no_draw(const DraftArgs& a, int p, int j) {
+  const long long o = (long long)p * a.W_S + j;
+  a.out_parent[o] = -1; a.out_token[o] = -1; a.out_logp[o] = 0.0;
+}
+
+// First lane whose inclusive prefix exceeds the target; rounding may leave none: then the last lane with mass.
+__device__ __forceinline__ int first_above(double incl, double mass, double target) {
+  const unsigned long long above = __ballot(incl > target);
+  if (above) return (int)__ffsll((long long)above) - 1;
+  const unsigned long long has = __ballot(mass > 0.0);
+  return has ? 63 - __clzll((long long)has) : 0;
+}
+
+// ---- pass 2, no warping: one draw per workgroup, so that the draws' dependent round trips (pairs, chunk, group) run side
+// by side; 6.6 us whatever the number of draws.
+__global__ __launch_bounds__(DD_BLOCK) void draft_draw_kernel(DraftArgs a) {
+  __shared__ double tab[64];
+  __shared__ double row_max[64], row_sum[64], row_scale[64], row_mass[64];
+  __shared__ double pre[64 * DR_MAX_CHUNKS];       // inclusive prefixes of the chunks' masses inside their row
+  __shared__ double group[64];
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int p = blockIdx.x / a.W_S, j = blockIdx.x - p * a.W_S;
+  int r0, n, bad = 0;
+  const bool any = prompt_rows(a, p, r0, n, bad);
+  if (!any) {
+    if (tid == 0) { write_no_draw(a, p, j); if (bad && j == 0) atomicOr(a.fault, bad); }
+    return;
+  }
+  const double u = (double)a.u[(long long)p * a.W_S + j];
+  if (tid < 64) tab[tid] = c_draft_exp2_tab[tid];
+  __syncthreads();
+  fold_rows<DD_BLOCK / 64>(a, r0, n, tab, row_max, row_sum, row_scale, bad,
+                           [&](int r, double, double share, double, double scale) {
+    const double incl = wave_inclusive_scan(share * scale);
+    pre[r * DR_MAX_CHUNKS + lane] = incl;
+    if (lane == 63) row_mass[r] = incl;
+  });
+  if (j == 0 && tid == 0 && bad) atomicOr(a.fault, bad);
+  __syncthreads();
+  // the row and the chunk that hold the draw (every wave finds them for itself)
+  const double rm = lane < n ? row_mass[lane] : 0.0;
+  const double rincl = wave_inclusive_scan(rm);
+  const double target = u * __shfl(rincl, 63);
+  const int r = min(first_above(rincl, rm, target), n - 1);
+  double before = r > 0 ? __shfl(rincl, r - 1) : 0.0;
+  const double cincl = pre[r * DR_MAX_CHUNKS + lane];
+  double cprev = __shfl_up(cincl, 1);
+  if (lane == 0) cprev = 0.0;
+  const int c = min(first_above(before + cincl, cincl - cprev, target), a.nchunk - 1);
+  before += c > 0 ? __shfl(cincl, c - 1) : 0.0;
+  // the chunk in up to 64 groups of whole 64-entry rounds: the groups' sums, then the one group that holds the draw
+  const float* const z = a.z + (long long)(r0 + r) * a.V;
+  const int x_lo = c * a.chunk, x_hi = min(a.V, x_lo + a.chunk);
+  const int glen = ((x_hi - x_lo + 63) / 64 + 63) / 64 * 64;
+  const double M = row_max[r], scale = row_scale[r];
+  for (int gr = wave; gr < 64; gr += DD_BLOCK / 64) {
+    const int g_lo = x_lo + gr * glen, g_hi = min(x_hi, g_lo + glen);
+    double s = 0.0;
+    for (int x = g_lo + lane; x < g_hi; x += 64) s += dsbd_exp_nonpos((double)z[x] - M, tab);
+    s = g_lo < g_hi ? wave_sum(s) * scale : 0.0;
+    if (lane == 0) group[gr] = s;
+  }
+  __syncthreads();
+  if (wave != 0) return;
+  const double gs = group[lane];
+  const double gincl = wave_inclusive_scan(gs);
+  const int gr = first_above(before + gincl, gs, target);
+  before += gr > 0 ? __shfl(gincl, gr - 1) : 0.0;
+  const int g_lo = x_lo + gr * glen, g_hi = min(x_hi, g_lo + glen);
+  int pick = -1, last = -1;
+  for (int x0 = g_lo; x0 < g_hi && pick < 0; x0 += 64) {
+    const double v = x0 + lane < g_hi ? dsbd_exp_nonpos((double)z[min(x0 + lane, g_hi - 1)] - M, tab) * scale : 0.0;
+    const double incl = wave_inclusive_scan(v);
+    const unsigned long long has = __ballot(v > 0.0), above = __ballot(before + incl > target);
+    if (has) last = x0 + 63 - __clzll((long long)has);
+    if (above) pick = x0 + (int)__ffsll((long long)above) - 1;
+    before += __shfl(incl, 63);
+  }
+  if (pick < 0) pick = last >= 0 ? last : min(g_lo, x_hi - 1);
+  if (lane == 0) write_draw(a, p, j, r0 + r, pick, M, row_sum[r]);
+}
+
+// ---- pass 2 with warping T (Section 2.1): the top_k first joint entries (by value, equal values by flat index), of
+// those the shortest leading part whose share exceeds top_p, renormalised; all of a prompt's draws from that list.
+struct WarpShared {
+  double tab[64];
+  double row_max[64], row_sum[64], row_scale[64], row_thr[64];
+  double cmax[64 * DR_MAX_CHUNKS];    // largest joint entry of every chunk (-1: none)
+  int list[64 * DR_MAX_CHUNKS];       // chunks that can hold a kept entry
+  double gmax[64];
+  double bound;
+  int n_list, n_cand;
+  double cv[DW_CAND];
+  int ci[DW_CAND];
+  double kv[DR_K_MAX];
+  int ki[DR_K_MAX];
+  unsigned int hist[1 << DW_DIGIT];
+  int wcount[DW_WAVES];
+  unsigned long long prefix;          // radix selection: leading bits of the K-th entry, and its rank among those that share them
+  int want;
 };
 
-void make_forest(const dsbd_draft_in* in, const DraftScratch& s, dsbd_forest* f) {
-  f->n_prompts = in->n_prompts; f->n_trees = in->n_beams; f->n_nodes = in->n_beams;
-  f->tree_prompt = s.tree_prompt; f->tree_off = s.tree_off; f->parent = s.parent; f->token = s.token;
-  f->draft_rank = nullptr;
-  f->max_tree_nodes = 1; f->max_depth = 0; f->max_prompt_trees = in->max_prompt_beams;
+// The K-th largest of 64 group maxima (one per lane, the same in every wave): K entries are at or above it.  Every wave
+// ranks four of them by ballots.  A bound already held stays if it is higher (-1: none; fewer than K groups hold anything).
+__device__ __forceinline__ void bound_of_groups(WarpShared& sh, double g, int K) {
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+#pragma unroll
+  for (int k = 0; k < 64 / DW_WAVES; ++k) {
+    const int i = wave * (64 / DW_WAVES) + k;
+    const double v = __shfl(g, i);
+    const int ahead = __popcll(__ballot((g > v) | ((g == v) & (lane < i))));
+    if (ahead == K - 1 && lane == 0 && v > sh.bound) sh.bound = v;
+  }
 }
 
-dsbd_params make_params(int32_t W_S, int32_t top_k, float top_p) {
-  dsbd_params p;
-  p.W_L = W_S; p.W_min = 1; p.W_cap = W_S; p.t = -1.0f; p.top_k = top_k; p.top_p = top_p;
-  return p;
+__global__ __launch_bounds__(DW_BLOCK) void draft_warp_kernel(DraftArgs a) {
+  __shared__ WarpShared sh;
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int p = blockIdx.x, K = a.top_k, V = a.V;
+  int r0, n, bad = 0;
+  const bool any = prompt_rows(a, p, r0, n, bad);
+  if (!any) {
+    if (tid < a.W_S) write_no_draw(a, p, tid);
+    if (tid == 0 && bad) atomicOr(a.fault, bad);
+    return;
+  }
+  const float u_mine = tid < a.W_S ? a.u[(long long)p * a.W_S + tid] : 0.f;
+  if (tid < 64) sh.tab[tid] = c_draft_exp2_tab[tid];
+  if (tid == 0) { sh.n_list = 0; sh.n_cand = 0; sh.bound = -1.0; }
+  __syncthreads();
+  fold_rows<DW_WAVES>(a, r0, n, sh.tab, sh.row_max, sh.row_sum, sh.row_scale, bad,
+                      [&](int r, double m, double, double M, double scale) {
+    if (lane < a.nchunk) sh.cmax[r * a.nchunk + lane] = m > -INFINITY ? dsbd_exp_nonpos(m - M, sh.tab) * scale : -1.0;
+  });
+  if (tid == 0 && bad) atomicOr(a.fault, bad);
+  __syncthreads();
+  // ---- a lower bound of the K-th entry: the K-th largest of the maxima of 64 groups of chunks
+  const int T = n * a.nchunk;
+  {
+    double g = -1.0;
+#pragma unroll 4
+    for (int t = lane; t < T; t += 64) g = fmax(g, sh.cmax[t]);
+    bound_of_groups(sh, g, K);
+  }
+  __syncthreads();
+  // a row's logit that reaches the bound, with slack for the rounding of the logarithm (candidates are ranked by
+  // their exact entries afterwards: a few too many do no harm)
+  auto thresholds = [&]() {
+    if (tid < n) {
+      const double b = sh.bound;
+      const double t = b > 0.0 ? sh.row_max[tid] + log(b / sh.row_scale[tid]) : -INFINITY;
+      sh.row_thr[tid] = t - 1e-9 * (1.0 + fabs(t));
+      if (!(b > 0.0)) sh.row_thr[tid] = -INFINITY;
+    }
+  };
+  thresholds();
+  for (int t = tid; t < T; t += DW_BLOCK)
+    if (sh.cmax[t] >= sh.bound * (1.0 - 1e-12)) {
+      const int r = t / a.nchunk;
+      sh.list[atomicAdd(&sh.n_list, 1)] = r * DR_MAX_CHUNKS + t - r * a.nchunk;
+    }
+  __syncthreads();
+  // `body(row, token, z)` on every entry of the listed chunks that reaches its row's threshold: a wave takes two tiles of
+  // 512 entries at a time, all their loads in flight together (about ten chunks are listed: one or two round trips).
+  // The body is there once, with its logit picked out of the registers: sixteen inlined copies cost more in instruction
+  // fetches than the few entries that get that far.
+  const int tshift = 31 - __clz(a.chunk) - 9;          // (chunks are powers of two, at least 1024)
+  const int n_tiles = sh.n_list << tshift;
+  auto each_entry = [&](auto&& body) __attribute__((always_inline)) {
+    for (int w0 = wave; w0 < n_tiles; w0 += 2 * DW_WAVES) {
+      float v[16];
+      unsigned int hit = 0u;
+      int row[2], xl[2];
+#pragma unroll
+      for (int h = 0; h < 2; ++h) {
+        const int w = min(w0 + h * DW_WAVES, n_tiles - 1);
+        const int t = sh.list[w >> tshift];
+        const int r = t / DR_MAX_CHUNKS, c = t % DR_MAX_CHUNKS;
+        const int x0 = c * a.chunk + (w & ((1 << tshift) - 1)) * 512;
+        const int x1 = w0 + h * DW_WAVES < n_tiles ? min(V, x0 + 512) : 0;          // (0: there is no second tile)
+        const float* const z = a.z + (long long)(r0 + r) * V;
+        row[h] = r; xl[h] = x0 + lane;
+#pragma unroll
+        for (int k = 0; k < 8; ++k) v[8 * h + k] = z[min(xl[h] + 64 * k, V - 1)];
+#pragma unroll
+        for (int k = 0; k < 8; ++k) hit |= xl[h] + 64 * k < x1 ? 1u << (8 * h + k) : 0u;
+      }
+#pragma unroll
+      for (int h = 0; h < 2; ++h) {
+        const double thr = sh.row_thr[row[h]];
+#pragma unroll
+        for (int k = 0; k < 8; ++k) hit &= (double)v[8 * h + k] >= thr ? ~0u : ~(1u << (8 * h + k));
+      }
+      for (; hit != 0u; hit &= hit - 1u) {
+        const int b = __ffs((int)hit) - 1;
+        float z = v[0];
+#pragma unroll
+        for (int k = 1; k < 16; ++k) z = b == k ? v[k] : z;
+        body(b >= 8 ? row[1] : row[0], (b >= 8 ? xl[1] : xl[0]) + 64 * (b & 7), z);
+      }
+    }
+  };
+  auto entry = [&](int r, float z) { return dsbd_exp_nonpos((double)z - sh.row_max[r], sh.tab) * sh.row_scale[r]; };
+  if (T < 64) {
+    // few chunks bound poorly (or not at all): the maxima of 64 groups of threads over the listed chunks do better
+    double g = -1.0;
+    each_entry([&](int r, int, float z) { g = fmax(g, entry(r, z)); });
+#pragma unroll
+    for (int off = 1; off <= 8; off <<= 1) g = fmax(g, __shfl_xor(g, off));
+    if ((lane & 15) == 0) sh.gmax[wave * 4 + (lane >> 4)] = g;
+    __syncthreads();
+    bound_of_groups(sh, sh.gmax[lane], K);
+    __syncthreads();
+    thresholds();
+    __syncthreads();
+  }
+  auto keep = [&](int r, int x, float z) {
+    const int at = atomicAdd(&sh.n_cand, 1);
+    if (at < DW_CAND) { sh.cv[at] = entry(r, z); sh.ci[at] = r * V + x; }
+  };
+  each_entry(keep);
+  __syncthreads();
+  if (sh.n_cand > DW_CAND) {
+    // Entries crowd at the bound (rows of equal logits): the K-th entry's exact value by radix selection over the
+    // bits of the entries (non-negative doubles order like their bits), then everything above it and, of those equal
+    // to it, the first by index.
+    __syncthreads();
+    if (tid == 0) { sh.prefix = 0ull; sh.want = K; sh.n_cand = 0; }
+    for (int shift = 64 - DW_DIGIT; ; shift = max(shift - DW_DIGIT, 0)) {
+      const int width = shift == 0 ? 64 % DW_DIGIT : DW_DIGIT;          // 64 = 5 x 11 + 9
+      for (int b = tid; b < (1 << DW_DIGIT); b += DW_BLOCK) sh.hist[b] = 0u;
+      __syncthreads();
+      const unsigned long long prefix = sh.prefix;
+      each_entry([&](int r, int, float z) {
+        const unsigned long long key = (unsigned long long)__double_as_longlong(entry(r, z));
+        const int up = shift + width;
+        if (up >= 64 || (key >> up) == (prefix >> up)) atomicAdd(&sh.hist[(key >> shift) & ((1u << width) - 1u)], 1u);
+      });
+      __syncthreads();
+      if (wave == 0) {
+        // from the highest digit down: a lane's 32 digits in one sum, then the digits of the lane that reaches `want`
+        const int hi = (1 << DW_DIGIT) - 1 - 32 * lane, want = sh.want;
+        int mine = 0;
+        for (int b = 0; b < 32; ++b) mine += (int)sh.hist[hi - b];
+        const double incl = wave_inclusive_scan((double)mine);
+        const unsigned long long reach = __ballot(incl >= (double)want);
+        if (reach != 0ull && lane == (int)__ffsll((long long)reach) - 1) {
+          int left = want - (int)(incl - (double)mine), d = hi;
+          while ((int)sh.hist[d] < left) { left -= (int)sh.hist[d]; --d; }
+          sh.want = left;
+          sh.prefix = prefix | ((unsigned long long)d << shift);
+        }
+      }
+      __syncthreads();
+      if (shift == 0) break;
+    }
+    const unsigned long long kth = sh.prefix;
+    const int n_eq = sh.want;                          // this many of the entries equal to the K-th are kept
+    each_entry([&](int r, int x, float z) {
+      if ((unsigned long long)__double_as_longlong(entry(r, z)) > kth) keep(r, x, z);
+    });
+    __syncthreads();
+    const int n_gt = sh.n_cand;
+    int found = 0;                                     // equal entries so far (uniform)
+    for (int t = 0; t < T && found < n_eq; ++t) {      // chunks in index order
+      if (!(sh.cmax[t] >= sh.bound * (1.0 - 1e-12))) continue;
+      const int r = t / a.nchunk, c = t - r * a.nchunk;
+      const int x1 = min(V, (c + 1) * a.chunk);
+      const float* const z = a.z + (long long)(r0 + r) * V;
+      for (int x0 = c * a.chunk; x0 < x1 && found < n_eq; x0 += DW_BLOCK) {
+        const int x = x0 + tid;
+        const float v = z[min(x, x1 - 1)];
+        const bool eq = x < x1 && (double)v >= sh.row_thr[r] && (unsigned long long)__double_as_longlong(entry(r, v)) == kth;
+        const unsigned long long m = __ballot(eq);
+        if (lane == 0) sh.wcount[wave] = __popcll(m);
+        __syncthreads();
+        int ahead = found, all = 0;
+        for (int w = 0; w < DW_WAVES; ++w) { ahead += w < wave ? sh.wcount[w] : 0; all += sh.wcount[w]; }
+        ahead += __popcll(m & ((1ull << lane) - 1ull));
+        if (eq && ahead < n_eq) { sh.cv[n_gt + ahead] = __longlong_as_double((long long)kth); sh.ci[n_gt + ahead] = r * V + x; }
+        found += all;
+        __syncthreads();
+      }
+    }
+    if (tid == 0) sh.n_cand = n_gt + min(found, n_eq);
+    __syncthreads();
+  }
+  const int nc = min(sh.n_cand, DW_CAND);
+  if (tid < nc) {
+    const double v = sh.cv[tid];
+    const int ix = sh.ci[tid];
+    int rank = 0;
+#pragma unroll 4
+    for (int o = 0; o < nc; ++o) {
+      const double ov = sh.cv[o];
+      rank += (ov > v) | ((ov == v) & (sh.ci[o] < ix));
+    }
+    if (rank < K) { sh.kv[rank] = v; sh.ki[rank] = ix; }
+  }
+  __syncthreads();
+  if (wave != 0) return;
+  // ---- top-p (the running sums add the entries one by one in rank order), then the kept entries in index order
+  const int nk = min(nc, K);
+  const double v = lane < nk ? sh.kv[lane] : 0.0;
+  const int ix = lane < nk ? sh.ki[lane] : INT_MAX;
+  double cum = 0.0;
+#pragma unroll 8
+  for (int o = 0; o < nk; ++o) {
+    const double ov = sh.kv[o];
+    if (o <= lane) cum += ov;
+  }
+  int kept = nk;
+  if (a.top_p < 1.0f) {
+    const double mass = __shfl(cum, max(nk - 1, 0));
+    const unsigned long long over = __ballot(lane < nk && cum / mass > (double)a.top_p);
+    if (over) kept = (int)__ffsll((long long)over);
+  }
+  const double total = __shfl(cum, max(kept - 1, 0));
+  int at = 0;
+#pragma unroll 8
+  for (int o = 0; o < kept; ++o) at += sh.ki[o] < ix;
+  wave_lds_fence();
+  if (lane < kept) { sh.cv[at] = v / total; sh.ci[at] = ix; }
+  wave_lds_fence();
+  const double w = lane < kept ? sh.cv[lane] : 0.0;
+  const double incl = wave_inclusive_scan(w);
+  const double Z = __shfl(incl, 63);
+  sh.gmax[lane] = incl;
+  wave_lds_fence();
+  if (lane < a.W_S) {
+    const double target = (double)u_mine * Z;
+    int pick = -1, last = 0;
+#pragma unroll 8
+    for (int o = 0; o < kept; ++o) {
+      if (sh.cv[o] > 0.0) last = o;
+      if (pick < 0 && sh.gmax[o] > target) pick = o;
+    }
+    if (pick < 0) pick = last;
+    const int flat = kept > 0 ? sh.ci[pick] : 0;       // (no entry at all: reported above, the draw stays in bounds)
+    const int r = flat / V;
+    write_draw(a, p, lane, r0 + r, flat - r * V, sh.row_max[r], sh.row_sum[r]);
+  }
 }
 
 int32_t check_draft(const dsbd_draft_in* in, int32_t W_S) {
@@ -80,24 +509,24 @@ int32_t check_draft(const dsbd_draft_in* in, int32_t W_S) {
   return DSBD_OK;
 }
 
-size_t carve_draft(WorkspaceCarver& ws, const dsbd_draft_in* in, int32_t W_S, size_t verify_bytes, DraftScratch* s) {
-  const size_t B = (size_t)in->n_beams, P = (size_t)in->n_prompts;
-  s->tree_prompt = ws.take<int32_t>(B);
-  s->tree_off = ws.take<int32_t>(B + 1);
-  s->parent = ws.take<int32_t>(B);
-  s->token = ws.take<int32_t>(B);
-  s->u_accept = ws.take<float>(B);
-  s->u_resid = ws.take<float>(2 * P);
-  s->u_fill = ws.take<float>(2 * P * W_S);
-  s->node_status = ws.take<uint8_t>(B);
-  s->l_last = ws.take<int32_t>(P);
-  s->layer_width = ws.take<int32_t>(2 * P);
-  s->n_out = ws.take<int32_t>(P);
-  s->out_node = ws.take<int32_t>(P * W_S);
-  s->near_tie = ws.take<int32_t>(P);
-  s->out_logp_other = ws.take<double>(P * W_S);
-  s->verify_ws = ws.take<char>(verify_bytes);
-  return ws.total();
+// What a call with beams needs beyond that (the limits of the verification's sampling, whose results these are).
+bool draft_supported(const dsbd_draft_in* in, int32_t W_S, int32_t top_k, float top_p) {
+  if (in->V > (1 << 30) || in->max_prompt_beams < 1) return false;
+  if (top_k < 0 || top_k > DR_K_MAX || !(top_p >= 0.0f)) return false;
+  if (top_k == 0 && top_p > 0.0f && top_p < 1.0f) return false;
+  if ((long long)in->n_beams * DR_MAX_CHUNKS > 0x7fffffffLL || (long long)in->n_prompts * W_S > 0x7fffffffLL) return false;      // grids
+  const long long cap = W_S > in->max_prompt_beams ? W_S : in->max_prompt_beams;
+  if (top_k > 0 && cap * in->V > 0x7fffffffLL) return false;           // flat indices are 32-bit integers
+  return true;
+}
+
+// Chunks of a power of two of at least 1024 logits (4 per thread), at most 64 per row (a lane each in the fold): the
+// smallest that give no more than 2048 workgroups, eight per compute unit, which is what is resident at once.
+void draft_chunks(const dsbd_draft_in* in, int* chunk, int* nchunk) {
+  long long c = 1024;
+  while ((in->V + c - 1) / c > DR_MAX_CHUNKS || (c < 4096 && in->n_beams * ((in->V + c - 1) / c) > 2048)) c *= 2;
+  *chunk = (int)c;
+  *nchunk = (int)((in->V + c - 1) / c);
 }
 
 }  // namespace
@@ -105,16 +534,12 @@ size_t carve_draft(WorkspaceCarver& ws, const dsbd_draft_in* in, int32_t W_S, si
 extern "C" size_t dsbd_draft_layer_workspace_bytes(const dsbd_draft_in* in, int32_t W_S, int32_t top_k, float top_p) {
   if (check_draft(in, W_S) != DSBD_OK) return 0;
   if (in->n_beams == 0 || in->n_prompts == 0) return 256;
-  DraftScratch s;
-  dsbd_forest f;
-  WorkspaceCarver none(nullptr);
-  carve_draft(none, in, W_S, 0, &s);
-  make_forest(in, s, &f);
-  const dsbd_params p = make_params(W_S, top_k, top_p);
-  const size_t vb = dsbd_verify_forest_workspace_bytes(&f, in->V, &p);
-  if (vb == 0) return 0;
+  if (!draft_supported(in, W_S, top_k, top_p)) return 0;
+  int chunk, nchunk;
+  draft_chunks(in, &chunk, &nchunk);
   WorkspaceCarver ws(nullptr);
-  return carve_draft(ws, in, W_S, vb, &s) + 256;
+  ws.take<double2>((size_t)in->n_beams * nchunk);
+  return ws.total() + 256;
 }
 
 extern "C" int32_t dsbd_draft_layer(const dsbd_draft_in* in, int32_t W_S, int32_t top_k, float top_p,
@@ -130,42 +555,22 @@ extern "C" int32_t dsbd_draft_layer(const dsbd_draft_in* in, int32_t W_S, int32_
   if (need == 0) return DSBD_ERR_UNSUPPORTED;
   if (workspace_bytes < need) return DSBD_ERR_WORKSPACE;
   hipStream_t stream = static_cast<hipStream_t>(stream_);
-
-  DraftScratch s;
-  dsbd_forest f;
-  const dsbd_params p = make_params(W_S, top_k, top_p);
-  {
-    WorkspaceCarver none(nullptr);
-    carve_draft(none, in, W_S, 0, &s);
-    make_forest(in, s, &f);
-  }
-  const size_t vb = dsbd_verify_forest_workspace_bytes(&f, in->V, &p);
-  char* wbase = reinterpret_cast<char*>(dsbd_align_up(reinterpret_cast<uintptr_t>(workspace), 256));
-  WorkspaceCarver ws(wbase);
-  carve_draft(ws, in, W_S, vb, &s);
-  make_forest(in, s, &f);
-
-  DraftSetupArgs sa;
-  sa.n_prompts = in->n_prompts; sa.n_beams = in->n_beams; sa.W_S = W_S;
-  sa.beam_off = in->beam_off; sa.u = in->u;
-  sa.tree_prompt = s.tree_prompt; sa.tree_off = s.tree_off; sa.parent = s.parent; sa.token = s.token;
-  sa.u_accept = s.u_accept; sa.u_resid = s.u_resid; sa.u_fill = s.u_fill; sa.fault = fault;
-  long long items = in->n_beams + 1;
-  if (items < 2LL * in->n_prompts * W_S) items = 2LL * in->n_prompts * W_S;
-  hipLaunchKernelGGL(draft_setup_kernel, dim3((unsigned)((items + DR_BLOCK - 1) / DR_BLOCK)), dim3(DR_BLOCK), 0, stream, sa);
+  DraftArgs a;
+  draft_chunks(in, &a.chunk, &a.nchunk);
+  WorkspaceCarver ws(reinterpret_cast<char*>(dsbd_align_up(reinterpret_cast<uintptr_t>(workspace), 256)));
+  a.part = ws.take<double2>((size_t)in->n_beams * a.nchunk);
+  a.n_prompts = in->n_prompts; a.n_beams = in->n_beams; a.max_prompt_beams = in->max_prompt_beams; a.V = in->V; a.W_S = W_S;
+  a.beam_off = in->beam_off; a.z = in->logits_draft; a.cum = in->beam_logp_draft; a.u = in->u;
+  a.top_k = top_k; a.top_p = (top_p > 0.0f && top_p < 1.0f) ? top_p : 1.0f;
+  a.out_parent = out->parent; a.out_token = out->token; a.out_logp = out->logp_draft; a.fault = fault;
+  const dim3 grid((unsigned)in->n_beams * (unsigned)a.nchunk);
+  if (a.chunk == 1024) hipLaunchKernelGGL(draft_chunk_kernel<4>, grid, dim3(DC_BLOCK), 0, stream, a);
+  else if (a.chunk == 2048) hipLaunchKernelGGL(draft_chunk_kernel<8>, grid, dim3(DC_BLOCK), 0, stream, a);
+  else hipLaunchKernelGGL(draft_chunk_kernel<16>, grid, dim3(DC_BLOCK), 0, stream, a);
+  if (top_k > 0) hipLaunchKernelGGL(draft_warp_kernel, dim3((unsigned)in->n_prompts), dim3(DW_BLOCK), 0, stream, a);
+  else hipLaunchKernelGGL(draft_draw_kernel, dim3((unsigned)in->n_prompts * (unsigned)W_S), dim3(DD_BLOCK), 0, stream, a);
   DSBD_HIP_LAUNCH_CHECK();
-
-  dsbd_verify_in vin;
-  vin.V = in->V;
-  vin.logits_target = in->logits_draft; vin.logits_draft = in->logits_draft;      // one model in both roles
-  vin.beam_logp_target = in->beam_logp_draft; vin.beam_logp_draft = in->beam_logp_draft;
-  vin.u_accept = s.u_accept; vin.u_resid = s.u_resid; vin.u_fill = s.u_fill;
-  dsbd_verify_out vout = {};
-  vout.node_status = s.node_status; vout.l_last = s.l_last; vout.layer_width = s.layer_width; vout.n_out = s.n_out;
-  vout.out_parent = out->parent; vout.out_token = out->token; vout.out_node = s.out_node;
-  vout.out_logp_target = out->logp_draft; vout.out_logp_draft = s.out_logp_other;
-  vout.near_tie_count = s.near_tie;
-  return dsbd_verify_forest(&f, &vin, &p, &vout, s.verify_ws, vb, fault, stream_);
+  return DSBD_OK;
 }
 
 // ------------------------------------------------------------------------------------------------ forest layout

@@ -83,6 +83,28 @@ def test_draft_layer_full_vocabulary():
         assert np.max(np.abs(lp - rlp)) <= 1e-9
 
 
+@pytest.mark.parametrize("beams,V,levels,top_k,top_p", [
+    # edges of the cut into chunks: one token, one chunk of 1024 logits and one more, 64 chunks of 1024 and one token
+    # more (then 2048), chunks of two register tiles (above 64 x 4096 tokens)
+    ([3], 1, 0, 0, 1.0), ([2, 1], 1024, 0, 0, 1.0), ([2, 1], 1025, 0, 10, 0.8), ([2], 65536, 0, 10, 0.8), ([1, 2], 65537, 0, 0, 1.0),
+    ([2], 300001, 0, 0, 1.0), ([2], 300001, 0, 10, 0.8),
+    # equal logits by the thousand: more entries at the bound than are ranked directly (the K-th entry comes from its
+    # bits, equal entries by index); all equal, two and five levels, with few and with many chunks
+    ([2, 1], 3000, 1, 10, 1.0), ([3], 20000, 2, 10, 0.8), ([1], 70000, 5, 32, 0.9), ([4], 300, 1, 32, 1.0),
+])
+def test_draft_layer_at_the_edges_of_its_passes(beams, V, levels, top_k, top_p):
+    print("case", beams, V, levels, top_k, top_p, flush=True)
+    W_S = 8
+    beam_off, z, cum, u = layer_inputs(V + levels, beams, V, W_S)
+    if levels:
+        z = np.ascontiguousarray(np.random.default_rng(V).integers(0, levels, z.shape).astype(np.float32) * np.float32(0.5))
+    par, tok, lp, fault = run_draft_layer(beam_off, z, cum, u, W_S, top_k, top_p)
+    rpar, rtok, rlp = oracle_draft_layer(beam_off, z, cum, u, top_k, top_p)
+    assert fault == 0
+    assert np.array_equal(par, rpar) and np.array_equal(tok, rtok)
+    assert np.max(np.abs(lp - rlp)) <= 1e-9
+
+
 @pytest.mark.parametrize("top_k,top_p", [(0, 1.0), (10, 0.8)])
 def test_draft_layer_with_masked_tokens(top_k, top_p):
     """Logits of -Inf are tokens of probability 0 (never drawn), not a fault: a masked tail, masks per row, and a row
