@@ -17,8 +17,8 @@
  *   - Every array argument is a DEVICE pointer owned by the caller unless marked "host".
  *     The structs themselves are host memory, read during the call only.
  *   - The library allocates no device memory and keeps no state between calls (apart from the measurement
- *     hook at the end of this header, the tuning knobs it reads once, and one extra stream with two events per
- *     device that dsbd_verify_forest creates at its first call or dsbd_init() creates).  Scratch memory comes
+ *     hook at the end of this header, the tuning knobs it reads once, and one event per device that
+ *     dsbd_verify_forest creates at its first call or dsbd_init() creates).  Scratch memory comes
  *     from the caller's `workspace` (device, 256-byte aligned), at least as large as the
  *     matching dsbd_*_workspace_bytes() says.  Its contents need not be initialised.
  *   - `stream` is a hipStream_t passed as void*.  Calls only enqueue work; outputs are valid
@@ -192,22 +192,19 @@ size_t dsbd_verify_forest_workspace_bytes(const dsbd_forest* forest, int32_t V, 
  *   - Limits: at most 64 input beams, 512 forest nodes and W_cap <= 64 per prompt.  Any number of prompts: when
  *     they need more workgroups than the device holds at once, the layer kernel is launched for one group of
  *     prompts after the other (Algorithm 1 runs per prompt).
- *   - Two kernels run side by side: the layer kernel on `stream`, and the pass over all logits that produces the
- *     per-node outputs (lse_*, node_logp_*) on a second stream that the library creates once per device; the second
- *     stream starts after everything `stream` holds at the time of the call and `stream` continues only when both
- *     kernels are done, so the caller sees ordinary stream semantics.  If all four per-node outputs are NULL the
- *     pass is left out; NaN and +Inf logits are then reported only for the rows of beams that enter a layer, and
- *     the two misuses of -Inf (a row of nothing else, a masked drafted token) not at all.
+ *   - One kernel: its first workgroups walk the layers, those behind them produce the per-node outputs (lse_*,
+ *     node_logp_*), one row of logits each, on the compute units the layers leave free.  If all four per-node outputs are
+ *     NULL that part is left out; NaN and +Inf logits are then reported only for the rows of beams that enter a layer,
+ *     and the two misuses of -Inf (a row of nothing else, a masked drafted token) not at all.
  *   - The layer kernel's workgroups wait for each other, so it needs its share of the device while it runs.
  *     Verifications on DIFFERENT streams are kept apart by the library: the first call that arrives on another
  *     stream than the one before waits for the device to drain (once per device and process), and from then on
  *     every layer kernel is ordered behind the previous one by an event (6 us per call, which callers that stay on
- *     one stream never pay).  A stream under graph capture: the call can be recorded (its second stream joins the
- *     capture through the fork and join events; a one-thread kernel in front of the layer kernel counts the replays in
- *     the workspace, so that every replay's exchange slots are told apart from the previous one's, which is why the
+ *     one stream never pay).  A stream under graph capture: the call can be recorded (a one-thread kernel
+ *     in front of the layer kernel counts the replays in the workspace, so that every replay's exchange slots are told apart from the previous one's, which is why the
  *     workspace must be the same memory at every replay), but it records nothing outside the capture: keep replays
  *     apart from other verifications yourself.  Also not covered: dsbd_verify_forest_static() before the
- *     library's second stream exists, and other processes on the device.  Foreign kernels that occupy compute
+ *     library's event exists, and other processes on the device.  Foreign kernels that occupy compute
  *     units only delay the layer kernel; every wait in it is bounded (3 s by default) and ends in
  *     DSBD_FAULT_SYNC_TIMEOUT with unusable outputs, never in a hang.
  *   - If a launch fails after the first kernel has been enqueued the call returns DSBD_ERR_HIP with that kernel
@@ -227,13 +224,13 @@ int32_t dsbd_verify_forest(const dsbd_forest* forest, const dsbd_verify_in* in, 
  * the workspace: it lives in a device array of dsbd_verify_forest_static_capacity() bytes (32 MiB) that is part of
  * the library's image (every GPU the library runs on holds its own copy until the process ends).  A problem whose
  * dsbd_verify_forest_workspace_bytes() exceeds the capacity is refused with DSBD_ERR_WORKSPACE and nothing is
- * enqueued.  The call allocates nothing: no device memory, no stream, no event; the statistics pass runs beside the
- * layer kernel only if an earlier ordinary call or dsbd_init() has already created the library's second stream on
- * this device, otherwise in front of it on the caller's stream.  Nothing in the array has to be cleared between
+ * enqueued.  The call allocates nothing: no device memory, no stream, no event; it takes part in the ordering of
+ * verifications on different streams only if an earlier ordinary call or dsbd_init() has already created the library's
+ * event on this device.  Nothing in the array has to be cleared between
  * calls (exchange slots are told apart by a per-launch tag).  All calls on one GPU share that GPU's array: calls
  * that overlap in time on one GPU (different streams, or host threads) race and give undefined results.
  *
- * dsbd_init() (optional): resolves the array's address and creates the second stream for the CURRENT device, so
+ * dsbd_init() (optional): resolves the array's address and creates the event for the CURRENT device, so
  * that the first call after it allocates nothing either.  Returns DSBD_OK or DSBD_ERR_HIP.
  */
 int32_t dsbd_init(void);
@@ -393,8 +390,8 @@ void dsbd_reload_knobs(void);
  * frees the events.  Not thread-safe; meant for benchmarks.
  */
 #define DSBD_KERNEL_ATTENTION     1   /* forest attention main kernel (streams K/V)            */
-#define DSBD_KERNEL_VOCAB_STATS   2   /* per-node vocabulary softmax statistics (streams logits) */
-#define DSBD_KERNEL_VERIFY_LAYERS 3   /* persistent layer-by-layer verification                */
+#define DSBD_KERNEL_VOCAB_STATS   2   /* no kernel of its own any more: records nothing          */
+#define DSBD_KERNEL_VERIFY_LAYERS 3   /* layer-by-layer verification, per-node statistics       */
 #define DSBD_KERNEL_KV_COMMIT     4   /* cache update (copies the surviving caches)             */
 int32_t dsbd_timing_enable(int32_t kernel, int32_t capacity);
 int32_t dsbd_timing_collect(float* ms, int32_t max_n);

@@ -376,7 +376,7 @@ def dsbd_verify_forest_select(forest: Forest, logits_target, logits_draft, beam_
 
 
 def dsbd_init():
-    """Optional set-up for the current device (second stream, address of the static scratch array)."""
+    """Optional set-up for the current device (ordering event, address of the static scratch array)."""
     _check(load_library().dsbd_init(), "dsbd_init")
 
 

@@ -18,10 +18,8 @@ SOURCES = ["attention.hip", "verify.hip", "select.hip", "commit.hip", "draft.hip
 FILE_FLAGS = {"attention.hip": os.environ.get("DSBD_ATTN_FLAGS", "-fno-honor-nans").split(),
               "verify.hip": os.environ.get("DSBD_VERIFY_FLAGS", "-mllvm -disable-machine-licm").split()
               + ["-Rpass-analysis=kernel-resource-usage"]}
-# The statistics pass runs beside the layer kernel, one workgroup (a wave of 32 registers per SIMD) per compute unit:
-# that needs the layer kernel's two waves per SIMD to leave 32 of the 512 registers of a SIMD lane free (handed out in
-# eights): at most 240 each.
-LAYER_KERNEL_VGPR_BUDGET = 240
+# two waves per SIMD (a workgroup of 512 threads per compute unit) share its 512 registers
+LAYER_KERNEL_VGPR_BUDGET = 256
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-fgpu-rdc-", "-Xclang", "-target-feature", "-Xclang",
          "-packed-fp32-ops", "-I" + os.path.join(ROOT, "include"), "-I" + CSRC]
 
@@ -34,8 +32,7 @@ def hipcc():
 
 
 def check_registers(report, verbose):
-    """Reads the compiler's resource report: warns when a layer kernel outgrows the register budget that lets the
-    statistics pass share its compute units, or spills.  Returns what is left of the compiler's output."""
+    """Reads the compiler's resource report: warns when a layer kernel outgrows its register budget or spills.  Returns what is left of the compiler's output."""
     import re
     rest, name = [], None
     for line in report.splitlines():
@@ -51,8 +48,7 @@ def check_registers(report, verbose):
             if verbose:
                 print("%s: %s vector registers" % (name, m.group(1)))
             if int(m.group(1)) > LAYER_KERNEL_VGPR_BUDGET:
-                print("WARNING: %s uses %s vector registers (budget %d): the statistics pass will no longer fit beside it"
-                      % (name, m.group(1), LAYER_KERNEL_VGPR_BUDGET))
+                print("WARNING: %s uses %s vector registers (budget %d)" % (name, m.group(1), LAYER_KERNEL_VGPR_BUDGET))
         m = re.search(r"ScratchSize \[bytes/lane\]: (\d+)", line)
         if m and name and "verify_layers_kernel" in name and int(m.group(1)) > 0:
             print("WARNING: %s spills %s bytes per lane" % (name, m.group(1)))

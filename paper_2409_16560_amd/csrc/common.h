@@ -36,19 +36,15 @@ struct DsbdKnobs {
   bool attn_waves8;            // DSBD_ATTN_WAVES8: 8 waves x 16 rows in the shared-tile kernel
   bool attn_staged;            // DSBD_ATTN_STAGED: the register-staged tile kernel also for head size 128
   bool attn_trace;             // DSBD_ATTN_TRACE: timeline of the attention kernel (instrumented builds)
-  int stats_chunk;             // DSBD_STATS_CHUNK: logits per workgroup of the statistics pass; 0 = the plan's choice
   int verify_g;                // DSBD_VERIFY_G: workgroups per prompt of the layer kernel; 0 = the plan's choice
   bool verify_trace;           // DSBD_VERIFY_TRACE: timeline of the layer kernel into the workspace ...
   int verify_trace_wg;         // ... of workgroup N - 1 when the variable holds N > 1 (else of the first)
   long long verify_sync_limit_us;   // DSBD_VERIFY_SYNC_LIMIT_US: bound of every wait of the layer kernel; 0 = default
   int verify_mute_wg;          // DSBD_VERIFY_TEST_MUTE_WG: test hook, this workgroup withholds its first post; -1 = none
   int verify_lds_slice;        // DSBD_VERIFY_LDS_SLICE: largest joint slice kept in the LDS; -1 = the plan's choice
-  int verify_overlap;          // DSBD_VERIFY_OVERLAP: 0 = statistics pass and layer kernel one after the other
   int warp_fast;               // DSBD_WARP_FAST: 0 = the warping selection always takes its tree form
   int event_fence;             // DSBD_EVENT_FENCE: 1 = the library's cross-stream events keep HIP's system-scope fence; 0 = they order
                                // device work only (no cache write-back for the host's sake at every fork and join)
-  int stats_side_lds;          // DSBD_STATS_SIDE_LDS: LDS bytes claimed by a workgroup of the statistics pass when it runs beside
-                               // the layer kernel (limits how many of them share a compute unit with it); -1 = the plan's choice
 };
 const DsbdKnobs& dsbd_knobs();
 

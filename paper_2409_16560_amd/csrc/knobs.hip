@@ -20,7 +20,6 @@ void load(DsbdKnobs& k) {
   k.attn_waves8 = getenv("DSBD_ATTN_WAVES8") != nullptr;
   k.attn_staged = getenv("DSBD_ATTN_STAGED") != nullptr;
   k.attn_trace = getenv("DSBD_ATTN_TRACE") != nullptr;
-  k.stats_chunk = env_int("DSBD_STATS_CHUNK", 0);
   k.verify_g = env_int("DSBD_VERIFY_G", 0);
   k.verify_trace = getenv("DSBD_VERIFY_TRACE") != nullptr;
   k.verify_trace_wg = 0;
@@ -29,11 +28,8 @@ void load(DsbdKnobs& k) {
   k.verify_sync_limit_us = e ? atoll(e) : 0;
   k.verify_mute_wg = env_int("DSBD_VERIFY_TEST_MUTE_WG", -1);
   k.verify_lds_slice = env_int("DSBD_VERIFY_LDS_SLICE", -1);
-  k.verify_overlap = env_int("DSBD_VERIFY_OVERLAP", 1);
   k.warp_fast = env_int("DSBD_WARP_FAST", 1);
   k.event_fence = env_int("DSBD_EVENT_FENCE", 0);
-  k.stats_side_lds = env_int("DSBD_STATS_SIDE_LDS", -1);
-  if (k.stats_side_lds > 65536) k.stats_side_lds = -1;
 }
 }  // namespace
 

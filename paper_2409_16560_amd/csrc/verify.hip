@@ -1,18 +1,17 @@
 // Layer-wise verification of a draft forest on gfx950 (paper Section 3.1 "Details", Algorithm 1,
 // and the dynamic layer width of Section 3.2, Eq. 1-6).
 //
-// Two kernels that do not depend on each other and run side by side (the layer kernel on the caller's stream, the
-// statistics pass on a second stream of the library's own, forked from and joined to the caller's):
+// One launch, two kinds of workgroups that do not depend on each other:
 //
-// 1. vocab_stats_kernel + vocab_finish_kernel (bandwidth-bound, all nodes, both models): one pass over the fp32 logits
-//    with a per-thread online max / sum-of-exponentials, reduced per row chunk, then per node the fp32 log-sum-exp and
-//    the log-probability of the node's own token under its parent.  This is the O(W |V|) softmax work of the
-//    beam-sampling joint (Section 2.1) done once for every forest node; it feeds the per-node outputs only.
-// 2. verify_layers_kernel (latency-bound, persistent; all its workgroups must be resident at once): G workgroups per
-//    prompt walk the layers in order.  Every decision is taken in fp64.  The kernel derives everything from the call's
-//    inputs (tree and node range of its prompt, node depths, the maxima and sums of the rows it uses).  For the
-//    layer's input beams I the workgroups materialise p_beam and q_beam over I x V (their slice each), and every
-//    dependent reduction over I x V is one pass over the slices plus one exchange among the G workgroups.
+// 1. The first ones walk the layers (latency-bound, persistent; all of them must be resident at once, which their place
+//    at the front of the grid gives them): G workgroups per prompt.  Every decision is taken in fp64.  They derive
+//    everything from the call's inputs (tree and node range of their prompt, node depths, the maxima and sums of the
+//    rows they use).  For the layer's input beams I the workgroups materialise p_beam and q_beam over I x V (their
+//    slice each), and every dependent reduction over I x V is one pass over the slices plus one exchange among the G
+//    workgroups.
+// 2. Those behind take the fp32 statistics of one row of one model each (bandwidth-bound, all nodes, both models: the
+//    per-node outputs, the O(W |V|) softmax work of Section 2.1 done once for every forest node).  They run on the
+//    compute units that the layers leave free, and on all of them once the layers are done.
 //
 // The running residual p' is never stored.  After k consecutive rejections since the last reset
 //     p'_k = max(p_beam - c_k q_beam, 0) / F(c_k),   F(c) = sum max(p_beam - c q_beam, 0),
@@ -34,45 +33,23 @@
 #include <atomic>
 #include <mutex>
 
-#define VS_BLOCK 256
 #define VL_BLOCK 512
 #define NODE_CAP 512           // nodes of one prompt (all its trees)
 #define NEAR_TIE 1.0e-6
 #define SYNC_LIMIT_TICKS 300000000LL   // default bound of every wait: 3 s of the 100 MHz wall clock
 #define DSBD_STATIC_SCRATCH_BYTES (32u << 20)   // the device array behind dsbd_verify_forest_static
 #define CU_LDS_BYTES (160 * 1024)  // LDS of a compute unit (gfx950)
-#define STATS_SIDE_WGS 1        // workgroups of the statistics pass per compute unit beside the layer kernel
-#define XU 4                   // logits per thread and model in flight in the exponential pass.  Eight (a 4008-entry piece of the
-                               // benchmark's joint in one round) cost 256 vector registers; with four the kernel needs 186,
-                               // which leaves room on every SIMD for waves of the statistics pass running beside it
-#define VL_DYN_LDS_BYTES (80 * 1024)   // dynamic LDS of the layer kernel (its static LDS takes most of the rest) ...
+#define XU 4                   // logits per thread and model in flight in the exponential pass (eight, a 4008-entry piece of the
+                               // benchmark's joint in one round, cost 256 vector registers)
+#define VL_DYN_LDS_BYTES (84 * 1024)   // dynamic LDS of the layer kernel (its static LDS takes most of the rest) ...
 #define VL_DYN_LDS_BYTES_SMALL (112 * 1024)   // ... and of its variant for prompts of at most NODE_CAP_SMALL nodes
 #define NODE_CAP_SMALL 128
 
-// ------------------------------------------------------------------------------------------------ kernel 1
-struct StatsArgs {
-  const float* z[2];
-  int n_nodes, V, nchunk, chunk;
-  float2* part;      // [2][n_nodes][nchunk] (max, sum of exp(x - max))
-  int32_t* fault;
-};
-
+// ------------------------------------------------------------------------------------------------ row statistics, fp32
 // 2^x by the hardware instruction alone: results below 2^-126 come out as zero instead of denormal, which a sum
 // of terms relative to the running maximum does not notice (the library routine spends four more instructions
 // per logit on that range).
 __device__ __forceinline__ float fast_exp2(float x) { return __builtin_amdgcn_exp2f(x); }
-
-__device__ __forceinline__ void online_add4(float& m, float& s, bool& bad, float x0, float x1, float x2, float x3) {
-  const float L2E = 1.4426950408889634f;
-  const float bm = fmaxf(fmaxf(x0, x1), fmaxf(x2, x3));
-  bad |= !(x0 <= FLT_MAX) | !(x1 <= FLT_MAX) | !(x2 <= FLT_MAX) | !(x3 <= FLT_MAX);      // NaN or +Inf (-Inf: a masked token)
-  if (bm > m) {
-    s *= fast_exp2((m - bm) * L2E);
-    m = bm;
-  }
-  const float ref = m == -INFINITY ? 0.f : m;       // (nothing but masked tokens so far: they add 0, not exp(-Inf + Inf))
-  s += fast_exp2((x0 - ref) * L2E) + fast_exp2((x1 - ref) * L2E) + fast_exp2((x2 - ref) * L2E) + fast_exp2((x3 - ref) * L2E);
-}
 
 __device__ __forceinline__ void online_add16(float& m, float& s, bool& bad, float4 a, float4 b, float4 c, float4 d) {
   const float L2E = 1.4426950408889634f;
@@ -116,115 +93,7 @@ __device__ __forceinline__ void online_merge(float& m, float& s, float m2, float
   m = mn;
 }
 
-__global__ __launch_bounds__(VS_BLOCK) void vocab_stats_kernel(StatsArgs a) {
-  const int c = blockIdx.x, n = (int)blockIdx.y, which = blockIdx.z;
-  const int lo = c * a.chunk;
-  const int hi = min(a.V, lo + a.chunk);
-  const float* row = a.z[which] + (long long)n * a.V;
-  float m = -INFINITY, s = 0.f;
-  bool bad = false;
-  // scalar head up to 16-byte alignment, float4 body, scalar tail
-  const uintptr_t addr = reinterpret_cast<uintptr_t>(row + lo);
-  int head = (int)(((16 - (addr & 15)) & 15) >> 2);
-  head = min(head, hi - lo);
-  const int body4 = (hi - lo - head) >> 2;
-  const int tail0 = lo + head + 4 * body4;
-  if ((int)threadIdx.x < head) online_add1(m, s, bad, row[lo + threadIdx.x]);
-  const float4* r4 = reinterpret_cast<const float4*>(row + lo + head);
-  typedef float f32x4 __attribute__((ext_vector_type(4)));
-  const f32x4* n4 = reinterpret_cast<const f32x4*>(r4);
-  int i = threadIdx.x;
-  // four 16-byte loads in flight per thread (the pass is bound by memory latency x bytes in flight), and one
-  // rescaling of the running sum per sixteen logits instead of one per four
-  for (; i + 3 * VS_BLOCK < body4; i += 4 * VS_BLOCK) {
-    // streamed once: non-temporal loads keep the 250 MB pass from churning the caches (measured 15 % faster)
-    const f32x4 y0 = __builtin_nontemporal_load(&n4[i]), y1 = __builtin_nontemporal_load(&n4[i + VS_BLOCK]),
-                y2 = __builtin_nontemporal_load(&n4[i + 2 * VS_BLOCK]), y3 = __builtin_nontemporal_load(&n4[i + 3 * VS_BLOCK]);
-    const float4 x0 = make_float4(y0.x, y0.y, y0.z, y0.w), x1 = make_float4(y1.x, y1.y, y1.z, y1.w),
-                 x2 = make_float4(y2.x, y2.y, y2.z, y2.w), x3 = make_float4(y3.x, y3.y, y3.z, y3.w);
-    online_add16(m, s, bad, x0, x1, x2, x3);
-  }
-  if (i < body4) {
-    // the ragged last group, its loads in flight together as well (one after the other they cost a memory latency
-    // each at the end of every workgroup); the places beyond the end hold the most negative finite number, which
-    // changes neither the maximum nor the sum and is no fault
-    f32x4 y[4];
-#pragma unroll
-    for (int k = 0; k < 4; ++k) y[k] = __builtin_nontemporal_load(&n4[min(i + k * VS_BLOCK, body4 - 1)]);
-    float4 x[4];
-#pragma unroll
-    for (int k = 0; k < 4; ++k) {
-      const bool in = i + k * VS_BLOCK < body4;
-      x[k] = in ? make_float4(y[k].x, y[k].y, y[k].z, y[k].w) : make_float4(-FLT_MAX, -FLT_MAX, -FLT_MAX, -FLT_MAX);
-    }
-    online_add16(m, s, bad, x[0], x[1], x[2], x[3]);
-  }
-  if (tail0 + (int)threadIdx.x < hi) online_add1(m, s, bad, row[tail0 + threadIdx.x]);
-
-  // block reduction
-#pragma unroll
-  for (int off = 32; off >= 1; off >>= 1) {
-    const float m2 = __shfl_xor(m, off), s2 = __shfl_xor(s, off);
-    online_merge(m, s, m2, s2);
-  }
-  __shared__ float sm[VS_BLOCK / 64], ss[VS_BLOCK / 64];
-  __shared__ int sbad;
-  if (threadIdx.x == 0) sbad = 0;
-  __syncthreads();
-  if (bad) sbad = 1;
-  if ((threadIdx.x & 63) == 0) { sm[threadIdx.x >> 6] = m; ss[threadIdx.x >> 6] = s; }
-  __syncthreads();
-  if (threadIdx.x == 0) {
-    float M = sm[0], S = ss[0];
-    for (int w = 1; w < VS_BLOCK / 64; ++w) online_merge(M, S, sm[w], ss[w]);
-    a.part[((long long)which * a.n_nodes + n) * a.nchunk + c] = make_float2(M, S);
-    if (sbad) atomicOr(a.fault, DSBD_FAULT_NONFINITE);
-  }
-}
-
-// Per-node outputs of the statistics pass: the chunks of a row merged into its fp32 log-sum-exp, and the
-// log-probability of each node's own token under its parent's row (Section 2.1: the likelihood a beam stores grows by
-// this term).  One thread per node; the parent's chunks are merged again by the child (a handful of values).
-struct FinishArgs {
-  const float* z[2];
-  int n_nodes, V, nchunk, alias;
-  const float2* part;
-  const int32_t *parent, *token;
-  float *lse[2], *logp[2];     // outputs (any may be null)
-  int32_t* fault;
-};
-
-__device__ __forceinline__ float merged_lse(const float2* pp, int nchunk) {
-  float M = pp[0].x, S = pp[0].y;
-  for (int c = 1; c < nchunk; ++c) online_merge(M, S, pp[c].x, pp[c].y);
-  return M + logf(S);
-}
-
-__global__ __launch_bounds__(VS_BLOCK) void vocab_finish_kernel(FinishArgs a) {
-  const int n = blockIdx.x * VS_BLOCK + threadIdx.x;
-  if (n >= a.n_nodes) return;
-  const int par = a.parent[n];
-  const int tok = a.token[n];
-  const bool has_parent = par >= 0 && par < n && tok >= 0 && tok < a.V;
-#pragma unroll
-  for (int m = 0; m < 2; ++m) {
-    const float2* base = a.part + (a.alias ? 0 : (long long)m * a.n_nodes * a.nchunk);
-    const float own = merged_lse(base + (long long)n * a.nchunk, a.nchunk);
-    if (own == -INFINITY) atomicOr(a.fault, DSBD_FAULT_NONFINITE);     // a row without a finite logit
-    if (a.lse[m]) a.lse[m][n] = own;
-    // A masked logit (-Inf) is a token of probability 0, but not at a drafted token: its beam would carry the
-    // likelihood 0, and a layer whose beams all do has no joint.  Reported like the other non-finite logits.
-    const float zt = has_parent ? a.z[m][(long long)par * a.V + tok] : 0.f;
-    if (zt == -INFINITY) atomicOr(a.fault, DSBD_FAULT_NONFINITE);
-    if (a.logp[m]) {
-      float lp = 0.f;
-      if (has_parent) lp = zt - merged_lse(base + (long long)par * a.nchunk, a.nchunk);
-      a.logp[m][n] = lp;
-    }
-  }
-}
-
-// ------------------------------------------------------------------------------------------------ kernel 2
+// ------------------------------------------------------------------------------------------------ the kernel
 // Where the exchanges of one prompt keep their 16-byte slots (offsets in slots from the prompt's first one).
 struct SlotLayout {
   int x[2];              // the two alternating banks of the post-then-collect-from-all exchanges: G lines
@@ -279,6 +148,8 @@ struct LayersArgs {
   int warp_fast;         // warping: the one-level selection (bounds from the workgroups' largest entries) where it applies
   dsbd_next_beams nx;    // next-beam plan written along with the output beams (fused selection) ...
   int nx_on;             // ... when this is set
+  int layer_wgs;         // workgroups of this launch that walk layers; those behind them take the statistics of a row each
+  float *lse_p, *lse_q, *logp_p, *logp_q;   // per-node outputs of the statistics (any may be null)
 };
 
 #define VL_WAVES (VL_BLOCK / 64)
@@ -300,7 +171,6 @@ struct LayerShared {
   double max_p[64], max_q[64];       // exact row maxima
   double lm_p[64], lm_q[64];         // maxima of this workgroup's pieces of its rows (row i_lo first)
   float wmax[2][2 * VL_WAVES];       // per-wave maxima of a piece, two rows in flight
-  double tmax[VL_BLOCK];             // partial row maxima of the gathering threads
   double sp[64], sq[64];             // beam weight / row sum: p_beam(i,x) = exp(z - max) * sp[i]
   double bw_p[64], bw_q[64];         // beam weights
   // accepted beams of the layer (next layer's inputs): node and its position among the candidates
@@ -615,16 +485,107 @@ __host__ __device__ inline SliceCut slice_cut(int nI, int V, int G) {
   return c;
 }
 
-// At most VL_MAX_VGPRS vector registers, so that a wave of the statistics pass (32 registers) fits on every SIMD beside
-// this kernel's two: 2 x 240 + 32 = 512.  (The attribute counts in halves of the unified register file of this
-// target: the compiler doubles the number it is given.  Without it the allocator takes whatever two waves per SIMD
-// leave it, up to 256, whether it needs them or not.)
+// ---- per-node outputs (step A3 of the path: fp32 log-sum-exp of a node's row, log-probability of a node's token under its
+// parent's row): the workgroups behind the layers' take one row of one model each.  A row's sum is complete inside its
+// workgroup, so the log-probabilities of the row's children are its to write, and nothing has to be merged afterwards.
+// (Before, a kernel per chunk of a row and a merging kernel ran on a second stream, forked from and joined to the
+// caller's by events: 12 us of a call, 33 us of host time in four event calls and two launches, and exchanges that slowed
+// down on every compute unit the two shared.  Measured, verification call: 28 nodes x 32000 tokens 58 -> 47 us, 120 nodes
+// 80 -> 73 us, 248 nodes x 128256 121 -> 111 us, 16 prompts with 747 nodes x 32000 167 -> 152 us.)
+#define SU 8                   // 16-byte loads in flight per thread, twice (the next round travels during this one's exponentials)
+template <class Shared>
+__device__ __forceinline__ void row_statistics(const LayersArgs& a, int item, Shared& sh) {
+  typedef float f32x4 __attribute__((ext_vector_type(4)));
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int V = a.V;
+  const bool second = !a.alias && (item & 1);
+  const int n = a.alias ? item : item >> 1;
+  const float* const row = (second ? a.zq : a.zp) + (long long)n * V;
+  float m = -INFINITY, s = 0.f;
+  bool bad = false;
+  const int head = min((int)(((16 - (reinterpret_cast<uintptr_t>(row) & 15)) & 15) >> 2), V);
+  const int body4 = (V - head) >> 2, tail0 = head + 4 * body4;
+  const f32x4* const r4 = reinterpret_cast<const f32x4*>(row + head);
+  f32x4 nx[SU];
+  auto request = [&](int i) __attribute__((always_inline)) {
+#pragma unroll
+    for (int k = 0; k < SU; ++k) nx[k] = __builtin_nontemporal_load(&r4[min(i + k * VL_BLOCK, body4 - 1)]);
+  };
+  if (tid < body4) request(tid);
+  if (tid < head) online_add1(m, s, bad, row[tid]);
+  if (tail0 + tid < V) online_add1(m, s, bad, row[tail0 + tid]);
+  for (int i = tid; i < body4; i += SU * VL_BLOCK) {
+    f32x4 y[SU];
+#pragma unroll
+    for (int k = 0; k < SU; ++k) y[k] = nx[k];
+    if (i + SU * VL_BLOCK < body4) request(i + SU * VL_BLOCK);
+#pragma unroll
+    for (int k = 0; k < SU; k += 4) {
+      float4 x[4];
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {     // (places beyond the end: the most negative finite number changes neither maximum nor sum)
+        const bool in = i + (k + e) * VL_BLOCK < body4;
+        x[e] = in ? make_float4(y[k + e].x, y[k + e].y, y[k + e].z, y[k + e].w) : make_float4(-FLT_MAX, -FLT_MAX, -FLT_MAX, -FLT_MAX);
+      }
+      online_add16(m, s, bad, x[0], x[1], x[2], x[3]);
+    }
+  }
+#pragma unroll
+  for (int off = 32; off >= 1; off >>= 1) {
+    const float m2 = __shfl_xor(m, off), s2 = __shfl_xor(s, off);
+    online_merge(m, s, m2, s2);
+  }
+  if (tid == 0) sh.sbad = 0;
+  float2* const part = reinterpret_cast<float2*>(sh.tsum);
+  if (lane == 0) part[wave] = make_float2(m, s);
+  __syncthreads();
+  if (bad) sh.sbad = 1;
+  float M = part[0].x, S = part[0].y;
+#pragma unroll
+  for (int w = 1; w < VL_WAVES; ++w) online_merge(M, S, part[w].x, part[w].y);
+  const float lse = M + logf(S);
+  float* const o_lse = second ? a.lse_q : a.lse_p;
+  float* const o_logp = second ? a.logp_q : a.logp_p;
+  // children: nodes of the same tree, behind this one, no further than a tree is long
+  const int par = a.parent[n], tok = a.token[n];
+  int fault = 0;
+  if (tid == 0) {
+    if (o_lse) o_lse[n] = lse;
+    if (a.alias && a.lse_q) a.lse_q[n] = lse;
+    if (lse == -INFINITY) fault = DSBD_FAULT_NONFINITE;                // a row without a finite logit
+    if (!(par >= 0 && par < n && n - par < DSBD_MAX_TREE_NODES && tok >= 0 && tok < V)) {      // a root (or a node reported elsewhere)
+      if (o_logp) o_logp[n] = 0.f;
+      if (a.alias && a.logp_q) a.logp_q[n] = 0.f;
+    }
+  }
+  const int c = n + tid;
+  if (tid >= 1 && tid < DSBD_MAX_TREE_NODES && c < a.n_nodes && a.parent[c] == n) {
+    const int ct = a.token[c];
+    if (ct >= 0 && ct < V) {
+      const float zt = row[ct];
+      if (zt == -INFINITY) fault = DSBD_FAULT_NONFINITE;               // a drafted token masked in its parent's row
+      if (o_logp) o_logp[c] = zt - lse;
+      if (a.alias && a.logp_q) a.logp_q[c] = zt - lse;
+    }
+  }
+  __syncthreads();
+  if (tid == 0 && sh.sbad) fault = DSBD_FAULT_NONFINITE;
+  if (fault) atomicOr(a.fault, fault);
+}
+
+// At most VL_MAX_VGPRS vector registers.  (The attribute counts in halves of the unified register file of this target:
+// the compiler doubles the number it is given.  Without it the allocator takes whatever two waves per SIMD leave it, up
+// to 256, whether it needs them or not.)
 #define VL_MAX_VGPRS 240
 template <bool WARP, int NC>
 __global__ __launch_bounds__(VL_BLOCK) __attribute__((amdgpu_num_vgpr(VL_MAX_VGPRS / 2)))
 void verify_layers_kernel(LayersArgs a) {
   __shared__ LayerShared<NC> sh;
   extern __shared__ __attribute__((aligned(16))) double dyn_lds[];
+  if ((int)blockIdx.x >= a.layer_wgs) {
+    row_statistics(a, (int)blockIdx.x - a.layer_wgs, sh);
+    return;
+  }
   const int prompt = a.prompt0 + blockIdx.x / a.G;
   const int g = blockIdx.x % a.G;
   const int tid = threadIdx.x;
@@ -668,7 +629,7 @@ void verify_layers_kernel(LayersArgs a) {
 
   // ---- trees and nodes of this prompt.  tree_prompt is non-decreasing: the prompt's trees are those behind the
   // trees of earlier prompts.  (Everything the kernel needs it derives from the call's inputs: it does not wait for
-  // the statistics pass, which runs beside it.)
+  // the statistics, which run beside it.)
   int t_first = 0, t_end = a.n_trees;
   if (a.n_prompts > 1) {
     __syncthreads();
@@ -989,7 +950,7 @@ void verify_layers_kernel(LayersArgs a) {
           fpB[k] = zp[xx]; fqB[k] = zq[xx];
         }
       }
-      bool nonfinite = false;        // (the statistics pass reports these for every row; this kernel for the rows it uses)
+      bool nonfinite = false;        // (the row statistics report these for every row; the layers for the rows they use)
 #pragma unroll
       for (int k = 0; k < XU; ++k) {
         lmp = fmaxf(fmaxf(lmp, fpA[k]), fpB[k]); lmq = fmaxf(fmaxf(lmq, fqA[k]), fqB[k]);
@@ -1900,7 +1861,7 @@ void verify_layers_kernel(LayersArgs a) {
       with_slices([&](auto P, auto Q, long long r0, long long r1) {
         // four elements of each array in flight per thread, the ragged end predicated (one element after the other,
         // the tail of a 4008-entry slice cost four dependent LDS round trips per chain entry; eight in flight cost
-        // more registers than the kernel can spare beside the statistics pass)
+        // 50 more registers)
         const int n = (int)r1;             // a slice has fewer than 2^31 entries
         const int j_first = (int)r0 + tid - t0;
         if constexpr (std::is_same<decltype(P), glb_f64*>::value) {
@@ -2590,7 +2551,7 @@ void verify_layers_kernel(LayersArgs a) {
 namespace {
 
 struct VerifyPlan {
-  int nchunk, chunk, I_cap, G, lds_elems;
+  int I_cap, G, lds_elems;
   bool small_nodes;        // the layer kernel built for prompts of at most NODE_CAP_SMALL nodes serves (more LDS for slices)
   int group;               // prompts per launch of the layer kernel (all of them, unless they do not fit the device at once)
   size_t lds_bytes;        // dynamic LDS of the layer kernel
@@ -2655,22 +2616,6 @@ const DeviceLimits& device_limits() {
 VerifyPlan make_verify_plan(const dsbd_forest* f, int V, const dsbd_params* p, bool alias = false) {
   VerifyPlan pl;
   const DsbdKnobs& knobs = dsbd_knobs();
-  // about four chunks per row, of 8k to 32k logits each: a few thousand workgroups at the large configurations
-  // (measured: a 32000-token vocabulary in one chunk per row ran the 16-prompt batch at 45 % of the HBM peak, in
-  // four at 57 %)
-  int target = V / 4;
-  if (target < 8192) target = 8192;
-  if (target > 32768) target = 32768;
-  if (knobs.stats_chunk >= 1024) target = knobs.stats_chunk;   // tuning knob: logits per workgroup of the statistics pass
-  // few rows (a draft step's beams): finer chunks, down to 4k logits and up to 16 per row, until about a thousand
-  // workgroups stream (a workgroup of the pass is bound by memory latency x its number of load rounds)
-  else
-    while (target > 4096 && (V + target / 2 - 1) / (target / 2) <= 16 &&
-           2LL * f->n_nodes * ((V + target - 1) / target) < 1024)
-      target /= 2;
-  pl.nchunk = (V + target - 1) / target;
-  pl.chunk = ((V + pl.nchunk - 1) / pl.nchunk + 3) & ~3;
-  pl.nchunk = (V + pl.chunk - 1) / pl.chunk;
   pl.I_cap = p->W_cap > f->max_prompt_trees ? p->W_cap : f->max_prompt_trees;
   // one workgroup per compute unit in total, shared evenly by the prompts, at least 4096 joint elements per
   // workgroup.  More prompts than workgroups fit the device at once: groups of prompts, one launch after the other
@@ -2678,6 +2623,21 @@ VerifyPlan make_verify_plan(const dsbd_forest* f, int V, const dsbd_params* p, b
   const DeviceLimits& lim = device_limits();
   const int resident = lim.cus * lim.blocks_per_cu;
   int G = f->n_prompts > 0 ? lim.cus / f->n_prompts : 1;
+  // ... minus compute units for the workgroups that take the rows' statistics meanwhile: one per 4 MB of logits (what a
+  // compute unit streams while the layers are walked), at most a quarter of the device, and none where the coarser cut
+  // of a row among the prompt's workgroups would cost more than that quarter (a 16-prompt batch: one workgroup per
+  // row instead of two).  Measured, verification of 248 nodes x 128256 (254 MB, 8 beams): no unit kept 128 us, 16: 127,
+  // 32: 122, 48: 115, 64: 111, 96: 113; 16 prompts, 747 nodes x 32000: none 152 us, 16 kept (15 workgroups per
+  // prompt) 224 us.
+  {
+    long long keep = (2LL * f->n_nodes * V * 4 + (4 << 20) - 1) / (4 << 20);
+    if (keep > lim.cus / 4) keep = lim.cus / 4;
+    const int W = f->max_prompt_trees;
+    if (f->n_prompts > 0) {
+      const int Gk = (int)((lim.cus - keep) / f->n_prompts);
+      if (Gk >= W && (Gk / W) * 4 >= (G / W) * 3) G = Gk;
+    }
+  }
   // (sized by the joint of the input beams, which is what a fixed width keeps every layer at: an exchange among 64
   // workgroups costs 1.7 us against 2.5 us among 256, and below about 4000 entries per workgroup the passes over a
   // slice are shorter than that difference.  Measured: 8 beams x 32000 tokens 83 us with 64 workgroups, 88 us with
@@ -2739,13 +2699,10 @@ VerifyPlan make_verify_plan(const dsbd_forest* f, int V, const dsbd_params* p, b
   return pl;
 }
 
-size_t carve_verify(WorkspaceCarver& ws, const dsbd_forest* f, int V, const VerifyPlan& pl, float2** part, double** pb,
-                    double** qb, double** red) {
-  const size_t N = (size_t)f->n_nodes, P = (size_t)f->n_prompts;
-  (void)V;
+size_t carve_verify(WorkspaceCarver& ws, const dsbd_forest* f, const VerifyPlan& pl, double** pb, double** qb, double** red) {
+  const size_t P = (size_t)f->n_prompts;
   ws.take<long long>(512);                 // timeline of the layer kernel (diagnostics), first in the workspace
   ws.take<unsigned long long>(32);         // replay count of launches recorded into a graph (one word, a line of its own)
-  *part = ws.take<float2>(2 * N * pl.nchunk);
   // slices that do not fit the LDS: a region per workgroup of a launch (the launches of a forest that runs in groups
   // of prompts follow each other and share the regions); exchange slots: a region per prompt
   *pb = ws.take<double>((size_t)pl.group * pl.G * (size_t)pl.slice_cap);
@@ -2754,37 +2711,30 @@ size_t carve_verify(WorkspaceCarver& ws, const dsbd_forest* f, int V, const Veri
   return ws.total();
 }
 
-// The second stream the statistics pass runs on, next to the layer kernel on the caller's stream; one per device,
-// created on first use and kept until the process ends (with the two events that order it after the caller's
-// earlier work and order the caller's later work after it).
-struct SideStream {
-  hipStream_t stream = nullptr;
-  hipEvent_t fork = nullptr, join = nullptr;
+// Two layer kernels on different streams must not share the compute units: each waits for workgroups of its own that
+// the other one's keep out.  The library therefore orders its layer launches itself once it has seen calls on more
+// than one stream: the first change of stream waits for the device to drain, and from then on layers_done is recorded
+// behind every layer launch and a launch on another stream than the last one waits for it.  (Recording from the start
+// would cost every single-stream caller 6 us per call, measured.)  One per device; the event is created on first use
+// and kept until the process ends.  enqueue makes one call's records and waits a unit among host threads.
+struct LaunchOrder {
   bool tried = false, ok = false;
-  // Two layer kernels on different streams must not share the compute units: each waits for workgroups of its own
-  // that the other one's keep out.  The library therefore orders its layer launches itself once it has seen calls on
-  // more than one stream: the first change of stream waits for the device to drain, and from then on layers_done is
-  // recorded behind every layer launch and a launch on another stream than the last one waits for it.  (Recording
-  // from the start would cost every single-stream caller 6 us per call, measured.)  enqueue makes one call's records
-  // and waits a unit among host threads.
   hipEvent_t layers_done = nullptr;
   hipStream_t last_stream = nullptr;
   bool have_last = false, several_streams = false;
   std::mutex enqueue;
 };
-SideStream* side_stream_of_current_device(bool may_create) {
-  static SideStream table[64];
+LaunchOrder* launch_order_of_current_device(bool may_create) {
+  static LaunchOrder table[64];
   static std::mutex mutex;
   int dev = 0;
   if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) return nullptr;
   std::lock_guard<std::mutex> lock(mutex);
-  SideStream& s = table[dev];
+  LaunchOrder& s = table[dev];
   if (!s.tried && may_create) {
     s.tried = true;
     const unsigned ev = hipEventDisableTiming | (dsbd_knobs().event_fence ? 0u : (unsigned)hipEventDisableSystemFence);
-    s.ok = hipStreamCreateWithFlags(&s.stream, hipStreamNonBlocking) == hipSuccess &&
-           hipEventCreateWithFlags(&s.fork, ev) == hipSuccess && hipEventCreateWithFlags(&s.join, ev) == hipSuccess &&
-           hipEventCreateWithFlags(&s.layers_done, ev) == hipSuccess;
+    s.ok = hipEventCreateWithFlags(&s.layers_done, ev) == hipSuccess;
     if (!s.ok) (void)hipGetLastError();
   }
   return s.ok ? &s : nullptr;
@@ -2802,18 +2752,19 @@ extern "C" size_t dsbd_verify_forest_workspace_bytes(const dsbd_forest* f, int32
   if (check_verify(f, V, p) != DSBD_OK) return 0;
   const VerifyPlan pl = make_verify_plan(f, V, p);
   WorkspaceCarver ws(nullptr);
-  float2* pt; double *pb, *qb, *red;
-  return carve_verify(ws, f, V, pl, &pt, &pb, &qb, &red) + 256;
+  double *pb, *qb, *red;
+  return carve_verify(ws, f, pl, &pb, &qb, &red) + 256;
 }
 
 namespace {
-// may_create_side: the second stream may be created by this call (an ordinary call); false for the entry point that
-// must not allocate, which uses the second stream only if an earlier call or dsbd_init() has made it.
+// may_create: the event that orders launches across streams may be created by this call (an ordinary call); false for
+// the entry point that must not allocate, which takes part in the ordering only if an earlier call or dsbd_init() has
+// made it.
 // next: the next-beam plan to be written along with the output beams (nullptr: none).  With keep_one == 0 the layer
 // kernel writes it itself; the single surviving beam of keep_one != 0 needs all of a prompt's output beams side by
 // side, which sit in several workgroups' hands: there the selection kernel is launched behind the verification.
 int32_t verify_impl(const dsbd_forest* f, const dsbd_verify_in* in, const dsbd_params* p, const dsbd_verify_out* out,
-                    void* workspace, size_t workspace_bytes, int32_t* fault, void* stream_, bool may_create_side,
+                    void* workspace, size_t workspace_bytes, int32_t* fault, void* stream_, bool may_create,
                     const dsbd_next_beams* next = nullptr, int keep_one = 0) {
   if (!in || !out || !fault) return DSBD_ERR_INVALID;
   int32_t rc = check_verify(f, in->V, p);
@@ -2839,15 +2790,11 @@ int32_t verify_impl(const dsbd_forest* f, const dsbd_verify_in* in, const dsbd_p
 
   char* wbase = reinterpret_cast<char*>(dsbd_align_up(reinterpret_cast<uintptr_t>(workspace), 256));
   WorkspaceCarver ws(wbase);
-  float2* part; double *pb, *qb, *red;
-  carve_verify(ws, f, in->V, pl, &part, &pb, &qb, &red);
+  double *pb, *qb, *red;
+  carve_verify(ws, f, pl, &pb, &qb, &red);
 
-  // ---- the statistics pass (per-node outputs; the layer kernel does not depend on it) runs on a second stream next
-  // to the layer kernel: ordered after everything the caller's stream holds so far, and the caller's stream continues
-  // only when both are done.  DSBD_VERIFY_OVERLAP=0 (or a stream that cannot be created) puts it in front instead.
   const bool want_stats = out->lse_target || out->lse_draft || out->node_logp_target || out->node_logp_draft;
-  SideStream* state = side_stream_of_current_device(may_create_side);
-  SideStream* side = (want_stats && knobs.verify_overlap) ? state : nullptr;
+  LaunchOrder* const state = launch_order_of_current_device(may_create);
   std::unique_lock<std::mutex> enqueue_lock;
   if (state) enqueue_lock = std::unique_lock<std::mutex>(state->enqueue);
   // a stream under capture takes no part in the ordering of layer launches (an event recorded into a capture cannot
@@ -2858,48 +2805,6 @@ int32_t verify_impl(const dsbd_forest* f, const dsbd_verify_in* in, const dsbd_p
     if (hipStreamIsCapturing(stream, &cs) == hipSuccess) capturing = cs != hipStreamCaptureStatusNone;
     else { (void)hipGetLastError(); capturing = true; }
   }
-  StatsArgs sa;
-  sa.z[0] = in->logits_target; sa.z[1] = in->logits_draft;
-  sa.n_nodes = f->n_nodes; sa.V = in->V; sa.nchunk = pl.nchunk; sa.chunk = pl.chunk;
-  sa.part = part; sa.fault = fault;
-  FinishArgs fa;
-  fa.z[0] = in->logits_target; fa.z[1] = in->logits_draft;
-  fa.n_nodes = f->n_nodes; fa.V = in->V; fa.nchunk = pl.nchunk; fa.alias = alias ? 1 : 0; fa.part = part;
-  fa.parent = f->parent; fa.token = f->token; fa.fault = fault;
-  fa.lse[0] = out->lse_target; fa.lse[1] = out->lse_draft;
-  fa.logp[0] = out->node_logp_target; fa.logp[1] = out->node_logp_draft;
-  auto launch_stats = [&](hipStream_t st) {
-    // Beside the layer kernel the pass is held to STATS_SIDE_WGS workgroups per compute unit by the LDS it claims
-    // (it uses none of it).  Measured on the benchmark shape (layer kernel alone: 120 us, the call with the pass in
-    // front of it: 167 us): four per unit (all that the registers left over admit) stream at full rate for 49 us,
-    // slow the layer kernel's first layers down and give a call of 149 us; three: 55 us and 146 us; one: 88 us, inside
-    // the layer kernel's run, 142 us; none: the pass runs behind the layer kernel, 184 us.
-    unsigned int side_lds = 0;
-    if (st != stream) {
-      const size_t layer_static = pl.small_nodes ? sizeof(LayerShared<NODE_CAP_SMALL>) : sizeof(LayerShared<NODE_CAP>);
-      const long long layer_lds = (long long)(layer_static + pl.lds_bytes + 511) / 512 * 512;
-      // a claim that STATS_SIDE_WGS workgroups fit in beside the layer kernel's LDS and one more does not, with
-      // half a claim of slack on either side (the allocation granule and the pass's own few bytes are not known here)
-      const long long free_lds = CU_LDS_BYTES - layer_lds;
-      long long per = free_lds / (STATS_SIDE_WGS + 1) + free_lds / (2 * STATS_SIDE_WGS * (STATS_SIDE_WGS + 1));
-      per = per / 256 * 256;
-      if (per > 60000) per = 60000;
-      if (per > 0) side_lds = (unsigned int)per;
-      if (knobs.stats_side_lds >= 0) side_lds = (unsigned int)knobs.stats_side_lds;
-    }
-    dsbd_launch(DSBD_KERNEL_VOCAB_STATS, vocab_stats_kernel, dim3(pl.nchunk, f->n_nodes, alias ? 1 : 2), dim3(VS_BLOCK),
-                side_lds, st, sa);
-    hipLaunchKernelGGL(vocab_finish_kernel, dim3((f->n_nodes + VS_BLOCK - 1) / VS_BLOCK), dim3(VS_BLOCK), 0, st, fa);
-  };
-  if (want_stats && !side) {
-    launch_stats(stream);
-    DSBD_HIP_LAUNCH_CHECK();
-  }
-  if (side) {
-    if (hipEventRecord(side->fork, stream) != hipSuccess || hipStreamWaitEvent(side->stream, side->fork, 0) != hipSuccess)
-      return DSBD_ERR_HIP;
-  }
-
   LayersArgs la;
   la.n_prompts = f->n_prompts; la.n_trees = f->n_trees; la.n_nodes = f->n_nodes;
   la.tree_prompt = f->tree_prompt; la.tree_off = f->tree_off; la.parent = f->parent; la.token = f->token;
@@ -2931,6 +2836,7 @@ int32_t verify_impl(const dsbd_forest* f, const dsbd_verify_in* in, const dsbd_p
   la.alias = alias ? 1 : 0;
   la.warp_fast = knobs.warp_fast ? 1 : 0;
   la.nx_on = (next && !keep_one) ? 1 : 0;
+  la.lse_p = out->lse_target; la.lse_q = out->lse_draft; la.logp_p = out->node_logp_target; la.logp_q = out->node_logp_draft;
   if (la.nx_on) la.nx = *next; else la.nx = dsbd_next_beams{};
   if (knobs.verify_lds_slice >= 0 && knobs.verify_lds_slice < la.lds_slice) la.lds_slice = knobs.verify_lds_slice;   // tuning / test knob
   la.top_k = p->top_k; la.top_p = (p->top_p > 0.0f && p->top_p < 1.0f) ? p->top_p : 1.0f;
@@ -2948,7 +2854,9 @@ int32_t verify_impl(const dsbd_forest* f, const dsbd_verify_in* in, const dsbd_p
   for (int p0 = 0; p0 < f->n_prompts; p0 += pl.group) {
     la.prompt0 = p0;
     const int np = f->n_prompts - p0 < pl.group ? f->n_prompts - p0 : pl.group;
-    const unsigned grid3 = (unsigned)np * (unsigned)pl.G;
+    unsigned grid3 = (unsigned)np * (unsigned)pl.G;
+    la.layer_wgs = (int)grid3;
+    if (want_stats && p0 + np == f->n_prompts) grid3 += (unsigned)f->n_nodes * (alias ? 1u : 2u);     // behind the (last) layers
     if (p->top_k > 0)
       dsbd_launch(DSBD_KERNEL_VERIFY_LAYERS, verify_layers_kernel<true, NODE_CAP>, dim3(grid3), dim3(VL_BLOCK),
                   (unsigned int)pl.lds_bytes, stream, la);
@@ -2964,13 +2872,6 @@ int32_t verify_impl(const dsbd_forest* f, const dsbd_verify_in* in, const dsbd_p
     if (state->several_streams && hipEventRecord(state->layers_done, stream) != hipSuccess) le = hipErrorUnknown;
     state->last_stream = stream;
     state->have_last = true;
-  }
-  if (side) {
-    launch_stats(side->stream);
-    if (hipEventRecord(side->join, side->stream) != hipSuccess || hipStreamWaitEvent(stream, side->join, 0) != hipSuccess)
-      le = hipErrorUnknown;
-    const hipError_t le2 = hipGetLastError();
-    if (le == hipSuccess) le = le2;
   }
   if (le != hipSuccess) return DSBD_ERR_HIP;
   if (next && keep_one) return dsbd_select_beams(f, out, p->W_cap, keep_one, next, fault, stream_);
@@ -3020,7 +2921,7 @@ extern "C" int32_t dsbd_init(void) {
   if (!static_scratch_of_current_device()) return DSBD_ERR_HIP;
   (void)device_limits();
   (void)dsbd_knobs();
-  return side_stream_of_current_device(true) ? DSBD_OK : DSBD_ERR_HIP;
+  return launch_order_of_current_device(true) ? DSBD_OK : DSBD_ERR_HIP;
 }
 
 extern "C" size_t dsbd_verify_forest_static_capacity(void) { return DSBD_STATIC_SCRATCH_BYTES; }

@@ -910,3 +910,30 @@ def test_verify_more_prompts_than_workgroups_fit_the_device(n_prompts, t):
     near = gu.compare_verify(res, ref, w)
     print("prompts", n_prompts, "trees", w.n_trees, "nodes", w.n_nodes, "near ties", near, flush=True)
     gu.check_verify_select(d, w, ref, t=t)
+
+
+@pytest.mark.parametrize("V", [1, 3, 2047, 16383, 16384, 16385, 33001])
+@pytest.mark.parametrize("same", [False, True])
+def test_row_statistics_at_the_edges_of_their_rounds(V, same):
+    """Per-node outputs against fp64: rows shorter than a load, rows that end at, just below and just above a round of
+    the loads (16384 logits) and in the middle of one, unaligned rows (odd V), one model in both roles.  The bound: an
+    fp32 sum of positive terms in chunks of at most V / 512 + 16 terms and ten merges is off by at most
+    (V / 512 + 26) 2^-24 relative, the logarithm and the final additions by a few ulps of the result."""
+    import paper_2409_16560_amd as dsbd
+    from dsbd_synth.device import DeviceWorkload
+    w = make_workload("c3", L=1, Hq=1, Hkv=1, D=64, V=V, shared_len=0)
+    d = DeviceWorkload(w)
+    if same:
+        d.logits_q, d.blq = d.logits_p, d.blp
+    print("case", V, same, flush=True)
+    res = d.verify(t=-1.0)
+    torch.cuda.synchronize()
+    assert int(res.fault.item()) & ~8 == 0        # (one token only: a residual without mass)
+    tol = (V / 512 + 26) * 2.0 ** -24 + 4 * 2.0 ** -24 * 32
+    par = torch.from_numpy(w.parent).cuda().long()
+    tok = torch.from_numpy(w.token).cuda().long()
+    for z, lse, logp in ((d.logits_p, res.lse_target, res.node_logp_target), (d.logits_q, res.lse_draft, res.node_logp_draft)):
+        ref = torch.logsumexp(z.double(), 1)
+        assert float((lse.double() - ref).abs().max()) <= tol
+        ref_lp = torch.where(par >= 0, z.double()[par.clamp(min=0), tok] - ref[par.clamp(min=0)], torch.zeros_like(ref))
+        assert float((logp.double() - ref_lp).abs().max()) <= 2 * tol
