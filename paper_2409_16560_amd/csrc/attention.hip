@@ -7,14 +7,15 @@
 //
 // Work decomposition (split-KV): one workgroup per (tree, KV head, row block, KV split).  Inside a
 // workgroup the 4 waves form RW row groups x TW token groups.  Every wave streams its own 32-token
-// steps of K and V straight from HBM into registers (no block-level barrier in the main loop) and
-// keeps 16*NRT query rows resident:
-//   S^T = K Q^T   MFMA 16x16x32 bf16, A = K (tokens x d) from global in operand layout,
-//                 B = Q^T held in registers for the whole kernel;
+// steps of K and V from HBM through registers into tiles of its own in the LDS (no block-level barrier in the main
+// loop) and keeps 16*NRT query rows resident:
+//   S^T = K Q^T   MFMA 16x16x32 bf16, A = K (tokens x d) from the tile, B = Q^T held in registers for the whole kernel;
 //   online softmax per query row, entirely lane-local: in the transposed product every lane owns
 //                 one query row (column l%16), its scores and its slice of the output accumulators;
-//   O^T += V^T P^T  MFMA 16x16x32, B = P^T built in registers from the S^T tile, A = V^T read from a
-//                 wave-private LDS tile into which V was written transposed (token pairs packed).
+//   O^T += V^T P^T  MFMA 16x16x32, B = P^T built in registers from the S^T tile, A = V^T through the transposing LDS read.
+// Bound by HBM: 16 prompts, 77 beams x 32 heads, 2.9 GB: 486 us = 6.05 TB/s (530 us while K came straight from memory in
+// operand layout, which takes a cache line in two instructions and so cannot be streamed past the caches); 8 beams x 32
+// heads x 2048 tokens, half of them shared: 36 us (40).
 // The ancestor mask never exists in memory: every wave derives the tree's topology itself (the parent array of
 // a tree is one load per lane, the parent chains are walked with lane shuffles), each lane keeps the 64-bit
 // ancestor bitmap of its row's node and tests bits while handling the (at most two) steps that cover the
@@ -32,7 +33,6 @@ typedef __attribute__((address_space(3))) v4i16 lds_v4i16;
 #define NEG_BIG (-1.0e30f)
 #define REF_SLACK 40.0f          // log2 headroom of the softmax reference before it is raised
 #define STEP 32                 // tokens per wave step (two 16-token MFMA tiles)
-#define VT_PITCH 36             // bf16 elements per row of the transposed V tile (32 + pad, multiple of 4)
 
 struct AttnArgs {
   const int32_t* tree_off;
@@ -66,9 +66,8 @@ __device__ __forceinline__ uint4 load_global_16(const void* p) {
   const u32x4 v = *(const __attribute__((address_space(1))) u32x4*)(p);
   return make_uint4(v.x, v.y, v.z, v.w);
 }
-// The same with the non-temporal hint, for data that one thread consumes whole with one load (the K/V tiles of
-// the shared-tile kernel: 9 % faster inside the benchmark's kernel mix).  Where a cache line is consumed by several
-// load instructions of a wave (K in operand layout, wave-private kernel) the hint costs 20 % instead.
+// The same with the non-temporal hint, for streams whose cache lines are consumed whole by one load instruction of a
+// wave (where several instructions share a line the hint costs 20 % instead of gaining 9 to 14 %).
 __device__ __forceinline__ uint4 load_global_16_nt(const void* p) {
   const u32x4 v = __builtin_nontemporal_load((const __attribute__((address_space(1))) u32x4*)(p));
   return make_uint4(v.x, v.y, v.z, v.w);
@@ -102,13 +101,17 @@ __global__ __launch_bounds__(256) void forest_attention_kernel(AttnArgs a) {
   constexpr int DT = D / 16;        // 16-row output tiles over the head dimension for O^T
   constexpr int ROWS_W = 16 * NRT;  // query rows per wave
   constexpr int ROWS_B = ROWS_W * RW;
-  constexpr int LPR = D / 8;        // lanes covering one V row with 16-byte loads
-  constexpr int TG = 64 / LPR;      // token groups among the lanes for V loads
-  constexpr int VROUNDS = STEP / (2 * TG);
+  constexpr int LPR = D / 8;        // lanes covering one K or V row with 16-byte loads
+  constexpr int TG = 64 / LPR;      // rows per load instruction of a wave
+  constexpr int ROUNDS = STEP / TG;
 
-  __shared__ __attribute__((aligned(16))) __bf16 vt_lds[4][D * VT_PITCH];
-  __shared__ __attribute__((aligned(16))) float comb_o[(TW - 1) * RW][ROWS_W][D + 4];
+  constexpr int KP = D + 8;         // pitch of a tile row in elements (16 bytes of padding)
+  constexpr int TILES_BYTES = 4 * 2 * STEP * KP * 2;
+  constexpr int COMB_BYTES = (TW - 1) * RW * ROWS_W * (D + 4) * 4;
+  // the waves' K and V tiles; after the last step the merge of the token groups takes their place
+  __shared__ __attribute__((aligned(16))) char smem[TILES_BYTES > COMB_BYTES ? TILES_BYTES : COMB_BYTES];
   __shared__ float comb_ml[(TW - 1) * RW][ROWS_W][2];
+  float (*comb_o)[ROWS_W][D + 4] = reinterpret_cast<float (*)[ROWS_W][D + 4]>(smem);
 
   const int lane = threadIdx.x & 63;
   const int wave = threadIdx.x >> 6;
@@ -194,15 +197,15 @@ __global__ __launch_bounds__(256) void forest_attention_kernel(AttnArgs a) {
     for (int dt = 0; dt < DT; ++dt) o[rt][dt] = floatx4{0.f, 0.f, 0.f, 0.f};
   }
 
-  __bf16* vt = vt_lds[wave];
-  const int v_dl = lane % LPR;       // 16-byte column of the V row this lane loads
-  const int v_tg = lane / LPR;       // token group
+  __bf16* const kt = reinterpret_cast<__bf16*>(smem) + wave * 2 * STEP * KP;     // this wave's tiles
+  __bf16* const vt = kt + STEP * KP;
+  const int ld_piece = lane % LPR;   // 16-byte piece of the row this lane loads
+  const int ld_tok = lane / LPR;     // row among those of a load instruction
 
   // a row block beyond the tree's rows has nothing to do (uniform over the workgroup)
   const bool block_live = rb * ROWS_B < R;
 
-  bf16x8 kf[2][DS];
-  uint4 vr[VROUNDS][2];             // raw V rows: 8 channels of one token per register quad
+  uint4 kr[ROUNDS], vr[ROUNDS];     // the next step's rows on their way from HBM to the tiles
 
   // step -> (segment, first token, tokens in the segment)
   auto locate = [&](int st, const __bf16*& kp, const __bf16*& vp, long long& stride, int& tok0, int& len, bool& tree) {
@@ -210,33 +213,23 @@ __global__ __launch_bounds__(256) void forest_attention_kernel(AttnArgs a) {
     else if (st < n0 + n1) { kp = k1; vp = v1; stride = a.token_stride; tok0 = (st - n0) * STEP; len = Lo; tree = false; }
     else { kp = k2; vp = v2; stride = stride2; tok0 = (st - n0 - n1) * STEP; len = n_b; tree = true; }
   };
-  auto load_k = [&](int st) {
+  // Whole rows per instruction, streamed past the caches: a line consumed by one instruction may carry the non-temporal
+  // hint, which the stream needs (a pure-load replay of the 16-prompt batch: 6.8 TB/s with it, 5.95 without; K loaded
+  // straight in operand layout takes a line in two instructions and was 20 % slower with the hint).
+  auto load_step = [&](int st) {
     const __bf16 *kp, *vp; long long stride; int tok0, len; bool tree;
     locate(st, kp, vp, stride, tok0, len, tree);
 #pragma unroll
-    for (int tt = 0; tt < 2; ++tt) {
-      const int tok = min(tok0 + 16 * tt + col, len - 1);
-      const __bf16* p = kp + (long long)tok * stride + 8 * qd;
-#pragma unroll
-      for (int j = 0; j < DS; ++j) kf[tt][j] = load_global_bf16x8(p + 32 * j);
-    }
-  };
-  auto load_v = [&](int st) {
-    const __bf16 *kp, *vp; long long stride; int tok0, len; bool tree;
-    locate(st, kp, vp, stride, tok0, len, tree);
-#pragma unroll
-    for (int k = 0; k < VROUNDS; ++k) {
-#pragma unroll
-      for (int h = 0; h < 2; ++h) {
-        const int tok = min(tok0 + 2 * TG * k + 2 * v_tg + h, len - 1);
-        vr[k][h] = load_global_16(vp + (long long)tok * stride + 8 * v_dl);
-      }
+    for (int k = 0; k < ROUNDS; ++k) {
+      const long long off = (long long)min(tok0 + TG * k + ld_tok, len - 1) * stride + 8 * ld_piece;
+      kr[k] = load_global_16_nt(kp + off);
+      vr[k] = load_global_16_nt(vp + off);
     }
   };
 
   int st = st_begin + tw;
   const bool active = block_live && st < st_end;
-  if (active) { load_k(st); load_v(st); }
+  if (active) load_step(st);
   // ---- topology of the tree (every wave for itself, while the first K/V loads travel): lane j = node j
   {
     uint64_t my_anc = 0;
@@ -251,8 +244,8 @@ __global__ __launch_bounds__(256) void forest_attention_kernel(AttnArgs a) {
     }
   }
 
-  // One step = 32 tokens of this wave: V goes to LDS transposed (two tokens packed per 32-bit write),
-  // the next step's V and K loads are issued as soon as their registers are free, S^T = K Q^T.
+  // One step = 32 tokens of this wave: its rows move from the registers to the wave's tiles, the next step's are
+  // requested, S^T = K Q^T.
   int tok0 = 0, nvalid = 0, st_next = 0;
   bool is_tree = false;
   floatx4 s[NRT][2];
@@ -263,40 +256,34 @@ __global__ __launch_bounds__(256) void forest_attention_kernel(AttnArgs a) {
     st_next = st + TW;
     wave_lds_fence();
 #pragma unroll
-    for (int k = 0; k < VROUNDS; ++k) {
-      const int tokp = 2 * TG * k + 2 * v_tg;          // even token index within the step
-      const uint32_t ta[4] = {vr[k][0].x, vr[k][0].y, vr[k][0].z, vr[k][0].w};   // token tokp, channels 2c, 2c+1
-      const uint32_t tb[4] = {vr[k][1].x, vr[k][1].y, vr[k][1].z, vr[k][1].w};   // token tokp + 1
-#pragma unroll
-      for (int c2 = 0; c2 < 4; ++c2) {
-        // (token, token+1) pairs of channel 2c (low halves) and 2c+1 (high halves)
-        const uint32_t lo = __builtin_amdgcn_perm(tb[c2], ta[c2], 0x05040100u);
-        const uint32_t hi = __builtin_amdgcn_perm(tb[c2], ta[c2], 0x07060302u);
-        *reinterpret_cast<uint32_t*>(&vt[(8 * v_dl + 2 * c2) * VT_PITCH + tokp]) = lo;
-        *reinterpret_cast<uint32_t*>(&vt[(8 * v_dl + 2 * c2 + 1) * VT_PITCH + tokp]) = hi;
-      }
+    for (int k = 0; k < ROUNDS; ++k) {
+      *reinterpret_cast<uint4*>(&kt[(TG * k + ld_tok) * KP + 8 * ld_piece]) = kr[k];
+      *reinterpret_cast<uint4*>(&vt[(TG * k + ld_tok) * KP + 8 * ld_piece]) = vr[k];
     }
     wave_lds_fence();
-    if (st_next < st_end) load_v(st_next);
+    if (st_next < st_end) load_step(st_next);
 #pragma unroll
-    for (int rt = 0; rt < NRT; ++rt)
+    for (int tt = 0; tt < 2; ++tt) {
+      bf16x8 kf[DS];
 #pragma unroll
-      for (int tt = 0; tt < 2; ++tt) {
+      for (int j = 0; j < DS; ++j) kf[j] = *reinterpret_cast<const bf16x8*>(&kt[(16 * tt + col) * KP + 32 * j + 8 * qd]);
+#pragma unroll
+      for (int rt = 0; rt < NRT; ++rt) {
         floatx4 acc = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-        for (int j = 0; j < DS; ++j) acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kf[tt][j], qf[rt][j], acc, 0, 0, 0);
+        for (int j = 0; j < DS; ++j) acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kf[j], qf[rt][j], acc, 0, 0, 0);
         s[rt][tt] = acc;
       }
-    if (st_next < st_end) load_k(st_next);
+    }
   };
-  // O^T += V^T P^T
+  // O^T += V^T P^T (V^T through the transposing LDS read, see the shared-tile kernel)
   auto step_pv = [&](const bf16x8 (&pf)[NRT]) {
 #pragma unroll
     for (int dt = 0; dt < DT; ++dt) {
-      union { uint2 u[2]; bf16x8 v; } vf;
-      const __bf16* rowp = &vt[(16 * dt + col) * VT_PITCH];
-      vf.u[0] = *reinterpret_cast<const uint2*>(rowp + 4 * qd);
-      vf.u[1] = *reinterpret_cast<const uint2*>(rowp + 16 + 4 * qd);
+      union { v4i16 h[2]; bf16x8 v; } vf;
+      const __bf16* rowp = &vt[(4 * qd + (col >> 2)) * KP + 16 * dt + 4 * (col & 3)];
+      vf.h[0] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_v4i16*)(rowp));
+      vf.h[1] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_v4i16*)(rowp + 16 * KP));
 #pragma unroll
       for (int rt = 0; rt < NRT; ++rt) o[rt][dt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(vf.v, pf[rt], o[rt][dt], 0, 0, 0);
     }
@@ -397,6 +384,7 @@ __global__ __launch_bounds__(256) void forest_attention_kernel(AttnArgs a) {
 
   // ---- merge the token groups of the workgroup through LDS
   if (TW > 1) {
+    __syncthreads();                   // every wave is done with its tiles
     if (tw > 0) {
       const int slot = (tw - 1) * RW + rw;
 #pragma unroll
