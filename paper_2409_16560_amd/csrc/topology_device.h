@@ -10,11 +10,9 @@ struct dsbd_tree_range {
   bool valid;       // false: the offsets are unusable and nothing of the tree may be touched
 };
 
-__device__ __forceinline__ dsbd_tree_range dsbd_tree_range_of(int b, int n_nodes, const int32_t* __restrict__ tree_off,
-                                                              int max_tree_nodes) {
+__device__ __forceinline__ dsbd_tree_range dsbd_tree_range_between(int base, int end, int n_nodes, int max_tree_nodes) {
   dsbd_tree_range t;
-  t.base = tree_off[b];
-  const int end = tree_off[b + 1];
+  t.base = base;
   t.bad = 0;
   t.valid = !(t.base < 0 || end > n_nodes || end <= t.base);
   t.n_all = t.valid ? end - t.base : 0;
@@ -25,6 +23,11 @@ __device__ __forceinline__ dsbd_tree_range dsbd_tree_range_of(int b, int n_nodes
     t.n = min(t.n, min(max_tree_nodes, DSBD_MAX_TREE_NODES));
   }
   return t;
+}
+
+__device__ __forceinline__ dsbd_tree_range dsbd_tree_range_of(int b, int n_nodes, const int32_t* __restrict__ tree_off,
+                                                              int max_tree_nodes) {
+  return dsbd_tree_range_between(tree_off[b], tree_off[b + 1], n_nodes, max_tree_nodes);
 }
 
 // This lane's entry of the tree's parent array (global index of node `lane`'s parent; -1 beyond the tree).

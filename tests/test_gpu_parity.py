@@ -937,3 +937,30 @@ def test_row_statistics_at_the_edges_of_their_rounds(V, same):
         assert float((lse.double() - ref).abs().max()) <= tol
         ref_lp = torch.where(par >= 0, z.double()[par.clamp(min=0), tok] - ref[par.clamp(min=0)], torch.zeros_like(ref))
         assert float((logp.double() - ref_lp).abs().max()) <= 2 * tol
+
+
+@pytest.mark.parametrize("D", [128, 64])
+@pytest.mark.parametrize("name,kw", [
+    # how the work is handed out: a lane per tree, a thread per tree (above 64 trees), plain arithmetic (above 256);
+    # long and short, large and small trees side by side, so that only some of them are split
+    ("6 unequal prompts", dict(n_prompts=6, W=(1, 2), L=(16, 2500), tree_nodes=(1, 40), Hq=8, Hkv=2)),
+    ("6 unequal prompts, narrow", dict(n_prompts=6, W=(1, 2), L=(16, 4500), tree_nodes=(1, 14), Hq=4, Hkv=2)),
+    ("70 trees", dict(n_prompts=70, W=1, L=(3, 900), tree_nodes=(1, 9), Hq=4, Hkv=1)),
+    ("70 trees, narrow", dict(n_prompts=70, W=1, L=(3, 900), tree_nodes=(1, 9), Hq=2, Hkv=2)),
+    ("260 trees", dict(n_prompts=260, W=1, L=(3, 60), tree_nodes=(1, 12), Hq=4, Hkv=1)),
+] + [
+    # rows per block at the edges of what the waves take: 32, 64 (two token halves up to here), 128, and one node more
+    ("%d nodes" % n, dict(n_prompts=1, W=2, L=700, tree_nodes=n, Hq=8, Hkv=2)) for n in (8, 9, 16, 17, 24, 32, 33, 48)
+])
+def test_forest_attention_work_places(name, kw, D):
+    gu = _gu()
+    w = make_workload("c4", V=64, D=D, **kw)
+    print("case", name, D, "trees", w.n_trees, "N", w.n_nodes, flush=True)
+    d = gu.DeviceWorkload(w)
+    anc = torch.zeros(w.n_nodes, dtype=torch.int64, device="cuda")
+    out, lse, fault = d.attention(anc_mask_out=anc)
+    torch.cuda.synchronize()
+    assert int(fault.item()) == 0
+    ref_out, ref_lse = gu.oracle_attention(w)
+    print("max abs err out/lse", gu.compare_attention(w, out, lse, ref_out, ref_lse), flush=True)
+    assert int((anc != 0).sum()) == w.n_nodes        # one wave per tree has written its bitmaps
