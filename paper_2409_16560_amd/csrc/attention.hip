@@ -917,45 +917,68 @@ void forest_attention_dma_kernel(AttnArgs a) {
 }
 
 // Merge the KV splits of the rows that have several: out = sum_s 2^(m_s-M) O_s / sum_s 2^(m_s-M) l_s.  The workgroups of
-// the rows' first splits have left where a row's partial results are.
-template <int D>
+// the rows' first splits have left where a row's partial results are.  SG threads share four channels of a row: each takes
+// every SG-th split, eight at a time with all their loads in flight, then they meet in the LDS.  Many rows are bound by
+// the partial results' bytes and take SG = 1 (8 beams x 31 nodes x 32 heads, 8 splits: 7.8 us, SG = 4: 11.1); few rows of
+// many splits by a thread's round trips, SG = 4 (2 x 23 nodes x 32 heads, 32 splits: 6.8 us against 8.0).
+template <int D, int SG>
 __global__ __launch_bounds__(AT_BLOCK) void forest_attention_combine_kernel(AttnArgs a) {
   constexpr int QPR = D / 4;                 // float4 quads per row
-  const long long gid = (long long)blockIdx.x * AT_BLOCK + threadIdx.x;
-  const long long row = gid / QPR;
-  const int quad = (int)(gid % QPR);
-  if (row >= (long long)a.n_nodes * a.Hq) return;
-  const int2 parts = a.row_parts[row];
+  constexpr int RPB = AT_BLOCK / (QPR * SG); // rows per workgroup
+  __shared__ floatx4 s_acc[SG][SG > 1 ? RPB * QPR : 1];
+  __shared__ float2 s_ml[SG][RPB];
+  const int lr = threadIdx.x % (RPB * QPR), sg = threadIdx.x / (RPB * QPR);
+  const long long row = (long long)blockIdx.x * RPB + lr / QPR;
+  const int quad = lr % QPR;
+  const bool in = row < (long long)a.n_nodes * a.Hq;
+  const int2 parts = in ? a.row_parts[row] : make_int2(0, 0);
   const int nsplit = parts.y;
   // (one part: already written by the main kernel; the rows of a tree with unusable offsets hold nothing to go by)
-  if (nsplit < 2 || nsplit > AT_MAX_SPLIT || parts.x < 0 ||
-      parts.x + (long long)(nsplit - 1) * a.rows_block >= (long long)a.n_slots * a.rows_block) return;
-  // Eight splits at a time with all their loads in flight (a loop of one load and one use per split is bound by
-  // memory latency); the running reference M is raised batch by batch.
+  const bool live = nsplit >= 2 && nsplit <= AT_MAX_SPLIT && parts.x >= 0 &&
+                    parts.x + (long long)(nsplit - 1) * a.rows_block < (long long)a.n_slots * a.rows_block;
   float M = NEG_BIG, L = 0.f;
   floatx4 acc = {0.f, 0.f, 0.f, 0.f};
-  for (int s0 = 0; s0 < nsplit; s0 += 8) {
-    float2 ml[8];
-    floatx4 v[8];
+  if (live) {
+    for (int s0 = sg; s0 < nsplit; s0 += 8 * SG) {
+      float2 ml[8];
+      floatx4 v[8];
 #pragma unroll
-    for (int j = 0; j < 8; ++j) {
-      const long long prow = parts.x + (long long)min(s0 + j, nsplit - 1) * a.rows_block;
-      ml[j] = *reinterpret_cast<const float2*>(&a.part_ml[prow * 2]);
-      v[j] = *reinterpret_cast<const floatx4*>(&a.part_o[prow * D + 4 * quad]);
-    }
-    float Mb = M;
-#pragma unroll
-    for (int j = 0; j < 8; ++j)
-      if (s0 + j < nsplit) Mb = fmaxf(Mb, ml[j].x);
-    const float keep = exp2f(M - Mb);                   // 1 when the reference stays
-    L *= keep; acc *= keep; M = Mb;
-#pragma unroll
-    for (int j = 0; j < 8; ++j)
-      if (s0 + j < nsplit) {
-        const float w = exp2f(ml[j].x - M);
-        L += w * ml[j].y;
-        acc += w * v[j];
+      for (int j = 0; j < 8; ++j) {
+        if (j > 0 && s0 + j * SG >= nsplit) continue;
+        const long long prow = parts.x + (long long)(s0 + j * SG) * a.rows_block;
+        ml[j] = *reinterpret_cast<const float2*>(&a.part_ml[prow * 2]);
+        v[j] = *reinterpret_cast<const floatx4*>(&a.part_o[prow * D + 4 * quad]);
       }
+      float Mb = M;
+#pragma unroll
+      for (int j = 0; j < 8; ++j)
+        if (s0 + j * SG < nsplit) Mb = fmaxf(Mb, ml[j].x);
+      const float keep = exp2f(M - Mb);                   // 1 when the reference stays
+      L *= keep; acc *= keep; M = Mb;
+#pragma unroll
+      for (int j = 0; j < 8; ++j)
+        if (s0 + j * SG < nsplit) {
+          const float w = exp2f(ml[j].x - M);
+          L += w * ml[j].y;
+          acc += w * v[j];
+        }
+    }
+  }
+  if constexpr (SG > 1) {
+    if (sg > 0) {
+      s_acc[sg][lr] = acc;
+      if (quad == 0) s_ml[sg][lr / QPR] = make_float2(M, L);
+    }
+    __syncthreads();
+  }
+  if (sg > 0 || !live) return;
+#pragma unroll
+  for (int g = 1; g < SG; ++g) {
+    const float2 o = s_ml[g][lr / QPR];
+    const float Mn = fmaxf(M, o.x), e1 = exp2f(M - Mn), e2 = exp2f(o.x - Mn);
+    L = L * e1 + o.y * e2;
+    acc = acc * e1 + s_acc[g][lr] * e2;
+    M = Mn;
   }
   write_row_part<D>(a, (int)(row / a.Hq), (int)(row % a.Hq), quad, M, L, acc);
 }
@@ -1031,8 +1054,12 @@ void launch_attention(const AttnPlan& p, const AttnArgs& a, hipStream_t stream) 
   else if (p.nrt == 1) dsbd_launch(DSBD_KERNEL_ATTENTION, forest_attention_kernel<D, 1>, grid, block, 0, stream, a);
   else dsbd_launch(DSBD_KERNEL_ATTENTION, forest_attention_kernel<D, 2>, grid, block, 0, stream, a);
   if (p.merge) {
-    const long long threads = (long long)a.n_nodes * a.Hq * (D / 4);
-    hipLaunchKernelGGL((forest_attention_combine_kernel<D>), dim3((unsigned)((threads + AT_BLOCK - 1) / AT_BLOCK)), block, 0, stream, a);
+    const long long rows = (long long)a.n_nodes * a.Hq, wgs = (rows * (D / 4) + AT_BLOCK - 1) / AT_BLOCK;
+    if (wgs < 256 && p.nsplit > 8) {          // fewer workgroups than compute units
+      hipLaunchKernelGGL((forest_attention_combine_kernel<D, 4>), dim3((unsigned)((rows * D + AT_BLOCK - 1) / AT_BLOCK)), block, 0, stream, a);
+    } else {
+      hipLaunchKernelGGL((forest_attention_combine_kernel<D, 1>), dim3((unsigned)wgs), block, 0, stream, a);
+    }
   }
 }
 
