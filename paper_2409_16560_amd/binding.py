@@ -154,12 +154,39 @@ def _ptr(t: Optional[torch.Tensor]):
 
 
 def _stream(stream):
-    s = stream if stream is not None else torch.cuda.current_stream()
-    return C.c_void_p(s.cuda_stream)
+    # (the raw handle of the current stream: building a torch.cuda.Stream object for it takes 3 us)
+    if stream is not None:
+        return stream.cuda_stream
+    return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
 
 
 def _i32(t, dev):
+    if isinstance(t, torch.Tensor) and t.dtype is torch.int32 and t.device == dev and t.is_contiguous():
+        return t
     return torch.as_tensor(t, dtype=torch.int32).to(dev).contiguous()
+
+
+# Zeroed fault words for calls that were not given one.  A torch.zeros(1) per call is a kernel launch of its own (5 us of
+# host time, 3 us on the device); here one fill serves 64 calls, each word is handed out once.  The words of a fill belong
+# to the stream it ran on, so every later user on that stream is ordered behind it.  At most 64 streams' worth is kept.
+_FAULT_WORDS = 64
+_fault_words = {}
+
+
+def _fault_word(dev):
+    if torch._C._cuda_isCurrentStreamCapturing():
+        return torch.zeros(1, dtype=torch.int32, device=dev)      # (the fill has to be part of the graph)
+    idx = dev.index if dev.index is not None else torch._C._cuda_getDevice()
+    key = (idx, torch._C._cuda_getCurrentRawStream(idx))
+    try:
+        return _fault_words[key].pop()
+    except (KeyError, IndexError):
+        words = list(torch.zeros(_FAULT_WORDS, dtype=torch.int32, device=dev).split(1))
+        mine = words.pop()
+        if len(_fault_words) >= 64:
+            _fault_words.clear()
+        _fault_words[key] = words
+        return mine
 
 
 class Forest:
@@ -255,7 +282,7 @@ def dsbd_forest_attention(forest: Forest, kv: PrefixKV, q, k_tree, v_tree, scale
     if lse is None and want_lse:
         lse = torch.empty((N, Hq), dtype=torch.float32, device=dev)
     if fault is None:
-        fault = torch.zeros(1, dtype=torch.int32, device=dev)
+        fault = _fault_word(dev)
     if workspace is None:
         nbytes = int(lib.dsbd_forest_attention_workspace_bytes(C.byref(f), C.byref(k), Hq, Hkv, D))
         if nbytes == 0 and N > 0:
@@ -299,7 +326,7 @@ class VerifyResult:
             e((N,), torch.float32), e((P,), torch.int32), e((P, Lw), torch.int32), e((P,), torch.int32),
             e((P, W_cap), torch.int32), e((P, W_cap), torch.int32), e((P, W_cap), torch.int32),
             e((P, W_cap), torch.float64), e((P, W_cap), torch.float64), e((P,), torch.int32),
-            torch.zeros(1, dtype=torch.int32, device=dev), W_cap)
+            _fault_word(dev), W_cap)
 
 
 def _params(W_L, W_min, W_cap, t, top_k=0, top_p=1.0):
@@ -422,8 +449,7 @@ class NextBeams:
         e = lambda shape, dt: torch.empty(shape, dtype=dt, device=dev)
         return NextBeams(e((P,), torch.int32), e((P, W_cap), torch.int32), e((P, W_cap), torch.int32),
                          e((P, W_cap), torch.int32), e((P, W_cap, plen), torch.int32), e((P, W_cap), torch.int32),
-                         e((P, W_cap), torch.float64), e((P, W_cap), torch.float64),
-                         torch.zeros(1, dtype=torch.int32, device=dev))
+                         e((P, W_cap), torch.float64), e((P, W_cap), torch.float64), _fault_word(dev))
 
 
 def dsbd_select_beams(forest: Forest, verified: VerifyResult, keep_one=False, result: NextBeams = None, stream=None):
@@ -471,7 +497,7 @@ def dsbd_commit_kv(forest: Forest, src: PrefixKV, k_tree, v_tree, plan: NextBeam
     assert dst.k_ptr.numel() == forest.n_prompts * W_cap
     Hkv, D = k_tree.shape[1], k_tree.shape[2]
     if fault is None:
-        fault = torch.zeros(1, dtype=torch.int32, device=k_tree.device)
+        fault = _fault_word(k_tree.device)
     rc = lib.dsbd_commit_kv(C.byref(f), C.byref(k), _ptr(k_tree), _ptr(v_tree), int(Hkv), int(D), C.byref(nx),
                             int(W_cap), C.byref(d), _ptr(fault), _stream(stream))
     _check(rc, "dsbd_commit_kv")
@@ -496,11 +522,11 @@ def dsbd_draft_layer(beam_off, logits_draft, beam_logp_draft, u, W_S, *, max_pro
     din = _DraftIn(int(P), int(n_beams), int(max_prompt_beams), int(V), _ptr(beam_off), _ptr(logits_draft),
                    _ptr(beam_logp_draft), _ptr(u))
     parent = torch.empty((P, W_S), dtype=torch.int32, device=dev)
-    token = torch.empty((P, W_S), dtype=torch.int32, device=dev)
+    token = torch.empty_like(parent)
     logp = torch.empty((P, W_S), dtype=torch.float64, device=dev)
     dout = _DraftOut(_ptr(parent), _ptr(token), _ptr(logp))
     if fault is None:
-        fault = torch.zeros(1, dtype=torch.int32, device=dev)
+        fault = _fault_word(dev)
     if workspace is None:
         nbytes = int(lib.dsbd_draft_layer_workspace_bytes(C.byref(din), int(W_S), int(top_k), float(top_p)))
         if nbytes == 0:
@@ -524,22 +550,27 @@ def dsbd_build_forest(root_off, layer_parent, layer_token, root_token=None, *, n
     gamma = int(layer_parent.shape[0]) if layer_parent is not None and layer_parent.numel() > 0 else 0
     W_S = int(layer_parent.shape[1]) // P if gamma else 0
     N = int(n_roots) + gamma * P * W_S
-    i32 = lambda n: torch.empty(max(n, 1), dtype=torch.int32, device=dev)
-    tree_prompt, tree_off, parent, token, rank = i32(n_roots), i32(n_roots + 1), i32(N), i32(N), i32(N)
-    node_of_root, node_of, mx = i32(n_roots), i32(gamma * P * W_S), i32(1)
-    fo = _ForestOut(_ptr(tree_prompt), _ptr(tree_off), _ptr(parent), _ptr(token), _ptr(rank), _ptr(node_of_root),
-                    _ptr(node_of), _ptr(mx))
+    # one allocation, cut into the arrays (their places are passed as numbers: an array of no entries has no pointer)
+    n_roots, D = int(n_roots), gamma * P * W_S
+    sizes = (n_roots, n_roots + 1, N, N, N, n_roots, D, 1)
+    buf = torch.empty(sum(sizes), dtype=torch.int32, device=dev)
+    tree_prompt, tree_off, parent, token, rank, node_of_root, node_of, mx = buf.split_with_sizes(sizes)
+    at, places = buf.data_ptr(), []
+    for n in sizes:
+        places.append(at)
+        at += 4 * n
+    fo = _ForestOut(*places)
     if fault is None:
-        fault = torch.zeros(1, dtype=torch.int32, device=dev)
+        fault = _fault_word(dev)
     for t_ in (root_off, layer_parent, layer_token, root_token):
         assert t_ is None or (t_.dtype == torch.int32 and t_.is_contiguous())
     rc = lib.dsbd_build_forest(int(P), int(n_roots), gamma, W_S, _ptr(root_off), _ptr(root_token),
                                _ptr(layer_parent) if gamma else None, _ptr(layer_token) if gamma else None,
                                C.byref(fo), _ptr(fault), _stream(stream))
     _check(rc, "dsbd_build_forest")
-    f = Forest(tree_prompt[:n_roots], tree_off[:n_roots + 1], parent[:N], token[:N], rank[:N], n_prompts=P,
+    f = Forest(tree_prompt, tree_off, parent, token, rank, n_prompts=P,
                max_tree_nodes=64, max_depth=gamma, max_prompt_trees=int(max_prompt_trees), device=dev)
-    return f, node_of_root[:n_roots], node_of[:gamma * P * W_S].view(gamma, P * W_S) if gamma else node_of[:0], mx, fault
+    return f, node_of_root, node_of.view(gamma, P * W_S) if gamma else node_of, mx, fault
 
 
 def dsbd_stream_read_probe(buf: torch.Tensor, reps: int = 10, stream=None) -> float:
