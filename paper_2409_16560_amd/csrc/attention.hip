@@ -1021,7 +1021,9 @@ AttnPlan make_plan(const dsbd_forest* f, const dsbd_kv* kv, int Hq, int Hkv, int
     p.nsplit = most_split;
     p.grid = units + (p.nsplit > 1 ? p.slots : 0);
   } else {
-    p.nsplit = 1;
+    // (more trees than threads fill the device by themselves, unless they have a single KV head)
+    p.nsplit = most > 0 ? (int)((p.slots + most - 1) / most) : 1;
+    if (p.nsplit > most_split) p.nsplit = most_split;
     if (const int v = dsbd_knobs().attn_nsplit; v >= 1 && v <= AT_MAX_SPLIT) p.nsplit = v;   // tuning knob: KV splits of every unit
     p.grid = most * p.nsplit;
   }

@@ -33,9 +33,6 @@ struct WorkspaceCarver {
 // Tuning overrides and test hooks from the environment, read once per process (knobs.hip).
 struct DsbdKnobs {
   int attn_nsplit;             // DSBD_ATTN_NSPLIT: KV splits per (tree, KV head, row block); 0 = the plan's choice
-  bool attn_waves8;            // DSBD_ATTN_WAVES8: 8 waves x 16 rows in the shared-tile kernel
-  bool attn_staged;            // DSBD_ATTN_STAGED: the register-staged tile kernel also for head size 128
-  bool attn_trace;             // DSBD_ATTN_TRACE: timeline of the attention kernel (instrumented builds)
   int verify_g;                // DSBD_VERIFY_G: workgroups per prompt of the layer kernel; 0 = the plan's choice
   bool verify_trace;           // DSBD_VERIFY_TRACE: timeline of the layer kernel into the workspace ...
   int verify_trace_wg;         // ... of workgroup N - 1 when the variable holds N > 1 (else of the first)
@@ -44,7 +41,7 @@ struct DsbdKnobs {
   int verify_lds_slice;        // DSBD_VERIFY_LDS_SLICE: largest joint slice kept in the LDS; -1 = the plan's choice
   int warp_fast;               // DSBD_WARP_FAST: 0 = the warping selection always takes its tree form
   int event_fence;             // DSBD_EVENT_FENCE: 1 = the library's cross-stream events keep HIP's system-scope fence; 0 = they order
-                               // device work only (no cache write-back for the host's sake at every fork and join)
+                               // device work only (no cache write-back for the host's sake at every one)
 };
 const DsbdKnobs& dsbd_knobs();
 

@@ -17,9 +17,6 @@ int env_int(const char* name, int dflt) {
 
 void load(DsbdKnobs& k) {
   k.attn_nsplit = env_int("DSBD_ATTN_NSPLIT", 0);
-  k.attn_waves8 = getenv("DSBD_ATTN_WAVES8") != nullptr;
-  k.attn_staged = getenv("DSBD_ATTN_STAGED") != nullptr;
-  k.attn_trace = getenv("DSBD_ATTN_TRACE") != nullptr;
   k.verify_g = env_int("DSBD_VERIFY_G", 0);
   k.verify_trace = getenv("DSBD_VERIFY_TRACE") != nullptr;
   k.verify_trace_wg = 0;
