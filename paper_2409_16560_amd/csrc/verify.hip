@@ -480,7 +480,7 @@ __host__ __device__ inline SliceCut slice_cut(int nI, int V, int G) {
     c.rows_per_wg = (nI + G - 1) / G; c.wg_per_row = 0; c.len = (long long)c.rows_per_wg * V;
   } else {
     c.rows_per_wg = 0; c.wg_per_row = G / nI;
-    c.len = (((long long)V + c.wg_per_row - 1) / c.wg_per_row + 1) & ~1LL;
+    c.len = (long long)((((unsigned int)V + c.wg_per_row - 1) / c.wg_per_row + 1) & ~1u);      // (V is at most 2^30)
   }
   return c;
 }
@@ -680,6 +680,65 @@ void verify_layers_kernel(LayersArgs a) {
   __syncthreads();
   stamp(4);
   if (sh.sbad & DSBD_FAULT_TOPOLOGY) { n_roots = 0; n_pn = 0; }
+  // this workgroup's share of I x V, as a function of the number of rows (worked out when that changes; 32-bit
+  // divisions only: as five 64-bit ones it took 1.3 us)
+  int geo_nI = -1, geo_ilo = 0, geo_ihi = -1, geo_pieces = 1;
+  SliceCut geo_cut = {0, 1, 0};
+  long long geo_lo = 0, geo_hi = 0;
+  auto set_geometry = [&](int rows_) {
+    const int rows = __builtin_amdgcn_readfirstlane(rows_);
+    if (rows == geo_nI) return;
+    geo_nI = rows;
+    geo_cut = slice_cut(rows, V, a.G);
+    int lo = 0, hi = 0;                                  // this workgroup's entries of row geo_ilo (pieces)
+    if (geo_cut.rows_per_wg > 0) {
+      const int first = min(rows, g * geo_cut.rows_per_wg), last = min(rows, first + geo_cut.rows_per_wg);
+      geo_ilo = first; geo_ihi = last - 1; geo_pieces = 1;
+      geo_lo = (long long)first * V; geo_hi = (long long)last * V;
+      return;
+    }
+    geo_pieces = (int)(((unsigned int)V + (unsigned int)geo_cut.len - 1u) / (unsigned int)geo_cut.len);
+    geo_ilo = min(rows, (int)((unsigned int)g / (unsigned int)geo_cut.wg_per_row));
+    if (geo_ilo < rows) {
+      const int k = g - geo_ilo * geo_cut.wg_per_row;
+      lo = (int)min((long long)V, k * geo_cut.len);
+      hi = (int)min((long long)V, (k + 1) * geo_cut.len);
+    }
+    geo_ihi = hi > lo ? geo_ilo : geo_ilo - 1;
+    geo_lo = (long long)geo_ilo * V + lo;
+    geo_hi = (long long)geo_ilo * V + hi;
+  };
+  // The first two rounds of logits of this workgroup's first row of a layer, requested as soon as the layer's rows are
+  // known; the book-keeping that needs no logits runs while they travel (its barriers order the LDS only).
+  float eA_p[XU], eA_q[XU], eB_p[XU], eB_q[XU];
+  bool early = false;
+#pragma unroll
+  for (int k = 0; k < XU; ++k) { eA_p[k] = 0.f; eA_q[k] = 0.f; eB_p[k] = 0.f; eB_q[k] = 0.f; }
+  auto request_first = [&](const int* row_nodes) __attribute__((always_inline)) {
+    early = geo_ihi >= geo_ilo;
+    if (!early) return;
+    const int i = geo_ilo;
+    const int node = row_nodes[i];
+    const int x_lo = (int)(max(geo_lo, (long long)i * V) - (long long)i * V);
+    const int x_hi = (int)(min(geo_hi, (long long)(i + 1) * V) - (long long)i * V);
+    const float* zp = a.zp + (long long)node * V;
+    const float* zq = a.zq + (long long)node * V;
+    const int xA = x_lo + tid, xB = xA + XU * VL_BLOCK;
+#pragma unroll
+    for (int k = 0; k < XU; ++k) {
+      const int xx = min(xA + k * VL_BLOCK, x_hi - 1);
+      eA_p[k] = zp[xx]; eA_q[k] = zq[xx];
+    }
+#pragma unroll
+    for (int k = 0; k < XU; ++k) {
+      const int xx = min(xB + k * VL_BLOCK, x_hi - 1);
+      eB_p[k] = zp[xx]; eB_q[k] = zq[xx];
+    }
+  };
+  if (n_roots > 0) {
+    set_geometry(n_roots);
+    request_first(sh.I_node);
+  }
   // node depths (and the validation of the parent pointers): one wave per tree walks the parent chains with lane
   // shuffles over the entries already in the LDS; depths land in S_tmp (prompt-local index)
   for (int b = wave; b < n_roots; b += VL_WAVES) {
@@ -703,7 +762,7 @@ void verify_layers_kernel(LayersArgs a) {
     // (the node's tree within the prompt rides in the bits above its depth: the next-beam plan names it)
     if (lane < t.n) sh.S_tmp[t.base - n_begin + lane] = (d_mine & NODE_DEPTH_MASK) | (b << NODE_TREE_SHIFT);
   }
-  __syncthreads();
+  lds_barrier();
   if (tid < n_pn) sh.n_depth[tid] = (short)sh.S_tmp[tid];      // (read after later barriers only)
   stamp(5);
   bad |= sh.sbad;
@@ -784,7 +843,7 @@ void verify_layers_kernel(LayersArgs a) {
     (&sh.acc_prev[0][0])[tid] = acc0_w;
     slot_post(slots + a.sl.acc0 + tid, __longlong_as_double((long long)acc0_w), acc0_tag);
   }
-  __syncthreads();
+  lds_barrier();
   stamp(6);
 
   // total over the workgroup of one value per thread: valid in every thread after the barrier inside
@@ -798,67 +857,17 @@ void verify_layers_kernel(LayersArgs a) {
   };
   auto give_up = [&]() { sh.abort = 1; atomicOr(a.fault, DSBD_FAULT_SYNC_TIMEOUT); };
 
-  // this workgroup's share of I x V, as a function of the number of rows
-  int geo_nI = -1, geo_ilo = 0, geo_ihi = -1, geo_pieces = 1;
-  SliceCut geo_cut = {0, 1, 0};
-  long long geo_lo = 0, geo_hi = 0;
-
-  // (worked out when the number of rows changes: a handful of 64-bit divisions, on every workgroup's critical
-  // path, that a fixed layer width repeats unchanged layer after layer)
-  auto set_geometry = [&](int rows) {
-    if (rows == geo_nI) return;
-    const long long all = (long long)rows * V;
-    geo_nI = rows;
-    geo_cut = slice_cut(rows, V, a.G);
-    geo_lo = all; geo_hi = all;
-    if (geo_cut.rows_per_wg > 0) {
-      geo_lo = min(all, (long long)g * geo_cut.rows_per_wg * V);
-      geo_hi = min(all, geo_lo + (long long)geo_cut.rows_per_wg * V);
-    } else if (g / geo_cut.wg_per_row < rows) {
-      const long long r0 = (long long)(g / geo_cut.wg_per_row) * V, k = g % geo_cut.wg_per_row;
-      geo_lo = r0 + min((long long)V, k * geo_cut.len);
-      geo_hi = r0 + min((long long)V, (k + 1) * geo_cut.len);
-    }
-    geo_ilo = (int)div_floor(geo_lo, V);
-    geo_ihi = geo_hi > geo_lo ? (int)div_floor(geo_hi - 1, V) : geo_ilo - 1;
-    geo_pieces = (int)((V + geo_cut.len - 1) / geo_cut.len);
-  };
   int passed_nacc = -1;      // >= 0: the layer before passed with this many accepted beams, not yet handed over
 
   stamp(1);
   for (int l = 1; l <= gamma + 1; ++l) {
     stamp(10 + l);
-    // The layer before passed: its accepted beams are this layer's inputs.  The first two rounds of logits of this
-    // workgroup's first row are requested BEFORE the hand-over's book-keeping, which then runs while they travel
-    // (its barriers order the LDS only).
-    float eA_p[XU], eA_q[XU], eB_p[XU], eB_q[XU];
-    bool early = false;
-#pragma unroll
-    for (int k = 0; k < XU; ++k) { eA_p[k] = 0.f; eA_q[k] = 0.f; eB_p[k] = 0.f; eB_q[k] = 0.f; }
+    // The layer before passed: its accepted beams are this layer's inputs.
     if (passed_nacc >= 0) {
       const int nacc = passed_nacc;
       passed_nacc = -1;
       set_geometry(nacc);
-      if (geo_ihi >= geo_ilo) {
-        const int i = geo_ilo;
-        const int node = sh.A_node[i];
-        const int x_lo = (int)(max(geo_lo, (long long)i * V) - (long long)i * V);
-        const int x_hi = (int)(min(geo_hi, (long long)(i + 1) * V) - (long long)i * V);
-        const float* zp = a.zp + (long long)node * V;
-        const float* zq = a.zq + (long long)node * V;
-        const int xA = x_lo + tid, xB = xA + XU * VL_BLOCK;
-#pragma unroll
-        for (int k = 0; k < XU; ++k) {
-          const int xx = min(xA + k * VL_BLOCK, x_hi - 1);
-          eA_p[k] = zp[xx]; eA_q[k] = zq[xx];
-        }
-#pragma unroll
-        for (int k = 0; k < XU; ++k) {
-          const int xx = min(xB + k * VL_BLOCK, x_hi - 1);
-          eB_p[k] = zp[xx]; eB_q[k] = zq[xx];
-        }
-        early = true;
-      }
+      request_first(sh.A_node);
       // cumulative likelihoods of the accepted beams (fp64)
       if (tid < nacc) {
         const int n = sh.A_node[tid];
@@ -916,6 +925,64 @@ void verify_layers_kernel(LayersArgs a) {
       if (n_lds > 0) body(pl, ql, 0LL, n_lds);
       body(pbg, qbg, n_lds, len);
     };
+
+    // ===== while the first logits travel: candidates = depth-l nodes whose parent is an input beam, in (rank, node) order
+    // (this and the beam weights stood behind the exponential pass, beside the wait for the row sums, and were longer
+    // than that wait)
+    int M = 0;
+    float czp = 0.f, czq = 0.f;
+    if (!bonus) {
+      if (tid == 0) sh.counter = 0;
+      lds_barrier();
+      if (tid < n_pn && (sh.n_depth[tid] & NODE_DEPTH_MASK) == l) {
+        const int n = n_begin + tid;
+        const int par = sh.n_parent[tid];
+        const bool cand = par >= n_begin && par < n && sh.slot_of[par - n_begin] >= 0;
+        if (cand) {
+          const int at = atomicAdd(&sh.counter, 1);
+          sh.S_tmp[at] = n;
+          sh.S_zp[at] = __int_as_float(sh.n_rank[tid]);        // (its logits are stored there later)
+        } else if (g == 0) {
+          a.out.node_status[n] = DSBD_PRUNED;
+        }
+      }
+      lds_barrier();
+      M = __builtin_amdgcn_readfirstlane(sh.counter);
+      if (tid < M) {
+        const int n = sh.S_tmp[tid], rk = __float_as_int(sh.S_zp[tid]);
+        int pos = 0;
+#pragma unroll 8
+        for (int j = 0; j < M; ++j) {
+          const int n2 = sh.S_tmp[j], rk2 = __float_as_int(sh.S_zp[j]);
+          pos += (int)(rk2 < rk) | ((int)(rk2 == rk) & (int)(n2 < n));
+        }
+        sh.S_node[pos] = n;
+      }
+    }
+    // ===== beside them the beam weights = softmax of the cumulative likelihoods over I (Section 2.1), by one wave
+    if (wave == VL_WAVES - 1) {
+      const bool valid = lane < nI;
+      const double cp = sh.cum_p[min(lane, nI - 1)], cq = sh.cum_q[min(lane, nI - 1)];
+      const double mp = wave_max_f64(cp), mq = wave_max_f64(cq);
+      const double ep = valid ? exp_nonpos(cp - mp, sh.exp_tab) : 0.0;
+      const double eq = valid ? exp_nonpos(cq - mq, sh.exp_tab) : 0.0;
+      const double zp = wave_sum(ep), zq = wave_sum(eq);
+      if (valid) { sh.bw_p[lane] = ep / zp; sh.bw_q[lane] = eq / zq; }
+      // no beam of the layer with a likelihood above 0 under one of the models (stored likelihoods of -Inf), or a
+      // likelihood that is no number: the joint is 0/0
+      const bool lost = !(mp > -INFINITY && mp < INFINITY && mq > -INFINITY && mq < INFINITY) || __ballot(cp != cp || cq != cq) != 0ull;
+      if (lost && g == 0 && lane == 0) atomicOr(a.fault, DSBD_FAULT_NONFINITE);
+    }
+    if (!bonus) {
+      lds_barrier();
+      if (tid < M) {      // logits at the candidate's (parent beam, token): in flight until the candidates are tested
+        const int n = sh.S_node[tid];
+        const int par = sh.n_parent[n - n_begin];
+        const int tok = sh.n_token[n - n_begin];
+        czp = a.zp[(long long)par * V + tok];
+        czq = a.zq[(long long)par * V + tok];
+      }
+    }
 
     // ===== p_beam / q_beam over I x V: exponentials and this workgroup's share of the row sums.  The exponentials
     // are taken against the maximum of the workgroup's own piece of the row (found here, in the same pass over the
@@ -1057,6 +1124,9 @@ void verify_layers_kernel(LayersArgs a) {
         sh.u.wpart[((i - i_lo) * VL_WAVES + wave) * 2 + 1] = s_q;
       }
     }
+    early = false;
+#pragma unroll
+    for (int k = 0; k < XU; ++k) { eA_p[k] = 0.f; eA_q[k] = 0.f; eB_p[k] = 0.f; eB_q[k] = 0.f; }     // (not carried through the layer)
     stamp(100);
     __syncthreads();
     // ===== all-reduce of the rows' maxima and sums.  Only the workgroups that hold a piece of row i post its four
@@ -1082,59 +1152,6 @@ void verify_layers_kernel(LayersArgs a) {
       if (!slot_wait(slots + a.sl.acc0 + lane, acc0_tag, v, a.sync_limit)) give_up();
       (&sh.acc_prev[0][0])[lane] = (unsigned long long)__double_as_longlong(v);
     }
-    // ===== meanwhile: beam weights = softmax of the cumulative likelihoods over I (Section 2.1), by one wave
-    if (wave == 1) {
-      const bool valid = lane < nI;
-      double mp = -INFINITY, mq = -INFINITY;
-      for (int i = 0; i < nI; ++i) { mp = fmax(mp, sh.cum_p[i]); mq = fmax(mq, sh.cum_q[i]); }
-      const double ep = valid ? exp_nonpos(sh.cum_p[lane] - mp, sh.exp_tab) : 0.0;
-      const double eq = valid ? exp_nonpos(sh.cum_q[lane] - mq, sh.exp_tab) : 0.0;
-      const double zp = wave_sum(ep), zq = wave_sum(eq);
-      if (valid) { sh.bw_p[lane] = ep / zp; sh.bw_q[lane] = eq / zq; }
-      // no beam of the layer with a likelihood above 0 under one of the models (stored likelihoods of -Inf), or a
-      // likelihood that is no number: the joint is 0/0
-      const bool lost = !(mp > -INFINITY && mp < INFINITY && mq > -INFINITY && mq < INFINITY) ||
-                        __ballot(valid && (sh.cum_p[min(lane, 63)] != sh.cum_p[min(lane, 63)] ||
-                                           sh.cum_q[min(lane, 63)] != sh.cum_q[min(lane, 63)])) != 0ull;
-      if (lost && g == 0 && lane == 0) atomicOr(a.fault, DSBD_FAULT_NONFINITE);
-    }
-
-    // ===== and candidates = depth-l nodes whose parent is an input beam, in (rank, node) order
-    int M = 0;
-    float czp = 0.f, czq = 0.f;
-    if (!bonus) {
-      if (tid == 0) sh.counter = 0;
-      __syncthreads();
-      if (tid < n_pn && (sh.n_depth[tid] & NODE_DEPTH_MASK) == l) {
-        const int n = n_begin + tid;
-        const int par = sh.n_parent[tid];
-        const bool cand = par >= n_begin && par < n && sh.slot_of[par - n_begin] >= 0;
-        if (cand) sh.S_tmp[atomicAdd(&sh.counter, 1)] = n;
-        else if (g == 0) a.out.node_status[n] = DSBD_PRUNED;
-      }
-      __syncthreads();
-      M = sh.counter;
-      if (tid < M) {
-        const int n = sh.S_tmp[tid];
-        const int rk = sh.n_rank[n - n_begin];
-        int pos = 0;
-        for (int j = 0; j < M; ++j) {
-          const int n2 = sh.S_tmp[j];
-          const int rk2 = sh.n_rank[n2 - n_begin];
-          pos += (rk2 < rk) || (rk2 == rk && n2 < n);
-        }
-        sh.S_node[pos] = n;
-      }
-      __syncthreads();
-      if (tid < M) {      // logits at the candidate's (parent beam, token): in flight while the row sums arrive
-        const int n = sh.S_node[tid];
-        const int par = sh.n_parent[n - n_begin];
-        const int tok = sh.n_token[n - n_begin];
-        czp = a.zp[(long long)par * V + tok];
-        czq = a.zq[(long long)par * V + tok];
-      }
-    }
-
     // ===== rows' maxima and totals: thread (r, c) gathers column c = (row, model) from every R-th workgroup that holds
     // part of it and folds the pieces (sum relative to the piece's maximum) as it goes; the R partial results of a
     // column sit in R neighbouring lanes of one wave and are put on the column's maximum and added up by lane
