@@ -30,6 +30,7 @@
 #include <float.h>
 #include <limits.h>
 #include <stdlib.h>
+#include <algorithm>
 #include <atomic>
 #include <mutex>
 
@@ -2655,13 +2656,24 @@ VerifyPlan make_verify_plan(const dsbd_forest* f, int V, const dsbd_params* p, b
       if (Gk >= W && (Gk / W) * 4 >= (G / W) * 3) G = Gk;
     }
   }
-  // (sized by the joint of the input beams, which is what a fixed width keeps every layer at: an exchange among 64
-  // workgroups costs 1.7 us against 2.5 us among 256, and below about 4000 entries per workgroup the passes over a
-  // slice are shorter than that difference.  Measured: 8 beams x 32000 tokens 83 us with 64 workgroups, 88 us with
-  // 256; with the dynamic width, which runs many more exchanges, 147 us against 165 us.)
+  // (sized by the joint of the input beams, which is what a fixed width keeps every layer at: shorter slices make shorter
+  // passes and more partners longer exchanges.  Measured, call in us at 16 / 32 / 48 / 64 / 96 / 128 / 160 / 192 workgroups
+  // of a prompt: 4 x 32000 joint entries 49.4 / 38.1 / 36.1 / 36.0 / 36.6 / 36.3 / 37.6 / 37.8; 8 x 32000: 99.8 / 65.8 / 50.1 /
+  // 48.2 / 48.0 / 48.1 / 48.3 / 48.4; 5 x 128256 warped: 185 / 149 / 112 / 106.8 / 103.6 / 103.5 / 104.0 / 106.5; 8 x 128256:
+  // 516 / 303 / 238 / 181 / 154 / 121 / 116 / 108.  5 x 128256 plain: 324 / 201 / 140 /
+  // 121 / 81 / 77 / 73 / 75.  So 2000 entries per workgroup up to 128 of them, 4000 beyond.)
   const long long joint = (long long)f->max_prompt_trees * V;
-  const int by_work = (int)((joint + 3999) / 4000);
-  if (G > by_work) G = by_work;
+  long long by_work = (joint + 1999) / 2000;
+  if (by_work > 128) by_work = std::max(128LL, (joint + 3999) / 4000);
+  // warping wants enough pieces for its one-level selection (4 x 32000, top_k 32: 64 workgroups 76 us, 128: 60)
+  if (p->top_k > 0 && by_work < 4 * p->top_k + f->max_prompt_trees && joint >= 128LL * (4 * p->top_k + f->max_prompt_trees))
+    by_work = 4 * p->top_k + f->max_prompt_trees;
+  // (every layer has slots of its own, so forests tens of layers deep keep to 4000: workspaces that fitted 32 MiB still do)
+  const long long slot_bytes = (long long)(f->max_depth + 1) * 4 * (pl.I_cap + (p->top_k > 0 ? p->top_k : 0)) * (long long)sizeof(Slot);
+  if (slot_bytes * by_work > (8LL << 20)) by_work = std::min(by_work, (joint + 3999) / 4000);
+  if (G > by_work) G = (int)by_work;
+  // (workgroups beyond a multiple of the rows hold no piece but take part in every exchange)
+  if (f->max_prompt_trees > 0 && G > f->max_prompt_trees) G -= G % f->max_prompt_trees;
   if (knobs.verify_g >= 1 && (long long)knobs.verify_g * f->n_prompts <= resident) G = knobs.verify_g;   // tuning knob
   if (G < 1) G = 1;
   if (G > 256) G = 256;

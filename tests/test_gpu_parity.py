@@ -965,3 +965,22 @@ def test_forest_attention_work_places(name, kw, D):
     ref_out, ref_lse = gu.oracle_attention(w)
     print("max abs err out/lse", gu.compare_attention(w, out, lse, ref_out, ref_lse), flush=True)
     assert int((anc != 0).sum()) == w.n_nodes        # one wave per tree has written its bitmaps
+
+
+@pytest.mark.parametrize("kw,warp", [
+    # workgroups of a prompt: rounded to a multiple of its beams, raised for the one-level selection of a large top_k,
+    # held back where every layer of a deep forest brings exchange slots of its own
+    (dict(W=3, V=5003, tree_nodes=9), {}),
+    (dict(W=5, V=3001, tree_nodes=7), dict(top_k=32, top_p=0.9)),
+    (dict(W=8, V=2600, tree_nodes=7), dict(top_k=32, top_p=0.9)),
+    (dict(W=2, V=20011, tree_nodes=40, tree="chain"), {}),
+    (dict(W=2, V=40003, tree_nodes=60, tree="chain"), dict(top_k=32, top_p=0.95)),
+    (dict(W=7, V=45007, tree_nodes=5), {}),
+])
+def test_verify_workgroups_per_prompt(kw, warp):
+    gu = _gu()
+    w = make_workload("c2", L=8, Hq=2, Hkv=1, D=64, **kw)
+    d = gu.DeviceWorkload(w)
+    res = d.verify(t=-1.0, **warp)
+    torch.cuda.synchronize()
+    gu.compare_verify(res, gu.oracle_verify(w, t=-1.0, **warp), w)
