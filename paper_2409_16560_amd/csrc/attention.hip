@@ -57,7 +57,7 @@ struct AttnArgs {
   int by_tree;                  // splits chosen tree by tree on the device (else `nsplit` for every unit)
   int nsplit, n_rowblocks;      // row blocks: of the largest tree the caller announces
   int rows_block;               // query rows per workgroup
-  int wg_slots, min_units;      // by_tree: workgroups to spread the work over; least units of split work (steps or tiles) per split
+  int wg_slots;                 // by_tree: workgroups to spread the work over
   int n_slots;                  // partial results there is room for (the main kernel's grid)
   float* part_o;                // [n_slots][rows_block][D]
   float* part_ml;               // [n_slots][rows_block][2]
@@ -116,7 +116,7 @@ __device__ __forceinline__ void lds_barrier() {
 // of one or two - a single split per unit: 92 us where 26 are enough; 24 trees of 700 to 3000 tokens: 35 us, now 25.)
 struct WorkShare {
   int steps[AT_BLOCK], count[AT_BLOCK];
-  float wsum[4];
+  float wsum[4], usum[4];
   int b, rel, nsplit, nrb;
 };
 struct Place {
@@ -133,11 +133,24 @@ __device__ __forceinline__ const __bf16* lane_pointer(const void* p, int l) {
   return reinterpret_cast<const __bf16*>(((unsigned long long)hi << 32) | lo);
 }
 
-// Splits of a tree's units.  Rounded down, so that the workgroups of split units do not outnumber the slots; what is
-// whole in exact arithmetic must not fall below.
-__device__ __forceinline__ int splits_of(const AttnArgs& a, int steps, float total) {
-  const int ns = (int)((float)steps * (float)a.wg_slots / total + 1e-3f);
-  return max(1, min(min(ns, steps / a.min_units), min(a.nsplit, AT_MAX_SPLIT)));
+// Most splits worth their partial results for a unit of so many steps (32 tokens of a wave; or 64-token tiles): four
+// steps or tiles per split, and as little as two tiles for up to four splits.  Measured, whole call, us at 2 / 4 / 6 / 8 / 16
+// splits: 32 units of 33 tiles 30.4 / 22.2 / 20.9 / 21.1 / 26.3; of 9 tiles 17.4 / 15.5 / 16.8 / 16.5; 8 units of 17 steps
+// 15.8 / 14.2 / 13.8 / 14.1.
+__host__ __device__ __forceinline__ int split_limit(int steps, bool tiles) {
+  const int four = steps / 4, two = steps / 2;
+  const int most = tiles && four < 4 ? (two < 4 ? two : 4) : four;
+  return most < 1 ? 1 : (most > AT_MAX_SPLIT ? AT_MAX_SPLIT : most);
+}
+
+// Splits of a tree's units: one, and its share of the workgroups that are left when every unit has one.  The shares are
+// rounded down, so that all workgroups together are no more than the slots (or the units, if those are more), which is
+// the grid (slots and units side by side before: a ninth more workgroups and workspace, equal times).
+// (What is whole in exact arithmetic must not fall below: the slack adds less than half a workgroup over all units.)
+__device__ __forceinline__ int splits_of(const AttnArgs& a, int steps, float total, float units, bool tiles) {
+  const float left = fmaxf((float)a.wg_slots - units, 0.f);
+  const int ns = 1 + (int)((float)steps * left / total + 1e-3f);
+  return max(1, min(min(ns, split_limit(steps, tiles)), a.nsplit));
 }
 
 // False: nothing to do for this workgroup.
@@ -166,10 +179,10 @@ __device__ __forceinline__ bool work_place(const AttnArgs& a, WorkShare& w, Plac
     measure(base, end, Ls, Lo, steps, nrb);
     if (lane >= a.n_trees) { steps = 0; nrb = 0; }
     else if (bid == 0 && tid < 64 && nrb == 0) atomicOr(a.fault, DSBD_FAULT_TOPOLOGY);
-    float total = (float)(nrb * a.Hkv) * (float)steps;
+    float units = (float)(nrb * a.Hkv), total = units * (float)steps;
 #pragma unroll
-    for (int off = 32; off >= 1; off >>= 1) total += __shfl_xor(total, off);
-    const int ns = splits_of(a, steps, total), count = a.Hkv * nrb * ns;
+    for (int off = 32; off >= 1; off >>= 1) { total += __shfl_xor(total, off); units += __shfl_xor(units, off); }
+    const int ns = splits_of(a, steps, total, units, UNIT == 64), count = a.Hkv * nrb * ns;
     int first = 0;
     for (int o = 0; o < a.n_trees; ++o) {
       const int so = __builtin_amdgcn_readlane(steps, o), co = __builtin_amdgcn_readlane(count, o);
@@ -193,13 +206,14 @@ __device__ __forceinline__ bool work_place(const AttnArgs& a, WorkShare& w, Plac
         measure(a.tree_off[tid], a.tree_off[tid + 1], shares ? a.shared_len[tid] : 0, a.len[tid], steps, nrb);
         if (bid == 0 && nrb == 0) atomicOr(a.fault, DSBD_FAULT_TOPOLOGY);
       }
-      float total = (float)(nrb * a.Hkv) * (float)steps;
+      float units = (float)(nrb * a.Hkv), total = units * (float)steps;
 #pragma unroll
-      for (int off = 32; off >= 1; off >>= 1) total += __shfl_xor(total, off);
-      if ((tid & 63) == 0) w.wsum[tid >> 6] = total;
+      for (int off = 32; off >= 1; off >>= 1) { total += __shfl_xor(total, off); units += __shfl_xor(units, off); }
+      if ((tid & 63) == 0) { w.wsum[tid >> 6] = total; w.usum[tid >> 6] = units; }
       if (tid == 0) w.b = -1;
       __syncthreads();
-      const int ns = splits_of(a, steps, (w.wsum[0] + w.wsum[1]) + (w.wsum[2] + w.wsum[3])), count = a.Hkv * nrb * ns;
+      const int ns = splits_of(a, steps, (w.wsum[0] + w.wsum[1]) + (w.wsum[2] + w.wsum[3]),
+                               (w.usum[0] + w.usum[1]) + (w.usum[2] + w.usum[3]), UNIT == 64), count = a.Hkv * nrb * ns;
       w.steps[tid] = steps;
       w.count[tid] = count;
       __syncthreads();
@@ -992,7 +1006,7 @@ struct AttnPlan {
   int rows_block, n_rowblocks;
   bool by_tree;
   int nsplit;                 // by_tree: the most splits any tree may get; else every unit's
-  int slots, min_units;
+  int slots;
   long long grid;             // workgroups of the main kernel
   bool merge;                 // some unit may be split
 };
@@ -1010,16 +1024,18 @@ AttnPlan make_plan(const dsbd_forest* f, const dsbd_kv* kv, int Hq, int Hkv, int
   long long units = (long long)Hkv * (f->n_trees + (long long)f->n_nodes * group / p.rows_block);
   const long long most = (long long)f->n_trees * Hkv * p.n_rowblocks;
   if (units > most) units = most;
-  p.slots = p.shared && D == 64 ? 768 : 512;      // workgroups resident at once: three or two per compute unit
-  p.min_units = p.shared ? 2 : 8;
+  p.slots = 512;                                  // workgroups resident at once: two per compute unit
   p.by_tree = f->n_trees <= AT_BLOCK && dsbd_knobs().attn_nsplit <= 0;
-  // no unit can exceed an even share where there are two rounds of workgroups anyway
-  int most_split = ((kv->max_len + unit - 1) / unit + 2) / p.min_units;
-  if (most_split > AT_MAX_SPLIT) most_split = AT_MAX_SPLIT;
-  if (most_split < 1 || (long long)f->n_trees * Hkv >= 2 * p.slots) most_split = 1;
+  // no unit can exceed an even share where there are two rounds of workgroups anyway; and what splitting takes off short
+  // units is less than the merge's launch (4 beams x 7 nodes x 32 heads, 128 units, us unsplit / in two / in four: 17 steps
+  // 13.0 / 14.1 / 14.4, 33 steps 19.7 / 18.4 / 17.7; 8 units of 9 steps 14.0 / 13.9 / 13.5, of 17 steps 17.2 / 15.8 / 14.2;
+  // 32 units of 5 tiles 15.1 / 15.5 / 14.7, of 3 tiles 12.9 / 14.3 / 14.1)
+  const int most_steps = (kv->max_len + unit - 1) / unit + 2;
+  int most_split = split_limit(most_steps, p.shared);
+  if (most_steps < (p.shared ? 7 : (units >= 64 ? 24 : 14)) || (long long)f->n_trees * Hkv >= 2 * p.slots) most_split = 1;
   if (p.by_tree) {
     p.nsplit = most_split;
-    p.grid = units + (p.nsplit > 1 ? p.slots : 0);
+    p.grid = p.nsplit > 1 && units < p.slots ? p.slots : units;
   } else {
     // (more trees than threads fill the device by themselves, unless they have a single KV head)
     p.nsplit = most > 0 ? (int)((p.slots + most - 1) / most) : 1;
@@ -1118,7 +1134,7 @@ extern "C" int32_t dsbd_forest_attention(const dsbd_forest* f, const dsbd_kv* kv
   a.scale_log2 = sc * 1.4426950408889634f;
   a.max_len = kv->max_len;
   a.by_tree = p.by_tree ? 1 : 0; a.nsplit = p.nsplit; a.n_rowblocks = p.n_rowblocks; a.rows_block = p.rows_block;
-  a.wg_slots = p.slots; a.min_units = p.min_units; a.n_slots = (int)p.grid;
+  a.wg_slots = p.slots; a.n_slots = (int)p.grid;
   a.out = static_cast<__bf16*>(out); a.lse = lse; a.fault = fault;
   if (D == 128) launch_attention<128>(p, a, stream);
   else launch_attention<64>(p, a, stream);
