@@ -133,13 +133,13 @@ __device__ __forceinline__ const __bf16* lane_pointer(const void* p, int l) {
   return reinterpret_cast<const __bf16*>(((unsigned long long)hi << 32) | lo);
 }
 
-// Most splits worth their partial results for a unit of so many steps (32 tokens of a wave; or 64-token tiles): four
-// steps or tiles per split, and as little as two tiles for up to four splits.  Measured, whole call, us at 2 / 4 / 6 / 8 / 16
-// splits: 32 units of 33 tiles 30.4 / 22.2 / 20.9 / 21.1 / 26.3; of 9 tiles 17.4 / 15.5 / 16.8 / 16.5; 8 units of 17 steps
-// 15.8 / 14.2 / 13.8 / 14.1.
+// Most splits worth their partial results for a unit of so many steps: eight 32-token steps of the wave-private kernel per
+// split (four: 32 units of 57 steps, 28 rows each, 18.5 -> 26.6 us); four 64-token tiles, and as little as two tiles for up to
+// four splits (whole call, us at 2 / 4 / 6 / 8 / 16 splits: 32 units of 33 tiles 30.4 / 22.2 / 20.9 / 21.1 / 26.3; of 9 tiles
+// 17.4 / 15.5 / 16.8 / 16.5).
 __host__ __device__ __forceinline__ int split_limit(int steps, bool tiles) {
   const int four = steps / 4, two = steps / 2;
-  const int most = tiles && four < 4 ? (two < 4 ? two : 4) : four;
+  const int most = !tiles ? steps / 8 : (four >= 4 ? four : (two < 4 ? two : 4));
   return most < 1 ? 1 : (most > AT_MAX_SPLIT ? AT_MAX_SPLIT : most);
 }
 
@@ -1032,7 +1032,7 @@ AttnPlan make_plan(const dsbd_forest* f, const dsbd_kv* kv, int Hq, int Hkv, int
   // 32 units of 5 tiles 15.1 / 15.5 / 14.7, of 3 tiles 12.9 / 14.3 / 14.1)
   const int most_steps = (kv->max_len + unit - 1) / unit + 2;
   int most_split = split_limit(most_steps, p.shared);
-  if (most_steps < (p.shared ? 7 : (units >= 64 ? 24 : 14)) || (long long)f->n_trees * Hkv >= 2 * p.slots) most_split = 1;
+  if (most_steps < (p.shared ? 7 : (units >= 64 ? 24 : 16)) || (long long)f->n_trees * Hkv >= 2 * p.slots) most_split = 1;
   if (p.by_tree) {
     p.nsplit = most_split;
     p.grid = p.nsplit > 1 && units < p.slots ? p.slots : units;
