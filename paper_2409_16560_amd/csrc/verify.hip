@@ -524,9 +524,10 @@ __device__ __forceinline__ void row_statistics(const LayersArgs& a, int item, Sh
     for (int k = 0; k < SU; k += 4) {
       float4 x[4];
 #pragma unroll
-      for (int e = 0; e < 4; ++e) {     // (places beyond the end: the most negative finite number changes neither maximum nor sum)
+      for (int e = 0; e < 4; ++e) {     // (places beyond the end are masked tokens: they change neither maximum nor sum, and a
+                                        // row of nothing else keeps its maximum of -Inf, by which it is found below)
         const bool in = i + (k + e) * VL_BLOCK < body4;
-        x[e] = in ? make_float4(y[k + e].x, y[k + e].y, y[k + e].z, y[k + e].w) : make_float4(-FLT_MAX, -FLT_MAX, -FLT_MAX, -FLT_MAX);
+        x[e] = in ? make_float4(y[k + e].x, y[k + e].y, y[k + e].z, y[k + e].w) : make_float4(-INFINITY, -INFINITY, -INFINITY, -INFINITY);
       }
       online_add16(m, s, bad, x[0], x[1], x[2], x[3]);
     }

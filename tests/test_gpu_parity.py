@@ -939,6 +939,36 @@ def test_row_statistics_at_the_edges_of_their_rounds(V, same):
         assert float((logp.double() - ref_lp).abs().max()) <= 2 * tol
 
 
+@pytest.mark.parametrize("V", [3, 1000, 16383, 16384, 16387, 32768, 32771])
+def test_a_row_of_masked_tokens_is_reported_also_at_a_leaf(V):
+    """A row of -Inf only raises DSBD_FAULT_NONFINITE and its log-sum-exp is -Inf, under either model and with one model
+    in both roles, also where the node has no child whose drafted token would be reported as masked.  Rows shorter than
+    a load round of the statistics (16384 logits), at, just off and well beyond whole rounds: places beyond a row's end
+    must not pass for finite logits.  The other rows' statistics are those of the same call without the mask."""
+    gu = _gu()
+    import paper_2409_16560_amd as dsbd
+    w = make_workload("c2", L=1, Hq=1, Hkv=1, D=64, V=V)
+    leaf = int(np.flatnonzero(~np.isin(np.arange(w.n_nodes), w.parent))[-1])
+    for model in ("target", "draft", "both"):
+        d = gu.DeviceWorkload(w)
+        if model == "both":
+            d.logits_q, d.blq = d.logits_p, d.blp
+        clean = d.verify()
+        torch.cuda.synchronize()
+        assert int(clean.fault.item()) & dsbd.DSBD_FAULT_NONFINITE == 0
+        (d.logits_q if model == "draft" else d.logits_p)[leaf].fill_(-float("inf"))
+        print("case", V, model, "leaf", leaf, flush=True)
+        res = d.verify()
+        torch.cuda.synchronize()
+        assert int(res.fault.item()) & dsbd.DSBD_FAULT_NONFINITE, model
+        others = torch.arange(w.n_nodes, device="cuda") != leaf
+        for m in ("target", "draft"):
+            lse, ref = getattr(res, "lse_" + m), getattr(clean, "lse_" + m)
+            assert torch.equal(lse[others], ref[others])
+            assert (float(lse[leaf]) == -float("inf")) == (model in (m, "both")), (model, m, float(lse[leaf]))
+            assert torch.equal(getattr(res, "node_logp_" + m), getattr(clean, "node_logp_" + m))
+
+
 @pytest.mark.parametrize("D", [128, 64])
 @pytest.mark.parametrize("name,kw", [
     # how the work is handed out: a lane per tree, a thread per tree (above 64 trees), plain arithmetic (above 256);
