@@ -142,9 +142,15 @@ __device__ __forceinline__ void fold_rows(const DraftArgs& a, int r0, int n, con
       if (lane < a.nchunk) ms = a.part[(long long)(r0 + r) * a.nchunk + lane];
     }
     const double M = wave_max_f64(ms.x);
-    const double share = ms.x > -INFINITY ? ms.y * dsbd_exp_nonpos(ms.x - M, tab) : 0.0;
+    double share = ms.x > -INFINITY ? ms.y * dsbd_exp_nonpos(ms.x - M, tab) : 0.0;
     const double S = wave_sum(share);
-    const double scale = __shfl(w, r) / S;
+    // A row without a finite logit (or with one that is no number: the chunks have reported that) has no entries: its
+    // beam is never continued, and the prompt's other beams keep their shares.  (Every wave sees rows of its own, so it
+    // reports for itself.)
+    const bool dead = !(S > 0.0 && S < INFINITY);
+    if (dead && lane == 0) atomicOr(a.fault, DSBD_FAULT_NONFINITE);
+    if (dead) share = 0.0;
+    const double scale = dead ? 0.0 : __shfl(w, r) / S;
     if (lane == 0) { row_max[r] = M; row_sum[r] = S; row_scale[r] = scale; }
     each(r, ms.x, share, M, scale);
   }
@@ -495,7 +501,7 @@ __global__ __launch_bounds__(DW_BLOCK) void draft_warp_kernel(DraftArgs a) {
       if (pick < 0 && sh.gmax[o] > target) pick = o;
     }
     if (pick < 0) pick = last;
-    const int flat = kept > 0 ? sh.ci[pick] : 0;       // (no entry at all: reported above, the draw stays in bounds)
+    const int flat = kept > 0 ? sh.ci[pick] : 0;       // (no entry at all: fold_rows has reported it, the draw stays in bounds)
     const int r = flat / V;
     write_draw(a, p, lane, r0 + r, flat - r * V, sh.row_max[r], sh.row_sum[r]);
   }

@@ -138,6 +138,36 @@ def test_draft_layer_skips_beams_of_probability_zero():
         assert np.max(np.abs(lp - rlp)) <= 1e-9
 
 
+@pytest.mark.parametrize("V", [900, 9000, 70000])
+@pytest.mark.parametrize("top_k,top_p", [(0, 1.0), (10, 0.8)])
+def test_draft_layer_reports_a_row_of_masked_tokens(V, top_k, top_p):
+    """A row without a finite logit raises DSBD_FAULT_NONFINITE, whether its beam has a likelihood or not, and never
+    gets a draw; the other beams' draws are those of a step in which the beam has the likelihood -Inf (weight 0; the
+    beam's share of the mass is lost).  A prompt of such rows alone is reported and its draws stay in bounds."""
+    for row, lp in ((1, None), (1, -np.inf), (9, None), (9, -np.inf), (12, None)):    # rows of different waves and prompts
+        beam_off, z, cum, u = layer_inputs(V + row, [10, 3], V, 8)
+        z[row, :] = -np.inf
+        if lp is not None:
+            cum[row] = lp
+        print("case", V, top_k, row, lp, flush=True)
+        par, tok, logp, fault = run_draft_layer(beam_off, z, cum, u, 8, top_k, top_p)
+        assert fault == 4 and not (par == row).any()
+        z2, cum2 = z.copy(), cum.copy()
+        z2[row, :] = 0.0                        # any finite row: its weight is 0
+        cum2[row] = -np.inf
+        with np.errstate(all="ignore"):
+            rpar, rtok, rlp = oracle_draft_layer(beam_off, z2, cum2, u, top_k, top_p)
+        assert np.array_equal(par, rpar) and np.array_equal(tok, rtok)
+        assert np.max(np.abs(logp - rlp)) <= 1e-9
+    beam_off, z, cum, u = layer_inputs(V, [2, 3], V, 8)
+    z[2:] = -np.inf
+    print("case", V, top_k, "a whole prompt", flush=True)
+    par, tok, logp, fault = run_draft_layer(beam_off, z, cum, u, 8, top_k, top_p)
+    assert fault == 4 and (tok >= 0).all() and (tok < V).all() and (par[1] >= 2).all() and (par[1] < 5).all()
+    rpar, rtok, rlp = oracle_draft_layer(beam_off[:2], z[:2], cum[:2], u[:1], top_k, top_p)
+    assert np.array_equal(par[:1], rpar) and np.array_equal(tok[:1], rtok)
+
+
 def test_draft_layer_reports_bad_inputs():
     beam_off, z, cum, u = layer_inputs(3, [3, 2], 500, 4)
     z_bad = z.copy(); z_bad[1, 17] = np.inf
