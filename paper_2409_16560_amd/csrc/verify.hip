@@ -1933,7 +1933,7 @@ void verify_layers_kernel(LayersArgs a) {
             // the first entry whose inclusive prefix exceeds the target (rounding: the last one with mass)
             const int pl_ = above ? (int)__ffsll((long long)above) - 1 : (mass ? 63 - __clzll((long long)mass) : 0);
             if (g == 0 && lane == pl_) {
-              const long long pick = sh.U_idx[pl_];
+              const long long pick = nU > 0 ? sh.U_idx[pl_] : 0;       // (no entry at all, reported as a fault: stay in bounds)
               const int i = (int)div_floor(pick, V);
               const int x = (int)(pick - (long long)i * V);
               const int node = sh.I_node[i];

@@ -969,6 +969,32 @@ def test_a_row_of_masked_tokens_is_reported_also_at_a_leaf(V):
             assert torch.equal(getattr(res, "node_logp_" + m), getattr(clean, "node_logp_" + m))
 
 
+@pytest.mark.parametrize("what", ["likelihoods", "masked rows", "NaN rows"])
+@pytest.mark.parametrize("V,top_k", [(500, 8), (20000, 10)])
+def test_warped_draws_from_a_joint_without_an_entry_stay_in_bounds(what, V, top_k):
+    """Inputs that leave the warped joint without an entry (every stored likelihood -Inf, rows of masked tokens or of
+    NaN alone) are reported; what the call then returns is unusable, but the nodes and tokens it names exist."""
+    gu = _gu()
+    import paper_2409_16560_amd as dsbd
+    w = make_workload("c2", L=1, Hq=1, Hkv=1, D=64, V=V, W=1 if what != "likelihoods" else 4)
+    if what == "likelihoods":
+        w.beam_logp_p[:] = -np.inf
+        w.beam_logp_q[:] = -np.inf
+    else:
+        w.logits_p[:] = w.logits_q[:] = -np.inf if what == "masked rows" else np.nan
+    d = gu.DeviceWorkload(w)
+    print("case", what, V, top_k, flush=True)
+    for res, nx in ((d.verify(top_k=top_k, top_p=0.8), None), d.verify_select(top_k=top_k, top_p=0.8)):
+        torch.cuda.synchronize()
+        assert int(res.fault.item()) & dsbd.DSBD_FAULT_NONFINITE
+        n = int(res.n_out[0])
+        par, tok = res.out_parent[0, :n].cpu().numpy(), res.out_token[0, :n].cpu().numpy()
+        assert ((par >= 0) & (par < w.n_nodes)).all() and ((tok >= 0) & (tok < V)).all()
+        if nx is not None:
+            src = nx.src_tree[0, :n].cpu().numpy()
+            assert ((src >= 0) & (src < w.n_trees)).all()
+
+
 @pytest.mark.parametrize("D", [128, 64])
 @pytest.mark.parametrize("name,kw", [
     # how the work is handed out: a lane per tree, a thread per tree (above 64 trees), plain arithmetic (above 256);
