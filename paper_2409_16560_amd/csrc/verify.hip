@@ -2632,16 +2632,19 @@ const DeviceLimits& device_limits() {
   return lim;
 }
 
-VerifyPlan make_verify_plan(const dsbd_forest* f, int V, const dsbd_params* p, bool alias = false) {
-  VerifyPlan pl;
-  const DsbdKnobs& knobs = dsbd_knobs();
-  pl.I_cap = p->W_cap > f->max_prompt_trees ? p->W_cap : f->max_prompt_trees;
+// Workgroups per prompt of the layer kernel.  `sparing`: 4000 joint entries each, whatever the problem (make_verify_plan).
+int layer_workgroups(const dsbd_forest* f, int V, const dsbd_params* p, bool sparing) {
   // one workgroup per compute unit in total, shared evenly by the prompts, at least 4096 joint elements per
   // workgroup.  More prompts than workgroups fit the device at once: groups of prompts, one launch after the other
   // (Algorithm 1 runs per prompt), one workgroup per prompt.
   const DeviceLimits& lim = device_limits();
-  const int resident = lim.cus * lim.blocks_per_cu;
+  const long long joint = (long long)f->max_prompt_trees * V;
   int G = f->n_prompts > 0 ? lim.cus / f->n_prompts : 1;
+  if (sparing) {
+    const long long by_work = (joint + 3999) / 4000;
+    if (G > by_work) G = (int)by_work;
+    return G < 1 ? 1 : G;
+  }
   // ... minus compute units for the workgroups that take the rows' statistics meanwhile: one per 4 MB of logits (what a
   // compute unit streams while the layers are walked), at most a quarter of the device, and none where the coarser cut
   // of a row among the prompt's workgroups would cost more than that quarter (a 16-prompt batch: one workgroup per
@@ -2663,21 +2666,23 @@ VerifyPlan make_verify_plan(const dsbd_forest* f, int V, const dsbd_params* p, b
   // 48.2 / 48.0 / 48.1 / 48.3 / 48.4; 5 x 128256 warped: 185 / 149 / 112 / 106.8 / 103.6 / 103.5 / 104.0 / 106.5; 8 x 128256:
   // 516 / 303 / 238 / 181 / 154 / 121 / 116 / 108.  5 x 128256 plain: 324 / 201 / 140 /
   // 121 / 81 / 77 / 73 / 75.  So 2000 entries per workgroup up to 128 of them, 4000 beyond.)
-  const long long joint = (long long)f->max_prompt_trees * V;
   long long by_work = (joint + 1999) / 2000;
   if (by_work > 128) by_work = std::max(128LL, (joint + 3999) / 4000);
   // warping wants enough pieces for its one-level selection (4 x 32000, top_k 32: 64 workgroups 76 us, 128: 60)
   if (p->top_k > 0 && by_work < 4 * p->top_k + f->max_prompt_trees && joint >= 128LL * (4 * p->top_k + f->max_prompt_trees))
     by_work = 4 * p->top_k + f->max_prompt_trees;
-  // (every layer has slots of its own, so forests tens of layers deep keep to 4000: workspaces that fitted 32 MiB still do)
-  const long long slot_bytes = (long long)(f->max_depth + 1) * 4 * (pl.I_cap + (p->top_k > 0 ? p->top_k : 0)) * (long long)sizeof(Slot);
-  if (slot_bytes * by_work > (8LL << 20)) by_work = std::min(by_work, (joint + 3999) / 4000);
   if (G > by_work) G = (int)by_work;
   // (workgroups beyond a multiple of the rows hold no piece but take part in every exchange)
   if (f->max_prompt_trees > 0 && G > f->max_prompt_trees) G -= G % f->max_prompt_trees;
-  if (knobs.verify_g >= 1 && (long long)knobs.verify_g * f->n_prompts <= resident) G = knobs.verify_g;   // tuning knob
   if (G < 1) G = 1;
-  if (G > 256) G = 256;
+  return G > 256 ? 256 : G;
+}
+
+VerifyPlan plan_with_workgroups(const dsbd_forest* f, int V, const dsbd_params* p, bool alias, int G) {
+  VerifyPlan pl;
+  const DeviceLimits& lim = device_limits();
+  const int resident = lim.cus * lim.blocks_per_cu;
+  pl.I_cap = p->W_cap > f->max_prompt_trees ? p->W_cap : f->max_prompt_trees;
   pl.G = G;
   pl.group = f->n_prompts;
   if ((long long)pl.group * G > resident) pl.group = resident / G;     // G is 1 here
@@ -2741,6 +2746,26 @@ size_t carve_verify(WorkspaceCarver& ws, const dsbd_forest* f, const VerifyPlan&
   return ws.total();
 }
 
+size_t verify_workspace(const dsbd_forest* f, const VerifyPlan& pl) {
+  WorkspaceCarver ws(nullptr);
+  double *pb, *qb, *red;
+  return carve_verify(ws, f, pl, &pb, &qb, &red) + 256;
+}
+
+// More workgroups per prompt bring more exchange slots (every layer has its own) and, where rows and workgroups do not
+// divide, longer slices in all.  The array behind dsbd_verify_forest_static is 32 MiB: a problem that fits it with 4000
+// joint entries per workgroup keeps to those if it would outgrow it otherwise.  (Both entry points take the same plan.)
+VerifyPlan make_verify_plan(const dsbd_forest* f, int V, const dsbd_params* p, bool alias = false) {
+  const DsbdKnobs& knobs = dsbd_knobs();
+  const DeviceLimits& lim = device_limits();
+  if (knobs.verify_g >= 1 && knobs.verify_g <= 256 && (long long)knobs.verify_g * f->n_prompts <= lim.cus * lim.blocks_per_cu)   // tuning knob
+    return plan_with_workgroups(f, V, p, alias, knobs.verify_g);
+  const VerifyPlan pl = plan_with_workgroups(f, V, p, alias, layer_workgroups(f, V, p, false));
+  if (verify_workspace(f, pl) <= (size_t)DSBD_STATIC_SCRATCH_BYTES) return pl;
+  const VerifyPlan small = plan_with_workgroups(f, V, p, alias, layer_workgroups(f, V, p, true));
+  return verify_workspace(f, small) <= (size_t)DSBD_STATIC_SCRATCH_BYTES ? small : pl;
+}
+
 // Two layer kernels on different streams must not share the compute units: each waits for workgroups of its own that
 // the other one's keep out.  The library therefore orders its layer launches itself once it has seen calls on more
 // than one stream: the first change of stream waits for the device to drain, and from then on layers_done is recorded
@@ -2780,10 +2805,7 @@ __global__ void bump_replay_count_kernel(unsigned long long* count) { *count += 
 
 extern "C" size_t dsbd_verify_forest_workspace_bytes(const dsbd_forest* f, int32_t V, const dsbd_params* p) {
   if (check_verify(f, V, p) != DSBD_OK) return 0;
-  const VerifyPlan pl = make_verify_plan(f, V, p);
-  WorkspaceCarver ws(nullptr);
-  double *pb, *qb, *red;
-  return carve_verify(ws, f, pl, &pb, &qb, &red) + 256;
+  return verify_workspace(f, make_verify_plan(f, V, p));
 }
 
 namespace {
@@ -2811,12 +2833,12 @@ int32_t verify_impl(const dsbd_forest* f, const dsbd_verify_in* in, const dsbd_p
       !out->out_node || !out->out_logp_target || !out->out_logp_draft || !out->near_tie_count)
     return DSBD_ERR_INVALID;
   if (!workspace) return DSBD_ERR_INVALID;
-  if (workspace_bytes < dsbd_verify_forest_workspace_bytes(f, in->V, p)) return DSBD_ERR_WORKSPACE;
-  hipStream_t stream = static_cast<hipStream_t>(stream_);
   const DsbdKnobs& knobs = dsbd_knobs();
-  // the same arrays given for both models: q_beam is p_beam and is kept, and computed, once
+  // the same arrays given for both models: q_beam is p_beam and is kept, and computed, once (in the same workspace)
   const bool alias = in->logits_target == in->logits_draft && in->beam_logp_target == in->beam_logp_draft;
   const VerifyPlan pl = make_verify_plan(f, in->V, p, alias);
+  if (workspace_bytes < verify_workspace(f, pl)) return DSBD_ERR_WORKSPACE;
+  hipStream_t stream = static_cast<hipStream_t>(stream_);
 
   char* wbase = reinterpret_cast<char*>(dsbd_align_up(reinterpret_cast<uintptr_t>(workspace), 256));
   WorkspaceCarver ws(wbase);

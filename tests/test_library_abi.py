@@ -112,6 +112,32 @@ def test_workspace_sizes_scale_with_the_problem():
         lib.dsbd_verify_forest_workspace_bytes(C.byref(big), 128256, C.byref(p))
 
 
+# prompts, beams, nodes per tree, depth, W_cap, V, top_k: problems whose workspace is at most 32 MiB with 4000 joint
+# entries per workgroup (the sizes there, in MiB), and above it with as many workgroups as would be fastest
+FITS_32_MIB = [((1, 1, 1, 0, 32, 50257, 0), 30.0), ((2, 2, 20, 19, 16, 32000, 32), 17.8), ((2, 4, 31, 30, 16, 50257, 4), 30.5),
+               ((3, 2, 8, 7, 16, 32000, 10), 24.2), ((3, 5, 1, 0, 32, 16000, 32), 29.7), ((4, 2, 8, 7, 24, 16000, 0), 23.9),
+               ((4, 2, 16, 15, 32, 8000, 20), 16.7), ((5, 8, 16, 4, 64, 4000, 32), 20.9), ((8, 5, 48, 47, 16, 4000, 10), 13.9),
+               ((16, 5, 20, 15, 24, 4000, 20), 28.8), ((24, 12, 16, 15, 64, 1000, 4), 30.2), ((100, 12, 32, 31, 32, 256, 1), 27.3)]
+
+
+def test_verifications_that_fit_the_static_array():
+    """dsbd_verify_forest_static takes what its 32 MiB hold: where more workgroups per prompt would outgrow the array,
+    the plan stays with fewer."""
+    import paper_2409_16560_amd.binding as b
+    lib = b.load_library()
+    capacity = lib.dsbd_verify_forest_static_capacity()
+    assert capacity == 32 << 20
+
+    def need(P, W, nodes, depth, W_cap, V, top_k):
+        f = b._Forest(P, P * W, P * W * nodes, None, None, None, None, None, nodes, depth, W)
+        p = b._Params(0, 1, W_cap, -1.0, top_k, 0.9 if top_k else 1.0)
+        return lib.dsbd_verify_forest_workspace_bytes(C.byref(f), V, C.byref(p))
+
+    for shape, mib in FITS_32_MIB:
+        assert 0 < need(*shape) <= mib * 2 ** 20 + 2 ** 16, shape
+    assert need(16, 8, 16, 15, 16, 32000, 0) > capacity          # slices of a full batch: refused, as before
+
+
 def test_prefix_kv_refuses_caches_of_different_strides():
     """One token stride and one head stride serve all caches (include/dsbd.h, dsbd_kv): head-major tensors of
     different lengths would be read out of bounds, so the binding refuses them; views of equally sized buffers pass."""
