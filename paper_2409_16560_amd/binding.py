@@ -167,21 +167,29 @@ def _i32(t, dev):
 
 
 # Zeroed fault words for calls that were not given one.  A torch.zeros(1) per call is a kernel launch of its own (5 us of
-# host time, 3 us on the device); here one fill serves 64 calls, each word is handed out once.  The words of a fill belong
-# to the stream it ran on, so every later user on that stream is ordered behind it.  At most 64 streams' worth is kept.
+# host time, 3 us on the device); here one fill serves 64 calls (the call that makes it pays for 64 views as well), each
+# word is handed out once.  The words of a fill belong to the stream it ran on, so every later user on that stream is
+# ordered behind it.  At most 64 streams' worth is kept.  A caller's modes do not outlive the call: the words are ordinary
+# tensors also when inference mode is on, and a call under capture, under a dispatch mode or on a stream that is not the
+# current one gets a word of its own, filled on the stream that the call runs on.
 _FAULT_WORDS = 64
 _fault_words = {}
 
 
-def _fault_word(dev):
-    if torch._C._cuda_isCurrentStreamCapturing():
-        return torch.zeros(1, dtype=torch.int32, device=dev)      # (the fill has to be part of the graph)
+def _fault_word(dev, stream=None):
     idx = dev.index if dev.index is not None else torch._C._cuda_getDevice()
-    key = (idx, torch._C._cuda_getCurrentRawStream(idx))
+    current = torch._C._cuda_getCurrentRawStream(idx)
+    if stream is not None and stream.cuda_stream != current:
+        with torch.cuda.stream(stream):
+            return torch.zeros(1, dtype=torch.int32, device=dev)
+    if torch._C._cuda_isCurrentStreamCapturing() or torch._C._len_torch_dispatch_stack():
+        return torch.zeros(1, dtype=torch.int32, device=dev)      # (under capture the fill has to be part of the graph)
+    key = (idx, current)
     try:
         return _fault_words[key].pop()
     except (KeyError, IndexError):
-        words = list(torch.zeros(_FAULT_WORDS, dtype=torch.int32, device=dev).split(1))
+        with torch.inference_mode(False):
+            words = list(torch.zeros(_FAULT_WORDS, dtype=torch.int32, device=dev).split(1))
         mine = words.pop()
         if len(_fault_words) >= 64:
             _fault_words.clear()
@@ -282,7 +290,7 @@ def dsbd_forest_attention(forest: Forest, kv: PrefixKV, q, k_tree, v_tree, scale
     if lse is None and want_lse:
         lse = torch.empty((N, Hq), dtype=torch.float32, device=dev)
     if fault is None:
-        fault = _fault_word(dev)
+        fault = _fault_word(dev, stream)
     if workspace is None:
         nbytes = int(lib.dsbd_forest_attention_workspace_bytes(C.byref(f), C.byref(k), Hq, Hkv, D))
         if nbytes == 0 and N > 0:
@@ -318,7 +326,7 @@ class VerifyResult:
         return _VerifyOut(*[_ptr(getattr(self, n)) for n, _ in _VerifyOut._fields_])
 
     @staticmethod
-    def allocate(forest: Forest, W_cap: int):
+    def allocate(forest: Forest, W_cap: int, stream=None):
         dev, N, P, Lw = forest.device, forest.n_nodes, forest.n_prompts, forest.max_depth + 2
         e = lambda shape, dt: torch.empty(shape, dtype=dt, device=dev)
         return VerifyResult(
@@ -326,7 +334,7 @@ class VerifyResult:
             e((N,), torch.float32), e((P,), torch.int32), e((P, Lw), torch.int32), e((P,), torch.int32),
             e((P, W_cap), torch.int32), e((P, W_cap), torch.int32), e((P, W_cap), torch.int32),
             e((P, W_cap), torch.float64), e((P, W_cap), torch.float64), e((P,), torch.int32),
-            _fault_word(dev), W_cap)
+            _fault_word(dev, stream), W_cap)
 
 
 def _params(W_L, W_min, W_cap, t, top_k=0, top_p=1.0):
@@ -355,7 +363,7 @@ def dsbd_verify_forest(forest: Forest, logits_target, logits_draft, beam_logp_ta
     vin = _VerifyIn(int(V), _ptr(logits_target), _ptr(logits_draft), _ptr(beam_logp_target), _ptr(beam_logp_draft),
                     _ptr(u_accept), _ptr(u_resid), _ptr(u_fill))
     if result is None:
-        result = VerifyResult.allocate(forest, W_cap)
+        result = VerifyResult.allocate(forest, W_cap, stream)
     if workspace is None:
         nbytes = int(lib.dsbd_verify_forest_workspace_bytes(C.byref(f), int(V), C.byref(p)))
         if nbytes == 0 and N > 0:
@@ -386,9 +394,9 @@ def dsbd_verify_forest_select(forest: Forest, logits_target, logits_draft, beam_
     vin = _VerifyIn(int(V), _ptr(logits_target), _ptr(logits_draft), _ptr(beam_logp_target), _ptr(beam_logp_draft),
                     _ptr(u_accept), _ptr(u_resid), _ptr(u_fill))
     if result is None:
-        result = VerifyResult.allocate(forest, W_cap)
+        result = VerifyResult.allocate(forest, W_cap, stream)
     if next_beams is None:
-        next_beams = NextBeams.allocate(forest, W_cap)
+        next_beams = NextBeams.allocate(forest, W_cap, stream)
     if workspace is None:
         nbytes = int(lib.dsbd_verify_forest_workspace_bytes(C.byref(f), int(V), C.byref(p)))
         if nbytes == 0 and N > 0:
@@ -444,19 +452,19 @@ class NextBeams:
         return _NextBeams(*[_ptr(getattr(self, n)) for n, _ in _NextBeams._fields_])
 
     @staticmethod
-    def allocate(forest: Forest, W_cap: int):
+    def allocate(forest: Forest, W_cap: int, stream=None):
         dev, P, plen = forest.device, forest.n_prompts, forest.max_depth + 1
         e = lambda shape, dt: torch.empty(shape, dtype=dt, device=dev)
         return NextBeams(e((P,), torch.int32), e((P, W_cap), torch.int32), e((P, W_cap), torch.int32),
                          e((P, W_cap), torch.int32), e((P, W_cap, plen), torch.int32), e((P, W_cap), torch.int32),
-                         e((P, W_cap), torch.float64), e((P, W_cap), torch.float64), _fault_word(dev))
+                         e((P, W_cap), torch.float64), e((P, W_cap), torch.float64), _fault_word(dev, stream))
 
 
 def dsbd_select_beams(forest: Forest, verified: VerifyResult, keep_one=False, result: NextBeams = None, stream=None):
     lib = load_library()
     f, v = forest.c_struct(), verified.c_struct()
     if result is None:
-        result = NextBeams.allocate(forest, verified.W_cap)
+        result = NextBeams.allocate(forest, verified.W_cap, stream)
     nx = result.c_struct()
     rc = lib.dsbd_select_beams(C.byref(f), C.byref(v), int(verified.W_cap), int(bool(keep_one)), C.byref(nx),
                                _ptr(result.fault), _stream(stream))
@@ -497,7 +505,7 @@ def dsbd_commit_kv(forest: Forest, src: PrefixKV, k_tree, v_tree, plan: NextBeam
     assert dst.k_ptr.numel() == forest.n_prompts * W_cap
     Hkv, D = k_tree.shape[1], k_tree.shape[2]
     if fault is None:
-        fault = _fault_word(k_tree.device)
+        fault = _fault_word(k_tree.device, stream)
     rc = lib.dsbd_commit_kv(C.byref(f), C.byref(k), _ptr(k_tree), _ptr(v_tree), int(Hkv), int(D), C.byref(nx),
                             int(W_cap), C.byref(d), _ptr(fault), _stream(stream))
     _check(rc, "dsbd_commit_kv")
@@ -526,7 +534,7 @@ def dsbd_draft_layer(beam_off, logits_draft, beam_logp_draft, u, W_S, *, max_pro
     logp = torch.empty((P, W_S), dtype=torch.float64, device=dev)
     dout = _DraftOut(_ptr(parent), _ptr(token), _ptr(logp))
     if fault is None:
-        fault = _fault_word(dev)
+        fault = _fault_word(dev, stream)
     if workspace is None:
         nbytes = int(lib.dsbd_draft_layer_workspace_bytes(C.byref(din), int(W_S), int(top_k), float(top_p)))
         if nbytes == 0:
@@ -561,7 +569,7 @@ def dsbd_build_forest(root_off, layer_parent, layer_token, root_token=None, *, n
         at += 4 * n
     fo = _ForestOut(*places)
     if fault is None:
-        fault = _fault_word(dev)
+        fault = _fault_word(dev, stream)
     for t_ in (root_off, layer_parent, layer_token, root_token):
         assert t_ is None or (t_.dtype == torch.int32 and t_.is_contiguous())
     rc = lib.dsbd_build_forest(int(P), int(n_roots), gamma, W_S, _ptr(root_off), _ptr(root_token),
