@@ -2632,6 +2632,17 @@ const DeviceLimits& device_limits() {
   return lim;
 }
 
+// Prompts of few nodes and no warping (whose scratch lists use the per-node arrays at full size) take the kernel variant
+// with the short per-node arrays, which leaves more of the LDS to the slices.
+bool small_prompts(const dsbd_forest* f, const dsbd_params* p) {
+  return p->top_k == 0 && (long long)f->max_prompt_trees * f->max_tree_nodes <= NODE_CAP_SMALL;
+}
+
+// Joint entries of a slice that the LDS holds (both arrays).
+long long lds_slice_entries(const dsbd_forest* f, const dsbd_params* p) {
+  return (small_prompts(f, p) ? VL_DYN_LDS_BYTES_SMALL : VL_DYN_LDS_BYTES) / 16;
+}
+
 // Workgroups per prompt of the layer kernel.  `sparing`: 4000 joint entries each, whatever the problem (make_verify_plan).
 int layer_workgroups(const dsbd_forest* f, int V, const dsbd_params* p, bool sparing) {
   // one workgroup per compute unit in total, shared evenly by the prompts, at least 4096 joint elements per
@@ -2645,19 +2656,18 @@ int layer_workgroups(const dsbd_forest* f, int V, const dsbd_params* p, bool spa
     if (G > by_work) G = (int)by_work;
     return G < 1 ? 1 : G;
   }
-  // ... minus compute units for the workgroups that take the rows' statistics meanwhile: one per 4 MB of logits (what a
-  // compute unit streams while the layers are walked), at most a quarter of the device, and none where the coarser cut
-  // of a row among the prompt's workgroups would cost more than that quarter (a 16-prompt batch: one workgroup per
-  // row instead of two).  Measured, verification of 248 nodes x 128256 (254 MB, 8 beams): no unit kept 128 us, 16: 127,
-  // 32: 122, 48: 115, 64: 111, 96: 113; 16 prompts, 747 nodes x 32000: none 152 us, 16 kept (15 workgroups per
-  // prompt) 224 us.
+  // ... minus compute units for the workgroups that take the rows' statistics meanwhile: one per MB of logits (30 GB/s for
+  // a unit on its own, over the 35 us that the shortest walks take), at most a quarter of the device, and none where the
+  // coarser slices would not fit the LDS any more.  Measured, verification in us with 0 / 32 / 64 units kept: 40 nodes x
+  // 128256, 8 beams 50 / 44 / 39 (dynamic width 75 / 66 / 65, top_k 10 81 / 75 / 75), 248 nodes 128 / 122 / 111; 16 prompts,
+  // 341 nodes x 32000 (8000-entry slices, 10667 with 64 kept): 88 / 112 / 112.
   {
-    long long keep = (2LL * f->n_nodes * V * 4 + (4 << 20) - 1) / (4 << 20);
+    long long keep = (2LL * f->n_nodes * V * 4 + (1 << 20) - 1) / (1 << 20);
     if (keep > lim.cus / 4) keep = lim.cus / 4;
     const int W = f->max_prompt_trees;
     if (f->n_prompts > 0) {
       const int Gk = (int)((lim.cus - keep) / f->n_prompts);
-      if (Gk >= W && (Gk / W) * 4 >= (G / W) * 3) G = Gk;
+      if (Gk >= W && slice_cut(W, V, Gk).len <= lds_slice_entries(f, p)) G = Gk;
     }
   }
   // (sized by the joint of the input beams, which is what a fixed width keeps every layer at: shorter slices make shorter
@@ -2687,10 +2697,8 @@ VerifyPlan plan_with_workgroups(const dsbd_forest* f, int V, const dsbd_params* 
   pl.group = f->n_prompts;
   if ((long long)pl.group * G > resident) pl.group = resident / G;     // G is 1 here
   if (pl.group < 1) pl.group = 1;
-  // prompts of few nodes and no warping (whose scratch lists use the per-node arrays at full size): the kernel
-  // variant with the short per-node arrays, which leaves more of the LDS to the slices
-  pl.small_nodes = p->top_k == 0 && (long long)f->max_prompt_trees * f->max_tree_nodes <= NODE_CAP_SMALL;
-  const long long cap = (pl.small_nodes ? VL_DYN_LDS_BYTES_SMALL : VL_DYN_LDS_BYTES) / (alias ? 8 : 16);   // one array instead of two when q_beam is p_beam
+  pl.small_nodes = small_prompts(f, p);
+  const long long cap = lds_slice_entries(f, p) * (alias ? 2 : 1);   // one array instead of two when q_beam is p_beam
   // exchange slots: every workgroup's slots of an exchange start a 128-byte line (no two writers per line)
   {
     auto up8 = [](int v) { return (v + LINE_SLOTS - 1) / LINE_SLOTS * LINE_SLOTS; };

@@ -1032,6 +1032,10 @@ def test_forest_attention_work_places(name, kw, D):
     (dict(W=2, V=20011, tree_nodes=40, tree="chain"), {}),
     (dict(W=2, V=40003, tree_nodes=60, tree="chain"), dict(top_k=32, top_p=0.95)),
     (dict(W=7, V=45007, tree_nodes=5), {}),
+    # compute units left to the row statistics: some, a quarter of the device, none (slices that would outgrow the LDS)
+    (dict(W=8, V=100003, tree_nodes=3), {}),
+    (dict(W=8, V=100003, tree_nodes=15), dict(top_k=10, top_p=0.8)),
+    (dict(W=8, V=60001, tree_nodes=7, n_prompts=3), {}),
 ])
 def test_verify_workgroups_per_prompt(kw, warp):
     gu = _gu()
