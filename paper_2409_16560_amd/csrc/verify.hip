@@ -149,7 +149,8 @@ struct LayersArgs {
   int warp_fast;         // warping: the one-level selection (bounds from the workgroups' largest entries) where it applies
   dsbd_next_beams nx;    // next-beam plan written along with the output beams (fused selection) ...
   int nx_on;             // ... when this is set
-  int layer_wgs;         // workgroups of this launch that walk layers; those behind them take the statistics of a row each
+  int layer_wgs;         // workgroups of this launch that walk layers; those behind them take the statistics of the rows ...
+  int stats_threads;     // ... with so many threads per row
   float *lse_p, *lse_q, *logp_p, *logp_q;   // per-node outputs of the statistics (any may be null)
 };
 
@@ -487,18 +488,23 @@ __host__ __device__ inline SliceCut slice_cut(int nI, int V, int G) {
 }
 
 // ---- per-node outputs (step A3 of the path: fp32 log-sum-exp of a node's row, log-probability of a node's token under its
-// parent's row): the workgroups behind the layers' take one row of one model each.  A row's sum is complete inside its
+// parent's row): the workgroups behind the layers' take the rows of both models.  A row's sum is complete inside its
 // workgroup, so the log-probabilities of the row's children are its to write, and nothing has to be merged afterwards.
 // (Before, a kernel per chunk of a row and a merging kernel ran on a second stream, forked from and joined to the
 // caller's by events: 12 us of a call, 33 us of host time in four event calls and two launches, and exchanges that slowed
-// down on every compute unit the two shared.  Measured, verification call: 28 nodes x 32000 tokens 58 -> 47 us, 120 nodes
-// 80 -> 73 us, 248 nodes x 128256 121 -> 111 us, 16 prompts with 747 nodes x 32000 167 -> 152 us.)
+// down on every compute unit the two shared.  Measured, verification call: 28 nodes x 32000 tokens 50 -> 38 us, 120 nodes
+// 75 -> 64 us, 248 nodes x 128256 123 -> 96 us, 16 prompts with 747 nodes x 32000 208 -> 188 us.)
+// TR threads take a row, so a workgroup has VL_BLOCK / TR rows side by side.
 #define SU 8                   // 16-byte loads in flight per thread, twice (the next round travels during this one's exponentials)
-template <class Shared>
-__device__ __forceinline__ void row_statistics(const LayersArgs& a, int item, Shared& sh) {
+template <int TR, class Shared>
+__device__ __forceinline__ void row_statistics(const LayersArgs& a, Shared& sh) {
   typedef float f32x4 __attribute__((ext_vector_type(4)));
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int tid = threadIdx.x % TR;
   const int V = a.V;
+  const int rows = a.n_nodes * (a.alias ? 1 : 2);
+  int item = ((int)blockIdx.x - a.layer_wgs) * (VL_BLOCK / TR) + (int)threadIdx.x / TR;
+  const bool live = item < rows;           // (the last workgroup may have threads left over: they repeat the last row)
+  item = min(item, rows - 1);
   const bool second = !a.alias && (item & 1);
   const int n = a.alias ? item : item >> 1;
   const float* const row = (second ? a.zq : a.zp) + (long long)n * V;
@@ -510,23 +516,27 @@ __device__ __forceinline__ void row_statistics(const LayersArgs& a, int item, Sh
   f32x4 nx[SU];
   auto request = [&](int i) __attribute__((always_inline)) {
 #pragma unroll
-    for (int k = 0; k < SU; ++k) nx[k] = __builtin_nontemporal_load(&r4[min(i + k * VL_BLOCK, body4 - 1)]);
+    for (int k = 0; k < SU; ++k) nx[k] = __builtin_nontemporal_load(&r4[min(i + k * TR, body4 - 1)]);
   };
   if (tid < body4) request(tid);
+  // children: nodes of the same tree, behind this one, no further than a tree is long
+  const int c = n + tid;
+  const bool child = tid >= 1 && tid < DSBD_MAX_TREE_NODES && c < a.n_nodes && a.parent[c] == n;
+  const int par = a.parent[n], tok = a.token[n];
   if (tid < head) online_add1(m, s, bad, row[tid]);
   if (tail0 + tid < V) online_add1(m, s, bad, row[tail0 + tid]);
-  for (int i = tid; i < body4; i += SU * VL_BLOCK) {
+  for (int i = tid; i < body4; i += SU * TR) {
     f32x4 y[SU];
 #pragma unroll
     for (int k = 0; k < SU; ++k) y[k] = nx[k];
-    if (i + SU * VL_BLOCK < body4) request(i + SU * VL_BLOCK);
+    if (i + SU * TR < body4) request(i + SU * TR);
 #pragma unroll
     for (int k = 0; k < SU; k += 4) {
       float4 x[4];
 #pragma unroll
       for (int e = 0; e < 4; ++e) {     // (places beyond the end are masked tokens: they change neither maximum nor sum, and a
                                         // row of nothing else keeps its maximum of -Inf, by which it is found below)
-        const bool in = i + (k + e) * VL_BLOCK < body4;
+        const bool in = i + (k + e) * TR < body4;
         x[e] = in ? make_float4(y[k + e].x, y[k + e].y, y[k + e].z, y[k + e].w) : make_float4(-INFINITY, -INFINITY, -INFINITY, -INFINITY);
       }
       online_add16(m, s, bad, x[0], x[1], x[2], x[3]);
@@ -537,31 +547,34 @@ __device__ __forceinline__ void row_statistics(const LayersArgs& a, int item, Sh
     const float m2 = __shfl_xor(m, off), s2 = __shfl_xor(s, off);
     online_merge(m, s, m2, s2);
   }
-  if (tid == 0) sh.sbad = 0;
-  float2* const part = reinterpret_cast<float2*>(sh.tsum);
-  if (lane == 0) part[wave] = make_float2(m, s);
-  __syncthreads();
-  if (bad) sh.sbad = 1;
-  float M = part[0].x, S = part[0].y;
+  bad = __ballot(bad) != 0ull;
+  if constexpr (TR > 64) {
+    float2* const part = reinterpret_cast<float2*>(sh.tsum);
+    const int wave = threadIdx.x >> 6, first = (int)threadIdx.x / TR * (TR / 64);
+    if ((threadIdx.x & 63) == 0) { part[2 * wave] = make_float2(m, s); part[2 * wave + 1].x = bad ? 1.f : 0.f; }
+    __syncthreads();
+    m = part[2 * first].x; s = part[2 * first].y; bad = part[2 * first + 1].x != 0.f;
 #pragma unroll
-  for (int w = 1; w < VL_WAVES; ++w) online_merge(M, S, part[w].x, part[w].y);
-  const float lse = M + logf(S);
+    for (int w = 1; w < TR / 64; ++w) {
+      online_merge(m, s, part[2 * (first + w)].x, part[2 * (first + w)].y);
+      bad |= part[2 * (first + w) + 1].x != 0.f;
+    }
+  }
+  if (!live) return;
+  const float lse = m + logf(s);
   float* const o_lse = second ? a.lse_q : a.lse_p;
   float* const o_logp = second ? a.logp_q : a.logp_p;
-  // children: nodes of the same tree, behind this one, no further than a tree is long
-  const int par = a.parent[n], tok = a.token[n];
   int fault = 0;
   if (tid == 0) {
     if (o_lse) o_lse[n] = lse;
     if (a.alias && a.lse_q) a.lse_q[n] = lse;
-    if (lse == -INFINITY) fault = DSBD_FAULT_NONFINITE;                // a row without a finite logit
+    if (bad || lse == -INFINITY) fault = DSBD_FAULT_NONFINITE;         // NaN or +Inf; a row without a finite logit
     if (!(par >= 0 && par < n && n - par < DSBD_MAX_TREE_NODES && tok >= 0 && tok < V)) {      // a root (or a node reported elsewhere)
       if (o_logp) o_logp[n] = 0.f;
       if (a.alias && a.logp_q) a.logp_q[n] = 0.f;
     }
   }
-  const int c = n + tid;
-  if (tid >= 1 && tid < DSBD_MAX_TREE_NODES && c < a.n_nodes && a.parent[c] == n) {
+  if (child) {
     const int ct = a.token[c];
     if (ct >= 0 && ct < V) {
       const float zt = row[ct];
@@ -570,8 +583,6 @@ __device__ __forceinline__ void row_statistics(const LayersArgs& a, int item, Sh
       if (a.alias && a.logp_q) a.logp_q[c] = zt - lse;
     }
   }
-  __syncthreads();
-  if (tid == 0 && sh.sbad) fault = DSBD_FAULT_NONFINITE;
   if (fault) atomicOr(a.fault, fault);
 }
 
@@ -585,7 +596,10 @@ void verify_layers_kernel(LayersArgs a) {
   __shared__ LayerShared<NC> sh;
   extern __shared__ __attribute__((aligned(16))) double dyn_lds[];
   if ((int)blockIdx.x >= a.layer_wgs) {
-    row_statistics(a, (int)blockIdx.x - a.layer_wgs, sh);
+    if (a.stats_threads == 64) row_statistics<64>(a, sh);
+    else if (a.stats_threads == 128) row_statistics<128>(a, sh);
+    else if (a.stats_threads == 256) row_statistics<256>(a, sh);
+    else row_statistics<VL_BLOCK>(a, sh);
     return;
   }
   const int prompt = a.prompt0 + blockIdx.x / a.G;
@@ -2657,17 +2671,27 @@ int layer_workgroups(const dsbd_forest* f, int V, const dsbd_params* p, bool spa
     return G < 1 ? 1 : G;
   }
   // ... minus compute units for the workgroups that take the rows' statistics meanwhile: one per MB of logits (30 GB/s for
-  // a unit on its own, over the 35 us that the shortest walks take), at most a quarter of the device, and none where the
-  // coarser slices would not fit the LDS any more.  Measured, verification in us with 0 / 32 / 64 units kept: 40 nodes x
-  // 128256, 8 beams 50 / 44 / 39 (dynamic width 75 / 66 / 65, top_k 10 81 / 75 / 75), 248 nodes 128 / 122 / 111; 16 prompts,
-  // 341 nodes x 32000 (8000-entry slices, 10667 with 64 kept): 88 / 112 / 112.
+  // a unit on its own, over the 35 us that the shortest walks take), at most a quarter of the device, as long as the
+  // coarser slices fit the LDS.  A lone prompt loses next to nothing by it (its exchanges get shorter as its passes get
+  // longer).  With several prompts it takes 90 MB of logits that would otherwise stand behind the layers (13 us), and
+  // 300 MB where the slices outgrow the LDS, up to twice its size (four times for warped joints, which are read less
+  // often).  The dynamic width on unwarped joints passes over the slices for every entry of its chains: there a row is
+  // never cut into less than 85 % of the pieces.  Measured, verification in us with 0 / a quarter of the units kept:
+  // 8 beams, 248 nodes x 128256 137 / 109 (t = 0.7 310 / 286, t = 0.9 and top_k 10 202 / 162), 64 nodes 73 / 62; 2 prompts of 8
+  // beams, 496 nodes x 32000 94 / 85, x 128256 199 / 181; 4 prompts, 992 nodes x 32000 120 / 111 (t = 0.7 304 / 341, an eighth
+  // 316; t = 0.9 and top_k 10 140 / 118), 256 nodes 78 / 79; 16 prompts of 4 beams, 1984 nodes x 16000 105 / 97 (t = 0.7 248 /
+  // 308), 341 nodes x 32000 88 / 112; 3 prompts, 103 nodes x 50273, t = 0.7: 84 / 78 / 72 / 66 workgroups each 104 / 104 / 98 / 99.
   {
-    long long keep = (2LL * f->n_nodes * V * 4 + (1 << 20) - 1) / (1 << 20);
+    const long long bytes = 2LL * f->n_nodes * V * 4;
+    long long keep = (bytes + (1 << 20) - 1) / (1 << 20);
     if (keep > lim.cus / 4) keep = lim.cus / 4;
-    const int W = f->max_prompt_trees;
-    if (f->n_prompts > 0) {
-      const int Gk = (int)((lim.cus - keep) / f->n_prompts);
-      if (Gk >= W && slice_cut(W, V, Gk).len <= lds_slice_entries(f, p)) G = Gk;
+    const int W = f->max_prompt_trees, P = f->n_prompts;
+    const bool warped = p->top_k > 0, chains = p->t >= 0.0f && !warped;
+    int Gk = P > 0 ? (int)((lim.cus - keep) / P) : 0;
+    if (P > 1 && chains) Gk = std::max(Gk, (G / W * 85 + 99) / 100 * W);
+    if (Gk >= W && Gk < G) {
+      const long long slice = slice_cut(W, V, Gk).len, room = lds_slice_entries(f, p);
+      if (P == 1 ? slice <= room : chains || bytes >= 300000000LL ? slice <= (warped ? 4 : 2) * room : bytes >= 90000000LL && slice <= room) G = Gk;
     }
   }
   // (sized by the joint of the input beams, which is what a fixed width keeps every layer at: shorter slices make shorter
@@ -2803,6 +2827,21 @@ LaunchOrder* launch_order_of_current_device(bool may_create) {
   return s.ok ? &s : nullptr;
 }
 
+// Threads per row of the row statistics.  A wave with a row of its own streams without a break between its loads and waits
+// for nobody; a workgroup on one row waits at its end for the slowest wave, for the row's few words and for the next
+// workgroup, on a compute unit that the layers' LDS leaves to one workgroup at a time.  So as few threads as still give
+// every compute unit that the layers leave free (or all of them, when they leave none: then the rows run behind the
+// layers) a workgroup, or nearly.  Measured, verification in us with 512 / 256 / 128 / 64 threads per row: 200 prompts, 8400
+// rows x 1000 172 / 120 / 87 / 80, x 8000 324 / 249 / 235 / 234; 8 prompts, 3968 rows x 32000 218 / 193 / 191 / 192; 1024 rows 110 /
+// 104 / 103 / 102; one prompt, 496 rows x 128256 109 / 98 / 97 / 96, 256 rows 78 / 78 / 78 / 81, 64 rows 52 / 52 / 52 / 76.
+int statistics_threads(const dsbd_forest* f, const VerifyPlan& pl, unsigned rows) {
+  const int cus = device_limits().cus;
+  const int left = cus - pl.group * pl.G, units = left > 0 ? left : cus;
+  int threads = 64;
+  while (threads < VL_BLOCK && (long long)rows * threads * 10 < (long long)units * VL_BLOCK * 9) threads *= 2;
+  return threads;
+}
+
 std::atomic<unsigned long long> g_launch_counter{0};
 
 // In front of a layer kernel that is recorded into a graph: every replay repeats the launch's arguments, so what tells
@@ -2911,12 +2950,15 @@ int32_t verify_impl(const dsbd_forest* f, const dsbd_verify_in* in, const dsbd_p
       return DSBD_ERR_HIP;
     }
   }
+  const unsigned rows = (unsigned)f->n_nodes * (alias ? 1u : 2u);
+  la.stats_threads = statistics_threads(f, pl, rows);
+  const unsigned rows_per_wg = VL_BLOCK / la.stats_threads;
   for (int p0 = 0; p0 < f->n_prompts; p0 += pl.group) {
     la.prompt0 = p0;
     const int np = f->n_prompts - p0 < pl.group ? f->n_prompts - p0 : pl.group;
     unsigned grid3 = (unsigned)np * (unsigned)pl.G;
     la.layer_wgs = (int)grid3;
-    if (want_stats && p0 + np == f->n_prompts) grid3 += (unsigned)f->n_nodes * (alias ? 1u : 2u);     // behind the (last) layers
+    if (want_stats && p0 + np == f->n_prompts) grid3 += (rows + rows_per_wg - 1) / rows_per_wg;     // behind the (last) layers
     if (p->top_k > 0)
       dsbd_launch(DSBD_KERNEL_VERIFY_LAYERS, verify_layers_kernel<true, NODE_CAP>, dim3(grid3), dim3(VL_BLOCK),
                   (unsigned int)pl.lds_bytes, stream, la);

@@ -969,6 +969,40 @@ def test_a_row_of_masked_tokens_is_reported_also_at_a_leaf(V):
             assert torch.equal(getattr(res, "node_logp_" + m), getattr(clean, "node_logp_" + m))
 
 
+@pytest.mark.parametrize("n_prompts", [1, 2, 4, 8])
+@pytest.mark.parametrize("V", [1, 5, 2047, 2048, 2053, 4096, 4099, 8192, 8195, 16387])
+def test_row_statistics_with_fewer_threads_per_row(n_prompts, V):
+    """The more rows there are, the fewer threads take one (512, 256, 128, 64 for 248, 496, 992, 1984 rows): per-node
+    outputs against fp64 at and off whole load rounds of each (32 logits per thread), a row of masked tokens and a row
+    with a NaN reported wherever they sit, also the last one.  The bound is that of the test above with a thread's
+    chunk of at most V / 64 + 16 terms."""
+    gu = _gu()
+    import paper_2409_16560_amd as dsbd
+    w = make_workload("c4", L=1, Hq=1, Hkv=1, D=64, V=V, n_prompts=n_prompts, W=4, tree="random", tree_nodes=31)
+    print("case", n_prompts, V, "rows", 2 * w.n_nodes, flush=True)
+    d = gu.DeviceWorkload(w)
+    res = d.verify(t=-1.0)
+    torch.cuda.synchronize()
+    assert int(res.fault.item()) & ~8 == 0        # (a vocabulary of one token: a residual without mass)
+    tol = (V / 64 + 26) * 2.0 ** -24 + 4 * 2.0 ** -24 * 32
+    par, tok = torch.from_numpy(w.parent).cuda().long(), torch.from_numpy(w.token).cuda().long()
+    for z, lse, logp in ((d.logits_p, res.lse_target, res.node_logp_target), (d.logits_q, res.lse_draft, res.node_logp_draft)):
+        ref = torch.logsumexp(z.double(), 1)
+        assert float((lse.double() - ref).abs().max()) <= tol
+        ref_lp = torch.where(par >= 0, z.double()[par.clamp(min=0), tok] - ref[par.clamp(min=0)], torch.zeros_like(ref))
+        assert float((logp.double() - ref_lp).abs().max()) <= 2 * tol
+    leaves = np.flatnonzero(~np.isin(np.arange(w.n_nodes), w.parent))
+    for n, value in ((leaves[-1], -np.inf), (leaves[0], np.nan), (w.n_nodes - 1, np.nan), (leaves[len(leaves) // 2], -np.inf)):
+        keep = d.logits_q[n].clone()
+        d.logits_q[n] = float(value)
+        bad = d.verify(t=-1.0)
+        torch.cuda.synchronize()
+        d.logits_q[n] = keep
+        assert int(bad.fault.item()) & dsbd.DSBD_FAULT_NONFINITE, (n, value)
+        others = torch.arange(w.n_nodes, device="cuda") != int(n)
+        assert torch.equal(bad.lse_draft[others], res.lse_draft[others]) and torch.equal(bad.lse_target, res.lse_target)
+
+
 @pytest.mark.parametrize("what", ["likelihoods", "masked rows", "NaN rows"])
 @pytest.mark.parametrize("V,top_k", [(500, 8), (20000, 10)])
 def test_warped_draws_from_a_joint_without_an_entry_stay_in_bounds(what, V, top_k):
