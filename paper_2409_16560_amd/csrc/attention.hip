@@ -24,6 +24,7 @@
 #include "common.h"
 #include "topology_device.h"
 #include <stdlib.h>
+#include <type_traits>
 
 typedef __attribute__((__vector_size__(8 * sizeof(__bf16)))) __bf16 bf16x8;
 typedef __attribute__((__vector_size__(4 * sizeof(float)))) float floatx4;
@@ -58,10 +59,15 @@ struct AttnArgs {
   int nsplit, n_rowblocks;      // row blocks: of the largest tree the caller announces
   int rows_block;               // query rows per workgroup
   int wg_slots;                 // by_tree: workgroups to spread the work over
-  int n_slots;                  // partial results there is room for (the main kernel's grid)
-  float* part_o;                // [n_slots][rows_block][D]
-  float* part_ml;               // [n_slots][rows_block][2]
-  int2* row_parts;              // [n_nodes*Hq] where a row's first partial result is, and how many there are (null: no splits)
+  // Partial results, one of two layouts (the plan takes the smaller): by split, the row of split s behind those of all
+  // rows of the splits before it; or a slot of part_pitch rows per workgroup, a unit's splits in consecutive slots.
+  int by_split;
+  int part_pitch;
+  long long part_stride;        // rows between a row's partial results of consecutive splits
+  long long part_rows;          // rows there is room for
+  float* part_o;                // [part_rows][D]
+  float* part_ml;               // [part_rows][2]
+  int2* row_parts;              // [n_nodes*Hq] a row's first partial result (slots), and how many there are (null: no splits)
   __bf16* out;                  // written by the main kernel where a unit is not split, else by the merge kernel
   float* lse;
   int32_t* fault;
@@ -101,6 +107,22 @@ __device__ __forceinline__ void wave_lds_fence() {
 // arithmetic.  Here only the LDS counter is drained; global loads stay in flight across the barrier.
 __device__ __forceinline__ void lds_barrier() {
   asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+}
+
+// Wave-wide sum by lane moves inside the SIMD (shuffles go through the LDS: twelve of them stood in front of a workgroup's
+// first loads, 0.4 us).
+template <int CTRL, int ROW_MASK>
+__device__ __forceinline__ float dpp_move_f32(float v) {           // lanes without a source lane read 0
+  return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), CTRL, ROW_MASK, 0xf, false));
+}
+__device__ __forceinline__ float wave_sum_f32(float v) {
+  v += dpp_move_f32<0xB1, 0xf>(v);    // quad_perm [1,0,3,2]
+  v += dpp_move_f32<0x4E, 0xf>(v);    // quad_perm [2,3,0,1]
+  v += dpp_move_f32<0x124, 0xf>(v);   // row_ror:4
+  v += dpp_move_f32<0x128, 0xf>(v);   // row_ror:8: every lane holds the total of its row of 16
+  v += dpp_move_f32<0x142, 0xa>(v);   // row_bcast:15 into rows 1 and 3
+  v += dpp_move_f32<0x143, 0xc>(v);   // row_bcast:31 into rows 2 and 3: lane 63 holds the total
+  return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), 63));
 }
 
 // ---- which part of the work a workgroup has
@@ -180,8 +202,7 @@ __device__ __forceinline__ bool work_place(const AttnArgs& a, WorkShare& w, Plac
     if (lane >= a.n_trees) { steps = 0; nrb = 0; }
     else if (bid == 0 && tid < 64 && nrb == 0) atomicOr(a.fault, DSBD_FAULT_TOPOLOGY);
     float units = (float)(nrb * a.Hkv), total = units * (float)steps;
-#pragma unroll
-    for (int off = 32; off >= 1; off >>= 1) { total += __shfl_xor(total, off); units += __shfl_xor(units, off); }
+    total = wave_sum_f32(total); units = wave_sum_f32(units);
     const int ns = splits_of(a, steps, total, units, UNIT == 64), count = a.Hkv * nrb * ns;
     int first = 0;
     for (int o = 0; o < a.n_trees; ++o) {
@@ -207,8 +228,7 @@ __device__ __forceinline__ bool work_place(const AttnArgs& a, WorkShare& w, Plac
         if (bid == 0 && nrb == 0) atomicOr(a.fault, DSBD_FAULT_TOPOLOGY);
       }
       float units = (float)(nrb * a.Hkv), total = units * (float)steps;
-#pragma unroll
-      for (int off = 32; off >= 1; off >>= 1) { total += __shfl_xor(total, off); units += __shfl_xor(units, off); }
+      total = wave_sum_f32(total); units = wave_sum_f32(units);
       if ((tid & 63) == 0) { w.wsum[tid >> 6] = total; w.usum[tid >> 6] = units; }
       if (tid == 0) w.b = -1;
       __syncthreads();
@@ -246,10 +266,21 @@ __device__ __forceinline__ bool work_place(const AttnArgs& a, WorkShare& w, Plac
   return true;
 }
 
+// Where this workgroup's rows leave their results: `rows` of them (all, but for trees with more nodes than announced or that
+// share nodes with others: slots hold no more), row rl at `at` + rl (slots) or + its number among all rows (by split).
+struct PartPlace { long long at; int rows; };
+__device__ __forceinline__ PartPlace part_place(const AttnArgs& a, int split, int nsplit, int rows) {
+  PartPlace p = {split * a.part_stride, rows};
+  if (!a.by_split) {
+    p.at = (long long)blockIdx.x * a.part_pitch;
+    if (nsplit > 1) p.rows = p.at + a.part_pitch <= a.part_rows ? min(rows, a.part_pitch) : 0;
+  }
+  return p;
+}
+
 // Four channels of a finished row: out = acc / L, and once per row the log-sum-exp.
 template <int D>
-__device__ __forceinline__ void write_row_part(const AttnArgs& a, int node, int head, int part, float M, float L, floatx4 acc) {
-  const long long row = (long long)node * a.Hq + head;
+__device__ __forceinline__ void write_row_part(const AttnArgs& a, long long row, int part, float M, float L, floatx4 acc) {
   const float inv = L > 0.f ? 1.f / L : 0.f;
   union { __bf16 h[4]; uint2 u; } pk;
 #pragma unroll
@@ -545,10 +576,11 @@ __global__ __launch_bounds__(AT_BLOCK) void forest_attention_kernel(AttnArgs a) 
   }
   __syncthreads();
   constexpr int QPR = D / 4;
+  const PartPlace place = part_place(a, split, nsplit, min(R - row0, ROWS_B));
 #pragma unroll
   for (int c = threadIdx.x; c < ROWS_B * QPR; c += AT_BLOCK) {
     const int rl = c / QPR, part = c % QPR, r = row0 + rl;
-    if (r >= R) break;                 // (rows rise with c)
+    if (rl >= place.rows) break;       // (rows rise with c)
     float m[TW], M = NEG_BIG, L = 0.f;
 #pragma unroll
     for (int w = 0; w < TW; ++w) { m[w] = wave_ml[w][rl][0]; M = fmaxf(M, m[w]); }
@@ -559,11 +591,11 @@ __global__ __launch_bounds__(AT_BLOCK) void forest_attention_kernel(AttnArgs a) 
       L += e * wave_ml[w][rl][1];
       acc += e * *reinterpret_cast<const floatx4*>(&reinterpret_cast<const float*>(tiles[w])[rl * OP + 4 * part]);
     }
-    const int node = base + r / a.group, head = g * a.group + r % a.group;
-    const long long prow = (long long)blockIdx.x * ROWS_B + rl;
-    if (part == 0 && split == 0 && a.row_parts) a.row_parts[(long long)node * a.Hq + head] = make_int2((int)prow, nsplit);
+    const int row = (base + r / a.group) * a.Hq + g * a.group + r % a.group;
+    const long long prow = place.at + (a.by_split ? row : rl);
+    if (part == 0 && split == 0 && a.row_parts) a.row_parts[row] = make_int2((int)prow, nsplit);
     if (nsplit == 1) {
-      write_row_part<D>(a, node, head, part, M, L, acc);
+      write_row_part<D>(a, row, part, M, L, acc);
     } else {
       if (part == 0) *reinterpret_cast<float2*>(&a.part_ml[prow * 2]) = make_float2(M, L);
       *reinterpret_cast<floatx4*>(&a.part_o[prow * D + 4 * part]) = acc;
@@ -608,6 +640,7 @@ void forest_attention_dma_kernel(AttnArgs a) {
   __shared__ __attribute__((aligned(16))) uint4 vB[SLOTS];
   __shared__ float half_ml[2 * ROWS_W][2];
   __shared__ float row_ml[ROWS_B][2];
+  __shared__ int row_id[ROWS_B];            // node * Hq + head
   __shared__ WorkShare share;
 
   const int tid = threadIdx.x;
@@ -909,20 +942,26 @@ void forest_attention_dma_kernel(AttnArgs a) {
     stage(array_of(rgrp));
     if (qd == 0)
 #pragma unroll
-      for (int rt = 0; rt < NRT; ++rt) { row_ml[rgrp * ROWS_W + rt * 16 + col][0] = m_run[rt]; row_ml[rgrp * ROWS_W + rt * 16 + col][1] = l_run[rt]; }
+      for (int rt = 0; rt < NRT; ++rt) {
+        const int rl = rgrp * ROWS_W + rt * 16 + col, r = rb * ROWS_B + rl;
+        row_ml[rl][0] = m_run[rt]; row_ml[rl][1] = l_run[rt];
+        row_id[rl] = (base + r / a.group) * a.Hq + g * a.group + r % a.group;
+      }
   }
   __syncthreads();
-  for (int c = tid; c < rows_here * QPR; c += AT_BLOCK) {
+  // (a short loop on purpose: every workgroup runs this once, and instructions that are not in the cache yet cost more
+  // than the LDS reads' round trips: written out over the rows 1.3 us more)
+  const PartPlace place = part_place(a, split, nsplit, rows_here);
+  for (int c = tid; c < place.rows * QPR; c += AT_BLOCK) {
     const int rl = c / QPR, part = c % QPR, lr = rl % ROWS_W;
     union { floatx4 f; uint4 u; } cv;
     cv.u = array_of(rl / ROWS_W)[lr * QPR + (part ^ (lr & 7))];
     const float M = row_ml[rl][0], L = row_ml[rl][1];
-    const int r = rb * ROWS_B + rl;
-    const int node = base + r / a.group, head = g * a.group + r % a.group;
-    const long long prow = (long long)blockIdx.x * ROWS_B + rl;
-    if (part == 0 && split == 0 && a.row_parts) a.row_parts[(long long)node * a.Hq + head] = make_int2((int)prow, nsplit);
+    const int row = row_id[rl];
+    const long long prow = place.at + (a.by_split ? row : rl);
+    if (part == 0 && split == 0 && a.row_parts) a.row_parts[row] = make_int2((int)prow, nsplit);
     if (nsplit == 1) {
-      write_row_part<D>(a, node, head, part, M, L, cv.f);
+      write_row_part<D>(a, row, part, M, L, cv.f);
     } else {
       if (part == 0) *reinterpret_cast<float2*>(&a.part_ml[prow * 2]) = make_float2(M, L);
       *reinterpret_cast<uint4*>(&a.part_o[prow * D + 4 * part]) = cv.u;
@@ -941,28 +980,45 @@ __global__ __launch_bounds__(AT_BLOCK) void forest_attention_combine_kernel(Attn
   constexpr int RPB = AT_BLOCK / (QPR * SG); // rows per workgroup
   __shared__ floatx4 s_acc[SG][SG > 1 ? RPB * QPR : 1];
   __shared__ float2 s_ml[SG][RPB];
-  const int lr = threadIdx.x % (RPB * QPR), sg = threadIdx.x / (RPB * QPR);
+  const int lr = threadIdx.x % (RPB * QPR), sg = SG > 1 ? __builtin_amdgcn_readfirstlane(threadIdx.x / (RPB * QPR)) : 0;      // (waves)
   const long long row = (long long)blockIdx.x * RPB + lr / QPR;
   const int quad = lr % QPR;
   const bool in = row < (long long)a.n_nodes * a.Hq;
+  // By split, the places of a row's results are known without its entry in row_parts: the first two that a thread may need
+  // travel beside it (what is read of a split that the row does not have is not used).
+  const float* po = a.part_o + row * D + 4 * quad;
+  const float* pml = a.part_ml + row * 2;
+  auto fetch = [&](int s, float2& ml, floatx4& v) __attribute__((always_inline)) {
+    const long long off = s * a.part_stride;            // (uniform)
+    ml = *reinterpret_cast<const float2*>(pml + off * 2);
+    v = *reinterpret_cast<const floatx4*>(po + off * D);
+  };
+  float2 ml[8];
+  floatx4 v[8];
+  if (a.by_split && in) {
+#pragma unroll
+    for (int j = 0; j < 2; ++j) fetch(min(sg + j * SG, a.nsplit - 1), ml[j], v[j]);
+  }
   const int2 parts = in ? a.row_parts[row] : make_int2(0, 0);
   const int nsplit = parts.y;
+  const long long first = a.by_split ? row : parts.x;
   // (one part: already written by the main kernel; the rows of a tree with unusable offsets hold nothing to go by)
-  const bool live = nsplit >= 2 && nsplit <= AT_MAX_SPLIT && parts.x >= 0 &&
-                    parts.x + (long long)(nsplit - 1) * a.rows_block < (long long)a.n_slots * a.rows_block;
+  const bool live = nsplit >= 2 && nsplit <= a.nsplit && first >= 0 && first + (nsplit - 1) * a.part_stride < a.part_rows;
   float M = NEG_BIG, L = 0.f;
   floatx4 acc = {0.f, 0.f, 0.f, 0.f};
-  if (live) {
-    for (int s0 = sg; s0 < nsplit; s0 += 8 * SG) {
-      float2 ml[8];
-      floatx4 v[8];
+  if (live && sg < nsplit) {
+    int s0 = sg;
+    if (!a.by_split) {
+      po = a.part_o + first * D + 4 * quad;
+      pml = a.part_ml + first * 2;
 #pragma unroll
-      for (int j = 0; j < 8; ++j) {
-        if (j > 0 && s0 + j * SG >= nsplit) continue;
-        const long long prow = parts.x + (long long)(s0 + j * SG) * a.rows_block;
-        ml[j] = *reinterpret_cast<const float2*>(&a.part_ml[prow * 2]);
-        v[j] = *reinterpret_cast<const floatx4*>(&a.part_o[prow * D + 4 * quad]);
-      }
+      for (int j = 0; j < 2; ++j)
+        if (s0 + j * SG < nsplit) fetch(s0 + j * SG, ml[j], v[j]);
+    }
+    while (true) {
+#pragma unroll
+      for (int j = 2; j < 8; ++j)
+        if (s0 + j * SG < nsplit) fetch(s0 + j * SG, ml[j], v[j]);
       float Mb = M;
 #pragma unroll
       for (int j = 0; j < 8; ++j)
@@ -976,6 +1032,11 @@ __global__ __launch_bounds__(AT_BLOCK) void forest_attention_combine_kernel(Attn
           L += w * ml[j].y;
           acc += w * v[j];
         }
+      s0 += 8 * SG;
+      if (s0 >= nsplit) break;
+#pragma unroll
+      for (int j = 0; j < 2; ++j)
+        if (s0 + j * SG < nsplit) fetch(s0 + j * SG, ml[j], v[j]);
     }
   }
   if constexpr (SG > 1) {
@@ -994,7 +1055,7 @@ __global__ __launch_bounds__(AT_BLOCK) void forest_attention_combine_kernel(Attn
     acc = acc * e1 + s_acc[g][lr] * e2;
     M = Mn;
   }
-  write_row_part<D>(a, (int)(row / a.Hq), (int)(row % a.Hq), quad, M, L, acc);
+  write_row_part<D>(a, row, quad, M, L, acc);
 }
 
 // ------------------------------------------------------------------------------------------------ host side
@@ -1009,6 +1070,10 @@ struct AttnPlan {
   int slots;
   long long grid;             // workgroups of the main kernel
   bool merge;                 // some unit may be split
+  bool by_split;              // layout of the partial results, see AttnArgs
+  int part_pitch;
+  long long part_stride, part_rows;
+  long long part_room;        // rows of partial results that the workspace holds: part_rows, or more (see make_plan)
 };
 
 AttnPlan make_plan(const dsbd_forest* f, const dsbd_kv* kv, int Hq, int Hkv, int D) {
@@ -1044,7 +1109,29 @@ AttnPlan make_plan(const dsbd_forest* f, const dsbd_kv* kv, int Hq, int Hkv, int
     p.grid = most * p.nsplit;
   }
   p.merge = p.nsplit > 1;
+  const long long rows = (long long)f->n_nodes * Hq;
+  p.part_pitch = p.rows_block < rmax ? p.rows_block : rmax;
+  // (trees are split only where all workgroups together are no more than the slots)
+  const long long slot_rows = (p.by_tree && p.grid > p.slots ? p.slots : p.grid) * p.part_pitch, split_rows = rows * p.nsplit;
+  p.by_split = split_rows < slot_rows;
+  p.part_stride = p.by_split ? rows : p.part_pitch;
+  p.part_rows = !p.merge ? 0 : (p.by_split ? split_rows : slot_rows);
+  // The workspace asked for covers what any forest within these bounds (fewer trees, nodes, tokens) can need, split or
+  // not, so that a buffer for a caller's largest call serves the others too.
+  const int room_split = most_steps < (p.shared ? 7 : 16) ? 1 : split_limit(most_steps, p.shared);
+  const long long room_slots = (long long)(f->n_trees > AT_BLOCK ? 2 : 1) * p.slots * p.part_pitch;
+  p.part_room = room_split < 2 ? 0 : (rows * room_split < room_slots ? rows * room_split : room_slots);
+  if (p.part_room < p.part_rows) p.part_room = p.part_rows;
   return p;
+}
+
+// The workspace: partial results and the rows' entries.
+size_t carve_attention(WorkspaceCarver& ws, const AttnPlan& p, const dsbd_forest* f, int Hq, int D, AttnArgs* a) {
+  float* const o = ws.take<float>((size_t)p.part_room * D);
+  float* const ml = ws.take<float>((size_t)p.part_room * 2);
+  int2* const parts = ws.take<int2>(p.part_room > 0 ? (size_t)f->n_nodes * Hq : 0);
+  if (a) { a->part_o = o; a->part_ml = ml; a->row_parts = p.merge ? parts : nullptr; }
+  return ws.total() + 256;
 }
 
 int32_t check_args(const dsbd_forest* f, const dsbd_kv* kv, int Hq, int Hkv, int D) {
@@ -1088,11 +1175,7 @@ extern "C" size_t dsbd_forest_attention_workspace_bytes(const dsbd_forest* f, co
   if (check_args(f, kv, Hq, Hkv, D) != DSBD_OK) return 0;
   const AttnPlan p = make_plan(f, kv, Hq, Hkv, D);
   WorkspaceCarver ws(nullptr);
-  const size_t rows = p.merge ? (size_t)p.grid * p.rows_block : 0;
-  ws.take<float>(rows * D);
-  ws.take<float>(rows * 2);
-  ws.take<int2>(p.merge ? (size_t)f->n_nodes * Hq : 0);
-  return ws.total() + 256;
+  return carve_attention(ws, p, f, Hq, D, nullptr);
 }
 
 extern "C" int32_t dsbd_forest_attention(const dsbd_forest* f, const dsbd_kv* kv, const void* q, const void* k_tree,
@@ -1109,19 +1192,18 @@ extern "C" int32_t dsbd_forest_attention(const dsbd_forest* f, const dsbd_kv* kv
   if ((reinterpret_cast<uintptr_t>(q) | reinterpret_cast<uintptr_t>(k_tree) | reinterpret_cast<uintptr_t>(v_tree) |
        reinterpret_cast<uintptr_t>(out)) & 15)
     return DSBD_ERR_INVALID;
-  if (workspace_bytes < dsbd_forest_attention_workspace_bytes(f, kv, Hq, Hkv, D)) return DSBD_ERR_WORKSPACE;
   hipStream_t stream = static_cast<hipStream_t>(stream_);
   const AttnPlan p = make_plan(f, kv, Hq, Hkv, D);
-  // (rows of partial results are counted in 32-bit integers)
-  if (p.grid > 0x7fffffffLL || (p.merge && p.grid * p.rows_block > 0x7fffffffLL)) return DSBD_ERR_UNSUPPORTED;
+  {
+    WorkspaceCarver none(nullptr);
+    if (workspace_bytes < carve_attention(none, p, f, Hq, D, nullptr)) return DSBD_ERR_WORKSPACE;
+  }
+  // (a slot's rows are counted in 32-bit integers)
+  if (p.grid > 0x7fffffffLL || (!p.by_split && p.part_rows > 0x7fffffffLL)) return DSBD_ERR_UNSUPPORTED;
 
   WorkspaceCarver ws(reinterpret_cast<char*>(dsbd_align_up(reinterpret_cast<uintptr_t>(workspace), 256)));
-  const size_t rows = p.merge ? (size_t)p.grid * p.rows_block : 0;
   AttnArgs a;
-  a.part_o = ws.take<float>(rows * D);
-  a.part_ml = ws.take<float>(rows * 2);
-  int2* const row_parts = ws.take<int2>(p.merge ? (size_t)f->n_nodes * Hq : 0);
-  a.row_parts = p.merge ? row_parts : nullptr;
+  carve_attention(ws, p, f, Hq, D, &a);
   a.tree_off = f->tree_off; a.parent = f->parent;
   a.max_tree_nodes = f->max_tree_nodes; a.max_depth = f->max_depth; a.anc_out = anc_mask_out;
   a.k_ptr = kv->k_ptr; a.v_ptr = kv->v_ptr; a.len = kv->len;
@@ -1134,7 +1216,8 @@ extern "C" int32_t dsbd_forest_attention(const dsbd_forest* f, const dsbd_kv* kv
   a.scale_log2 = sc * 1.4426950408889634f;
   a.max_len = kv->max_len;
   a.by_tree = p.by_tree ? 1 : 0; a.nsplit = p.nsplit; a.n_rowblocks = p.n_rowblocks; a.rows_block = p.rows_block;
-  a.wg_slots = p.slots; a.n_slots = (int)p.grid;
+  a.wg_slots = p.slots;
+  a.by_split = p.by_split ? 1 : 0; a.part_pitch = p.part_pitch; a.part_stride = p.part_stride; a.part_rows = p.part_rows;
   a.out = static_cast<__bf16*>(out); a.lse = lse; a.fault = fault;
   if (D == 128) launch_attention<128>(p, a, stream);
   else launch_attention<64>(p, a, stream);

@@ -112,12 +112,42 @@ def test_workspace_sizes_scale_with_the_problem():
         lib.dsbd_verify_forest_workspace_bytes(C.byref(big), 128256, C.byref(p))
 
 
+def test_attention_workspace_of_a_larger_forest_serves_a_smaller_one():
+    """The workspace never shrinks with the forest's bounds (trees, nodes, largest tree, tokens), whatever the plan does
+    with each of them, and stays what the partial results of one round of workgroups take: a caller may size one buffer
+    for its largest call."""
+    import random
+    import paper_2409_16560_amd.binding as b
+    lib = b.load_library()
+
+    def need(T, N, largest, L, Hq, Hkv, D):
+        f = b._Forest(T, T, N, None, None, None, None, None, largest, 3, 8)
+        kv = b._KV(None, None, None, None, None, None, Hkv * D, D, L)
+        return lib.dsbd_forest_attention_workspace_bytes(C.byref(f), C.byref(kv), Hq, Hkv, D)
+
+    rng = random.Random(3)
+    for _ in range(20000):
+        Hkv = rng.choice([1, 2, 4, 8, 32])
+        heads = (Hkv * rng.choice([1, 2, 4, 8]), Hkv, rng.choice([64, 128]))
+        T, largest = rng.choice([1, 2, 5, 8, 20, 64, 77, 200, 256, 257, 300, 511, 512, 600, 2000]), rng.randint(1, 64)
+        N, L = rng.randint(T, T * largest), rng.choice([0, 10, 100, 200, 440, 500, 800, 2000, 8000, 50000])
+        T2, largest2, L2 = rng.randint(1, T), rng.randint(1, largest), rng.randint(0, L)
+        if T2 > min(N, T2 * largest2):
+            continue
+        N2 = rng.randint(T2, min(N, T2 * largest2))
+        big = need(T, N, largest, L, *heads)
+        assert 0 < need(T2, N2, largest2, L2, *heads) <= big, (T, N, largest, L, T2, N2, largest2, L2, heads)
+        slots = 1024 if T > 256 else 512
+        assert big <= slots * 128 * (heads[2] + 2) * 4 + 8 * N * heads[0] + 4096
+    # one beam of 9 nodes behind 2048 tokens: as many partial results as rows and splits, not a block per workgroup
+    assert need(1, 9, 9, 2048, 32, 8, 128) <= 8 * 9 * 32 * 130 * 4 + 8 * 9 * 32 + 4096
+
+
 # prompts, beams, nodes per tree, depth, W_cap, V, top_k: problems whose workspace is at most 32 MiB with 4000 joint
-# entries per workgroup (the sizes there, in MiB), and above it with as many workgroups as would be fastest
-FITS_32_MIB = [((1, 1, 1, 0, 32, 50257, 0), 30.0), ((2, 2, 20, 19, 16, 32000, 32), 17.8), ((2, 4, 31, 30, 16, 50257, 4), 30.5),
-               ((3, 2, 8, 7, 16, 32000, 10), 24.2), ((3, 5, 1, 0, 32, 16000, 32), 29.7), ((4, 2, 8, 7, 24, 16000, 0), 23.9),
-               ((4, 2, 16, 15, 32, 8000, 20), 16.7), ((5, 8, 16, 4, 64, 4000, 32), 20.9), ((8, 5, 48, 47, 16, 4000, 10), 13.9),
-               ((16, 5, 20, 15, 24, 4000, 20), 28.8), ((24, 12, 16, 15, 64, 1000, 4), 30.2), ((100, 12, 32, 31, 32, 256, 1), 27.3)]
+# entries per workgroup, and may be above it with as many workgroups as would be fastest
+FITS_32_MIB = [(1, 1, 1, 0, 32, 50257, 0), (2, 2, 20, 19, 16, 32000, 32), (2, 4, 31, 30, 16, 50257, 4), (3, 2, 8, 7, 16, 32000, 10),
+               (3, 5, 1, 0, 32, 16000, 32), (4, 2, 8, 7, 24, 16000, 0), (4, 2, 16, 15, 32, 8000, 20), (5, 8, 16, 4, 64, 4000, 32),
+               (8, 5, 48, 47, 16, 4000, 10), (16, 5, 20, 15, 24, 4000, 20), (24, 12, 16, 15, 64, 1000, 4), (100, 12, 32, 31, 32, 256, 1)]
 
 
 def test_verifications_that_fit_the_static_array():
@@ -133,8 +163,8 @@ def test_verifications_that_fit_the_static_array():
         p = b._Params(0, 1, W_cap, -1.0, top_k, 0.9 if top_k else 1.0)
         return lib.dsbd_verify_forest_workspace_bytes(C.byref(f), V, C.byref(p))
 
-    for shape, mib in FITS_32_MIB:
-        assert 0 < need(*shape) <= mib * 2 ** 20 + 2 ** 16, shape
+    for shape in FITS_32_MIB:
+        assert 0 < need(*shape) <= capacity, shape
     assert need(16, 8, 16, 15, 16, 32000, 0) > capacity          # slices of a full batch: refused, as before
 
 
