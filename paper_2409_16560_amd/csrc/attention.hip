@@ -155,13 +155,14 @@ __device__ __forceinline__ const __bf16* lane_pointer(const void* p, int l) {
   return reinterpret_cast<const __bf16*>(((unsigned long long)hi << 32) | lo);
 }
 
-// Most splits worth their partial results for a unit of so many steps: eight 32-token steps of the wave-private kernel per
-// split (four: 32 units of 57 steps, 28 rows each, 18.5 -> 26.6 us); four 64-token tiles, and as little as two tiles for up to
-// four splits (whole call, us at 2 / 4 / 6 / 8 / 16 splits: 32 units of 33 tiles 30.4 / 22.2 / 20.9 / 21.1 / 26.3; of 9 tiles
-// 17.4 / 15.5 / 16.8 / 16.5).
+// Most splits worth their partial results for a unit of so many steps.  Wave-private kernel (32-token steps, a wave each): four
+// steps per split (whole call, us at 1 / 2 / 3 / 4 / 6 / 8 splits: 8 units of 17 steps 17.4 / 15.2 / 15.5 / 13.7 / 13.2 / 13.3; 32
+// units of 23 steps 15.3 / 14.3 / 13.2 / 13.1 / 11.7 / 11.7).  Tile kernel: four 64-token tiles, and as little as two tiles for
+// up to four splits (at 2 / 4 / 6 / 8 / 16 splits: 32 units of 33 tiles 30.4 / 22.2 / 20.9 / 21.1 / 26.3; of 9 tiles 17.4 / 15.5 /
+// 16.8 / 16.5).
 __host__ __device__ __forceinline__ int split_limit(int steps, bool tiles) {
   const int four = steps / 4, two = steps / 2;
-  const int most = !tiles ? steps / 8 : (four >= 4 ? four : (two < 4 ? two : 4));
+  const int most = !tiles ? four : (four >= 4 ? four : (two < 4 ? two : 4));
   return most < 1 ? 1 : (most > AT_MAX_SPLIT ? AT_MAX_SPLIT : most);
 }
 
@@ -1096,15 +1097,23 @@ AttnPlan make_plan(const dsbd_forest* f, const dsbd_kv* kv, int Hq, int Hkv, int
   long long units = (long long)Hkv * (f->n_trees + (long long)f->n_nodes * group / p.rows_block);
   const long long most = (long long)f->n_trees * Hkv * p.n_rowblocks;
   if (units > most) units = most;
-  p.slots = 512;                                  // workgroups resident at once: two per compute unit
-  p.by_tree = f->n_trees <= AT_BLOCK && dsbd_knobs().attn_nsplit <= 0;
-  // no unit can exceed an even share where there are two rounds of workgroups anyway; and what splitting takes off short
-  // units is less than the merge's launch (4 beams x 7 nodes x 32 heads, 128 units, us unsplit / in two / in four: 17 steps
-  // 13.0 / 14.1 / 14.4, 33 steps 19.7 / 18.4 / 17.7; 8 units of 9 steps 14.0 / 13.9 / 13.5, of 17 steps 17.2 / 15.8 / 14.2;
-  // 32 units of 5 tiles 15.1 / 15.5 / 14.7, of 3 tiles 12.9 / 14.3 / 14.1)
   const int most_steps = (kv->max_len + unit - 1) / unit + 2;
+  p.by_tree = f->n_trees <= AT_BLOCK && dsbd_knobs().attn_nsplit <= 0;
+  // Workgroups to spread the work over: as many as are resident at once, two per compute unit (one for 32 rows of 128
+  // channels in the wave-private kernel, which take a SIMD's registers).  Wave-private work of less than four steps per
+  // wave that way is quicker on one workgroup per unit: some units would have two to run and the others wait for them (us
+  // at 256 / 512 workgroups or the next fewer that come out even: 64 units of 36 steps 16.1 / 16.5, 80 units of 36 steps, 24
+  // rows, 20.6 / 32.7, 128 units of 65 steps 29.8 / 28.7).
+  p.slots = 512;
+  if (!p.shared && ((D == 128 && p.nrt == 2) || units * most_steps < 16LL * 512)) p.slots = 256;
+  // Short units stay whole: what splitting takes off them is less than the merge's launch, the less so the more units there
+  // are (us unsplit / in two / three / four: 8 units of 8 steps 12.7 / 13.0 / 12.9 / 12.9, of 11 steps 14.3 / 15.1 / 13.0 / 12.8;
+  // 64 units of 11 steps 11.5 / 12.7 / 11.2 / 11.2; 96 units of 15 steps 13.0 / 13.6, of 17 steps 14.3 / 14.0; 128 units of 17
+  // steps 14.5 / 15.1, of 23 steps 16.5 / 16.4; 32 units of 5 tiles 15.1 / 15.5 / - / 14.7, of 3 tiles 12.9 / 14.3 / - / 14.1).  And
+  // with two rounds of workgroups none is split (a tree much longer than the others could still gain by it; not measured).
+  const int worth = p.shared ? 7 : (units <= 64 ? 12 : (units < 128 ? 18 : 24));
   int most_split = split_limit(most_steps, p.shared);
-  if (most_steps < (p.shared ? 7 : (units >= 64 ? 24 : 16)) || (long long)f->n_trees * Hkv >= 2 * p.slots) most_split = 1;
+  if (most_steps < worth || (long long)f->n_trees * Hkv >= 2 * 512) most_split = 1;
   if (p.by_tree) {
     p.nsplit = most_split;
     p.grid = p.nsplit > 1 && units < p.slots ? p.slots : units;
@@ -1125,9 +1134,14 @@ AttnPlan make_plan(const dsbd_forest* f, const dsbd_kv* kv, int Hq, int Hkv, int
   p.part_rows = !p.merge ? 0 : (p.by_split ? split_rows : slot_rows);
   // The workspace asked for covers what any forest within these bounds (fewer trees, nodes, tokens) can need, split or
   // not, so that a buffer for a caller's largest call serves the others too.
-  const int room_split = most_steps < (p.shared ? 7 : 16) ? 1 : split_limit(most_steps, p.shared);
-  const long long room_slots = (long long)(f->n_trees > AT_BLOCK ? 2 : 1) * p.slots * p.part_pitch;
-  p.part_room = room_split < 2 ? 0 : (rows * room_split < room_slots ? rows * room_split : room_slots);
+  auto room = [&](bool tiles) -> long long {       // (smaller trees may take the other kernel)
+    const int steps = (kv->max_len + (tiles ? 64 : STEP) - 1) / (tiles ? 64 : STEP) + 2;
+    const int splits = steps < (tiles ? 7 : 12) ? 1 : split_limit(steps, tiles), pitch = tiles ? p.part_pitch : (p.part_pitch < 32 ? p.part_pitch : 32);
+    const long long by_slot = (f->n_trees > AT_BLOCK ? 1024LL : 512LL) * pitch;
+    return splits < 2 ? 0 : (rows * splits < by_slot ? rows * splits : by_slot);
+  };
+  p.part_room = room(false);
+  if (p.shared && p.part_room < room(true)) p.part_room = room(true);
   if (p.part_room < p.part_rows) p.part_room = p.part_rows;
   return p;
 }

@@ -1038,6 +1038,7 @@ def test_warped_draws_from_a_joint_without_an_entry_stay_in_bounds(what, V, top_
     ("70 trees", dict(n_prompts=70, W=1, L=(3, 900), tree_nodes=(1, 9), Hq=4, Hkv=1)),
     ("70 trees, narrow", dict(n_prompts=70, W=1, L=(3, 900), tree_nodes=(1, 9), Hq=2, Hkv=2)),
     ("260 trees", dict(n_prompts=260, W=1, L=(3, 60), tree_nodes=(1, 12), Hq=4, Hkv=1)),
+    ("short units, split", dict(n_prompts=1, W=3, L=(350, 720), tree_nodes=(1, 9), Hq=32, Hkv=16)),
     ("260 trees, split", dict(n_prompts=260, W=1, L=(3, 400), tree_nodes=(1, 12), Hq=4, Hkv=1)),
     # many rows of many splits: partial results in a slot per workgroup (above: by split), in either kernel
     ("large trees, slots", dict(n_prompts=1, W=8, L=4200, tree_nodes=64, Hq=8, Hkv=2)),
