@@ -729,10 +729,12 @@ void forest_attention_dma_kernel(AttnArgs a) {
   const int ld_piece = (lane % PPR) ^ swz(ld_tok);
   // A whole tile (no ragged end) needs no per-lane arithmetic at all: the lane's byte offset inside the tile's
   // first round of tokens is a constant of the segment, the tile and the round are uniform.
+  // (That offset is a 32-bit number: caches with 64 million elements or more from token to token take the general form.)
+  const bool near = a.token_stride >= 0 && a.token_stride < (1LL << 26);
   auto issue = [&](int ti, auto& Kb, auto& Vb) {
     const __bf16 *kp, *vp; long long stride; int tok0, len; bool tree;
     locate(ti, kp, vp, stride, tok0, len, tree);
-    if (tok0 + TILE <= len) {
+    if (near && tok0 + TILE <= len) {
       const char* const kb = reinterpret_cast<const char*>(kp + (long long)tok0 * stride);
       const char* const vb = reinterpret_cast<const char*>(vp + (long long)tok0 * stride);
       const unsigned int lo = (unsigned int)ld_tok * (unsigned int)(stride * 2) + (unsigned int)(ld_piece * 16);

@@ -235,6 +235,28 @@ def test_head_major_cache_layout():
     assert torch.equal(out, ref[0]) and torch.equal(lse, ref[1])
 
 
+@pytest.mark.parametrize("D", [64, 128])
+def test_caches_with_tokens_far_apart(D):
+    """Views into one buffer of several GB whose tokens lie 2 ^ 27 bytes and more apart: the tile kernel's byte offset
+    inside a round of tokens no longer fits 32 bits.  The same values packed give the same bits."""
+    gu = _gu()
+    import paper_2409_16560_amd as dsbd
+    w = make_workload("c2", L=70, V=64, Hq=8, Hkv=2, D=D, W=1, tree_nodes=15, tree="random")
+    d = gu.DeviceWorkload(w)
+    ref = d.attention()
+    k, v = gu.bf16_dev(w.k_own[0]), gu.bf16_dev(w.v_own[0])
+    for stride in ((1 << 26) + 8, 150_000_000):           # elements; 31 * 2 * stride passes 2 ^ 32
+        buf = torch.empty(69 * stride + 2 * 2 * D, dtype=torch.bfloat16, device="cuda")
+        kf = buf.as_strided((70, 2, D), (stride, D, 1), 0)
+        vf = buf.as_strided((70, 2, D), (stride, D, 1), 2 * D)
+        kf.copy_(k); vf.copy_(v)
+        print("case", D, stride, flush=True)
+        out, lse, fault = dsbd.dsbd_forest_attention(d.forest, dsbd.PrefixKV([kf], [vf]), d.q, d.k_tree, d.v_tree)
+        torch.cuda.synchronize()
+        assert int(fault.item()) == 0 and torch.equal(out, ref[0]) and torch.equal(lse, ref[1])
+        del buf, kf, vf
+
+
 VERIFY_CASES = [
     ("c1", {}, 0),
     ("c2", dict(V=1000), 0),
