@@ -29,6 +29,7 @@
 #include <type_traits>
 #include <float.h>
 #include <limits.h>
+#include <math.h>
 #include <stdlib.h>
 #include <algorithm>
 #include <atomic>
@@ -2829,16 +2830,23 @@ LaunchOrder* launch_order_of_current_device(bool may_create) {
 
 // Threads per row of the row statistics.  A wave with a row of its own streams without a break between its loads and waits
 // for nobody; a workgroup on one row waits at its end for the slowest wave, for the row's few words and for the next
-// workgroup, on a compute unit that the layers' LDS leaves to one workgroup at a time.  So as few threads as still give
-// every compute unit that the layers leave free (or all of them, when they leave none: then the rows run behind the
-// layers) a workgroup, or nearly.  Measured, verification in us with 512 / 256 / 128 / 64 threads per row: 200 prompts, 8400
+// workgroup, on a compute unit that the layers' LDS leaves to one workgroup at a time: 1, 1.06, 1.15 and 1.35 of the time
+// per row for 64 to 512 threads.  Against that stand the rounds that the workgroups make on the compute units that the layers
+// leave free (or on all of them, when they leave none: then the rows run behind the layers).  Measured, verification in us with 512 / 256 / 128 / 64 threads per row: 200 prompts, 8400
 // rows x 1000 172 / 120 / 87 / 80, x 8000 324 / 249 / 235 / 234; 8 prompts, 3968 rows x 32000 218 / 193 / 191 / 192; 1024 rows 110 /
 // 104 / 103 / 102; one prompt, 496 rows x 128256 109 / 98 / 97 / 96, 256 rows 78 / 78 / 78 / 81, 64 rows 52 / 52 / 52 / 76.
 int statistics_threads(const dsbd_forest* f, const VerifyPlan& pl, unsigned rows) {
   const int cus = device_limits().cus;
   const int left = cus - pl.group * pl.G, units = left > 0 ? left : cus;
   int threads = 64;
-  while (threads < VL_BLOCK && (long long)rows * threads * 10 < (long long)units * VL_BLOCK * 9) threads *= 2;
+  double best = 0.0;
+  for (int t = 64; t <= VL_BLOCK; t *= 2) {
+    const int rows_per_wg = VL_BLOCK / t;
+    double rounds = ceil((double)rows / rows_per_wg) / units;
+    rounds = rounds <= 3.0 ? ceil(rounds) : rounds + 0.5;
+    const double cost = rounds * rows_per_wg * (t == 64 ? 1.0 : t == 128 ? 1.06 : t == 256 ? 1.15 : 1.35);
+    if (t == 64 || cost < best) { best = cost; threads = t; }
+  }
   return threads;
 }
 

@@ -991,10 +991,10 @@ def test_a_row_of_masked_tokens_is_reported_also_at_a_leaf(V):
             assert torch.equal(getattr(res, "node_logp_" + m), getattr(clean, "node_logp_" + m))
 
 
-@pytest.mark.parametrize("n_prompts", [1, 2, 4, 8])
-@pytest.mark.parametrize("V", [1, 5, 2047, 2048, 2053, 4096, 4099, 8192, 8195, 16387])
+@pytest.mark.parametrize("n_prompts,V", [(P, V) for P in (1, 2, 4) for V in (1, 5, 2048, 4096, 4099, 8192, 8195, 16384, 16387)] +
+                         [(32, V) for V in (1, 2047, 2048, 2053, 4099)])
 def test_row_statistics_with_fewer_threads_per_row(n_prompts, V):
-    """The more rows there are, the fewer threads take one (512, 256, 128, 64 for 248, 496, 992, 1984 rows): per-node
+    """The more rows there are, the fewer threads take one (512, 256, 128, 64 for 248, 496, 992, 7936 rows): per-node
     outputs against fp64 at and off whole load rounds of each (32 logits per thread), a row of masked tokens and a row
     with a NaN reported wherever they sit, also the last one.  The bound is that of the test above with a thread's
     chunk of at most V / 64 + 16 terms."""
