@@ -104,6 +104,11 @@ typedef struct dsbd_kv {
   int32_t max_len;                  /* host bound: >= shared_len[b] + len[b] for every tree           */
 } dsbd_kv;
 
+/*
+ * Workspace of the call below: at most 68 MB of partial results plus 8 bytes per query row (nothing for short
+ * prefixes).  With the heads fixed it never shrinks as the bounds grow (n_trees, n_nodes, max_tree_nodes, max_len), so
+ * a buffer sized for a caller's largest call serves every smaller one.
+ */
 size_t dsbd_forest_attention_workspace_bytes(const dsbd_forest* forest, const dsbd_kv* prefix,
                                              int32_t Hq, int32_t Hkv, int32_t D);
 
@@ -193,7 +198,7 @@ size_t dsbd_verify_forest_workspace_bytes(const dsbd_forest* forest, int32_t V, 
  *     they need more workgroups than the device holds at once, the layer kernel is launched for one group of
  *     prompts after the other (Algorithm 1 runs per prompt).
  *   - One kernel: its first workgroups walk the layers, those behind them produce the per-node outputs (lse_*,
- *     node_logp_*), one row of logits each, on the compute units the layers leave free.  If all four per-node outputs are
+ *     node_logp_*) from the rows of logits, on the compute units the layers leave free.  If all four per-node outputs are
  *     NULL that part is left out; NaN and +Inf logits are then reported only for the rows of beams that enter a layer,
  *     and the two misuses of -Inf (a row of nothing else, a masked drafted token) not at all.
  *   - The layer kernel's workgroups wait for each other, so it needs its share of the device while it runs.
@@ -201,9 +206,9 @@ size_t dsbd_verify_forest_workspace_bytes(const dsbd_forest* forest, int32_t V, 
  *     stream than the one before waits for the device to drain (once per device and process), and from then on
  *     every layer kernel is ordered behind the previous one by an event (6 us per call, which callers that stay on
  *     one stream never pay).  A stream under graph capture: the call can be recorded (a one-thread kernel
- *     in front of the layer kernel counts the replays in the workspace, so that every replay's exchange slots are told apart from the previous one's, which is why the
- *     workspace must be the same memory at every replay), but it records nothing outside the capture: keep replays
- *     apart from other verifications yourself.  Also not covered: dsbd_verify_forest_static() before the
+ *     in front of the layer kernel counts the replays in the workspace, so that every replay's exchange slots are told
+ *     apart from the previous one's, which is why the workspace must be the same memory at every replay), but it
+ *     records nothing outside the capture: keep replays apart from other verifications yourself.  Also not covered: dsbd_verify_forest_static() before the
  *     library's event exists, and other processes on the device.  Foreign kernels that occupy compute
  *     units only delay the layer kernel; every wait in it is bounded (3 s by default) and ends in
  *     DSBD_FAULT_SYNC_TIMEOUT with unusable outputs, never in a hang.
@@ -224,7 +229,7 @@ int32_t dsbd_verify_forest(const dsbd_forest* forest, const dsbd_verify_in* in, 
  * the workspace: it lives in a device array of dsbd_verify_forest_static_capacity() bytes (32 MiB) that is part of
  * the library's image (every GPU the library runs on holds its own copy until the process ends).  A problem whose
  * dsbd_verify_forest_workspace_bytes() exceeds the capacity is refused with DSBD_ERR_WORKSPACE and nothing is
- * enqueued.  The call allocates nothing: no device memory, no stream, no event; it takes part in the ordering of
+ * enqueued (the plan uses fewer workgroups per prompt where only that fits).  The call allocates nothing: no device memory, no stream, no event; it takes part in the ordering of
  * verifications on different streams only if an earlier ordinary call or dsbd_init() has already created the library's
  * event on this device.  Nothing in the array has to be cleared between
  * calls (exchange slots are told apart by a per-launch tag).  All calls on one GPU share that GPU's array: calls
@@ -319,7 +324,8 @@ typedef struct dsbd_draft_in {
   int32_t V;
   const int32_t* beam_off;         /* [n_prompts+1] device: beams of prompt p are rows beam_off[p] .. beam_off[p+1]-1 */
   const float*   logits_draft;     /* [n_beams,V] small model's logits at those beams (-Inf = a masked token, */
-                                   /*   never drawn; a row needs one finite logit)                            */
+                                   /*   never drawn; a row needs one finite logit: one without is reported as */
+                                   /*   DSBD_FAULT_NONFINITE and gets no draw)                                */
   const double*  beam_logp_draft;  /* [n_beams] their stored log-likelihoods under the small model (-Inf: a   */
                                    /*   beam that is never continued; finite for one beam of every prompt)    */
   const float*   u;                /* [n_prompts,W_S] uniforms in [0,1), one per draw                        */
@@ -390,8 +396,8 @@ void dsbd_reload_knobs(void);
  * frees the events.  Not thread-safe; meant for benchmarks.
  */
 #define DSBD_KERNEL_ATTENTION     1   /* forest attention main kernel (streams K/V)            */
-#define DSBD_KERNEL_VOCAB_STATS   2   /* no kernel of its own any more: records nothing          */
-#define DSBD_KERNEL_VERIFY_LAYERS 3   /* layer-by-layer verification, per-node statistics       */
+#define DSBD_KERNEL_VOCAB_STATS   2   /* accepted, but records nothing: part of kernel 3's launch */
+#define DSBD_KERNEL_VERIFY_LAYERS 3   /* layer-by-layer verification and per-node statistics     */
 #define DSBD_KERNEL_KV_COMMIT     4   /* cache update (copies the surviving caches)             */
 int32_t dsbd_timing_enable(int32_t kernel, int32_t capacity);
 int32_t dsbd_timing_collect(float* ms, int32_t max_n);

@@ -23,6 +23,7 @@
 // Partial (m, l, O) of the KV splits go to the workspace; a second kernel merges them.
 #include "common.h"
 #include "topology_device.h"
+#include "wave_f64.h"
 #include <stdlib.h>
 #include <type_traits>
 
@@ -93,36 +94,12 @@ __device__ __forceinline__ bf16x8 load_global_bf16x8(const void* p) {
   return c.v;
 }
 
-__device__ __forceinline__ void wave_lds_fence() {
-  // orders this wave's LDS writes before its later LDS reads (other lanes' data); LDS executes a
-  // wave's operations in order, so only the compiler needs to be held back
-  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-  __builtin_amdgcn_wave_barrier();
-  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-}
-
 // Workgroup barrier that orders LDS traffic only.  __syncthreads() carries a workgroup-scope fence, for
 // which the compiler waits for ALL outstanding memory operations (vmcnt(0)) - including the K/V loads of
 // the next tile that were issued on purpose before the barrier, which would then never overlap with the
 // arithmetic.  Here only the LDS counter is drained; global loads stay in flight across the barrier.
 __device__ __forceinline__ void lds_barrier() {
   asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
-}
-
-// Wave-wide sum by lane moves inside the SIMD (shuffles go through the LDS: twelve of them stood in front of a workgroup's
-// first loads, 0.4 us).
-template <int CTRL, int ROW_MASK>
-__device__ __forceinline__ float dpp_move_f32(float v) {           // lanes without a source lane read 0
-  return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), CTRL, ROW_MASK, 0xf, false));
-}
-__device__ __forceinline__ float wave_sum_f32(float v) {
-  v += dpp_move_f32<0xB1, 0xf>(v);    // quad_perm [1,0,3,2]
-  v += dpp_move_f32<0x4E, 0xf>(v);    // quad_perm [2,3,0,1]
-  v += dpp_move_f32<0x124, 0xf>(v);   // row_ror:4
-  v += dpp_move_f32<0x128, 0xf>(v);   // row_ror:8: every lane holds the total of its row of 16
-  v += dpp_move_f32<0x142, 0xa>(v);   // row_bcast:15 into rows 1 and 3
-  v += dpp_move_f32<0x143, 0xc>(v);   // row_bcast:31 into rows 2 and 3: lane 63 holds the total
-  return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), 63));
 }
 
 // ---- which part of the work a workgroup has
@@ -132,7 +109,7 @@ __device__ __forceinline__ float wave_sum_f32(float v) {
 // lane (up to 64 trees) or a thread (up to 256) per tree, its steps, its share of the total, the splits of its units; the
 // trees' workgroups are handed out in order of falling length, so that what runs last is short.  With a lane per tree
 // everything the workgroup needs to know of its tree arrives with the same round trip to memory, and no barrier is
-// needed.  With more trees than threads, or a pinned number of splits, every unit gets `nsplit` splits and the place is
+// needed (the sums go by lane moves: twelve shuffles through the LDS cost 0.4 us in front of the first loads).  With more trees than threads, or a pinned number of splits, every unit gets `nsplit` splits and the place is
 // plain arithmetic.
 // (One number of splits for all units, from the bounds the host knows, gave a sampled forest - one tree of 48 nodes, four
 // of one or two - a single split per unit: 92 us where 26 are enough; 24 trees of 700 to 3000 tokens: 35 us, now 25.)
@@ -982,7 +959,7 @@ void forest_attention_dma_kernel(AttnArgs a) {
 // Merge the KV splits of the rows that have several: out = sum_s 2^(m_s-M) O_s / sum_s 2^(m_s-M) l_s.  The workgroups of
 // the rows' first splits have left where a row's partial results are.  SG threads share four channels of a row: each takes
 // every SG-th split, eight at a time with all their loads in flight, then they meet in the LDS.  Many rows are bound by
-// the partial results' bytes and take SG = 1 (8 beams x 31 nodes x 32 heads, 8 splits: 7.8 us, SG = 4: 11.1); few rows of
+// the partial results' bytes and take SG = 1 (8 beams x 31 nodes x 32 heads, 8 splits: 7.5 us, SG = 4: 11.1); few rows of
 // many splits by a thread's round trips, SG = 4 (2 x 23 nodes x 32 heads, 32 splits: 6.8 us against 8.0).
 template <int D, int SG>
 __global__ __launch_bounds__(AT_BLOCK) void forest_attention_combine_kernel(AttnArgs a) {

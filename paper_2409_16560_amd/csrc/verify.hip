@@ -9,7 +9,7 @@
 //    rows they use).  For the layer's input beams I the workgroups materialise p_beam and q_beam over I x V (their
 //    slice each), and every dependent reduction over I x V is one pass over the slices plus one exchange among the G
 //    workgroups.
-// 2. Those behind take the fp32 statistics of one row of one model each (bandwidth-bound, all nodes, both models: the
+// 2. Those behind take the fp32 statistics of the rows of both models (bandwidth-bound, all nodes: the
 //    per-node outputs, the O(W |V|) softmax work of Section 2.1 done once for every forest node).  They run on the
 //    compute units that the layers leave free, and on all of them once the layers are done.
 //

@@ -1,5 +1,4 @@
-// Sums, maxima and prefix sums over the 64 lanes of a wave (fp64 mostly), for the kernels that take decisions in
-// double precision.
+// Sums, maxima and prefix sums over the 64 lanes of a wave (fp64 mostly).
 #pragma once
 #include <hip/hip_runtime.h>
 
@@ -46,7 +45,22 @@ __device__ __forceinline__ float wave_max_f32(float v) {
   return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), 63));
 }
 
-// The same for doubles.
+// The sum in single precision.
+template <int CTRL, int ROW_MASK>
+__device__ __forceinline__ float dpp_move_f32(float v) {           // lanes without a source lane read 0
+  return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), CTRL, ROW_MASK, 0xf, false));
+}
+__device__ __forceinline__ float wave_sum_f32(float v) {
+  v += dpp_move_f32<0xB1, 0xf>(v);    // quad_perm [1,0,3,2]
+  v += dpp_move_f32<0x4E, 0xf>(v);    // quad_perm [2,3,0,1]
+  v += dpp_move_f32<0x124, 0xf>(v);   // row_ror:4
+  v += dpp_move_f32<0x128, 0xf>(v);   // row_ror:8: every lane holds the total of its row
+  v += dpp_move_f32<0x142, 0xa>(v);   // row_bcast:15 into rows 1 and 3
+  v += dpp_move_f32<0x143, 0xc>(v);   // row_bcast:31 into rows 2 and 3: lane 63 holds the total
+  return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), 63));
+}
+
+// The maximum for doubles.
 template <int CTRL, int ROW_MASK>
 __device__ __forceinline__ double dpp_other_f64(double v) {        // lanes without a source lane read their own value
   const int lo = __double2loint(v), hi = __double2hiint(v);

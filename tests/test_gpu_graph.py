@@ -17,7 +17,7 @@ def test_replays_of_a_captured_verification_on_new_inputs(top_k, top_p, static):
     one meant for callers under capture."""
     import gpu_util as gu
     import paper_2409_16560_amd as dsbd
-    dsbd.dsbd_init()                      # (second stream and events exist before the capture)
+    dsbd.dsbd_init()                      # (the library's event exists before the capture)
     kw = dict(L=1, Hq=1, Hkv=1, D=64, V=6000, draft_top_k=3 if top_k else 0)
     ws_ = [make_workload("c5", seed=40 + r, noise_std=0.6, **kw) for r in range(4)]
     d = gu.DeviceWorkload(ws_[0])

@@ -46,13 +46,13 @@ def test_forest_attention_matches_oracle(cfg, kw):
     print("max abs err out/lse", err, flush=True)
 
 
-# The three main kernels: wave-private K/V streams (at most 32 rows per stream, 16 or 32 of them), the register-staged
-# shared tile (head size 64), the tile loaded straight into the LDS (head size 128); each with a ragged last tile and
-# a shared leading segment whose end falls inside a split.
+# The main kernels: wave-private K/V streams (at most 32 rows per stream, 16 or 32 of them) and the tile loaded straight
+# into the LDS (both head sizes); each with a ragged last tile and a shared leading segment whose end falls inside a
+# split.
 SPLIT_KERNELS = [
     ("wave-private, 15 rows", "c3", dict(L=777, shared_len=301, Hq=8, Hkv=8)),
     ("wave-private, 30 rows", "c3", dict(L=777, shared_len=301, Hq=8, Hkv=4)),
-    ("shared tile, D=64", "c5", dict(L=1100, shared_len=413, Hq=16, Hkv=4, D=64)),
+    ("tile into LDS, D=64", "c5", dict(L=1100, shared_len=413, Hq=16, Hkv=4, D=64)),
     ("tile into LDS, D=128", "c5", dict(L=1100, shared_len=413, Hq=16, Hkv=4)),
     ("tile into LDS, 63-node trees", "c5", dict(L=600, shared_len=0, Hq=8, Hkv=2, tree_nodes=63, tree="binary_bfs", W=3)),
 ]
@@ -191,24 +191,19 @@ def test_forest_attention_random_shapes(sweep):
             raise AssertionError("sweep %d case %d (%s): %s" % (sweep, case, spec, e))
 
 
+@pytest.mark.parametrize("D", [128, 64])
 @pytest.mark.parametrize("cfg,kw", [("c5", dict(L=333)), ("c5", dict(L=96, Hq=16, Hkv=4, tree_nodes=63, tree="binary_bfs")),
                                     ("c3", dict(L=300, shared_len=101, Hq=8, Hkv=1))])
-def test_register_staged_tile_kernel(cfg, kw, knobs):
-    """Head size 128 with many rows per K/V stream normally runs the kernel that loads its tiles straight into the
-    LDS; the register-staged kernel (what head size 64 uses) is selected by a knob and must give the same."""
+def test_tile_kernel_many_rows_per_stream(cfg, kw, D):
+    """Many query rows per K/V stream, short ragged prefixes, both head sizes."""
     gu = _gu()
-    w = make_workload(cfg, V=64, **kw)
+    w = make_workload(cfg, V=64, D=D, **kw)
     d = gu.DeviceWorkload(w)
     ref_out, ref_lse = gu.oracle_attention(w)
     out, lse, fault = d.attention()
     torch.cuda.synchronize()
-    knobs.set("DSBD_ATTN_STAGED", "1")
-    out2, lse2, fault2 = d.attention()
-    torch.cuda.synchronize()
-    assert int(fault.item()) == 0 and int(fault2.item()) == 0
+    assert int(fault.item()) == 0
     gu.compare_attention(w, out, lse, ref_out, ref_lse)
-    gu.compare_attention(w, out2, lse2, ref_out, ref_lse)
-    assert float((out.float() - out2.float()).abs().max()) <= 2e-2
 
 
 def test_shared_prefix_equals_duplicated_prefix():

@@ -15,8 +15,7 @@ def _both(w, t, top_k=0, top_p=1.0):
     import paper_2409_16560_amd as dsbd
     from dsbd_synth.device import DeviceWorkload
     d = DeviceWorkload(w)
-    # the static entry point first: in a fresh process it then runs before the library's second stream exists (the
-    # statistics pass in front of the layer kernel), after other tests with the stream in place (beside it)
+    # the static entry point first: in a fresh process it then runs before the library's event exists
     res = dsbd.VerifyResult.allocate(d.forest, w.W_cap)
     dsbd.dsbd_verify_forest_static(d.forest, d.logits_p, d.logits_q, d.blp, d.blq, d.u_accept, d.u_resid, d.u_fill, res,
                                    W_cap=w.W_cap, t=t, top_k=top_k, top_p=top_p)
