@@ -1080,7 +1080,7 @@ def test_forest_attention_work_places(name, kw, D):
 
 @pytest.mark.parametrize("kw,warp", [
     # workgroups of a prompt: rounded to a multiple of its beams, raised for the one-level selection of a large top_k,
-    # held back where every layer of a deep forest brings exchange slots of its own
+    # held at what the static workspace takes for the exchange slots of a deep forest's layers
     (dict(W=3, V=5003, tree_nodes=9), {}),
     (dict(W=5, V=3001, tree_nodes=7), dict(top_k=32, top_p=0.9)),
     (dict(W=8, V=2600, tree_nodes=7), dict(top_k=32, top_p=0.9)),
