@@ -3,16 +3,22 @@
 //
 // The cache of a next-iteration beam = the own cache segment of the input beam it descends from, followed by the
 // key/value rows of the forest nodes on the path root .. the node the output beam hangs from (the plan written by
-// dsbd_select_beams).  A pure copy, bound by HBM bandwidth: one workgroup per (destination beam, K or V, chunk of
-// 16 tokens), 16-byte pieces, four loads in flight per thread.  A destination that IS its source buffer (the beam
-// continues in place) only gets the tree rows appended.
+// dsbd_select_beams).  A pure copy, bound by HBM bandwidth.  A destination that IS its source buffer (the beam continues
+// in place) only gets the tree rows appended.
+//
+// A workgroup takes 16 tokens of K or of V of one prompt and works through the prompt's sources: 16-byte pieces, eight
+// loads in flight per thread, and every piece goes to all the destinations that continue this source, so a source is read
+// once however many next beams share it.
 #include "common.h"
+#include <algorithm>
 
 #define CM_BLOCK 256
-#define CM_TOKENS 16           // tokens per workgroup (measured: 16 -> 72 us, 64 -> 79 us, 128 -> 115 us on the benchmark plan)
+#define CM_TOKENS 16           // tokens per workgroup (8: 43.7 us, 24: 45.7, 32: 49.1 on the plan above)
+#define CM_LOADS 8             // 16-byte loads in flight per thread (4: 46.8 us; 512 threads with 4: 45.3)
+#define CM_GRID 2048           // workgroups that the device holds at once (grids of twice that: 47.4 us)
 
 struct CommitArgs {
-  int n_prompts, n_trees, n_nodes, W_cap, plen, Hkv, D;
+  int n_prompts, n_trees, n_nodes, W_cap, plen, Hkv, D, shares;
   const void* const* src_k; const void* const* src_v; const int32_t* src_len;
   long long token_stride, head_stride;      // elements; the same layout for sources and destinations
   const __bf16 *k_tree, *v_tree;            // [n_nodes, Hkv, D]
@@ -25,77 +31,94 @@ struct CommitArgs {
 typedef unsigned int cm_u32x4 __attribute__((ext_vector_type(4)));
 typedef __attribute__((address_space(1))) cm_u32x4 cm_gvec;
 
+__device__ __forceinline__ unsigned long long cm_lane(unsigned long long v, int l) {
+  const unsigned int lo = (unsigned int)__builtin_amdgcn_readlane((int)(unsigned int)v, l);
+  const unsigned int hi = (unsigned int)__builtin_amdgcn_readlane((int)(unsigned int)(v >> 32), l);
+  return ((unsigned long long)hi << 32) | lo;
+}
+
+// Workgroup (chunk x {K, V}, share, prompt): the sources number share, share + shares, .. of the prompt.
 __global__ __launch_bounds__(CM_BLOCK) void commit_kv_kernel(CommitArgs a) {
-  const int chunk = blockIdx.x, j = blockIdx.y, is_v = blockIdx.z;
-  const int tid = threadIdx.x;
-  const int p = j / a.W_cap, s = j % a.W_cap;
-  const bool speaker = chunk == 0 && is_v == 0 && tid == 0;     // one thread per destination reports and writes the length
-  int nn = a.n_next[p];
-  nn = max(0, min(nn, a.W_cap));
-  if (s >= nn) { if (speaker) a.dst_len[j] = 0; return; }
+  const int chunk = blockIdx.x >> 1, share = blockIdx.y, p = blockIdx.z, is_v = blockIdx.x & 1;
+  const int tid = threadIdx.x, lane = tid & 63;
+  // the prompt's destinations, one per lane
+  const bool slot = lane < a.W_cap;
+  const int j0 = p * a.W_cap, j = j0 + min(lane, a.W_cap - 1);
+  const int nn = max(0, min(a.n_next[p], a.W_cap));
   const int b = a.src_tree[j];
-  if (b < 0 || b >= a.n_trees) {
-    if (speaker) { a.dst_len[j] = 0; atomicOr(a.fault, DSBD_FAULT_TOPOLOGY); }
-    return;
-  }
-  // the source length is the caller's: the grid covers max_len + path tokens, so a longer source cannot be copied
-  const int L_raw = a.src_len[b];
-  const int L = max(0, min(L_raw, a.max_len));
+  const char* const dk = static_cast<const char*>(a.dst_k[j]);
+  const char* const dv = static_cast<const char*>(a.dst_v[j]);
   const int pl = max(0, min(a.path_len[j], a.plen));
-  const int total = L + pl;
+  const bool known = b >= 0 && b < a.n_trees;
+  const int bc = known ? b : 0;
+  int L_raw = 0;
+  const char *sk = nullptr, *sv = nullptr;
+  if (a.n_trees > 0) {
+    L_raw = a.src_len[bc];
+    sk = static_cast<const char*>(a.src_k[bc]); sv = static_cast<const char*>(a.src_v[bc]);
+  }
+  // the source length is the caller's: the grid covers max_len tokens, so a longer source cannot be copied
+  const int L = max(0, min(L_raw, a.max_len));
   // Both planes are checked by every workgroup (the K and the V workgroups of a destination must take the same
   // decision: a destination with a usable K buffer and a null or misaligned V buffer is left untouched as a whole).
-  const char* src_kp = static_cast<const char*>(a.src_k[b]);
-  const char* src_vp = static_cast<const char*>(a.src_v[b]);
-  char* dst_kp = static_cast<char*>(a.dst_k[j]);
-  char* dst_vp = static_cast<char*>(a.dst_v[j]);
-  const bool bad = L_raw < 0 || L_raw > a.max_len || total > a.capacity || !dst_kp || !dst_vp ||
-                   (L > 0 && (!src_kp || !src_vp)) ||
-                   ((reinterpret_cast<uintptr_t>(dst_kp) | reinterpret_cast<uintptr_t>(src_kp) |
-                     reinterpret_cast<uintptr_t>(dst_vp) | reinterpret_cast<uintptr_t>(src_vp)) & 15);
-  const char* src = is_v ? src_vp : src_kp;
-  char* dst = is_v ? dst_vp : dst_kp;
-  if (bad) {      // uniform over the destination's workgroups: the destination is left untouched
-    if (speaker) { a.dst_len[j] = 0; atomicOr(a.fault, DSBD_FAULT_BOUNDS); }
-    return;
+  const bool bad = L_raw < 0 || L_raw > a.max_len || L + pl > a.capacity || !dk || !dv || (L > 0 && (!sk || !sv)) ||
+                   ((reinterpret_cast<uintptr_t>(dk) | reinterpret_cast<uintptr_t>(sk) |
+                     reinterpret_cast<uintptr_t>(dv) | reinterpret_cast<uintptr_t>(sv)) & 15);
+  const bool on = lane < nn, good = on && known && !bad;
+  if (chunk == 0 && share == 0 && !is_v && tid == lane && slot) {      // one thread per destination reports and writes the length
+    a.dst_len[j] = good ? L + pl : 0;
+    if (on && !good) atomicOr(a.fault, known ? DSBD_FAULT_BOUNDS : DSBD_FAULT_TOPOLOGY);
   }
-  if (speaker) a.dst_len[j] = total;
-  const int t0 = chunk * CM_TOKENS;
-  const int t1 = min(total, t0 + CM_TOKENS);
-  if (t0 >= t1) return;
-  const bool in_place = dst == src;          // the beam keeps its buffer: only the tree rows are appended
-  const __bf16* rows = is_v ? a.v_tree : a.k_tree;
+  const unsigned long long src = reinterpret_cast<unsigned long long>(is_v ? sv : sk);
+  const unsigned long long dst = reinterpret_cast<unsigned long long>(is_v ? dv : dk);
   const int CG = a.D / 8;                    // 16-byte pieces per (token, head)
   const int per_tok = a.Hkv * CG;
-  const int n_piece = (t1 - t0) * per_tok;
-  auto src_of = [&](int piece, long long& doff) -> const char* {
-    const int t = t0 + piece / per_tok;
-    const int r = piece % per_tok;
-    const int g = r / CG, c = r % CG;
-    doff = ((long long)t * a.token_stride + (long long)g * a.head_stride + c * 8) * 2;
-    if (t < L) return in_place ? nullptr : src + doff;
-    int node = a.path[(long long)j * a.plen + (t - L)];
-    if (node < 0 || node >= a.n_nodes) { atomicOr(a.fault, DSBD_FAULT_TOPOLOGY); return nullptr; }
-    return reinterpret_cast<const char*>(rows + ((long long)node * a.Hkv + g) * a.D + c * 8);
+  auto place = [&](int t, int r) -> long long {      // byte offset of piece r of token t in a cache
+    return ((long long)t * a.token_stride + (long long)(r / CG) * a.head_stride + r % CG * 8) * 2;
   };
-  for (int i0 = tid; i0 < n_piece; i0 += 4 * CM_BLOCK) {
-    cm_u32x4 v[4];
-    long long doff[4];
-    bool have[4];
+
+  // ---- the sources' tokens
+  const int t0 = chunk * CM_TOKENS;
+  unsigned long long left = __builtin_amdgcn_ballot_w64(good && t0 < L && dst != src);
+  for (int n = 0; left; ++n) {
+    const int q0 = (int)__ffsll((long long)left) - 1;
+    const unsigned long long takers = left & __builtin_amdgcn_ballot_w64(b == __builtin_amdgcn_readlane(b, q0));
+    left &= ~takers;
+    if (n % a.shares != share) continue;
+    const char* const from = reinterpret_cast<const char*>(cm_lane(src, q0));
+    const int n_piece = (min(__builtin_amdgcn_readlane(L, q0), t0 + CM_TOKENS) - t0) * per_tok;
+    for (int i0 = tid; i0 < n_piece; i0 += CM_LOADS * CM_BLOCK) {
+      cm_u32x4 v[CM_LOADS];
+      long long off[CM_LOADS];
 #pragma unroll
-    for (int k = 0; k < 4; ++k) {
-      const int i = i0 + k * CM_BLOCK;
-      have[k] = false;
-      if (i < n_piece) {
-        const char* sp = src_of(i, doff[k]);
-        // plain loads (several next beams usually copy the same source: let the caches serve the repeats),
-        // non-temporal stores (the copies are not read again before the next iteration)
-        if (sp) { v[k] = *(const cm_gvec*)(sp); have[k] = true; }
+      for (int k = 0; k < CM_LOADS; ++k) {
+        const int i = min(i0 + k * CM_BLOCK, n_piece - 1);
+        off[k] = place(t0 + i / per_tok, i % per_tok);
+        v[k] = __builtin_nontemporal_load((const cm_gvec*)(from + off[k]));
+      }
+      for (unsigned long long m = takers; m; m &= m - 1) {
+        char* const to = reinterpret_cast<char*>(cm_lane(dst, (int)__ffsll((long long)m) - 1));
+#pragma unroll
+        for (int k = 0; k < CM_LOADS; ++k)
+          if (i0 + k * CM_BLOCK < n_piece) __builtin_nontemporal_store(v[k], (cm_gvec*)(to + off[k]));
       }
     }
-#pragma unroll
-    for (int k = 0; k < 4; ++k)
-      if (have[k]) __builtin_nontemporal_store(v[k], (cm_gvec*)(dst + doff[k]));
+  }
+
+  // ---- the destinations' path rows, handed out over the workgroups of the prompt
+  const __bf16* const rows = is_v ? a.v_tree : a.k_tree;
+  const unsigned long long mine = __builtin_amdgcn_ballot_w64(good && pl > 0 && (unsigned)lane % ((gridDim.x >> 1) * gridDim.y) == chunk * gridDim.y + share);
+  for (unsigned long long m = mine; m; m &= m - 1) {
+    const int q = (int)__ffsll((long long)m) - 1;
+    const int qL = __builtin_amdgcn_readlane(L, q), n_piece = __builtin_amdgcn_readlane(pl, q) * per_tok;
+    char* const to = reinterpret_cast<char*>(cm_lane(dst, q));
+    for (int i = tid; i < n_piece; i += CM_BLOCK) {
+      const int k = i / per_tok, r = i % per_tok;
+      const int node = a.path[(long long)(j0 + q) * a.plen + k];
+      if (node < 0 || node >= a.n_nodes) { atomicOr(a.fault, DSBD_FAULT_TOPOLOGY); continue; }
+      const cm_u32x4 v = *(const cm_gvec*)(rows + ((long long)node * per_tok + r) * 8);
+      __builtin_nontemporal_store(v, (cm_gvec*)(to + place(qL + k, r)));
+    }
   }
 }
 
@@ -122,12 +145,13 @@ extern "C" int32_t dsbd_commit_kv(const dsbd_forest* f, const dsbd_kv* src, cons
   a.n_next = next->n_next; a.src_tree = next->src_tree; a.path_len = next->path_len; a.path = next->path;
   a.dst_k = dst->k_ptr; a.dst_v = dst->v_ptr; a.dst_len = dst->len; a.capacity = dst->capacity; a.max_len = src->max_len;
   a.fault = fault;
-  const long long max_tokens = (long long)src->max_len + a.plen;
-  const long long chunks = (max_tokens + CM_TOKENS - 1) / CM_TOKENS;
+  const long long chunks = std::max(1LL, ((long long)src->max_len + CM_TOKENS - 1) / CM_TOKENS);
   const long long slots = (long long)f->n_prompts * W_cap;
-  if (chunks > 0x7fffffffLL || slots > 65535) return DSBD_ERR_UNSUPPORTED;
+  if (chunks > 0x3fffffffLL || slots > 65535) return DSBD_ERR_UNSUPPORTED;
+  // a prompt's sources side by side where its chunks leave compute units idle
+  a.shares = (int)std::max(1LL, std::min((long long)W_cap, CM_GRID / (chunks * 2 * f->n_prompts)));
   hipStream_t stream = static_cast<hipStream_t>(stream_);
-  dsbd_launch(DSBD_KERNEL_KV_COMMIT, commit_kv_kernel, dim3((unsigned)chunks, (unsigned)slots, 2), dim3(CM_BLOCK), 0, stream, a);
+  dsbd_launch(DSBD_KERNEL_KV_COMMIT, commit_kv_kernel, dim3(2 * (unsigned)chunks, (unsigned)a.shares, (unsigned)f->n_prompts), dim3(CM_BLOCK), 0, stream, a);
   DSBD_HIP_LAUNCH_CHECK();
   return DSBD_OK;
 }
