@@ -99,10 +99,7 @@ __device__ __forceinline__ void online_merge(float& m, float& s, float m2, float
 // Where the exchanges of one prompt keep their 16-byte slots (offsets in slots from the prompt's first one).
 struct SlotLayout {
   int x[2];              // the two alternating banks of the post-then-collect-from-all exchanges: G lines
-  int xc[2];             // ... and of the group sums of their two-hop form: SUM_GROUPS lines
   int r, r_w, r_stride;  // row sums of layer l: r + (l - 1) * r_stride, r_w slots per workgroup
-  int s, s_stride;       // early chain entry of layer l: s + (l - 1) * s_stride, a line per workgroup
-  int sc, sc_stride;     // its group sums: sc + (l - 1) * sc_stride, SUM_GROUPS lines
   int b, b_w;            // warping: every workgroup's candidate list, b_w slots each
   int c;                 // warping: the groups' merged lists (b_w slots each)
   int d;                 // warping: the final entries, posted by the prompt's first workgroup
@@ -199,6 +196,9 @@ struct LayerShared {
   double Pa[NC + 2], Pb[NC + 2];
   double wsum[2][VL_WAVES];
   unsigned long long acc_prev[2][NACC];   // the accumulator words' values before their next exchange
+  int x_have;                        // the exchange under way is collected (chain entry kx + 1 is in cc / FF)
+  int stop;                          // accept loop: the chain entry on its way is not needed, its collection may be left
+  unsigned int handed;               // accept loop: wave totals handed to the collecting wave so far
   double scan_w[VL_WAVES];
   double tsum[VL_BLOCK];
   double gpart[256];                 // one partial per workgroup of the prompt (G <= 256)
@@ -358,42 +358,6 @@ __device__ __forceinline__ bool wave_collect4(Slot* bank, int G, int g, double o
   }
 }
 
-// Sum over the prompt's G workgroups of one value each, for the first wave of every workgroup; the value is already
-// posted (or being posted) in the workgroup's line of `bank`.  With more than SUM_GROUP workgroups the sum takes two
-// hops: the first workgroup of every group of SUM_GROUP adds up its group's values and posts the group sum in
-// `gbank`, and everybody adds up the at most SUM_GROUPS group sums.  Each workgroup then polls 16 + 16 lines instead
-// of 256, and all of them add the same numbers in the same order.  False if a wait gave up.
-#define SUM_GROUP 16
-#define SUM_GROUPS 16
-__device__ __forceinline__ bool wave_sum_groups(Slot* bank, Slot* gbank, int G, int g, double own,
-                                                unsigned long long tag, long long limit, double& total) {
-  const int lane = threadIdx.x & 63;
-  if (G <= SUM_GROUP) {
-    double v[4];
-    const bool ok = wave_collect4(bank, G, g, own, tag, v, limit);
-    total = wave_sum((v[0] + v[1]) + (v[2] + v[3]));
-    return ok;
-  }
-  bool ok = true;
-  const int first = g - g % SUM_GROUP, n_groups = (G + SUM_GROUP - 1) / SUM_GROUP;
-  double gs_own = 0.0;
-  if (g == first) {
-    const int n_mem = min(SUM_GROUP, G - first);
-    double v = 0.0;
-    if (lane == 0) v = own;
-    else if (lane < n_mem) ok = slot_wait(bank + (long long)(first + lane) * LINE_SLOTS, tag, v, limit);
-    gs_own = wave_sum(v);
-    if (lane == 0) slot_post(gbank + (long long)(g / SUM_GROUP) * LINE_SLOTS, gs_own, tag);
-  }
-  double c = 0.0;
-  if (lane < n_groups) {
-    if (g == first && lane == g / SUM_GROUP) c = gs_own;          // the workgroup's own group sum needs no round trip
-    else ok = slot_wait(gbank + (long long)lane * LINE_SLOTS, tag, c, limit) && ok;
-  }
-  total = wave_sum(c);
-  return __builtin_amdgcn_ballot_w64(!ok) == 0ull;
-}
-
 // Sum over the prompt's G workgroups of one value in [0, 4) each, in one hop: every workgroup adds its value, as a
 // 2^-52 fixed-point number with a 1 in the count field above it, to one of NACC accumulator words (an agent-scope
 // integer atomic: the order of the additions does not matter, so the sum is the same in every run), and one wave
@@ -403,32 +367,43 @@ __device__ __forceinline__ bool wave_sum_groups(Slot* bank, Slot* gbank, int G, 
 // read by the prompt's first workgroup before anybody adds and handed round with the first layer's row sums).  The
 // difference decodes as (members << 54) + sum as long as the sum stays below 2^54 units and there are fewer than 1024
 // members per word.  Two banks alternate as for the slot exchanges.  Measured among 256 workgroups: 1.8 us against
-// 2.45 us for the two-hop slot exchange (a microbenchmark of both on the same box).
-__device__ __forceinline__ bool wave_sum_accumulators(unsigned long long* accs, unsigned long long* prev, int G, int g,
-                                                      double own, long long limit, double& total) {
+// 2.45 us for a two-hop slot exchange (a microbenchmark of both on the same box).
+// Posting and collecting are separate, so that an exchange can travel beside other work; every workgroup collects what it
+// posted before it posts again (only then has nobody left the bank before the last to be collected).
+__device__ __forceinline__ void accumulators_post(unsigned long long* accs, int G, int g, double own) {
+  if (G == 1 || (threadIdx.x & 63) != 0) return;
+  const unsigned long long q = (unsigned long long)__double2ull_rn(fmin(fmax(own, 0.0), 3.999) * 4503599627370496.0);
+  __hip_atomic_fetch_add(&accs[(g % NACC) * 16], (1ull << ACC_FIELD_BITS) + q, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+enum { ACC_DONE = 0, ACC_TIMEOUT = 1, ACC_STOPPED = 2 };
+// One wave.  `stop`: a word of the LDS by which another wave of the workgroup calls the wait off (ACC_STOPPED: the exchange
+// is still to be collected); null: none.
+__device__ __forceinline__ int accumulators_collect(unsigned long long* accs, unsigned long long* prev, int G, double own,
+                                                    long long limit, const int* stop, double& total) {
   const int lane = threadIdx.x & 63;
-  if (G == 1) { total = own; return true; }
-  if (lane == 0) {
-    const unsigned long long q = (unsigned long long)__double2ull_rn(fmin(fmax(own, 0.0), 3.999) * 4503599627370496.0);
-    __hip_atomic_fetch_add(&accs[(g % NACC) * 16], (1ull << ACC_FIELD_BITS) + q, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-  }
-  bool ok = true;
-  unsigned long long field = 0;
+  if (G == 1) { total = own; return ACC_DONE; }
+  unsigned long long field = 0, w = 0;
+  bool have = true;
+  unsigned long long members = 0, before = 0;
   if (lane < NACC) {
-    const unsigned long long members = lane < G ? (unsigned long long)((G - lane + NACC - 1) / NACC) : 0ull;
-    if (members) {
-      const unsigned long long before = prev[lane];
-      long long t0 = 0;
-      for (int spin = 0;; ++spin) {
-        const unsigned long long w = __hip_atomic_load(&accs[lane * 16], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        const unsigned long long diff = w - before;
-        if ((diff >> ACC_FIELD_BITS) == members) { field = diff & ((1ull << ACC_FIELD_BITS) - 1); prev[lane] = w; break; }
-        if (spin == 0) t0 = wall_clock64();
-        else if ((spin & 15) == 0 && wall_clock64() - t0 > limit) { ok = false; break; }
-        __builtin_amdgcn_s_sleep(1);
-      }
-    }
+    members = lane < G ? (unsigned long long)((G - lane + NACC - 1) / NACC) : 0ull;
+    before = prev[lane];
+    have = members == 0;
   }
+  long long t0 = 0;
+  for (int spin = 0;; ++spin) {
+    if (!have) {
+      w = __hip_atomic_load(&accs[lane * 16], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      const unsigned long long diff = w - before;
+      if ((diff >> ACC_FIELD_BITS) == members) { field = diff & ((1ull << ACC_FIELD_BITS) - 1); have = true; }
+    }
+    if (__builtin_amdgcn_ballot_w64(!have) == 0ull) break;
+    if (stop && __hip_atomic_load(stop, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP) != 0) return ACC_STOPPED;
+    if (spin == 0) t0 = wall_clock64();
+    else if ((spin & 15) == 0 && wall_clock64() - t0 > limit) return ACC_TIMEOUT;
+    __builtin_amdgcn_s_sleep(1);
+  }
+  if (lane < NACC && members) prev[lane] = w;
   // the eight words' fields added up by lane moves inside the SIMD (quads, then the other quad of the eight) and the
   // first lane's total read back as a uniform value: no LDS round trips on the chain's critical path
   static_assert(NACC == 8, "the reduction below is written for eight words");
@@ -441,7 +416,7 @@ __device__ __forceinline__ bool wave_sum_accumulators(unsigned long long* accs, 
     field = ((unsigned long long)hi << 32) | lo;
   }
   total = (double)field * (1.0 / 4503599627370496.0);
-  return __builtin_amdgcn_ballot_w64(!ok) == 0ull;
+  return ACC_DONE;
 }
 
 __device__ __forceinline__ Slot* prompt_slots(const LayersArgs& a, int prompt) {
@@ -616,9 +591,8 @@ void verify_layers_kernel(LayersArgs a) {
   const unsigned long long nonce =
       a.nonce + (a.replay ? (__hip_atomic_load(a.replay, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) << 40) : 0ull);
   // (selected, not indexed: a run-time index into the kernel's argument block would move the whole block into scratch memory)
-  const int slx0 = a.sl.x[0], slx1 = a.sl.x[1], slxc0 = a.sl.xc[0], slxc1 = a.sl.xc[1];
+  const int slx0 = a.sl.x[0], slx1 = a.sl.x[1];
   auto bank_x = [&](unsigned int n) { return (n & 1) ? slx1 : slx0; };
-  auto bank_xc = [&](unsigned int n) { return (n & 1) ? slxc1 : slxc0; };
   unsigned int wsum_round = 0; // alternates the two wsum buffers
   unsigned int decide_round = 0;
   int trace_n = 0;
@@ -634,13 +608,16 @@ void verify_layers_kernel(LayersArgs a) {
   // to the others in tagged slots, collected during the first layer
   unsigned long long* const accs = reinterpret_cast<unsigned long long*>(slots + a.sl.acc);
   const unsigned long long acc0_tag = exchange_tag(nonce + 0xFFFFFFull);
-  unsigned int achg = 0;       // accumulator exchanges so far (alternates their two banks)
+  unsigned int achg = 0;       // accumulator exchanges posted so far (alternates their two banks)
+  bool x_open = false;         // the last of them is not known to be collected by every workgroup
+  double x_own = 0.0;          // what this workgroup posted in it
+  unsigned int handovers = 0;  // rounds of the accept loop's handing over of wave totals
   // (requested here, used at the end of the prologue: the round trip through the memory system runs beside it)
   unsigned long long acc0_w = 0;
   if (g == 0 && tid < 2 * NACC)
     acc0_w = __hip_atomic_load(&accs[tid * 16], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 
-  if (tid == 0) { sh.abort = 0; sh.sbad = 0; sh.sgamma = 0; sh.counter = 0; sh.found = 0; }
+  if (tid == 0) { sh.abort = 0; sh.sbad = 0; sh.sgamma = 0; sh.counter = 0; sh.found = 0; sh.handed = 0u; }
   double exp_tab_mine = 0.0;     // (the table entry travels while the prompt's trees are looked up; stored below)
   if (tid < 64) exp_tab_mine = c_exp2_tab[tid];
 
@@ -943,6 +920,17 @@ void verify_layers_kernel(LayersArgs a) {
       body(pbg, qbg, n_lds, len);
     };
 
+    // a chain entry of the layer before that nobody needed: collected now (by the wave that does nothing else here), so
+    // that the words' values are known when the next exchange is posted
+    if (x_open) {
+      if (wave == 1 && sh.x_have == 0) {
+        double unused;
+        const unsigned int at = achg - 1;
+        if (accumulators_collect(accs + (size_t)(at & 1) * NACC * 16, sh.acc_prev[at & 1], a.G, x_own, a.sync_limit, nullptr, unused) != ACC_DONE)
+          give_up();
+      }
+      x_open = false;
+    }
     // ===== while the first logits travel: candidates = depth-l nodes whose parent is an input beam, in (rank, node) order
     // (this and the beam weights stood behind the exponential pass, beside the wait for the row sums, and were longer
     // than that wait)
@@ -1853,32 +1841,23 @@ void verify_layers_kernel(LayersArgs a) {
       sh.S_pb[tid] = pbx; sh.S_qb[tid] = qbx; sh.S_u[tid] = uf;
       sh.S_flag[tid] = (unsigned char)(((double)uf <= ratio ? 1 : 0) | (fabs(ratio - (double)uf) <= NEAR_TIE ? 2 : 0));
     }
-    if (tid == 0) { sh.cc[1] = 0.0; sh.FF[1] = 1.0; sh.kmax = 1; sh.acc_n = 0; sh.pos = 0; sh.kidx = 1; }
+    if (tid == 0) { sh.cc[1] = 0.0; sh.FF[1] = 1.0; sh.kmax = 1; sh.acc_n = 0; sh.pos = 0; sh.kidx = 1; sh.x_have = 0; sh.stop = 0; }
     // Entry 2 of the residual chain (c = 1) is needed by the first rejection of nearly every layer: its partial
-    // sums are posted ahead of time and collected only when it is asked for.
-    bool spec = false;
-    Slot* spec_bank = nullptr;
-    Slot* spec_gbank = nullptr;
-    unsigned long long spec_tag = 0;
-    double spec_own = 0.0;
+    // sums are posted ahead of time.
     stamp(26);
     if (!WARP && M > 0) {
-      const double tot = wg_total(f1);      // barrier inside: also publishes the scaled slices
+      x_own = wg_total(f1);                 // barrier inside: also publishes the scaled slices
       stamp(27);
-      epoch += 1;
-      spec_tag = exchange_tag(nonce + epoch);
-      spec_bank = slots + a.sl.s + (long long)(l - 1) * a.sl.s_stride;
-      spec_gbank = slots + a.sl.sc + (long long)(l - 1) * a.sl.sc_stride;
-      if (tid == 0) dense_post(spec_bank, a.G, g, tot, spec_tag);
-      spec_own = tot;
-      spec = true;
+      if (wave == 0) accumulators_post(accs + (size_t)(achg & 1) * NACC * 16, a.G, g, x_own);
+      achg += 1;
+      x_open = true;
     } else {
       __syncthreads();
     }
 
     // fp64 log-sum-exp of the input beams' rows: needed at the end of the layer only, so one wave takes the
     // logarithms while the first wave is busy with the decisions (or the others with the sampling prefix sums)
-    if (wave == 1 && lane < nI) {
+    if (wave == 2 && lane < nI) {
       sh.lse_p[lane] = sh.max_p[lane] + log(sh.lse_p[lane]);
       sh.lse_q[lane] = sh.max_q[lane] + log(sh.lse_q[lane]);
     }
@@ -2308,48 +2287,48 @@ void verify_layers_kernel(LayersArgs a) {
         pos += last + 1;
         if (accm) { nacc += 1; k = 1; } else { k += nv; }
       }
-      if (lane == 0) { near_tie += near_add; sh.pos = pos; sh.acc_n = nacc; sh.kidx = k; sh.state[round & 1] = state; }
+      if (lane == 0) {
+        near_tie += near_add; sh.pos = pos; sh.acc_n = nacc; sh.kidx = k; sh.state[round & 1] = state;
+        // (finished without the entry that is on its way)
+        if (state == 0 && (nacc >= WL || k <= kmax)) __hip_atomic_store(&sh.stop, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+      }
     };
 
-    // Appends entry kmax+1 to the residual chain: every workgroup sums its slice, the first wave exchanges the
-    // partial sums and, if asked to, carries on with the decisions right away.  All threads leave through one
-    // barrier; false = a wait gave up.
-    auto extend_chain = [&](bool then_decide) -> bool {
-      if (spec) {                      // entry 2 is already on its way
-        if (wave == 0) {
-          double F;
-          if (!wave_sum_groups(spec_bank, spec_gbank, a.G, g, spec_own, spec_tag, a.sync_limit, F)) give_up();
-          if (lane == 0) { sh.cc[2] = 1.0; sh.FF[2] = F; sh.kmax = 2; }
-          if (then_decide) decide(decide_round, 2);
-        }
-        spec = false;
-      } else {
-        const int k = sh.kmax;
+    // The open exchange's value, entry k + 1 of the chain, by the wave that calls (all its lanes).
+    auto collect_entry = [&](int k, const int* stop) __attribute__((always_inline)) {
+      const unsigned int at = achg - 1;
+      double F;
+      const int r = accumulators_collect(accs + (size_t)(at & 1) * NACC * 16, sh.acc_prev[at & 1], a.G, x_own, a.sync_limit, stop, F);
+      if (r == ACC_TIMEOUT) give_up();
+      if (r == ACC_DONE && lane == 0) { sh.cc[k + 1] = sh.cc[k] + sh.FF[k]; sh.FF[k + 1] = F; sh.x_have = 1; }
+    };
+    // Appends entry kmax+1 to the residual chain: every workgroup sums its slice (unless the entry is under way), the
+    // second wave exchanges the partial sums.  All threads leave through one barrier; false = a wait gave up.
+    auto extend_chain = [&]() -> bool {
+      const int k = sh.kmax;
+      if constexpr (WARP) {          // every workgroup holds the whole warped joint: the total is F itself
+        const double c = sh.cc[k] + sh.FF[k];
+        const double tot = wg_total(slice_sum(c, 0, VL_BLOCK));
+        if (tid == 0) { sh.cc[k + 1] = c; sh.FF[k + 1] = tot; sh.kmax = k + 1; }
+        __syncthreads();
+        return true;
+      }
+      if (!x_open) {
         const double c = sh.cc[k] + sh.FF[k];
         stamp(46);
         const double sl = slice_sum(c, 0, VL_BLOCK);
         stamp(43);
-        const double tot = wg_total(sl);
+        x_own = wg_total(sl, true);
         stamp(44);
-        if constexpr (WARP) {          // every workgroup holds the whole warped joint: the total is F itself
-          if (wave == 0) {
-            if (lane == 0) { sh.cc[k + 1] = c; sh.FF[k + 1] = tot; sh.kmax = k + 1; }
-            if (then_decide) decide(decide_round, k + 1);
-          }
-          __syncthreads();
-          return true;
-        }
-        unsigned long long* const x_acc = accs + (size_t)(achg & 1) * NACC * 16;
-        unsigned long long* const x_prev = sh.acc_prev[achg & 1];
+        if (wave == 1) accumulators_post(accs + (size_t)(achg & 1) * NACC * 16, a.G, g, x_own);
         achg += 1;
-        if (wave == 0) {
-          double F;
-          if (!wave_sum_accumulators(x_acc, x_prev, a.G, g, tot, a.sync_limit, F)) give_up();
-          stamp(45);
-          if (lane == 0) { sh.cc[k + 1] = c; sh.FF[k + 1] = F; sh.kmax = k + 1; }
-          if (then_decide) decide(decide_round, k + 1);
-        }
       }
+      if (wave == 1) {
+        collect_entry(k, nullptr);
+        if (lane == 0) sh.kmax = k + 1;
+      }
+      x_open = false;
+      stamp(45);
       __syncthreads();
       return sh.abort == 0;
     };
@@ -2380,7 +2359,7 @@ void verify_layers_kernel(LayersArgs a) {
       } else {
         bool dead = false;
         for (int j = 1; j <= M && !dead; ++j) {
-          if (!extend_chain(false)) return;
+          if (!extend_chain()) return;
           dead = !(sh.FF[j + 1] > 0.0);
         }
       }
@@ -2475,51 +2454,64 @@ void verify_layers_kernel(LayersArgs a) {
     if (g == 0 && tid == 0) a.out.layer_width[(long long)prompt * Lw + l] = WL;
 
     stamp(40);
-    // ===== sequential accept / reject.  The first wave takes the decisions as far as the chain reaches; meanwhile
-    // the other seven waves already sum their slices for the chain entry that would come next, so a rejection that
-    // needs it finds the partial sums ready to post (and an acceptance that ends the layer just drops them).
-    {
-      bool posted = spec;              // the next entry's partial sums are on their way: F(1), from the scaling pass
-      Slot* x_bank = spec_bank;
-      Slot* x_gbank = spec_gbank;
-      unsigned long long x_tag = spec_tag;
-      double x_own = spec_own;
+    // ===== sequential accept / reject.  The first wave takes the decisions as far as the chain reaches.  Meanwhile the
+    // other seven sum their slices for the chain entry that would come next, and the second hands the totals to the other
+    // workgroups and collects theirs: entries do not depend on decisions, so an entry takes as long as the longer of
+    // the two (a rejection took 2.45 us with the exchange behind the decision: 1.05 to 1.3 us and 1.2).
+    if constexpr (WARP) {
       while (true) {
         const int k = sh.kmax;         // entries 1..k exist (read after a barrier: uniform)
         const double c_next = sh.cc[k] + sh.FF[k];
         stamp(41);
         if (wave == 0) decide(decide_round, k);
-        double tot = 0.0;
-        // (the barriers of this loop order LDS values only: chain entries, decisions, wave totals; slices are
-        // read-only here and the outputs written meanwhile are read by nobody in this kernel)
-        if (!posted) tot = wg_total(slice_sum(c_next, 64, VL_BLOCK - 64), true);   // barrier inside
-        else lds_barrier();
+        const double tot = wg_total(slice_sum(c_next, 64, VL_BLOCK - 64), true);   // barrier inside
         const int st = sh.state[decide_round & 1];
         decide_round += 1;             // the next outcome goes to the other entry: nobody still reads it
         stamp(42);
         if (st != 1) break;
-        if constexpr (WARP) {
-          if (tid == 0) { sh.cc[k + 1] = c_next; sh.FF[k + 1] = tot; sh.kmax = k + 1; }
-          __syncthreads();
-          continue;
-        }
-        // the entry posted ahead of time (c = 1) comes through its slots; every later one through the accumulators
-        const bool via_acc = !posted;
-        unsigned long long* const x_acc = accs + (size_t)(achg & 1) * NACC * 16;
-        unsigned long long* const x_prev = sh.acc_prev[achg & 1];
-        if (via_acc) achg += 1;
+        if (tid == 0) { sh.cc[k + 1] = c_next; sh.FF[k + 1] = tot; sh.kmax = k + 1; }
+        __syncthreads();
+      }
+    } else {
+      int kx = sh.kmax;                // entries 1..kx exist (the same in every thread)
+      while (true) {
+        stamp(41);
+        // (the barriers of this loop order LDS values only: chain entries, decisions, wave totals; slices are
+        // read-only here and the outputs written meanwhile are read by nobody in this kernel)
+        const bool produce = !x_open && kx <= M;         // (M rejections reach entry M + 1)
         if (wave == 0) {
-          double F;
-          const bool ok_x = via_acc ? wave_sum_accumulators(x_acc, x_prev, a.G, g, tot, a.sync_limit, F)
-                                    : wave_sum_groups(x_bank, x_gbank, a.G, g, x_own, x_tag, a.sync_limit, F);
-          if (!ok_x) give_up();
-          if (lane == 0) { sh.cc[k + 1] = c_next; sh.FF[k + 1] = F; sh.kmax = k + 1; }
+          if (lane == 0) sh.kmax = kx;
+          decide(decide_round, kx);
+        } else if (produce) {
+          const double c_next = sh.cc[kx] + sh.FF[kx];
+          const double ts = wave_sum(slice_sum(c_next, 64, VL_BLOCK - 64));
+          double* const ws = sh.wsum[wsum_round & 1];
+          if (wave >= 2) {
+            if (lane == 0) {
+              ws[wave] = ts;
+              asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+              __hip_atomic_fetch_add(&sh.handed, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+            }
+          } else {
+            const unsigned int want = (handovers + 1) * (VL_WAVES - 2);
+            while (__hip_atomic_load(&sh.handed, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP) != want) {}
+            asm volatile("" ::: "memory");
+            x_own = (ts + (ws[2] + ws[3])) + ((ws[4] + ws[5]) + (ws[6] + ws[7]));
+            if (lane == 0) sh.x_have = 0;
+            accumulators_post(accs + (size_t)(achg & 1) * NACC * 16, a.G, g, x_own);
+          }
         }
-        posted = false;
-        spec = false;
-        stamp(45);
+        if (produce) { wsum_round += 1; handovers += 1; achg += 1; x_open = true; }
+        if (wave == 1 && x_open) collect_entry(kx, &sh.stop);
+        stamp(42);
         lds_barrier();
+        const int st = sh.state[decide_round & 1];
+        decide_round += 1;             // the next outcome goes to the other entry: nobody still reads it
         if (sh.abort) return;
+        if (st != 1) break;
+        x_open = false;                // the decisions go on with the new entry
+        kx += 1;
+        stamp(45);
       }
     }
     const int nacc = sh.acc_n, pos_end = sh.pos, kcur = sh.kidx, kmax_end = sh.kmax;
@@ -2551,7 +2543,7 @@ void verify_layers_kernel(LayersArgs a) {
       // p' = p'_kcur; its chain entry may still be missing if the last candidate was rejected
       int k = kcur;
       if (k > kmax_end) {
-        if (!extend_chain(false)) return;
+        if (WARP || !x_open || sh.x_have == 0) { if (!extend_chain()) return; }
       }
       if (k > 1 && !(sh.FF[k] > 0.0)) {
         if (g == 0 && tid == 0) atomicOr(a.fault, DSBD_FAULT_ZERO_RESIDUAL);
@@ -2732,12 +2724,8 @@ VerifyPlan plan_with_workgroups(const dsbd_forest* f, int V, const dsbd_params* 
     int off = 0;
     sl.x[0] = off; off += G * LINE_SLOTS;
     sl.x[1] = off; off += G * LINE_SLOTS;
-    sl.xc[0] = off; off += SUM_GROUPS * LINE_SLOTS;
-    sl.xc[1] = off; off += SUM_GROUPS * LINE_SLOTS;
     sl.r_w = up8(4 * pl.I_cap);
     sl.r = off; sl.r_stride = G * sl.r_w; off += layers * sl.r_stride;
-    sl.s = off; sl.s_stride = G * LINE_SLOTS; off += layers * sl.s_stride;
-    sl.sc = off; sl.sc_stride = SUM_GROUPS * LINE_SLOTS; off += layers * sl.sc_stride;
     sl.b = sl.c = sl.d = sl.wb = off; sl.b_w = 0; sl.wb_stride = 0;
     if (p->top_k > 0) {
       sl.b_w = up8(4 * p->top_k);
