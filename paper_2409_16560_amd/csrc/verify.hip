@@ -199,7 +199,7 @@ struct LayerShared {
   int x_have;                        // the exchange under way is collected (chain entry kx + 1 is in cc / FF)
   int stop;                          // accept loop: the chain entry on its way is not needed, its collection may be left
   unsigned int handed;               // accept loop: wave totals handed to the collecting wave so far
-  double scan_w[VL_WAVES];
+  double scan_w[VL_WAVES], scan_w2[VL_WAVES];
   double tsum[VL_BLOCK];
   double gpart[256];                 // one partial per workgroup of the prompt (G <= 256)
   double ptot[256];                  // p_beam total of every workgroup's slice, worked out from the layer's row sums
@@ -240,20 +240,6 @@ __device__ __forceinline__ long long div_floor(long long a, long long b) {
 // values, this form lets the first wave's status stores and slot posts stay in flight across the barrier.
 __device__ __forceinline__ void lds_barrier() {
   asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
-}
-
-// Inclusive prefix sum over the block's threads in thread order (fixed tree: identical in every workgroup
-// that scans the same values).
-template <class Shared>
-__device__ __forceinline__ double block_inclusive_scan(double v, Shared& sh) {
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  v = wave_inclusive_scan(v);
-  __syncthreads();
-  if (lane == 63) sh.scan_w[wave] = v;
-  __syncthreads();
-  double before = 0.0;
-  for (int w = 0; w < wave; ++w) before += sh.scan_w[w];
-  return before + v;
 }
 
 // ---- exchange among the G workgroups of one prompt
@@ -1906,285 +1892,17 @@ void verify_layers_kernel(LayersArgs a) {
       return (s0 + s1) + (s2 + s3);
     };
 
-    // Draws `cnt` samples (uniforms u[0..cnt)) from the weights max(p_beam - c q_beam, 0) (use_q) or p_beam over
-    // I x V by inverse CDF in flat order; the workgroup owning a sample writes output slot out_base + j.
-    auto draw = [&](double c, bool use_q, const float* u, int cnt, int out_base) -> bool {
-      if constexpr (WARP) {
-        // the weights live on the short list (ascending flat index) that every workgroup holds: one wave scans
-        // it, the first workgroup writes the samples
-        __syncthreads();           // the rows' log-sum-exps (another wave's work since the fold) are in place
-        if (wave == 0) {
-          const int nU = sh.nU;
-          double w = 0.0;
-          if (lane < nU) w = use_q ? fmax(sh.U_p[lane] - c * sh.U_q[lane], 0.0) : sh.U_p[lane];
-          double incl = w;
-          incl = wave_inclusive_scan(incl);
-          const double Z = __shfl(incl, 63);
-          const unsigned long long mass = __ballot(w > 0.0);
-          for (int j = 0; j < cnt; ++j) {
-            const double target = (double)u[j] * Z;
-            const unsigned long long above = __ballot(incl > target);
-            // the first entry whose inclusive prefix exceeds the target (rounding: the last one with mass)
-            const int pl_ = above ? (int)__ffsll((long long)above) - 1 : (mass ? 63 - __clzll((long long)mass) : 0);
-            if (g == 0 && lane == pl_) {
-              const long long pick = nU > 0 ? sh.U_idx[pl_] : 0;       // (no entry at all, reported as a fault: stay in bounds)
-              const int i = (int)div_floor(pick, V);
-              const int x = (int)(pick - (long long)i * V);
-              const int node = sh.I_node[i];
-              const long long o = (long long)prompt * a.W_cap + out_base + j;
-              a.out.out_parent[o] = node;
-              a.out.out_token[o] = x;
-              a.out.out_node[o] = -1;
-              const double lp_o = sh.cum_p[i] + ((double)a.zp[(long long)node * V + x] - sh.lse_p[i]);
-              const double lq_o = sh.cum_q[i] + ((double)a.zq[(long long)node * V + x] - sh.lse_q[i]);
-              a.out.out_logp_target[o] = lp_o;
-              a.out.out_logp_draft[o] = lq_o;
-              emit_next(out_base + j, node, x, lp_o, lq_o);
-            }
-          }
-        }
-        __syncthreads();
-        return true;
-      }
-      float uj = 0.f;
-      if (tid < cnt) uj = u[tid];
-      // inclusive prefixes over this workgroup's threads (contiguous chunks) ...
-      long long per = (len + VL_BLOCK - 1) / VL_BLOCK;
-      if (!in_lds) {                      // slices in the workspace: chunks of a power of two (at least one) entries
-        long long p2 = 1;
-        while (p2 < per) p2 <<= 1;
-        per = p2;
-      }
-      const long long t_lo = min(len, per * tid), t_hi = min(len, t_lo + per);   // slice-local
-      double ts = 0.0;
-      if (in_lds) {
-        if (use_q) for (int j = (int)t_lo; j < (int)t_hi; ++j) ts += fmax((double)pl[j] - c * (double)ql[j], 0.0);
-        else for (int j = (int)t_lo; j < (int)t_hi; ++j) ts += (double)pl[j];
-      } else {
-        // A thread walking its own chunk would make every load of a wave touch 64 cache lines (measured: 14 us for a
-        // 16000-entry slice).  Instead a wave reads the 64 chunks of its threads 64 consecutive entries at a time and
-        // adds them up across the lanes: `per` rounds, each holding 64 / per whole chunks or a 64th of one.
-        const long long w_lo = per * 64 * wave;
-        auto weight = [&](long long jj) -> double {
-          if (jj >= len) return 0.0;
-          if (jj < n_lds) return use_q ? fmax((double)pl[(int)jj] - c * (double)ql[(int)jj], 0.0) : (double)pl[(int)jj];
-          return use_q ? fmax((double)pbg[jj] - c * (double)qbg[jj], 0.0) : (double)pbg[jj];
-        };
-        // eight rounds from r0 on (rounds beyond `lim` count nothing): one home for all eight in all but one group of
-        // a wave, and then loads without branches between them, which the compiler keeps in flight together
-        auto weights8 = [&](long long r0, long long lim, double (&w)[8]) {
-          const long long b0 = w_lo + r0 * 64, b1 = w_lo + min(r0 + 8, lim) * 64;     // the group's range (uniform)
-          if (b0 >= n_lds && b0 < len) {
-#pragma unroll
-            for (int k = 0; k < 8; ++k) {
-              const long long jj = b0 + k * 64 + lane, jc = min(jj, len - 1);
-              const double pv = pbg[jc], qv = use_q ? (double)qbg[jc] : 0.0;
-              const double v = use_q ? fmax(pv - c * qv, 0.0) : pv;
-              w[k] = (r0 + k < lim && jj < len) ? v : 0.0;
-            }
-          } else if (b1 <= n_lds) {
-#pragma unroll
-            for (int k = 0; k < 8; ++k) {
-              const int jc = (int)min(b0 + k * 64 + lane, n_lds - 1);
-              const double pv = pl[jc], qv = use_q ? (double)ql[jc] : 0.0;
-              const double v = use_q ? fmax(pv - c * qv, 0.0) : pv;
-              w[k] = (r0 + k < lim) ? v : 0.0;
-            }
-          } else {
-#pragma unroll
-            for (int k = 0; k < 8; ++k) w[k] = r0 + k < lim ? weight(b0 + k * 64 + lane) : 0.0;
-          }
-        };
-        if (per < 64) {
-          // sums over aligned groups of `per` lanes by lane moves inside the SIMD (one LDS exchange for groups of 32);
-          // a group's first lane leaves the chunk's total in the table, where its thread picks it up
-          const int S = 64 / (int)per;                  // chunks per round
-          for (long long r0 = 0; r0 < per; r0 += 8) {
-            double w[8];
-            weights8(r0, per, w);
-#pragma unroll
-            for (int k = 0; k < 8; ++k) {
-              double v = w[k];
-              if (per >= 2) v += dpp_move_f64<0xB1, 0xf>(v);      // quad_perm [1,0,3,2]
-              if (per >= 4) v += dpp_move_f64<0x4E, 0xf>(v);      // quad_perm [2,3,0,1]
-              if (per >= 8) v += dpp_move_f64<0x141, 0xf>(v);     // row_half_mirror: the other quad of the eight
-              if (per >= 16) v += dpp_move_f64<0x140, 0xf>(v);    // row_mirror: the other half of the sixteen
-              if (per >= 32) v += __shfl_xor(v, 16);
-              if (r0 + k < per && (lane & ((int)per - 1)) == 0)
-                sh.tsum[wave * 64 + (int)(r0 + k) * S + lane / (int)per] = v;
-            }
-          }
-          wave_lds_fence();
-          ts = sh.tsum[tid];
-        } else {
-          const long long rpc = per / 64;                // rounds per chunk (a power of two); chunk after chunk
-          double acc = 0.0;
-          for (long long r0 = 0; r0 < per; r0 += 8) {
-            double w[8];
-            weights8(r0, per, w);                                                       // per >= 64 is a multiple of 8
-#pragma unroll
-            for (int k = 0; k < 8; ++k) {
-              acc += w[k];
-              if (((r0 + k + 1) & (rpc - 1)) == 0) {
-                const double tot = wave_sum(acc);
-                if (lane == (int)((r0 + k) / rpc)) ts = tot;
-                acc = 0.0;
-              }
-            }
-          }
-        }
-      }
-      stamp(70);
-      const double tincl = block_inclusive_scan(ts, sh);
-      sh.tsum[tid] = tincl;
-      if (tid == 0) sh.counter = 0;
-      __syncthreads();
-      // ... and over the workgroups (same order everywhere), gathered and scanned by one wave
-      // (p_beam itself: the totals are known from the row sums, see above; the same in every workgroup of the prompt)
-      const bool known_totals = !use_q && sh.ptot_ok != 0;
-      unsigned long long tag = 0;
-      Slot* bank = nullptr;
-      if (!known_totals) {
-        epoch += 1;
-        tag = exchange_tag(nonce + epoch);
-        bank = slots + bank_x(xchg++);
-      }
-      if (wave == 0) {
-        double v[4];
-        if (!known_totals) {
-          const double mine = sh.tsum[VL_BLOCK - 1];
-          if (lane == 0) dense_post(bank, a.G, g, mine, tag);
-          if (!wave_collect4(bank, a.G, g, mine, tag, v, a.sync_limit)) give_up();
-#pragma unroll
-          for (int k = 0; k < 4; ++k) if (lane + 64 * k < a.G) sh.gpart[lane + 64 * k] = v[k];
-          wave_lds_fence();          // now four consecutive workgroups per lane
-        }
-        lds_f64* const totals = known_totals ? (lds_f64*)sh.ptot : (lds_f64*)sh.gpart;
-#pragma unroll
-        for (int k = 0; k < 4; ++k) {
-          const int w = 4 * lane + k;
-          bool holds = w < a.G;
-          if (known_totals) holds = holds && w / cut.wg_per_row < nI && w % cut.wg_per_row < geo_pieces;
-          v[k] = holds ? (double)totals[w] : 0.0;
-        }
-        int nz = -1;                 // the last workgroup that holds any mass (uniform: from ballots)
-#pragma unroll
-        for (int k = 0; k < 4; ++k) {
-          const unsigned long long has = __ballot(v[k] > 0.0);
-          if (has) nz = max(nz, 4 * (63 - __clzll((long long)has)) + k);
-        }
-        v[1] += v[0]; v[2] += v[1]; v[3] += v[2];
-        double incl = v[3];
-        incl = wave_inclusive_scan(incl);
-        double excl = __shfl_up(incl, 1);
-        if (lane == 0) excl = 0.0;
-#pragma unroll
-        for (int k = 0; k < 4; ++k) if (4 * lane + k < a.G) sh.gpart[4 * lane + k] = excl + v[k];
-        if (lane == 0) sh.found = nz;
-      }
-      __syncthreads();
-      stamp(71);
-      if (sh.abort) return false;
-      const double Z = sh.gpart[a.G - 1];
-      const double before = g > 0 ? sh.gpart[g - 1] : 0.0;
-      if (tid < cnt) {
-        const double target = (double)uj * Z;
-        sh.d_target[tid] = target;
-        // owner: the first workgroup whose inclusive prefix exceeds the target (rounding: the last one with mass)
-        int lo = 0, hi = a.G;
-        while (lo < hi) { const int mid = (lo + hi) >> 1; if (sh.gpart[mid] > target) hi = mid; else lo = mid + 1; }
-        const int owner = lo < a.G ? lo : max(sh.found, 0);
-        if (owner == g) sh.S_tmp[atomicAdd(&sh.counter, 1)] = tid;
-      }
-      __syncthreads();
-      stamp(72);
-      const int n_mine = sh.counter;
-      for (int k = 0; k < n_mine; ++k) {
-        const int j = sh.S_tmp[k];
-        const double target = sh.d_target[j];
-        // the thread whose inclusive prefix is the first to exceed the target (rounding: the last one with mass,
-        // found by the last thread)
-        const bool above = before + sh.tsum[tid] > target;
-        const bool prev_above = tid > 0 && (before + sh.tsum[tid - 1] > target);
-        const bool holder = (above && !prev_above) || (tid == VL_BLOCK - 1 && !above);
-        auto emit = [&](long long pick) {
-          pick = min(pick + e_lo, total - 1);   // back to the flat index over I x V
-          const int i = (int)div_floor(pick, V);
-          const int x = (int)(pick - (long long)i * V);
-          const int node = sh.I_node[i];
-          const long long o = (long long)prompt * a.W_cap + out_base + j;
-          a.out.out_parent[o] = node;
-          a.out.out_token[o] = x;
-          a.out.out_node[o] = -1;
-          const double lp_o = sh.cum_p[i] + ((double)a.zp[(long long)node * V + x] - sh.lse_p[i]);
-          const double lq_o = sh.cum_q[i] + ((double)a.zq[(long long)node * V + x] - sh.lse_q[i]);
-          a.out.out_logp_target[o] = lp_o;
-          a.out.out_logp_draft[o] = lq_o;
-          emit_next(out_base + j, node, x, lp_o, lq_o);
-        };
-        if (in_lds) {
-          if (holder) {
-            int th = tid;
-            if (!above)
-              while (th > 0 && !(sh.tsum[th] > sh.tsum[th - 1])) --th;
-            const long long c_lo = min(len, per * th), c_hi = min(len, c_lo + per);
-            double accl = before + (th > 0 ? sh.tsum[th - 1] : 0.0);
-            long long pick = -1, last = -1;
-            for (long long jj = c_lo; jj < c_hi; ++jj) {
-              const double v = use_q ? fmax((double)pl[(int)jj] - c * (double)ql[(int)jj], 0.0) : (double)pl[(int)jj];
-              if (v > 0.0) last = jj;
-              accl += v;
-              if (accl > target) { pick = jj; break; }
-            }
-            if (pick < 0) pick = last >= 0 ? last : c_lo;
-            emit(pick);
-          }
-        } else {
-          // slices in the workspace: one thread walking its chunk would wait for a load per element, so the first wave
-          // takes the chunk 64 entries at a time (coalesced loads, a scan across the lanes)
-          if (holder) {
-            int th = tid;
-            if (!above)
-              while (th > 0 && !(sh.tsum[th] > sh.tsum[th - 1])) --th;
-            sh.pick_th = th;
-          }
-          __syncthreads();
-          if (wave == 0) {
-            const int th = sh.pick_th;
-            const long long c_lo = min(len, per * th), c_hi = min(len, c_lo + per);
-            double start = before + (th > 0 ? sh.tsum[th - 1] : 0.0);
-            long long pick = -1, last = -1;
-            for (long long b0 = c_lo; b0 < c_hi && pick < 0; b0 += 64) {
-              const long long jj = b0 + lane;
-              double v = 0.0;
-              if (jj < c_hi) v = use_q ? fmax(ldp(jj) - c * ldq(jj), 0.0) : ldp(jj);
-              double incl = v;
-              incl = wave_inclusive_scan(incl);
-              const unsigned long long mass = __ballot(v > 0.0);
-              if (mass) last = b0 + 63 - __clzll((long long)mass);
-              const unsigned long long over = __ballot(start + incl > target);
-              if (over) pick = b0 + __ffsll((long long)over) - 1;
-              start += __shfl(incl, 63);
-            }
-            if (pick < 0) pick = last >= 0 ? last : c_lo;
-            if (lane == 0) emit(pick);
-          }
-          __syncthreads();                   // sh.pick_th is free again
-        }
-      }
-      __syncthreads();
-      return true;
-    };
-
     stamp(23);
+    // What the last layer draws: `d_cnt` beams into the output slots from d_base on, the first of them from the residual
+    // max(p_beam - d_c q_beam, 0) (d_resid), the others from p_beam.
+    int d_cnt, d_base = 0;
+    bool d_resid = false;
+    double d_c = 0.0;
     if (bonus) {
       // ===== every draft layer passed: W_L beams from p_beam^(gamma+1)
-      if (!draw(0.0, false, u_fill + (long long)l * a.W_cap, min(W_in, a.W_cap), 0)) return;
-      n_out = min(W_in, a.W_cap);
+      d_cnt = n_out = min(W_in, a.W_cap);
       if (g == 0 && tid == 0) a.out.layer_width[(long long)prompt * Lw + l] = W_in;
-      break;
-    }
-
+    } else {
     int WL = W_in;             // width of the layer, known before the first decision
 
     // The accept / reject decisions of Algorithm 1 in candidate order, as far as the chain allows.
@@ -2519,7 +2237,11 @@ void verify_layers_kernel(LayersArgs a) {
       for (int i = pos_end + tid; i < M; i += VL_BLOCK) a.out.node_status[sh.S_node[i]] = DSBD_REJECTED;
 
     stamp(50);
-    if (nacc < WL) {
+    if (nacc >= WL) {          // the layer passed: handed over at the top of the next layer
+      passed_nacc = nacc;
+      continue;
+    }
+    {
       // cumulative likelihoods of the accepted beams (fp64)
       if (tid < nacc) {
         const int n = sh.A_node[tid];
@@ -2549,18 +2271,287 @@ void verify_layers_kernel(LayersArgs a) {
         if (g == 0 && tid == 0) atomicOr(a.fault, DSBD_FAULT_ZERO_RESIDUAL);
         k = 1;
       }
-      const double c = sh.cc[k];
-      if (!draw(c, k > 1, u_res + l, 1, nacc)) return;
-      const int fills = WL - nacc - 1;
-      if (fills > 0)
-        if (!draw(0.0, false, u_fill + (long long)l * a.W_cap, fills, nacc + 1)) return;
+      d_resid = k > 1;
+      d_c = sh.cc[k];
+      d_base = nacc;
+      d_cnt = WL - nacc;
       l_last = l;
       n_out = WL;
-      break;
+    }
     }
 
-    // ===== the layer passed: handed over at the top of the next layer
-    passed_nacc = nacc;
+    // ===== the draws, by inverse CDF over I x V in flat order; the workgroup that owns a draw writes its output slot.
+    // (One copy of this code for all draws of a prompt, and one pass for the residual's draw and the others: instructions
+    // that run once come from memory.)
+    const float d_u = tid >= d_cnt ? 0.f : bonus ? u_fill[(long long)l * a.W_cap + tid]
+                                          : tid == 0 ? u_res[l] : u_fill[(long long)l * a.W_cap + tid - 1];
+    auto emit = [&](long long pick, int j) {           // (flat index over I x V)
+      const int i = (int)div_floor(pick, V);
+      const int x = (int)(pick - (long long)i * V);
+      const int node = sh.I_node[i];
+      const long long o = (long long)prompt * a.W_cap + d_base + j;
+      a.out.out_parent[o] = node;
+      a.out.out_token[o] = x;
+      a.out.out_node[o] = -1;
+      const double lp_o = sh.cum_p[i] + ((double)a.zp[(long long)node * V + x] - sh.lse_p[i]);
+      const double lq_o = sh.cum_q[i] + ((double)a.zq[(long long)node * V + x] - sh.lse_q[i]);
+      a.out.out_logp_target[o] = lp_o;
+      a.out.out_logp_draft[o] = lq_o;
+      emit_next(d_base + j, node, x, lp_o, lq_o);
+    };
+    if constexpr (WARP) {
+      // the weights live on the short list (ascending flat index) that every workgroup holds: one wave scans it, the
+      // first workgroup writes the samples
+      __syncthreads();           // the rows' log-sum-exps (another wave's work since the fold) are in place
+      if (wave == 0) {
+        const int nU = sh.nU;
+        const double wp = lane < nU ? sh.U_p[lane] : 0.0, wr = lane < nU ? fmax(wp - d_c * sh.U_q[lane], 0.0) : 0.0;
+        for (int j = 0; j < d_cnt; ++j) {
+          const double w = d_resid && j == 0 ? wr : wp;
+          const double incl = wave_inclusive_scan(w);
+          const unsigned long long mass = __ballot(w > 0.0);
+          const double target = (double)__shfl(d_u, j) * __shfl(incl, 63);
+          const unsigned long long above = __ballot(incl > target);
+          // the first entry whose inclusive prefix exceeds the target (rounding: the last one with mass)
+          const int pl_ = above ? (int)__ffsll((long long)above) - 1 : (mass ? 63 - __clzll((long long)mass) : 0);
+          if (g == 0 && lane == pl_) emit(nU > 0 ? sh.U_idx[pl_] : 0, j);       // (no entry at all, reported as a fault: stay in bounds)
+        }
+      }
+      break;
+    } else {
+    const bool d_plain = d_cnt > (d_resid ? 1 : 0);    // draws from p_beam
+    lds_f64* const ts_r = (lds_f64*)sh.tsum;           // inclusive prefixes over the workgroup's threads: the residual's weights ...
+    lds_f64* const ts_p = (lds_f64*)&sh.u;             // ... and p_beam's
+    static_assert(sizeof(sh.u) >= sizeof(sh.tsum), "a prefix per thread");
+    // every thread's total over its chunk of the slice
+    long long per = (len + VL_BLOCK - 1) / VL_BLOCK;
+    if (!in_lds) {                      // slices in the workspace: chunks of a power of two (at least one) entries
+      long long p2 = 1;
+      while (p2 < per) p2 <<= 1;
+      per = p2;
+    }
+    const long long t_lo = min(len, per * tid), t_hi = min(len, t_lo + per);   // slice-local
+    double tot_r = 0.0, tot_p = 0.0;
+    if (in_lds) {
+      for (int j = (int)t_lo; j < (int)t_hi; ++j) {
+        const double pv = pl[j];
+        if (d_resid) tot_r += fmax(pv - d_c * (double)ql[j], 0.0);
+        tot_p += pv;
+      }
+    } else {
+      for (int kind = d_resid ? 0 : 1; kind < (d_plain ? 2 : 1); ++kind) {
+        const bool use_q = kind == 0;
+        const double c = d_c;
+        double ts = 0.0;
+        // A thread walking its own chunk would make every load of a wave touch 64 cache lines (measured: 14 us for a
+        // 16000-entry slice).  Instead a wave reads the 64 chunks of its threads 64 consecutive entries at a time and
+        // adds them up across the lanes: `per` rounds, each holding 64 / per whole chunks or a 64th of one.
+        const long long w_lo = per * 64 * wave;
+        auto weight = [&](long long jj) -> double {
+          if (jj >= len) return 0.0;
+          if (jj < n_lds) return use_q ? fmax((double)pl[(int)jj] - c * (double)ql[(int)jj], 0.0) : (double)pl[(int)jj];
+          return use_q ? fmax((double)pbg[jj] - c * (double)qbg[jj], 0.0) : (double)pbg[jj];
+        };
+        // eight rounds from r0 on (rounds beyond `lim` count nothing): one home for all eight in all but one group of
+        // a wave, and then loads without branches between them, which the compiler keeps in flight together
+        auto weights8 = [&](long long r0, long long lim, double (&w)[8]) {
+          const long long b0 = w_lo + r0 * 64, b1 = w_lo + min(r0 + 8, lim) * 64;     // the group's range (uniform)
+          if (b0 >= n_lds && b0 < len) {
+#pragma unroll
+            for (int k = 0; k < 8; ++k) {
+              const long long jj = b0 + k * 64 + lane, jc = min(jj, len - 1);
+              const double pv = pbg[jc], qv = use_q ? (double)qbg[jc] : 0.0;
+              const double v = use_q ? fmax(pv - c * qv, 0.0) : pv;
+              w[k] = (r0 + k < lim && jj < len) ? v : 0.0;
+            }
+          } else if (b1 <= n_lds) {
+#pragma unroll
+            for (int k = 0; k < 8; ++k) {
+              const int jc = (int)min(b0 + k * 64 + lane, n_lds - 1);
+              const double pv = pl[jc], qv = use_q ? (double)ql[jc] : 0.0;
+              const double v = use_q ? fmax(pv - c * qv, 0.0) : pv;
+              w[k] = (r0 + k < lim) ? v : 0.0;
+            }
+          } else {
+#pragma unroll
+            for (int k = 0; k < 8; ++k) w[k] = r0 + k < lim ? weight(b0 + k * 64 + lane) : 0.0;
+          }
+        };
+        if (per < 64) {
+          // sums over aligned groups of `per` lanes by lane moves inside the SIMD (one LDS exchange for groups of 32);
+          // a group's first lane leaves the chunk's total in the table, where its thread picks it up
+          const int S = 64 / (int)per;                  // chunks per round
+          for (long long r0 = 0; r0 < per; r0 += 8) {
+            double w[8];
+            weights8(r0, per, w);
+#pragma unroll
+            for (int k = 0; k < 8; ++k) {
+              double v = w[k];
+              if (per >= 2) v += dpp_move_f64<0xB1, 0xf>(v);      // quad_perm [1,0,3,2]
+              if (per >= 4) v += dpp_move_f64<0x4E, 0xf>(v);      // quad_perm [2,3,0,1]
+              if (per >= 8) v += dpp_move_f64<0x141, 0xf>(v);     // row_half_mirror: the other quad of the eight
+              if (per >= 16) v += dpp_move_f64<0x140, 0xf>(v);    // row_mirror: the other half of the sixteen
+              if (per >= 32) v += __shfl_xor(v, 16);
+              if (r0 + k < per && (lane & ((int)per - 1)) == 0)
+                sh.tsum[wave * 64 + (int)(r0 + k) * S + lane / (int)per] = v;
+            }
+          }
+          wave_lds_fence();
+          ts = sh.tsum[tid];
+        } else {
+          const long long rpc = per / 64;                // rounds per chunk (a power of two); chunk after chunk
+          double acc = 0.0;
+          for (long long r0 = 0; r0 < per; r0 += 8) {
+            double w[8];
+            weights8(r0, per, w);                                                       // per >= 64 is a multiple of 8
+#pragma unroll
+            for (int k = 0; k < 8; ++k) {
+              acc += w[k];
+              if (((r0 + k + 1) & (rpc - 1)) == 0) {
+                const double tot = wave_sum(acc);
+                if (lane == (int)((r0 + k) / rpc)) ts = tot;
+                acc = 0.0;
+              }
+            }
+          }
+        }
+        if (use_q) tot_r = ts; else tot_p = ts;
+        wave_lds_fence();
+      }
+    }
+    stamp(70);
+    const double incl_r = wave_inclusive_scan(tot_r), incl_p = wave_inclusive_scan(tot_p);
+    __syncthreads();
+    if (lane == 63) { sh.scan_w[wave] = incl_r; sh.scan_w2[wave] = incl_p; }
+    if (tid == 0) sh.counter = 0;
+    __syncthreads();
+    double before_r = 0.0, before_p = 0.0;
+    for (int w = 0; w < wave; ++w) { before_r += sh.scan_w[w]; before_p += sh.scan_w2[w]; }
+    ts_r[tid] = before_r + incl_r;
+    ts_p[tid] = before_p + incl_p;
+    // ... and over the workgroups (same order everywhere), gathered and scanned by one wave for either kind: the first for
+    // the residual, whose totals have to be exchanged, the second for p_beam, whose totals are known from the row sums
+    // (see above; the same in every workgroup of the prompt) unless a gathering thread saw several pieces.
+    // (These are the prompt's last exchanges: nobody waits for their banks to be free again.)
+    lds_f64* const pre_r = (lds_f64*)sh.gpart;
+    lds_f64* const pre_p = (lds_f64*)sh.ptot;
+    if ((wave == 0 && d_resid) || (wave == 1 && d_plain)) {
+      const bool known_totals = wave == 1 && sh.ptot_ok != 0;
+      lds_f64* const tab = wave == 0 ? pre_r : pre_p;
+      double v[4];
+      if (!known_totals) {
+        const unsigned long long tag = exchange_tag(nonce + epoch + 1 + wave);
+        Slot* const bank = slots + bank_x(xchg + wave);
+        double mine = 0.0;
+        for (int w = 0; w < VL_WAVES; ++w) mine += wave == 0 ? sh.scan_w[w] : sh.scan_w2[w];
+        if (lane == 0) dense_post(bank, a.G, g, mine, tag);
+        if (!wave_collect4(bank, a.G, g, mine, tag, v, a.sync_limit)) give_up();
+#pragma unroll
+        for (int k = 0; k < 4; ++k) if (lane + 64 * k < a.G) tab[lane + 64 * k] = v[k];
+        wave_lds_fence();          // now four consecutive workgroups per lane
+      }
+#pragma unroll
+      for (int k = 0; k < 4; ++k) {
+        const int w = 4 * lane + k;
+        bool holds = w < a.G;
+        if (known_totals) holds = holds && w / cut.wg_per_row < nI && w % cut.wg_per_row < geo_pieces;
+        v[k] = holds ? (double)tab[w] : 0.0;
+      }
+      int nz = -1;                 // the last workgroup that holds any mass (uniform: from ballots)
+#pragma unroll
+      for (int k = 0; k < 4; ++k) {
+        const unsigned long long has = __ballot(v[k] > 0.0);
+        if (has) nz = max(nz, 4 * (63 - __clzll((long long)has)) + k);
+      }
+      v[1] += v[0]; v[2] += v[1]; v[3] += v[2];
+      double incl = v[3];
+      incl = wave_inclusive_scan(incl);
+      double excl = __shfl_up(incl, 1);
+      if (lane == 0) excl = 0.0;
+#pragma unroll
+      for (int k = 0; k < 4; ++k) if (4 * lane + k < a.G) tab[4 * lane + k] = excl + v[k];
+      if (lane == 0) sh.W_cnt[wave] = nz;
+    }
+    __syncthreads();
+    stamp(71);
+    if (sh.abort) return;
+    if (tid < d_cnt) {
+      const bool resid = d_resid && tid == 0;
+      lds_f64* const tab = resid ? pre_r : pre_p;
+      const double target = (double)d_u * tab[a.G - 1];
+      sh.d_target[tid] = target;
+      // owner: the first workgroup whose inclusive prefix exceeds the target (rounding: the last one with mass)
+      int lo = 0, hi = a.G;
+      while (lo < hi) { const int mid = (lo + hi) >> 1; if (tab[mid] > target) hi = mid; else lo = mid + 1; }
+      const int owner = lo < a.G ? lo : max(sh.W_cnt[resid ? 0 : 1], 0);
+      if (owner == g) sh.S_tmp[atomicAdd(&sh.counter, 1)] = tid;
+    }
+    __syncthreads();
+    stamp(72);
+    const int n_mine = sh.counter;
+    for (int k = 0; k < n_mine; ++k) {
+      const int j = sh.S_tmp[k];
+      const bool resid = d_resid && j == 0;
+      lds_f64* const ts = resid ? ts_r : ts_p;
+      const double before = g > 0 ? (double)(resid ? pre_r : pre_p)[g - 1] : 0.0;
+      const double target = sh.d_target[j];
+      // the thread whose inclusive prefix is the first to exceed the target (rounding: the last one with mass,
+      // found by the last thread)
+      const bool above = before + ts[tid] > target;
+      const bool prev_above = tid > 0 && (before + ts[tid - 1] > target);
+      const bool holder = (above && !prev_above) || (tid == VL_BLOCK - 1 && !above);
+      if (in_lds) {
+        if (holder) {
+          int th = tid;
+          if (!above)
+            while (th > 0 && !(ts[th] > ts[th - 1])) --th;
+          const long long c_lo = min(len, per * th), c_hi = min(len, c_lo + per);
+          double accl = before + (th > 0 ? (double)ts[th - 1] : 0.0);
+          long long pick = -1, last = -1;
+          for (long long jj = c_lo; jj < c_hi; ++jj) {
+            const double v = resid ? fmax((double)pl[(int)jj] - d_c * (double)ql[(int)jj], 0.0) : (double)pl[(int)jj];
+            if (v > 0.0) last = jj;
+            accl += v;
+            if (accl > target) { pick = jj; break; }
+          }
+          if (pick < 0) pick = last >= 0 ? last : c_lo;
+          emit(min(pick + e_lo, total - 1), j);
+        }
+      } else {
+        // slices in the workspace: one thread walking its chunk would wait for a load per element, so the first wave
+        // takes the chunk 64 entries at a time (coalesced loads, a scan across the lanes)
+        if (holder) {
+          int th = tid;
+          if (!above)
+            while (th > 0 && !(ts[th] > ts[th - 1])) --th;
+          sh.pick_th = th;
+        }
+        __syncthreads();
+        if (wave == 0) {
+          const int th = sh.pick_th;
+          const long long c_lo = min(len, per * th), c_hi = min(len, c_lo + per);
+          double start = before + (th > 0 ? (double)ts[th - 1] : 0.0);
+          long long pick = -1, last = -1;
+          for (long long b0 = c_lo; b0 < c_hi && pick < 0; b0 += 64) {
+            const long long jj = b0 + lane;
+            double v = 0.0;
+            if (jj < c_hi) v = resid ? fmax(ldp(jj) - d_c * ldq(jj), 0.0) : ldp(jj);
+            double incl = v;
+            incl = wave_inclusive_scan(incl);
+            const unsigned long long mass = __ballot(v > 0.0);
+            if (mass) last = b0 + 63 - __clzll((long long)mass);
+            const unsigned long long over = __ballot(start + incl > target);
+            if (over) pick = b0 + __ffsll((long long)over) - 1;
+            start += __shfl(incl, 63);
+          }
+          if (pick < 0) pick = last >= 0 ? last : c_lo;
+          if (lane == 0) emit(min(pick + e_lo, total - 1), j);
+        }
+        __syncthreads();                   // sh.pick_th is free again
+      }
+    }
+    break;
+    }
   }
 
   stamp(99);
