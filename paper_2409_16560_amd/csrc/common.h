@@ -39,7 +39,7 @@ struct DsbdKnobs {
   long long verify_sync_limit_us;   // DSBD_VERIFY_SYNC_LIMIT_US: bound of every wait of the layer kernel; 0 = default
   int verify_mute_wg;          // DSBD_VERIFY_TEST_MUTE_WG: test hook, this workgroup withholds its first post; -1 = none
   int verify_lds_slice;        // DSBD_VERIFY_LDS_SLICE: largest joint slice kept in the LDS; -1 = the plan's choice
-  int warp_fast;               // DSBD_WARP_FAST: 0 = the warping selection always takes its tree form
+  int warp_fast;               // DSBD_WARP_FAST: 0 = the warped rows' entries are always selected one by one, as where they crowd
   int event_fence;             // DSBD_EVENT_FENCE: 1 = the library's cross-stream events keep HIP's system-scope fence; 0 = they order
                                // device work only (no cache write-back for the host's sake at every one)
 };

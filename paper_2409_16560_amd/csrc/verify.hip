@@ -22,9 +22,15 @@
 //
 // All G workgroups of a prompt run the same sequential program on the same reduced values (summed in
 // the same order), so their control flow stays identical without any broadcast.
+//
+// Warped joints (top-k / top-p) have at most 64 entries, which come out of the rows' records (verify_rows.hip, launched in
+// front): one workgroup walks a prompt's layers and exchanges nothing (verify_layers_kernel<true>).  Measured, verification
+// in us, against layers formed and selected from on up to 256 workgroups: 53 nodes x 128256 58 -> 47, 103 nodes of 3 prompts
+// x 50273 88 -> 45, 577 nodes of 16 prompts x 32000 160 -> 104, 28 nodes x 32000 89 -> 46, 248 nodes x 128256 142 -> 126.
 #include "common.h"
 #include "topology_device.h"
 #include "exp_nonpos.h"
+#include "verify_rows.h"
 #include "wave_f64.h"
 #include <type_traits>
 #include <float.h>
@@ -100,16 +106,10 @@ __device__ __forceinline__ void online_merge(float& m, float& s, float m2, float
 struct SlotLayout {
   int x[2];              // the two alternating banks of the post-then-collect-from-all exchanges: G lines
   int r, r_w, r_stride;  // row sums of layer l: r + (l - 1) * r_stride, r_w slots per workgroup
-  int b, b_w;            // warping: every workgroup's candidate list, b_w slots each
-  int c;                 // warping: the groups' merged lists (b_w slots each)
-  int d;                 // warping: the final entries, posted by the prompt's first workgroup
-  int wb, wb_stride;     // warping, one-level form: the workgroups' candidates of layer l at wb + (l - 1) * wb_stride, b_w
-                         // slots per workgroup (two counts, then value | index)
   int acc;               // accumulator words of the one-hop sums: 2 banks x NACC lines
   int acc0;              // their values at launch, posted by the prompt's first workgroup: 2 x NACC slots
   int prompt_stride;
 };
-#define WARP_RESULT_SLOTS 193     // count + 64 x (index, p, q)
 
 struct LayersArgs {
   int n_prompts, n_trees, n_nodes;
@@ -144,7 +144,9 @@ struct LayersArgs {
   int mute_wg;           // test hook: this workgroup withholds its first post (-1: none), so that its partners'
                          // bounded waits give up and the error path can be exercised without a hang
   int32_t* fault;
-  int warp_fast;         // warping: the one-level selection (bounds from the workgroups' largest entries) where it applies
+  const char* rec;       // warping: the records of all rows (verify_rows.h), `rec_stride` bytes apart
+  long long rec_stride;
+  int rec_compact;
   dsbd_next_beams nx;    // next-beam plan written along with the output beams (fused selection) ...
   int nx_on;             // ... when this is set
   int layer_wgs;         // workgroups of this launch that walk layers; those behind them take the statistics of the rows ...
@@ -210,8 +212,7 @@ struct LayerShared {
   int U_idx[64];
   double U_p[64], U_q[64];
   int nU;
-  double W_tau[2];                   // lower bounds of the slice's K-th entries
-  int W_cnt[2];                      // entries kept per model after the merge
+  int last_mass[2];                  // draws: the last workgroup that holds any mass, of either kind of weights
   int state[2];                      // outcome of the decision rounds, alternating entries
   int kmax, counter, abort, found, sbad, sgamma;
   int acc_n, pos, kidx;        // accept loop: accepted so far, next candidate, chain index of p'
@@ -409,28 +410,13 @@ __device__ __forceinline__ Slot* prompt_slots(const LayersArgs& a, int prompt) {
   return reinterpret_cast<Slot*>(a.red) + (long long)prompt * a.sl.prompt_stride;
 }
 
-// ---- selection of the largest joint entries (warping T).  Entries are ranked by descending value, equal values by
-// ascending flat index; a candidate is (value, index), "none" is (-1, INT_MAX).
-#define WARP_K_MAX 32
-#define WARP_CAND 512          // candidates per model a merge can hold (WARP_GROUP lists of WARP_K_MAX entries)
-#define WARP_GROUP 16          // workgroups whose lists one workgroup merges
-__device__ __forceinline__ bool cand_before(double va, int ia, double vb, int ib) {
-  // no short circuit: the operands are loaded side by side instead of one after a branch on the other
-  return (va > vb) | ((va == vb) & (ia < ib));
-}
+#define WARP_K_MAX VR_K_MAX
 __device__ __forceinline__ double readlane_f64(double v, int l) {
   const int lo = __builtin_amdgcn_readlane(__double2loint(v), l), hi = __builtin_amdgcn_readlane(__double2hiint(v), l);
   return __hiloint2double(hi, lo);
 }
-// first candidate in rank order among one per lane; the same result in every lane
-__device__ __forceinline__ void wave_first(double& v, int& i) {
-#pragma unroll
-  for (int off = 32; off >= 1; off >>= 1) {
-    const double ov = __shfl_xor(v, off);
-    const int oi = __shfl_xor(i, off);
-    if (cand_before(ov, oi, v, i)) { v = ov; i = oi; }
-  }
-}
+// The value of the lane below (lane 0: 0.0).
+__device__ __forceinline__ double lane_from_below(double v) { return dpp_move_f64<0x138, 0xf>(v); }      // wave_shr:1
 
 // How a layer's joint over nI rows of V entries is cut among G workgroups (host and device use the same rule).
 struct SliceCut {
@@ -557,7 +543,7 @@ __global__ __launch_bounds__(VL_BLOCK) __attribute__((amdgpu_num_vgpr(VL_MAX_VGP
 void verify_layers_kernel(LayersArgs a) {
   __shared__ LayerShared<NC> sh;
   extern __shared__ __attribute__((aligned(16))) double dyn_lds[];
-  if ((int)blockIdx.x >= a.layer_wgs) {
+  if (!WARP && (int)blockIdx.x >= a.layer_wgs) {
     if (a.stats_threads == 64) row_statistics<64>(a, sh);
     else if (a.stats_threads == 128) row_statistics<128>(a, sh);
     else if (a.stats_threads == 256) row_statistics<256>(a, sh);
@@ -571,7 +557,7 @@ void verify_layers_kernel(LayersArgs a) {
   const int V = a.V;
   unsigned int epoch = 0;      // exchanges so far (sets the tag); identical in every workgroup of the prompt
   unsigned int xchg = 0;       // of those, the ones on the two alternating banks
-  Slot* const slots = prompt_slots(a, prompt);
+  Slot* const slots = WARP ? nullptr : prompt_slots(a, prompt);      // (one workgroup walks a prompt's warped layers: no exchanges)
   // (a replayed launch: the replay count, which the kernel in front of this one has just raised, sets the tags apart
   // from those of the graph's earlier replays)
   const unsigned long long nonce =
@@ -600,7 +586,7 @@ void verify_layers_kernel(LayersArgs a) {
   unsigned int handovers = 0;  // rounds of the accept loop's handing over of wave totals
   // (requested here, used at the end of the prologue: the round trip through the memory system runs beside it)
   unsigned long long acc0_w = 0;
-  if (g == 0 && tid < 2 * NACC)
+  if (!WARP && g == 0 && tid < 2 * NACC)
     acc0_w = __hip_atomic_load(&accs[tid * 16], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 
   if (tid == 0) { sh.abort = 0; sh.sbad = 0; sh.sgamma = 0; sh.counter = 0; sh.found = 0; sh.handed = 0u; }
@@ -695,6 +681,7 @@ void verify_layers_kernel(LayersArgs a) {
 #pragma unroll
   for (int k = 0; k < XU; ++k) { eA_p[k] = 0.f; eA_q[k] = 0.f; eB_p[k] = 0.f; eB_q[k] = 0.f; }
   auto request_first = [&](const int* row_nodes) __attribute__((always_inline)) {
+    if constexpr (WARP) return;
     early = geo_ihi >= geo_ilo;
     if (!early) return;
     const int i = geo_ilo;
@@ -819,7 +806,7 @@ void verify_layers_kernel(LayersArgs a) {
   int near_tie = 0;          // meaningful in thread 0
   int l_last = gamma + 1;
   int n_out = 0;
-  if (g == 0 && tid < 2 * NACC) {
+  if (!WARP && g == 0 && tid < 2 * NACC) {
     (&sh.acc_prev[0][0])[tid] = acc0_w;
     slot_post(slots + a.sl.acc0 + tid, __longlong_as_double((long long)acc0_w), acc0_tag);
   }
@@ -906,6 +893,28 @@ void verify_layers_kernel(LayersArgs a) {
       body(pbg, qbg, n_lds, len);
     };
 
+    // warping: entry r of row i's record of model m, for the thread's first place among 2 x nI x K
+    RowHead rec_head = {1.0, 0.f, 0};
+    RowEntry rec_entry = {0.f, 0};
+    auto row_record = [&](int node, int m, int r, RowHead& h, RowEntry& e) {
+      const char* const at = a.rec + (a.alias ? (long long)node : 2LL * node + m) * a.rec_stride;
+      h = *reinterpret_cast<const RowHead*>(at);
+      if (a.rec_compact) {
+        if (r >= h.n) e.x = 0;
+        else if (a.rec_compact == 1) e.x = reinterpret_cast<const uint8_t*>(at + sizeof(RowHead))[r];
+        else e.x = reinterpret_cast<const uint16_t*>(at + sizeof(RowHead))[r];
+        e.z = (m ? a.zq : a.zp)[(long long)node * V + e.x];
+      } else {
+        e = reinterpret_cast<const RowEntry*>(at + sizeof(RowHead))[min(r, V - 1)];     // (a record has room for min(K, V); places behind its n entries are not used)
+      }
+    };
+    if constexpr (WARP) {
+      const int n_cand = nI * a.top_k;
+      if (tid < 2 * n_cand) {
+        const int m = tid >= n_cand ? 1 : 0, e = tid - m * n_cand;
+        row_record(sh.I_node[e / a.top_k], m, e % a.top_k, rec_head, rec_entry);
+      }
+    }
     // a chain entry of the layer before that nobody needed: collected now (by the wave that does nothing else here), so
     // that the words' values are known when the next exchange is posted
     if (x_open) {
@@ -975,6 +984,8 @@ void verify_layers_kernel(LayersArgs a) {
       }
     }
 
+    double f1 = 0.0;                         // this thread's part of F(1) = sum max(p_beam - q_beam, 0) (second entry of the chain)
+    if constexpr (!WARP) {
     // ===== p_beam / q_beam over I x V: exponentials and this workgroup's share of the row sums.  The exponentials
     // are taken against the maximum of the workgroup's own piece of the row (found here, in the same pass over the
     // logits); the pieces' maxima travel with their sums and are folded into the row's maximum and total below.
@@ -1148,11 +1159,6 @@ void verify_layers_kernel(LayersArgs a) {
     // column sit in R neighbouring lanes of one wave and are put on the column's maximum and added up by lane
     // exchanges that pair the lanes symmetrically (no table in the LDS, no barrier in between): every lane of a
     // column, in every workgroup of the prompt, gets the same bits.
-    bool warp_pieces = false;               // warping: the table of the workgroups' largest entries is filled
-    if constexpr (WARP) {
-      if (tid < 256) { sh.gpart[tid] = -1.0; sh.ptot[tid] = -1.0; }     // (workgroups without a piece keep this)
-      lds_barrier();                          // (the gathering threads below write other entries than their own)
-    }
     {
       const int ncols = 2 * nI;
       int cshift = 0;
@@ -1172,9 +1178,6 @@ void verify_layers_kernel(LayersArgs a) {
           double vs = 0.0, vm = 0.0;
           Slot* const sl0 = rs_bank + (long long)w * a.sl.r_w + 4 * i + (c & 1);
           mine = mine && slot_wait2(sl0, sl0 + 2, rs_tag, vs, vm, a.sync_limit);
-          if constexpr (WARP) {              // (kept for the table of the workgroups' largest entries, below)
-            if (cut.rows_per_wg == 0) ((c & 1) ? sh.ptot : sh.gpart)[min(w, 255)] = vm;
-          }
           const double Mn = fmax(accM, vm);
           accS = accS * exp_nonpos(accM - Mn, sh.exp_tab) + vs * exp_nonpos(vm - Mn, sh.exp_tab);
           accM = Mn;
@@ -1209,29 +1212,8 @@ void verify_layers_kernel(LayersArgs a) {
       // the draws that fill a layer up) then needs no exchange of the workgroups' totals.  Only where a gathering
       // thread holds exactly one piece (its sum and maximum are still in its registers).
       // (entries of workgroups without a piece are never written: the reader knows which those are)
-      const bool single_piece = !WARP && cut.rows_per_wg == 0 && geo_pieces <= R;
+      const bool single_piece = cut.rows_per_wg == 0 && geo_pieces <= R;
       if (tid == 0) sh.ptot_ok = single_piece ? 1 : 0;
-      if constexpr (WARP) {
-        // Every workgroup's largest entry of either joint follows from what the gathering threads hold (a piece's
-        // largest exponential is 1 against the piece's own maximum): p_beam's largest entry in the piece of row i is
-        // (beam weight / row sum) exp(piece maximum - row maximum).  Every workgroup evaluates this alike, bit for
-        // bit, for every workgroup of the prompt (rows cut into pieces, a piece per workgroup; with whole rows per
-        // workgroup the table is left alone and the selection below takes its tree form).
-        // (worth it with many more workgroups than entries to keep: the K-th largest of a few largest entries is a
-        // poor bound.  Measured: 16 workgroups per prompt, K = 10: 247 us against the tree form's 202 us; 64
-        // workgroups, K = 32: 177 against 167 us; 64 and K = 10: 115 against 131 us; 256 and K = 10: 146 against 176 us.)
-        warp_pieces = cut.rows_per_wg == 0 && nI * geo_pieces >= 4 * a.top_k;
-        if (warp_pieces && c < ncols) {
-          const int i = c >> 1;
-          const double scale = ((c & 1) ? sh.bw_q[i] : sh.bw_p[i]) / tot;
-          double* const tab = (c & 1) ? sh.ptot : sh.gpart;
-          const int w_lo = i * cut.wg_per_row, w_hi = w_lo + geo_pieces - 1;
-          for (int w = w_lo + r; w <= w_hi; w += R) {        // the pieces this thread gathered: their maxima are in the table
-            const double vm = tab[min(w, 255)];
-            tab[min(w, 255)] = vm > -INFINITY ? scale * exp_nonpos(vm - cm, sh.exp_tab) : -1.0;     // (an empty piece holds nothing)
-          }
-        }
-      }
       if (single_piece && c < ncols && (c & 1) == 0 && r < geo_pieces) {
         const int i = c >> 1;
         sh.ptot[i * cut.wg_per_row + r] = (sh.bw_p[i] / tot) * (accS * exp_nonpos(accM - cm, sh.exp_tab));
@@ -1239,13 +1221,7 @@ void verify_layers_kernel(LayersArgs a) {
       __syncthreads();
     }
     stamp(24);
-    // scaling, fused with this thread's part of F(1) = sum max(p_beam - q_beam, 0) (second entry of the chain)
-    double f1 = 0.0;
-    double tmax_p = -1.0, tmax_q = -1.0;     // warping: the largest scaled entries this thread has seen
-    // (the one-level selection of the warped kernel needs no scaled slices: it scales the few entries it compares
-    // on the fly and the slices are dead afterwards; only its fallback, the tree form, runs this pass after all)
-    const bool defer_scaling = WARP && a.warp_fast && a.G > 1 && warp_pieces;
-    auto scale_pass = [&]() {
+    // scaling, fused with this thread's part of F(1)
     for (int i = i_lo; i <= i_hi; ++i) {
       const long long j_lo = max(e_lo, (long long)i * V) - e_lo;
       const long long j_hi = min(e_hi, (long long)(i + 1) * V) - e_lo;
@@ -1263,541 +1239,134 @@ void verify_layers_kernel(LayersArgs a) {
           for (int k = 0; k < 4; ++k) {
             pv[k] *= fp; qv[k] *= fq;
             P[j + k * VL_BLOCK] = pv[k]; Q[j + k * VL_BLOCK] = qv[k];
-            if constexpr (WARP) { tmax_p = fmax(tmax_p, pv[k]); tmax_q = fmax(tmax_q, qv[k]); }
-            else f1 += fmax(pv[k] - qv[k], 0.0);
+            f1 += fmax(pv[k] - qv[k], 0.0);
           }
         }
         for (; j < j_end; j += VL_BLOCK) {
           const double pv = P[j] * fp, qv = Q[j] * fq;
           P[j] = pv; Q[j] = qv;
-          if constexpr (WARP) { tmax_p = fmax(tmax_p, pv); tmax_q = fmax(tmax_q, qv); }
-          else f1 += fmax(pv - qv, 0.0);
+          f1 += fmax(pv - qv, 0.0);
         }
       });
     }
-    };
-    if (!defer_scaling) scale_pass();
+    }
     if constexpr (WARP) {
-      // ===== warping T: top-k / top-p on the two joints (Section 2.1; Section 3.1 "Details": p_beam = T o p/P).
-      // Every workgroup finds the K first entries of its slice.  The lists travel up a tree: the first workgroup
-      // of every group of WARP_GROUP merges its group's lists, the prompt's first workgroup merges the groups'
-      // lists, cuts the result by top-p, renormalises and posts the surviving entries (at most 2K), which every
-      // workgroup then holds: the rest of the layer needs no further exchange.
-      __syncthreads();                       // the scaled slices are complete
-      const int K = a.top_k;
+      // ===== warping T: top-k / top-p on the two joints (Section 2.1; Section 3.1 "Details": p_beam = T o p/P).  A joint's
+      // K first entries (by value, equal values by flat index) are among the K first of its rows, which the rows' records
+      // hold: every entry's value from its logit in one form that depends on the row only (equal logits of a row give
+      // equal values), then their ranks by counting.
+      const int K = a.top_k, n_cand = nI * K;            // at most 64 x 32 per model
       typedef __attribute__((address_space(3))) int lds_i32;
-      // scratch (all rewritten later in the layer): candidates in S_pb/S_qb (values) and S_zp/S_zq (indices),
-      // lists in Pa (values: p then q) and Pb (indices); collected lists in the dynamic LDS (the slices are not
-      // needed any more by then): values [model][source * K + rank], then the indices
-      lds_f64* const cvp = (lds_f64*)sh.S_pb; lds_f64* const cvq = (lds_f64*)sh.S_qb;
-      lds_i32* const cip = (lds_i32*)sh.S_zp; lds_i32* const ciq = (lds_i32*)sh.S_zq;
-      lds_f64* const lv = (lds_f64*)sh.Pa; lds_i32* const li = (lds_i32*)sh.Pb;
-      lds_f64* const gv = (lds_f64*)dyn_lds;
-      lds_i32* const gi = (lds_i32*)(dyn_lds + 2 * WARP_CAND);
-      // The K first of na candidates by counting for each those ahead of it, eight threads per candidate and 64
-      // candidates per pass; ranks nobody takes keep what the caller put there.
-      auto rank_cands = [&](lds_f64* va, lds_i32* ia, int na, lds_f64* ov, lds_i32* oi) {
-        const int part = tid & 7;
-        for (int t0 = 0; t0 < na; t0 += VL_BLOCK / 8) {
-          const int t = t0 + (tid >> 3);
-          const bool has = t < na;
-          const double v = has ? va[t] : 0.0;
-          const int ix = has ? ia[t] : 0;
-          int rank = 0;
-          if (has) {
-            int c = part;
-            for (; c + 24 < na; c += 32) {     // four candidates per round, their loads in flight together
-              double o[4];
-              int oi4[4];
-#pragma unroll
-              for (int k = 0; k < 4; ++k) { o[k] = va[c + 8 * k]; oi4[k] = ia[c + 8 * k]; }
-#pragma unroll
-              for (int k = 0; k < 4; ++k) rank += cand_before(o[k], oi4[k], v, ix) ? 1 : 0;
-            }
-            for (; c < na; c += 8) rank += cand_before(va[c], ia[c], v, ix) ? 1 : 0;
-          }
-          rank += __shfl_xor(rank, 1);
-          rank += __shfl_xor(rank, 2);
-          rank += __shfl_xor(rank, 4);
-          if (has && part == 0 && rank < K) { ov[rank] = v; oi[rank] = ix; }
+      typedef double f64x2 __attribute__((ext_vector_type(2)));
+      typedef __attribute__((address_space(3))) f64x2 lds_f64x2;
+      const int stride = (n_cand + 1) & ~1;
+      lds_f64* const cv = (lds_f64*)dyn_lds;             // [2][stride] values of p_beam's and q_beam's entries, row by row, then
+      lds_i32* const ci = (lds_i32*)(dyn_lds + 2 * stride);      // their flat indices
+      lds_f64* const lv = (lds_f64*)sh.Pa; lds_i32* const li = (lds_i32*)sh.Pb;      // the K first of either, in rank order
+      lds_barrier();                                     // the beam weights are there
+      for (int t = tid; t < 2 * n_cand; t += VL_BLOCK) {
+        const int m = t >= n_cand ? 1 : 0, e = t - m * n_cand, i = e / K, r = e - i * K;
+        RowHead h = rec_head;
+        RowEntry x = rec_entry;
+        if (t != tid) row_record(sh.I_node[i], m, r, h, x);
+        const double scale = (m ? sh.bw_q[i] : sh.bw_p[i]) / h.sum, top = (double)h.max;
+        if (r == 0) {
+          (m ? sh.max_q : sh.max_p)[i] = top; (m ? sh.sq : sh.sp)[i] = scale; (m ? sh.lse_q : sh.lse_p)[i] = h.sum;
         }
-      };
-      // candidates (counts in W_cnt) -> lists; missing ranks are "none" (-1, INT_MAX), which sorts last
-      auto rank_select = [&]() {
-        if (tid < 2 * K) { lv[tid] = -1.0; li[tid] = INT_MAX; }
-        __syncthreads();
-        rank_cands(cvp, cip, min(sh.W_cnt[0], WARP_CAND), lv, li);
-        rank_cands(cvq, ciq, min(sh.W_cnt[1], WARP_CAND), lv + K, li + K);
-      };
-      // everything at or above the bounds W_tau is a candidate (counts in W_cnt; the arrays hold the first WARP_CAND)
-      bool scaled = !defer_scaling;          // the slices hold joint entries (else exponentials against the piece's maximum)
-      auto collect_at_or_above = [&]() {
-        // (a little below the bounds: the values compared here and the ones the candidates are ranked by, below, may
-        // differ in the last bits)
-        const double tp = sh.W_tau[0] * (1.0 - 1e-12), tq = sh.W_tau[1] * (1.0 - 1e-12);
-        // (unscaled slices: one piece of one row per workgroup; the same products as the scaling pass forms)
-        double mp = 1.0, mq = 1.0;
-        if (!scaled && i_lo <= i_hi) {
-          mp = sh.sp[i_lo] * exp_nonpos(sh.lm_p[0] - sh.max_p[i_lo], sh.exp_tab);
-          mq = sh.sq[i_lo] * exp_nonpos(sh.lm_q[0] - sh.max_q[i_lo], sh.exp_tab);
-        }
-        auto offer = [&](long long j, double vp_raw, double vq_raw) {
-          const double vp = vp_raw * mp, vq = vq_raw * mq;
-          if (vp >= tp) {
-            const int c = atomicAdd(&sh.W_cnt[0], 1);
-            if (c < WARP_CAND) { cvp[c] = vp; cip[c] = (int)(e_lo + j); }
-          }
-          if (vq >= tq) {
-            const int c = atomicAdd(&sh.W_cnt[1], 1);
-            if (c < WARP_CAND) { cvq[c] = vq; ciq[c] = (int)(e_lo + j); }
-          }
-        };
-        with_slices([&](auto P, auto Q, long long r0, long long r1) {
-          long long j = r0 + tid;
-          for (; j + 3 * VL_BLOCK < r1; j += 4 * VL_BLOCK) {
-            double pv[4], qv[4];
-#pragma unroll
-            for (int k = 0; k < 4; ++k) { pv[k] = P[j + k * VL_BLOCK]; qv[k] = Q[j + k * VL_BLOCK]; }
-#pragma unroll
-            for (int k = 0; k < 4; ++k) offer(j + k * VL_BLOCK, pv[k], qv[k]);
-          }
-          for (; j < r1; j += VL_BLOCK) offer(j, P[j], Q[j]);
-        });
-      };
-      // ===== One-level selection (many more workgroups per prompt than entries to keep).  A lower bound of the joint's
-      // K-th entry comes from the table of every workgroup's largest entry, which every workgroup holds without an
-      // exchange (filled where the row sums are gathered); one pass collects what the slice holds at or above it (a
-      // handful of entries per prompt); the workgroups that can hold candidates post them, everybody collects and
-      // ranks them itself: one exchange, no tree, and every workgroup ends up with the lists, so the result needs no
-      // broadcast either.  If the candidates do not fit (a workgroup's share of the slots, 64 posting workgroups,
-      // WARP_CAND entries in all: many equal values, or the large entries crowded into a few slices), every workgroup
-      // sees that in the same counts and the tree form below takes over.  The candidates' slots are a region per
-      // layer, written once per launch: only the workgroups that post are waited for, so a workgroup without
-      // candidates (and, in a later layer, without a piece of a row) may still be reading a layer's lines when the
-      // others have moved on.
-      bool fast = a.warp_fast && a.G > 1 && warp_pieces;      // uniform over the prompt's workgroups
-      bool fast_done = false;
-      lds_f64* const all_p = (lds_f64*)sh.gpart;        // [G] every workgroup's largest entry of p_beam ...
-      lds_f64* const all_q = (lds_f64*)sh.ptot;         // ... and of q_beam (-1: the workgroup holds nothing)
-      lds_f64* const stage = (lds_f64*)sh.tsum;         // [64][8] first lines of the workgroups that hold candidates
-      lds_i32* const wl = (lds_i32*)sh.A_idx;           // [64] those workgroups
-      lds_f64* const off_p = (lds_f64*)sh.A_cum_p;      // [64] where their candidates go in the joint lists ...
-      lds_f64* const off_q = (lds_f64*)sh.A_cum_q;      // ... (as doubles: small integers, exact)
-      const double slack = 1.0 - 1e-12;                 // (a workgroup's own largest entry may differ from the table's in the last bit)
-      unsigned long long tag_w = 0;
-      int nW = 0;
-      while (true) {
-        // ---- the bounds W_tau
-        if (fast) {
-          // The K-th largest of the workgroups' largest entries, or anything below it, is a lower bound of the joint's
-          // K-th entry (K entries of K different workgroups are at or above it).  One wave per model finds it;
-          // fewer than K values leave -1: everything passes, the counts below show it, and the tree form takes over.
-          tag_w = exchange_tag(nonce + epoch + 1);
-          epoch += 1;
-          if (tid < 2) sh.W_cnt[tid] = 0;
-          if (wave < 2) {
-            lds_f64* const arr = wave ? all_q : all_p;
-            // (as 32-bit patterns of the values rounded down to floats, which order like the values; the answer is
-            // built from the leading bit down: the largest pattern, its low 12 bits zero, that K values reach)
-            unsigned int key[4];
-#pragma unroll
-            for (int k = 0; k < 4; ++k) {
-              const int w = lane * 4 + k;
-              const double v = w < a.G ? arr[w] : -1.0;
-              key[k] = v > 0.0 ? (unsigned int)__float_as_int(__double2float_rd(v)) : 0u;
-            }
-            unsigned int prefix = 0;
-#pragma unroll 1
-            for (int b = 30; b >= 12; --b) {
-              const unsigned int cand = prefix | (1u << b);
-              const int cnt = __popcll(__ballot(key[0] >= cand)) + __popcll(__ballot(key[1] >= cand)) +
-                              __popcll(__ballot(key[2] >= cand)) + __popcll(__ballot(key[3] >= cand));
-              if (cnt >= K) prefix = cand;
-            }
-            const float kth = prefix ? __int_as_float((int)prefix) : -1.0f;    // fewer than K values: everything passes
-            if (lane == 0) sh.W_tau[wave] = (double)kth;
-          }
-          __syncthreads();
-          stamp(57);
-          // the workgroups that can hold candidates (by the table, with a little slack), in workgroup order
-          {
-            const double tp = sh.W_tau[0] * slack, tq = sh.W_tau[1] * slack;
-            const bool flagged = tid < a.G && (all_p[min(tid, 255)] >= tp || all_q[min(tid, 255)] >= tq);
-            const unsigned long long fm = __ballot(flagged);
-            if (lane == 0) sh.scan_w[wave] = (double)__popcll(fm);
-            __syncthreads();
-            int before = 0, all = 0;
-#pragma unroll
-            for (int w = 0; w < VL_WAVES; ++w) { const int cw = (int)sh.scan_w[w]; before += w < wave ? cw : 0; all += cw; }
-            const int pos = before + __popcll(fm & ((1ull << lane) - 1ull));
-            if (flagged && pos < 64) wl[pos] = tid;
-            nW = all;
-          }
-        } else {
-          // Tree form (1): a lower bound of the slice's K-th entry: the K-th largest of the maxima of 64 groups of
-          // eight threads (K of the slice's entries, from different groups, are at or above it)
-          double gp = tmax_p, gq = tmax_q;
-#pragma unroll
-          for (int off = 1; off <= 4; off <<= 1) { gp = fmax(gp, __shfl_xor(gp, off)); gq = fmax(gq, __shfl_xor(gq, off)); }
-          if ((lane & 7) == 0) { sh.tsum[wave * 8 + (lane >> 3)] = gp; sh.tsum[64 + wave * 8 + (lane >> 3)] = gq; }
-          if (tid < 2) sh.W_cnt[tid] = 0;
-          __syncthreads();
-          stamp(57);
-          // four threads count, for one of the 2 x 64 maxima, those ahead of it; the one with K - 1 ahead is the bound
-          const int m = tid >> 8, i = (tid >> 2) & 63, part = tid & 3;
-          const double v = sh.tsum[m * 64 + i];
-          int rank = 0;
-#pragma unroll
-          for (int j = 0; j < 16; ++j) {
-            const int c = part + 4 * j;
-            const double o = sh.tsum[m * 64 + c];
-            rank += (o > v || (o == v && c < i)) ? 1 : 0;
-          }
-          rank += __shfl_xor(rank, 1);
-          rank += __shfl_xor(rank, 2);
-          if (part == 0 && rank == K - 1) sh.W_tau[m] = v;    // -1 when fewer than K groups hold anything: everything passes
-        }
-        __syncthreads();
-        stamp(58);
-        collect_at_or_above();               // (2) everything at or above the bound is a candidate
-        __syncthreads();
-        // The candidates are ranked by value, equal values by index, and equal logits of a row must give equal
-        // values for that wherever in the row they sit (logits that came out of 16-bit arithmetic tie all the time).
-        // A slice entry is exp(z - piece maximum) x a factor of the piece: two roundings that differ from piece to
-        // piece.  So the few candidates get their value once more from the logit itself, in the one form that
-        // depends on the row only (the form the candidates of the accept tests use as well).  (Taken inside the
-        // pass above, by the thread that finds a candidate, it measured no faster, and slower with many candidates.)
-        auto canonical_values = [&]() {
-          const int n_p = min(sh.W_cnt[0], WARP_CAND), n_q = min(sh.W_cnt[1], WARP_CAND);
-          for (int t = tid; t < n_p + n_q; t += VL_BLOCK) {
-            const bool is_q = t >= n_p;
-            const int c = is_q ? t - n_p : t;
-            const int flat = is_q ? ciq[c] : cip[c];
-            if (flat < 0 || (long long)flat >= (long long)nI * V) continue;       // ("none": nothing to look up)
-            const int i = (int)div_floor(flat, V);
-            const int x = flat - i * V;
-            const float z = (is_q ? a.zq : a.zp)[(long long)sh.I_node[i] * V + x];
-            const double v = exp_nonpos((double)z - (is_q ? sh.max_q[i] : sh.max_p[i]), sh.exp_tab) * (is_q ? sh.sq[i] : sh.sp[i]);
-            if (is_q) cvq[c] = v; else cvp[c] = v;
-          }
-        };
-        canonical_values();
-        __syncthreads();
-        stamp(60);
-        if (fast) {
-          // ---- the candidates of the workgroups that can hold any: counts and the first three in the first line
-          // of the workgroup's slots (one round trip for nearly everything), the rest behind it
-          const int cp = sh.W_cnt[0], cq = sh.W_cnt[1];
-          const int room = (a.sl.b_w - 2) / 2;             // entries a workgroup can post
-          const bool post = all_p[g] >= sh.W_tau[0] * slack || all_q[g] >= sh.W_tau[1] * slack;
-          Slot* const wb_l = slots + a.sl.wb + (long long)(l - 1) * a.sl.wb_stride;     // this layer's region
-          Slot* const mine = wb_l + (long long)g * a.sl.b_w;
-          const int n_posted = cp + cq <= room ? cp + cq : 0;
-          if (post && tid < max(8, 2 + 2 * n_posted)) {
-            double payload;
-            if (tid < 2) payload = (double)(tid ? cq : cp);
-            else {
-              const int e = (tid - 2) >> 1;
-              if (e >= n_posted) payload = -1.0;
-              else payload = (tid & 1) ? (double)(e < cp ? cip[e] : ciq[e - cp]) : (e < cp ? cvp[e] : cvq[e - cp]);
-            }
-            slot_post(mine + tid, payload, tag_w);
-          }
-          const int n_poll = 8 * min(nW, 64);
-          for (int t = tid; t < n_poll; t += VL_BLOCK) {
-            double v = 0.0;
-            if (!slot_wait(wb_l + (long long)wl[t >> 3] * a.sl.b_w + (t & 7), tag_w, v, a.sync_limit)) give_up();
-            stage[t] = v;
-          }
-          __syncthreads();                                 // (also: everybody has posted from the candidate arrays)
-          if (sh.abort) return;
-          stamp(62);
-          if (wave < 2) {                                  // where every workgroup's candidates go, a wave per model
-            const bool in = lane < min(nW, 64);
-            const double mine_c = in ? stage[lane * 8 + wave] : 0.0;
-            const bool crowded = in && stage[lane * 8] + stage[lane * 8 + 1] > (double)room;
-            const double incl = wave_inclusive_scan(mine_c);
-            if (in) (wave ? off_q : off_p)[lane] = incl - mine_c;
-            const double total = __shfl(incl, 63);
-            const bool bad_w = __ballot(crowded) != 0ull || total > (double)WARP_CAND || nW > 64;
-            if (lane == 0) { sh.W_cnt[wave] = (int)total; sh.state[wave] = bad_w ? 1 : 0; }
-          }
-          __syncthreads();
-          const bool crowded_any = (sh.state[0] | sh.state[1]) != 0;
-          if (crowded_any) {                               // the same counts in every workgroup: all take the tree form
-            __syncthreads();                               // (the flags are read; the tree form writes them again)
-            if (!scaled) { scale_pass(); scaled = true; __syncthreads(); }
-            fast = false;
-            continue;
-          }
-          for (int t = tid; t < nW * 64; t += VL_BLOCK) {      // (room < 64)
-            const int j = t >> 6, e = t & 63;
-            const int cpj = (int)stage[j * 8], cqj = (int)stage[j * 8 + 1];
-            if (e >= cpj + cqj) continue;
-            double v, ix;
-            if (e < 3) { v = stage[j * 8 + 2 + 2 * e]; ix = stage[j * 8 + 3 + 2 * e]; }
-            else {
-              Slot* const at = wb_l + (long long)wl[j] * a.sl.b_w + 2 + 2 * e;
-              v = 0.0; ix = 0.0;
-              if (!slot_wait2(at, at + 1, tag_w, v, ix, a.sync_limit)) give_up();
-            }
-            if (e < cpj) { const int at_l = (int)off_p[j] + e; cvp[at_l] = v; cip[at_l] = (int)ix; }
-            else { const int at_l = (int)off_q[j] + e - cpj; cvq[at_l] = v; ciq[at_l] = (int)ix; }
-          }
-          __syncthreads();
-          if (sh.abort) return;
-          stamp(63);
-        } else if (sh.W_cnt[0] > WARP_CAND || sh.W_cnt[1] > WARP_CAND) {
-          // too many entries at or above the bound (many equal values, or a vocabulary of a few hundred tokens):
-          // every wave extracts the K first of its lanes' elements a rank at a time; those become the candidates
-          __syncthreads();                     // everybody has read the counts
-          double pv_prev = INFINITY, qv_prev = INFINITY;
-          int pi_prev = -1, qi_prev = -1;
-          for (int r = 0; r < K; ++r) {
-            double bp = -1.0, bq = -1.0;
-            int ip = INT_MAX, iq = INT_MAX;
-            for (long long j = tid; j < len; j += VL_BLOCK) {
-              const int fi = (int)(e_lo + j);
-              const double vp = ldp(j), vq = ldq(j);
-              if (cand_before(pv_prev, pi_prev, vp, fi) && cand_before(vp, fi, bp, ip)) { bp = vp; ip = fi; }
-              if (cand_before(qv_prev, qi_prev, vq, fi) && cand_before(vq, fi, bq, iq)) { bq = vq; iq = fi; }
-            }
-            wave_first(bp, ip);
-            wave_first(bq, iq);
-            if (lane == 0) { cvp[wave * K + r] = bp; cip[wave * K + r] = ip; cvq[wave * K + r] = bq; ciq[wave * K + r] = iq; }
-            pv_prev = bp; pi_prev = ip; qv_prev = bq; qi_prev = iq;
-          }
-          if (tid < 2) sh.W_cnt[tid] = VL_WAVES * K;
-          __syncthreads();
-          canonical_values();
-        }
-        rank_select();                         // barrier inside, after the counts are final
-        __syncthreads();
-        stamp(61);
-        fast_done = fast;
-        break;
+        const bool real = r < h.n;
+        cv[m * stride + e] = real ? exp_nonpos((double)x.z - top, sh.exp_tab) * scale : -1.0;
+        ci[m * stride + e] = real ? i * V + x.x : INT_MAX;
       }
-      unsigned long long tag_d = 0;
-      if (!fast_done) {
-      // (3) up the tree.  A list travels as 4K words (model, rank, value | index).
-      auto post_list = [&](Slot* where, unsigned long long tag) {
-        if (tid < 4 * K) {
-          const int m = tid / (2 * K), r = (tid % (2 * K)) >> 1;
-          const double payload = (tid & 1) ? (double)li[m * K + r] : lv[m * K + r];
-          slot_post(where + tid, payload, tag);
-        }
-      };
-      // n_src lists, b_w slots apart from `from` on, into gv / gi; up to four slots in flight per thread
-      auto collect_lists = [&](Slot* from, unsigned long long tag, int n_src) {
-        const int nS = n_src * 4 * K;
-        bool okc = true;
-        for (int s0 = tid; s0 < nS && okc; s0 += 4 * VL_BLOCK) {
-          bool have[4];
-          double val[4];
-#pragma unroll
-          for (int k = 0; k < 4; ++k) { have[k] = s0 + k * VL_BLOCK >= nS; val[k] = 0.0; }
-          long long t0 = 0;
-          for (int spin = 0;; ++spin) {
-            unsigned long long w0[4], w1[4];
-#pragma unroll
-            for (int k = 0; k < 4; ++k) {
-              w0[k] = 0; w1[k] = 0;
-              if (!have[k]) {
-                const int sk = s0 + k * VL_BLOCK;
-                Slot* sl = from + (long long)(sk / (4 * K)) * a.sl.b_w + sk % (4 * K);
-                w0[k] = __hip_atomic_load(&sl->w0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                w1[k] = __hip_atomic_load(&sl->w1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-              }
-            }
-#pragma unroll
-            for (int k = 0; k < 4; ++k)
-              if (!have[k] && (w0[k] ^ w1[k]) == tag) { val[k] = __longlong_as_double((long long)w0[k]); have[k] = true; }
-            if (have[0] && have[1] && have[2] && have[3]) break;
-            if (spin == 0) t0 = wall_clock64();
-            else if ((spin & 15) == 0 && wall_clock64() - t0 > a.sync_limit) { okc = false; break; }
-            __builtin_amdgcn_s_sleep(1);
-          }
-#pragma unroll
-          for (int k = 0; k < 4; ++k) {
-            const int sk = s0 + k * VL_BLOCK;
-            if (sk < nS && okc) {
-              const int src = sk / (4 * K), c = sk % (4 * K);
-              const int m = c / (2 * K), r = (c % (2 * K)) >> 1;
-              if (c & 1) gi[m * WARP_CAND + src * K + r] = (int)val[k];
-              else gv[m * WARP_CAND + src * K + r] = val[k];
-            }
-          }
-        }
-        if (!okc) give_up();
-      };
-      // The K first of n_src <= 16 collected lists, each in rank order: one or two levels of four-way merges.  In
-      // a merge an entry's rank is its own rank plus the numbers of entries of the three partner lists ahead of
-      // it (binary searches, side by side, branch-free); ranks K and beyond drop out.
-      auto merge_pass = [&](lds_f64* sv0, lds_i32* si0, lds_f64* sv1, lds_i32* si1, int n,
-                            lds_f64* dv0, lds_i32* di0, lds_f64* dv1, lds_i32* di1) {
-        for (int t = tid; t < 2 * n * K; t += VL_BLOCK) {
-          const int m = t >= n * K ? 1 : 0, e = t - m * n * K;
-          const int src = e / K, r = e - src * K;
-          lds_f64* const sv = m ? sv1 : sv0;
-          lds_i32* const si = m ? si1 : si0;
-          const double v = sv[e];
-          const int ix = si[e];
-          // entries of a partner list ahead of this one: the longest leading part of which all are (steps 32,
-          // 16, .. 1; a partner that does not exist has length 0 and is read at this entry's own list)
-          int po[3], len_j[3], cnt[3];
-#pragma unroll
-          for (int j = 0; j < 3; ++j) {
-            const int o = (src & ~3) + ((src + 1 + j) & 3);
-            po[j] = (o < n ? o : src) * K; len_j[j] = o < n ? K : 0; cnt[j] = 0;
-          }
-#pragma unroll
-          for (int step = 32; step >= 1; step >>= 1) {
-            if (step > K) continue;          // uniform: short lists need fewer halvings
-            double pv3[3];
-            int pi3[3];
-#pragma unroll
-            for (int j = 0; j < 3; ++j) {
-              const int at = min(cnt[j] + step - 1, K - 1);
-              pv3[j] = sv[po[j] + at]; pi3[j] = si[po[j] + at];
-            }
-#pragma unroll
-            for (int j = 0; j < 3; ++j)
-              cnt[j] += ((cnt[j] + step - 1 < len_j[j]) & cand_before(pv3[j], pi3[j], v, ix)) ? step : 0;
-          }
-          const int rank = r + cnt[0] + cnt[1] + cnt[2];
-          if (rank < K && ix != INT_MAX) {
-            (m ? dv1 : dv0)[(src >> 2) * K + rank] = v;
-            (m ? di1 : di0)[(src >> 2) * K + rank] = ix;
-          }
-        }
-      };
-      auto fill_none = [&](lds_f64* v0, lds_i32* i0, lds_f64* v1, lds_i32* i1, int cnt) {
-        for (int t = tid; t < 2 * cnt; t += VL_BLOCK) {
-          const int m = t >= cnt ? 1 : 0, e = t - m * cnt;
-          (m ? v1 : v0)[e] = -1.0;
-          (m ? i1 : i0)[e] = INT_MAX;
-        }
-      };
-      // gv / gi -> lv / li.  The candidate arrays (first 4K entries per model) must hold "none" on entry: the
-      // caller fills them before it collects, so that the barrier after the collection covers both.
-      auto merge_lists = [&](int n) {
-        if (n <= 4) {
-          fill_none(lv, li, lv + K, li + K, K);
-          __syncthreads();
-          merge_pass(gv, gi, gv + WARP_CAND, gi + WARP_CAND, n, lv, li, lv + K, li + K);
-          __syncthreads();
-          return;
-        }
-        merge_pass(gv, gi, gv + WARP_CAND, gi + WARP_CAND, n, cvp, cip, cvq, ciq);
-        fill_none(lv, li, lv + K, li + K, K);
-        __syncthreads();
-        merge_pass(cvp, cip, cvq, ciq, (n + 3) >> 2, lv, li, lv + K, li + K);
-        __syncthreads();
-      };
-      if (a.G > 1) {
-        const int first = g - g % WARP_GROUP;
-        const int n_mem = min(WARP_GROUP, a.G - first);
-        const int n_groups = (a.G + WARP_GROUP - 1) / WARP_GROUP;
-        const unsigned long long tag_b = exchange_tag(nonce + epoch + 1), tag_c = exchange_tag(nonce + epoch + 2);
-        tag_d = exchange_tag(nonce + epoch + 3);
-        epoch += 3;
-        post_list(slots + a.sl.b + (long long)g * a.sl.b_w, tag_b);
-        if (g == first) {                    // the group's first workgroup merges the group's lists
-          fill_none(cvp, cip, cvq, ciq, 4 * K);
-          collect_lists(slots + a.sl.b + (long long)first * a.sl.b_w, tag_b, n_mem);
-          __syncthreads();
-          stamp(62);
-          if (sh.abort) return;
-          merge_lists(n_mem);
-          stamp(63);
-          if (n_groups > 1) post_list(slots + a.sl.c + (long long)(g / WARP_GROUP) * a.sl.b_w, tag_c);
-        }
-        if (g == 0 && n_groups > 1) {        // the prompt's first workgroup merges the groups' lists
-          fill_none(cvp, cip, cvq, ciq, 4 * K);
-          collect_lists(slots + a.sl.c, tag_c, n_groups);
-          __syncthreads();
-          stamp(64);
-          if (sh.abort) return;
-          merge_lists(n_groups);
-        }
-      }
-      }   // (tree form)
-      stamp(65);
-      if (g == 0 || fast_done) {
-        if (wave == 0) {
-          // (4) top-p on the kept entries (rank order: the shortest leading part whose share exceeds top_p) and
-          // renormalisation; lanes 0..31 carry p_beam's list, lanes 32..63 q_beam's, one rank each.  The running
-          // sums add the entries one by one in rank order.
-          const int r = lane & 31, half = lane & 32;
-          const bool is_q = half != 0;
-          const int ix = r < K ? li[(is_q ? K : 0) + r] : INT_MAX;
-          const bool real = ix != INT_MAX;
-          const double v = real ? lv[(is_q ? K : 0) + r] : 0.0;
-          double cum = 0.0;
-          int partner = -1;                  // lane of the other list's entry with the same index
-          {
-            // (the lists are read from the LDS, every lane of a half the same word: one read serves 32 lanes; lane
-            // reads of the other lanes' registers cost a scalar round trip each)
-            const int own = is_q ? K : 0, oth = is_q ? 0 : K;
-            for (int c = 0; c < K; ++c) {
-              const int i_own = li[own + c], i_oth = li[oth + c];
-              const double v_own = i_own != INT_MAX ? lv[own + c] : 0.0;
-              if (c <= r) cum += v_own;
-              if (i_oth == ix) partner = (is_q ? 0 : 32) + c;
-            }
-          }
-          const unsigned long long real_m = __ballot(real);
-          const int n = __popcll(is_q ? (real_m >> 32) : (real_m & 0xffffffffull));     // real entries lead the list
-          int keep = n;
-          if (a.top_p < 1.0f) {
-            const double mass = __shfl(cum, half + max(n - 1, 0));
-            const unsigned long long over_m = __ballot(real && cum / mass > (double)a.top_p);
-            const unsigned int mine = (unsigned int)(is_q ? (over_m >> 32) : (over_m & 0xffffffffull));
-            if (mine) keep = __ffs((int)mine);
-          }
-          const double z = __shfl(cum, half + max(keep - 1, 0));
-          const bool kept = r < keep;
-          const double w = kept ? v / z : 0.0;
-          // (5) union of the two supports, ascending flat index: a q entry whose index p_beam also keeps is
-          // carried by the p entry
-          const double w_partner = __shfl(w, max(partner, 0));       // 0 when the partner was cut
-          const int kept_partner = __shfl((int)kept, max(partner, 0));
-          const bool both = real && partner >= 0 && kept_partner;
-          const double other = (both && !is_q) ? w_partner : 0.0;
-          const bool valid = kept && !(is_q && both);
-          int rank = 0;
-          {
-            // the valid entries' indices side by side in the LDS (lane c: p_beam's list, 32 + c: q_beam's)
-            lds_i32* const vx = (lds_i32*)sh.A_idx;
-            vx[lane] = valid ? ix : INT_MAX;
-            wave_lds_fence();
-            for (int c = 0; c < K; ++c) rank += (vx[c] < ix ? 1 : 0) + (vx[32 + c] < ix ? 1 : 0);
-          }
-          if (valid) { sh.U_idx[rank] = ix; sh.U_p[rank] = is_q ? 0.0 : w; sh.U_q[rank] = is_q ? w : other; }
-          const unsigned long long vm = __ballot(valid);
-          if (lane == 0) sh.nU = __popcll(vm);
-        }
-        __syncthreads();
-        if (!fast_done && a.G > 1 && tid < 1 + 6 * K) {          // (6) ... and down again: the count, then (index, p, q) of at most 2K entries
-          const int u = (tid - 1) / 3, f = (tid - 1) % 3;
-          double payload = 0.0;
-          if (tid == 0) payload = (double)sh.nU;
-          else if (u < sh.nU) payload = f == 0 ? (double)sh.U_idx[u] : (f == 1 ? sh.U_p[u] : sh.U_q[u]);
-          slot_post(slots + a.sl.d + tid, payload, tag_d);
+      if (tid < 2 * K) { lv[tid] = -1.0; li[tid] = INT_MAX; }      // ("none", which sorts last)
+      if (tid < 2 && stride > n_cand) cv[tid * stride + n_cand] = -1.0;
+      __syncthreads();
+      stamp(60);
+      // Ranks by counting the entries ahead, PT threads each (of equal values the one in front has the lower index: rows are in
+      // index order, and so are equal logits of a row).  A single row's list has the ranks already.  (Merging the rows' lists
+      // entry by entry, a row per lane, took 0.24 us an entry.)
+      if (nI == 1) {
+        for (int t = tid; t < 2 * K; t += VL_BLOCK) {
+          const int m = t >= K ? 1 : 0, r = t - m * K;
+          if (cv[m * stride + r] >= 0.0) { lv[t] = cv[m * stride + r]; li[t] = ci[m * stride + r]; }
         }
       } else {
-        if (tid < 1 + 6 * K) {
-          double v = 0.0;
-          if (!slot_wait(slots + a.sl.d + tid, tag_d, v, a.sync_limit)) give_up();
-          const int u = (tid - 1) / 3, f = (tid - 1) % 3;
-          if (tid == 0) sh.nU = (int)v;
-          else if (f == 0) sh.U_idx[u] = (int)v;
-          else if (f == 1) sh.U_p[u] = v;
-          else sh.U_q[u] = v;
+        int PT = 16;
+        while (PT > 1 && PT * 2 * n_cand > VL_BLOCK) PT >>= 1;
+        const int part = tid & (PT - 1);
+        for (int t0 = 0; t0 < 2 * n_cand; t0 += VL_BLOCK / PT) {
+          const int t = t0 + tid / PT;
+          const bool has = t < 2 * n_cand;
+          const int m = has && t >= n_cand ? 1 : 0, e = has ? t - m * n_cand : 0;
+          const double v = cv[m * stride + e];
+          int rank = 0;
+          if (has && v >= 0.0) {
+            const lds_f64x2* const all = (const lds_f64x2*)(cv + m * stride);
+#pragma unroll 8
+            for (int c = part; c < stride / 2; c += PT) {
+              const f64x2 o = all[c];
+              rank += ((o.x > v) | ((o.x == v) & (2 * c < e))) + ((o.y > v) | ((o.y == v) & (2 * c + 1 < e)));
+            }
+          }
+          for (int off = 1; off < PT; off <<= 1) rank += __shfl_xor(rank, off);
+          if (has && v >= 0.0 && part == 0 && rank < K) { lv[m * K + rank] = v; li[m * K + rank] = ci[m * stride + e]; }
         }
-        __syncthreads();
-        if (sh.abort) return;
       }
+      __syncthreads();
+      stamp(61);
+      if (wave == 0) {
+        // top-p on the kept entries (rank order: the shortest leading part whose share exceeds top_p) and
+        // renormalisation; lanes 0..31 carry p_beam's list, lanes 32..63 q_beam's, one rank each.  The running
+        // sums add the entries one by one in rank order.
+        const int r = lane & 31, half = lane & 32;
+        const bool is_q = half != 0;
+        const int ix = r < K ? li[(is_q ? K : 0) + r] : INT_MAX;
+        const bool real = ix != INT_MAX;
+        const double v = real ? lv[(is_q ? K : 0) + r] : 0.0;
+        double cum = 0.0;
+        int partner = -1;                  // lane of the other list's entry with the same index
+        {
+          // (the lists are read from the LDS, every lane of a half the same word: one read serves 32 lanes; lane
+          // reads of the other lanes' registers cost a scalar round trip each)
+          const int own = is_q ? K : 0, oth = is_q ? 0 : K;
+          for (int c = 0; c < K; ++c) {
+            const int i_own = li[own + c], i_oth = li[oth + c];
+            const double v_own = i_own != INT_MAX ? lv[own + c] : 0.0;
+            if (c <= r) cum += v_own;
+            if (i_oth == ix) partner = (is_q ? 0 : 32) + c;
+          }
+        }
+        const unsigned long long real_m = __ballot(real);
+        const int n = __popcll(is_q ? (real_m >> 32) : (real_m & 0xffffffffull));     // real entries lead the list
+        int keep = n;
+        if (a.top_p < 1.0f) {
+          const double mass = __shfl(cum, half + max(n - 1, 0));
+          const unsigned long long over_m = __ballot(real && cum / mass > (double)a.top_p);
+          const unsigned int mine = (unsigned int)(is_q ? (over_m >> 32) : (over_m & 0xffffffffull));
+          if (mine) keep = __ffs((int)mine);
+        }
+        const double z = __shfl(cum, half + max(keep - 1, 0));
+        const bool kept = r < keep;
+        const double w = kept ? v / z : 0.0;
+        // union of the two supports, ascending flat index: a q entry whose index p_beam also keeps is
+        // carried by the p entry
+        const double w_partner = __shfl(w, max(partner, 0));       // 0 when the partner was cut
+        const int kept_partner = __shfl((int)kept, max(partner, 0));
+        const bool both = real && partner >= 0 && kept_partner;
+        const double other = (both && !is_q) ? w_partner : 0.0;
+        const bool valid = kept && !(is_q && both);
+        int rank = 0;
+        {
+          // the valid entries' indices side by side in the LDS (lane c: p_beam's list, 32 + c: q_beam's)
+          lds_i32* const vx = (lds_i32*)sh.A_idx;
+          vx[lane] = valid ? ix : INT_MAX;
+          wave_lds_fence();
+          for (int c = 0; c < K; ++c) rank += (vx[c] < ix ? 1 : 0) + (vx[32 + c] < ix ? 1 : 0);
+        }
+        if (valid) { sh.U_idx[rank] = ix; sh.U_p[rank] = is_q ? 0.0 : w; sh.U_q[rank] = is_q ? w : other; }
+        const unsigned long long vm = __ballot(valid);
+        if (lane == 0) sh.nU = __popcll(vm);
+        }
+      __syncthreads();
     }
     stamp(25);
     // p_beam and q_beam at every candidate's (parent beam, token)
@@ -2085,41 +1654,37 @@ void verify_layers_kernel(LayersArgs a) {
       __syncthreads();
       int Wt = 0;
       if (M < 64) {
-        // up to 63 drafts (every forest of the paper's shapes): the table fits one wave, lane m = row m, and the
-        // steps are ordered by wavefront fences instead of workgroup barriers.  Same sums in the same order as the
-        // general form below.
+        // up to 63 drafts (every forest of the paper's shapes): the table fits one wave, lane m = row m, and everything is
+        // in its registers: the other rows' values come by lane reads and by moving a column a lane at a time.  Same sums
+        // in the same order as the general form below.  (With the values in the LDS, every term a dependent read: 5.4 us
+        // for 12 drafts and a few columns, now 2.)
         if (wave == 0) {
           const int m = lane;
-          if (m >= 1 && m <= M) {
-            double alpha = 1.0;            // no residual mass left: accepted with certainty
-            if (m + 1 <= kdone && sh.FF[m] > 0.0) alpha = 1.0 - sh.FF[m + 1] / sh.FF[m];
-            sh.u.w.alpha[m] = alpha;
+          const bool row = m >= 1 && m <= M;
+          double alpha = 1.0;              // no residual mass left: accepted with certainty
+          if (row && m + 1 <= kdone && sh.FF[m] > 0.0) alpha = 1.0 - sh.FF[m + 1] / sh.FF[m];
+          // first[m] = alpha_m prod_{j<m} (1 - alpha_j); Pa = P(m,0) = prod_{j<=m} (1 - alpha_j)
+          double first = alpha, Pa = 1.0;
+          const double rest = 1.0 - alpha;
+          for (int j = 1; j <= M; ++j) {
+            const double rj = readlane_f64(rest, j);
+            if (j < m) first *= rj;
+            if (j <= m) Pa *= rj;
           }
-          wave_lds_fence();
-          if (m >= 1 && m <= M) {
-            double f = sh.u.w.alpha[m];
-            for (int j = 1; j < m; ++j) f *= (1.0 - sh.u.w.alpha[j]);
-            sh.u.w.first[m] = f;
-          }
-          if (m <= M) {
-            double none = 1.0;
-            for (int j = 1; j <= m; ++j) none *= (1.0 - sh.u.w.alpha[j]);
-            sh.Pa[m] = none;
-          }
-          wave_lds_fence();
           double below = 0.0;              // sum_{k<K} P(M,k)
           const int Kmax = min(M, a.W_cap);
           for (int K = 1; K <= Kmax; ++K) {
-            below += sh.Pa[M];             // column K-1 is in Pa (uniform over the wave)
+            below += readlane_f64(Pa, M);  // Pa holds column K-1
             if (!(1.0 - below >= thr)) break;
             Wt = K;
             if (K == Kmax) break;
-            double tot = 0.0;
-            if (m <= M && m >= K)
-              for (int i = 1; i <= m; ++i) tot += sh.u.w.first[i] * ((m - i >= K - 1) ? sh.Pa[m - i] : 0.0);
-            wave_lds_fence();              // everybody has read column K-1
-            if (m <= M) sh.Pa[m] = tot;
-            wave_lds_fence();
+            // column K from column K-1: P(m,K) = sum_{i=1..m} first[i] P(m-i,K-1), zero for m < K (and P(m,K-1) for m < K-1)
+            double tot = 0.0, moved = m >= K - 1 ? Pa : 0.0;
+            for (int i = 1; i <= M; ++i) {
+              moved = lane_from_below(moved);              // P(m-i,K-1); 0 from beyond row 0
+              tot += readlane_f64(first, i) * moved;
+            }
+            Pa = m >= K && m <= M ? tot : 0.0;
           }
           if (lane == 0) sh.found = Wt;
         }
@@ -2303,18 +1868,24 @@ void verify_layers_kernel(LayersArgs a) {
       // the weights live on the short list (ascending flat index) that every workgroup holds: one wave scans it, the
       // first workgroup writes the samples
       __syncthreads();           // the rows' log-sum-exps (another wave's work since the fold) are in place
-      if (wave == 0) {
+      if (wave == 0 && g == 0) {
         const int nU = sh.nU;
         const double wp = lane < nU ? sh.U_p[lane] : 0.0, wr = lane < nU ? fmax(wp - d_c * sh.U_q[lane], 0.0) : 0.0;
-        for (int j = 0; j < d_cnt; ++j) {
-          const double w = d_resid && j == 0 ? wr : wp;
-          const double incl = wave_inclusive_scan(w);
-          const unsigned long long mass = __ballot(w > 0.0);
-          const double target = (double)__shfl(d_u, j) * __shfl(incl, 63);
-          const unsigned long long above = __ballot(incl > target);
-          // the first entry whose inclusive prefix exceeds the target (rounding: the last one with mass)
-          const int pl_ = above ? (int)__ffsll((long long)above) - 1 : (mass ? 63 - __clzll((long long)mass) : 0);
-          if (g == 0 && lane == pl_) emit(nU > 0 ? sh.U_idx[pl_] : 0, j);       // (no entry at all, reported as a fault: stay in bounds)
+        lds_f64* const pre = (lds_f64*)sh.tsum;          // inclusive prefixes: p_beam's, then the residual's
+        pre[lane] = wave_inclusive_scan(wp);
+        pre[64 + lane] = wave_inclusive_scan(wr);
+        const unsigned long long mass_p = __ballot(wp > 0.0), mass_r = __ballot(wr > 0.0);
+        wave_lds_fence();
+        if (lane < d_cnt) {                              // a draw per lane: the first entry whose prefix exceeds the target
+          const bool resid = d_resid && lane == 0;
+          lds_f64* const tab = pre + (resid ? 64 : 0);
+          const unsigned long long mass = resid ? mass_r : mass_p;
+          const double target = (double)d_u * tab[63];
+          int at = 0;
+#pragma unroll
+          for (int step = 32; step >= 1; step >>= 1) at += tab[at + step - 1] > target ? 0 : step;
+          if (!(tab[at] > target)) at = mass ? 63 - __clzll((long long)mass) : 0;      // (rounding: the last one with mass)
+          emit(nU > 0 ? sh.U_idx[at] : 0, lane);         // (no entry at all, reported as a fault: stay in bounds)
         }
       }
       break;
@@ -2470,7 +2041,7 @@ void verify_layers_kernel(LayersArgs a) {
       if (lane == 0) excl = 0.0;
 #pragma unroll
       for (int k = 0; k < 4; ++k) if (4 * lane + k < a.G) tab[4 * lane + k] = excl + v[k];
-      if (lane == 0) sh.W_cnt[wave] = nz;
+      if (lane == 0) sh.last_mass[wave] = nz;
     }
     __syncthreads();
     stamp(71);
@@ -2483,7 +2054,7 @@ void verify_layers_kernel(LayersArgs a) {
       // owner: the first workgroup whose inclusive prefix exceeds the target (rounding: the last one with mass)
       int lo = 0, hi = a.G;
       while (lo < hi) { const int mid = (lo + hi) >> 1; if (tab[mid] > target) hi = mid; else lo = mid + 1; }
-      const int owner = lo < a.G ? lo : max(sh.W_cnt[resid ? 0 : 1], 0);
+      const int owner = lo < a.G ? lo : max(sh.last_mass[resid ? 0 : 1], 0);
       if (owner == g) sh.S_tmp[atomicAdd(&sh.counter, 1)] = tid;
     }
     __syncthreads();
@@ -2616,15 +2187,12 @@ const DeviceLimits& device_limits() {
                               hipFuncAttributeMaxDynamicSharedMemorySize, VL_DYN_LDS_BYTES);
     (void)hipFuncSetAttribute(reinterpret_cast<const void*>(verify_layers_kernel<false, NODE_CAP_SMALL>),
                               hipFuncAttributeMaxDynamicSharedMemorySize, VL_DYN_LDS_BYTES_SMALL);
-    int nb = 0, nb2 = 0, nb3 = 0;
+    int nb = 0, nb3 = 0;
     if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, verify_layers_kernel<false, NODE_CAP>, VL_BLOCK, VL_DYN_LDS_BYTES) != hipSuccess || nb < 1)
       nb = 1;
-    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb2, verify_layers_kernel<true, NODE_CAP>, VL_BLOCK, VL_DYN_LDS_BYTES) != hipSuccess || nb2 < 1)
-      nb2 = 1;
     if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb3, verify_layers_kernel<false, NODE_CAP_SMALL>, VL_BLOCK, VL_DYN_LDS_BYTES_SMALL) != hipSuccess || nb3 < 1)
       nb3 = 1;
-    if (nb3 < nb2) nb2 = nb3;
-    lim.blocks_per_cu = nb < nb2 ? nb : nb2;
+    lim.blocks_per_cu = nb < nb3 ? nb : nb3;
     (void)hipGetLastError();
   });
   return lim;
@@ -2658,37 +2226,33 @@ int layer_workgroups(const dsbd_forest* f, int V, const dsbd_params* p, bool spa
   // a unit on its own, over the 35 us that the shortest walks take), at most a quarter of the device, as long as the
   // coarser slices fit the LDS.  A lone prompt loses next to nothing by it (its exchanges get shorter as its passes get
   // longer).  With several prompts it takes 90 MB of logits that would otherwise stand behind the layers (13 us), and
-  // 300 MB where the slices outgrow the LDS, up to twice its size (four times for warped joints, which are read less
-  // often).  The dynamic width on unwarped joints passes over the slices for every entry of its chains: there a row is
+  // 300 MB where the slices outgrow the LDS, up to twice its size.  The dynamic width on unwarped joints passes over the slices for every entry of its chains: there a row is
   // never cut into less than 85 % of the pieces.  Measured, verification in us with 0 / a quarter of the units kept:
-  // 8 beams, 248 nodes x 128256 137 / 109 (t = 0.7 310 / 286, t = 0.9 and top_k 10 202 / 162), 64 nodes 73 / 62; 2 prompts of 8
+  // 8 beams, 248 nodes x 128256 137 / 109 (t = 0.7 310 / 286), 64 nodes 73 / 62; 2 prompts of 8
   // beams, 496 nodes x 32000 94 / 85, x 128256 199 / 181; 4 prompts, 992 nodes x 32000 120 / 111 (t = 0.7 304 / 341, an eighth
-  // 316; t = 0.9 and top_k 10 140 / 118), 256 nodes 78 / 79; 16 prompts of 4 beams, 1984 nodes x 16000 105 / 97 (t = 0.7 248 /
+  // 316), 256 nodes 78 / 79; 16 prompts of 4 beams, 1984 nodes x 16000 105 / 97 (t = 0.7 248 /
   // 308), 341 nodes x 32000 88 / 112; 3 prompts, 103 nodes x 50273, t = 0.7: 84 / 78 / 72 / 66 workgroups each 104 / 104 / 98 / 99.
   {
     const long long bytes = 2LL * f->n_nodes * V * 4;
     long long keep = (bytes + (1 << 20) - 1) / (1 << 20);
     if (keep > lim.cus / 4) keep = lim.cus / 4;
     const int W = f->max_prompt_trees, P = f->n_prompts;
-    const bool warped = p->top_k > 0, chains = p->t >= 0.0f && !warped;
+    const bool chains = p->t >= 0.0f;
     int Gk = P > 0 ? (int)((lim.cus - keep) / P) : 0;
     if (P > 1 && chains) Gk = std::max(Gk, (G / W * 85 + 99) / 100 * W);
     if (Gk >= W && Gk < G) {
       const long long slice = slice_cut(W, V, Gk).len, room = lds_slice_entries(f, p);
-      if (P == 1 ? slice <= room : chains || bytes >= 300000000LL ? slice <= (warped ? 4 : 2) * room : bytes >= 90000000LL && slice <= room) G = Gk;
+      if (P == 1 ? slice <= room : chains || bytes >= 300000000LL ? slice <= 2 * room : bytes >= 90000000LL && slice <= room) G = Gk;
     }
   }
   // (sized by the joint of the input beams, which is what a fixed width keeps every layer at: shorter slices make shorter
   // passes and more partners longer exchanges.  Measured, call in us at 16 / 32 / 48 / 64 / 96 / 128 / 160 / 192 workgroups
   // of a prompt: 4 x 32000 joint entries 49.4 / 38.1 / 36.1 / 36.0 / 36.6 / 36.3 / 37.6 / 37.8; 8 x 32000: 99.8 / 65.8 / 50.1 /
-  // 48.2 / 48.0 / 48.1 / 48.3 / 48.4; 5 x 128256 warped: 185 / 149 / 112 / 106.8 / 103.6 / 103.5 / 104.0 / 106.5; 8 x 128256:
+  // 48.2 / 48.0 / 48.1 / 48.3 / 48.4; 8 x 128256:
   // 516 / 303 / 238 / 181 / 154 / 121 / 116 / 108.  5 x 128256 plain: 324 / 201 / 140 /
   // 121 / 81 / 77 / 73 / 75.  So 2000 entries per workgroup up to 128 of them, 4000 beyond.)
   long long by_work = (joint + 1999) / 2000;
   if (by_work > 128) by_work = std::max(128LL, (joint + 3999) / 4000);
-  // warping wants enough pieces for its one-level selection (4 x 32000, top_k 32: 64 workgroups 76 us, 128: 60)
-  if (p->top_k > 0 && by_work < 4 * p->top_k + f->max_prompt_trees && joint >= 128LL * (4 * p->top_k + f->max_prompt_trees))
-    by_work = 4 * p->top_k + f->max_prompt_trees;
   if (G > by_work) G = (int)by_work;
   // (workgroups beyond a multiple of the rows hold no piece but take part in every exchange)
   if (f->max_prompt_trees > 0 && G > f->max_prompt_trees) G -= G % f->max_prompt_trees;
@@ -2717,14 +2281,6 @@ VerifyPlan plan_with_workgroups(const dsbd_forest* f, int V, const dsbd_params* 
     sl.x[1] = off; off += G * LINE_SLOTS;
     sl.r_w = up8(4 * pl.I_cap);
     sl.r = off; sl.r_stride = G * sl.r_w; off += layers * sl.r_stride;
-    sl.b = sl.c = sl.d = sl.wb = off; sl.b_w = 0; sl.wb_stride = 0;
-    if (p->top_k > 0) {
-      sl.b_w = up8(4 * p->top_k);
-      sl.b = off; off += G * sl.b_w;
-      sl.c = off; off += (G + WARP_GROUP - 1) / WARP_GROUP * sl.b_w;
-      sl.d = off; off += up8(WARP_RESULT_SLOTS);
-      sl.wb = off; sl.wb_stride = G * sl.b_w; off += layers * sl.wb_stride;
-    }
     sl.acc = off; off += 2 * NACC * LINE_SLOTS;
     sl.acc0 = off; off += up8(2 * NACC);
     sl.prompt_stride = off;
@@ -2738,11 +2294,7 @@ VerifyPlan plan_with_workgroups(const dsbd_forest* f, int V, const dsbd_params* 
   need = (need + 1) & ~1LL;
   pl.slice_cap = need;
   pl.lds_elems = (int)(need < cap ? need : cap);
-  // warping: the candidate lists of a merge (2 x WARP_CAND values and indices) sit in the dynamic LDS
-  if (p->top_k > 0 && pl.lds_elems < (3 * WARP_CAND + 1) / 2) pl.lds_elems = (3 * WARP_CAND + 1) / 2;
-  pl.lds_bytes = (size_t)pl.lds_elems * (alias ? 8 : 16);
-  if (p->top_k > 0 && pl.lds_bytes < (size_t)((3 * WARP_CAND + 1) / 2) * 16) pl.lds_bytes = (size_t)((3 * WARP_CAND + 1) / 2) * 16;
-  pl.lds_bytes = (pl.lds_bytes + 15) & ~(size_t)15;
+  pl.lds_bytes = ((size_t)pl.lds_elems * (alias ? 8 : 16) + 15) & ~(size_t)15;
   return pl;
 }
 
@@ -2756,6 +2308,37 @@ size_t carve_verify(WorkspaceCarver& ws, const dsbd_forest* f, const VerifyPlan&
   *qb = ws.take<double>((size_t)pl.group * pl.G * (size_t)pl.slice_cap);
   *red = ws.take<double>(P * (size_t)pl.sl.prompt_stride * 2);
   return ws.total();
+}
+
+// Warped joints: one workgroup walks a prompt's layers from the rows' records.
+VerifyPlan warped_plan(const dsbd_forest* f, const dsbd_params* p) {
+  VerifyPlan pl = {};
+  pl.I_cap = p->W_cap > f->max_prompt_trees ? p->W_cap : f->max_prompt_trees;
+  pl.G = 1;
+  pl.group = f->n_prompts;
+  pl.lds_bytes = dsbd_align_up((size_t)2 * (pl.I_cap * p->top_k + 1) * (sizeof(double) + sizeof(int)), 16);     // a layer's candidates
+  return pl;
+}
+
+size_t carve_warped(WorkspaceCarver& ws, const dsbd_forest* f, const RowsPlan& rp, RowsArgs* ra) {
+  const size_t rows = (size_t)f->n_nodes * 2;
+  ws.take<long long>(512);                 // timeline of the layer kernel
+  const bool in_records = rp.compact && rp.nchunk == 1;
+  ra->part = ws.take<double2>(in_records ? 0 : rows * rp.nchunk);
+  if (in_records) ra->part = nullptr;
+  ra->sub = ws.take<float>(in_records ? 0 : rows * rp.nchunk * VR_SUBS);
+  if (in_records) ra->sub = nullptr;
+  ra->rec = ws.take<char>(rows * (size_t)rp.rec_stride);
+  return ws.total();
+}
+
+// Records with logits, unless they would push the workspace above the 32 MiB of dsbd_verify_forest_static and the tokens fit
+// 16 bits (large batches over vocabularies of a few hundred tokens): a dependent load per layer more.
+RowsPlan warped_rows(const dsbd_forest* f, int V, int K) {
+  WorkspaceCarver ws(nullptr);
+  RowsArgs ra;
+  const RowsPlan plain = rows_plan(V, K, 0);
+  return V <= 65536 && carve_warped(ws, f, plain, &ra) + 256 > (size_t)DSBD_STATIC_SCRATCH_BYTES ? rows_plan(V, K, V <= 256 ? 1 : 2) : plain;
 }
 
 size_t verify_workspace(const dsbd_forest* f, const VerifyPlan& pl) {
@@ -2839,6 +2422,11 @@ __global__ void bump_replay_count_kernel(unsigned long long* count) { *count += 
 
 extern "C" size_t dsbd_verify_forest_workspace_bytes(const dsbd_forest* f, int32_t V, const dsbd_params* p) {
   if (check_verify(f, V, p) != DSBD_OK) return 0;
+  if (p->top_k > 0) {
+    WorkspaceCarver ws(nullptr);
+    RowsArgs ra;
+    return carve_warped(ws, f, warped_rows(f, V, p->top_k), &ra) + 256;
+  }
   return verify_workspace(f, make_verify_plan(f, V, p));
 }
 
@@ -2870,17 +2458,21 @@ int32_t verify_impl(const dsbd_forest* f, const dsbd_verify_in* in, const dsbd_p
   const DsbdKnobs& knobs = dsbd_knobs();
   // the same arrays given for both models: q_beam is p_beam and is kept, and computed, once (in the same workspace)
   const bool alias = in->logits_target == in->logits_draft && in->beam_logp_target == in->beam_logp_draft;
-  const VerifyPlan pl = make_verify_plan(f, in->V, p, alias);
-  if (workspace_bytes < verify_workspace(f, pl)) return DSBD_ERR_WORKSPACE;
+  const bool warped = p->top_k > 0;
+  const VerifyPlan pl = warped ? warped_plan(f, p) : make_verify_plan(f, in->V, p, alias);
+  if (workspace_bytes < (warped ? dsbd_verify_forest_workspace_bytes(f, in->V, p) : verify_workspace(f, pl))) return DSBD_ERR_WORKSPACE;
   hipStream_t stream = static_cast<hipStream_t>(stream_);
 
   char* wbase = reinterpret_cast<char*>(dsbd_align_up(reinterpret_cast<uintptr_t>(workspace), 256));
   WorkspaceCarver ws(wbase);
-  double *pb, *qb, *red;
-  carve_verify(ws, f, pl, &pb, &qb, &red);
+  double *pb = nullptr, *qb = nullptr, *red = nullptr;
+  RowsArgs ra;
+  const RowsPlan rp = warped_rows(f, in->V, p->top_k);
+  if (warped) carve_warped(ws, f, rp, &ra); else carve_verify(ws, f, pl, &pb, &qb, &red);
 
   const bool want_stats = out->lse_target || out->lse_draft || out->node_logp_target || out->node_logp_draft;
-  LaunchOrder* const state = launch_order_of_current_device(may_create);
+  // (the workgroups of warped layers wait for nobody: they need no order among launches)
+  LaunchOrder* const state = warped ? nullptr : launch_order_of_current_device(may_create);
   std::unique_lock<std::mutex> enqueue_lock;
   if (state) enqueue_lock = std::unique_lock<std::mutex>(state->enqueue);
   // a stream under capture takes no part in the ordering of layer launches (an event recorded into a capture cannot
@@ -2912,7 +2504,8 @@ int32_t verify_impl(const dsbd_forest* f, const dsbd_verify_in* in, const dsbd_p
   // workspace can pass for a value of this one, so the slots need no clearing.
   la.nonce = (g_launch_counter.fetch_add(1, std::memory_order_relaxed) + 1) << 24;
   la.replay = nullptr;
-  if (capturing) {
+  la.rec = nullptr; la.rec_stride = 0; la.rec_compact = 0;
+  if (capturing && !warped) {
     unsigned long long* const count = reinterpret_cast<unsigned long long*>(wbase + 512 * sizeof(long long));
     hipLaunchKernelGGL(bump_replay_count_kernel, dim3(1), dim3(1), 0, stream, count);
     la.replay = count;
@@ -2920,7 +2513,6 @@ int32_t verify_impl(const dsbd_forest* f, const dsbd_verify_in* in, const dsbd_p
   la.G = pl.G; la.I_cap = pl.I_cap; la.sl = pl.sl; la.lds_elems = pl.lds_elems; la.fault = fault;
   la.lds_slice = pl.lds_elems;
   la.alias = alias ? 1 : 0;
-  la.warp_fast = knobs.warp_fast ? 1 : 0;
   la.nx_on = (next && !keep_one) ? 1 : 0;
   la.lse_p = out->lse_target; la.lse_q = out->lse_draft; la.logp_p = out->node_logp_target; la.logp_q = out->node_logp_draft;
   if (la.nx_on) la.nx = *next; else la.nx = dsbd_next_beams{};
@@ -2937,6 +2529,22 @@ int32_t verify_impl(const dsbd_forest* f, const dsbd_verify_in* in, const dsbd_p
       return DSBD_ERR_HIP;
     }
   }
+  if (warped) {
+    ra.n_nodes = f->n_nodes; ra.V = in->V; ra.K = p->top_k; ra.chunk = rp.chunk; ra.nchunk = rp.nchunk;
+    ra.alias = la.alias; ra.zp = in->logits_target; ra.zq = in->logits_draft;
+    ra.parent = f->parent; ra.token = f->token; ra.rec_stride = rp.rec_stride; ra.compact = rp.compact;
+    ra.lse_p = out->lse_target; ra.lse_q = out->lse_draft; ra.logp_p = out->node_logp_target; ra.logp_q = out->node_logp_draft;
+    ra.fault = fault;
+    ra.direct = knobs.warp_fast ? INT_MAX : 0;
+    if (launch_verify_rows(ra, stream) != hipSuccess) return DSBD_ERR_HIP;
+    la.rec = ra.rec; la.rec_stride = rp.rec_stride; la.rec_compact = rp.compact;
+    la.layer_wgs = f->n_prompts; la.prompt0 = 0;
+    dsbd_launch(DSBD_KERNEL_VERIFY_LAYERS, verify_layers_kernel<true, NODE_CAP>, dim3((unsigned)f->n_prompts), dim3(VL_BLOCK),
+                (unsigned int)pl.lds_bytes, stream, la);
+    DSBD_HIP_LAUNCH_CHECK();
+    if (next && keep_one) return dsbd_select_beams(f, out, p->W_cap, keep_one, next, fault, stream_);
+    return DSBD_OK;
+  }
   const unsigned rows = (unsigned)f->n_nodes * (alias ? 1u : 2u);
   la.stats_threads = statistics_threads(f, pl, rows);
   const unsigned rows_per_wg = VL_BLOCK / la.stats_threads;
@@ -2946,10 +2554,7 @@ int32_t verify_impl(const dsbd_forest* f, const dsbd_verify_in* in, const dsbd_p
     unsigned grid3 = (unsigned)np * (unsigned)pl.G;
     la.layer_wgs = (int)grid3;
     if (want_stats && p0 + np == f->n_prompts) grid3 += (rows + rows_per_wg - 1) / rows_per_wg;     // behind the (last) layers
-    if (p->top_k > 0)
-      dsbd_launch(DSBD_KERNEL_VERIFY_LAYERS, verify_layers_kernel<true, NODE_CAP>, dim3(grid3), dim3(VL_BLOCK),
-                  (unsigned int)pl.lds_bytes, stream, la);
-    else if (pl.small_nodes)
+    if (pl.small_nodes)
       dsbd_launch(DSBD_KERNEL_VERIFY_LAYERS, verify_layers_kernel<false, NODE_CAP_SMALL>, dim3(grid3), dim3(VL_BLOCK),
                   (unsigned int)pl.lds_bytes, stream, la);
     else

@@ -1,0 +1,303 @@
+// Row work of a warped verification (paper Section 2.1: T cuts the joints to their top_k first entries, then by top-p):
+// for every row of both models its maximum, its fp64 sum of exponentials and its top_k first entries, plus the per-node
+// fp32 outputs (log-sum-exp of a node's row, log-probability of a node's token under its parent's row).
+//
+// A joint's top_k first entries are among the top_k first entries of its rows, so the layer walk gets by with these records
+// and never touches the logits again: it needs no slices of the joint and no partner workgroups (verify.hip).  All rows
+// are taken at once, whether the walk reaches them or not: their sums are outputs anyway.  (Before, every layer formed its
+// joint over I x V on up to 256 workgroups and selected from it by exchanges: 15 us of a layer's 22; now 4 of 11.)
+//
+// Two kernels:
+//  1. verify_chunk_kernel: a wave per chunk of a row, no barrier: maximum, sum, and the maxima of the chunk's halves.
+//     Bound by fp64 exponentials as soon as there are many: both models' rows of 53 nodes x 128256 (54 MB) take 15 us, of 248
+//     nodes (254 MB) 60; without the exponentials 13 and 36 (7.1 TB/s).  Fewer instructions per exponential (rounding by an
+//     addition, the power of two put into the table entry's exponent) changed nothing, a table of 256 entries with a
+//     polynomial of degree 4 took 5 us off 248 nodes and nothing off 53.
+//  2. verify_row_kernel: a workgroup per row folds the chunks, bounds the row's K-th entry by the K-th largest of the
+//     maxima of groups of halves (K entries reach it) and reads again only the halves that reach the bound.  A chain of round
+//     trips: 6 us for 106 rows, 9 for 496 (with 256 threads per row, which take the halves three after the other: 14).
+#include "verify_rows.h"
+#include "exp_nonpos.h"
+#include "wave_f64.h"
+#include <float.h>
+#include <limits.h>
+
+#define VR_BLOCK 256           // chunk kernel
+#define VR_ROW_BLOCK 1024      // row kernel
+#define VR_ROW_WAVES (VR_ROW_BLOCK / 64)
+#define VR_CAND 1024           // candidates that are ranked directly
+
+namespace {
+
+__constant__ double c_rows_exp2_tab[64] = {DSBD_EXP2_TABLE_64};
+
+// (rows of an odd vocabulary start anywhere; the loads are as wide all the same)
+typedef float vr_f32x4 __attribute__((ext_vector_type(4), aligned(4)));
+
+__device__ __forceinline__ const float* row_logits(const RowsArgs& a, int row) {
+  return a.alias ? a.zp + (long long)row * a.V : ((row & 1) ? a.zq : a.zp) + (long long)(row >> 1) * a.V;
+}
+
+#define VR_TILE 1024           // logits a wave takes at a time: four 16-byte loads per lane
+struct Tile { vr_f32x4 v[4]; };
+
+__device__ __forceinline__ Tile load_tile(const float* __restrict__ z, int x0, int x_end) {
+  const int lane = threadIdx.x & 63;
+  Tile t;
+  if (x0 + VR_TILE <= x_end) {
+#pragma unroll
+    for (int k = 0; k < 4; ++k) t.v[k] = __builtin_nontemporal_load(reinterpret_cast<const vr_f32x4*>(z + x0 + k * 256 + lane * 4));
+  } else {
+#pragma unroll
+    for (int k = 0; k < 4; ++k)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const int x = x0 + k * 256 + lane * 4 + e;
+        const float w = z[min(x, x_end - 1)];
+        t.v[k][e] = x < x_end ? w : -INFINITY;             // (places beyond the row's end: masked tokens)
+      }
+  }
+  return t;
+}
+
+// The maxima of a tile's halves, its maximum and its sum of exponentials against that.
+__device__ __forceinline__ void take_tile(const Tile& t, const double* tab, bool& bad, float (&half)[VR_SUBS], float& m, double& s) {
+#pragma unroll
+  for (int p = 0; p < VR_SUBS; ++p) {
+    float q = -INFINITY;
+#pragma unroll
+    for (int k = 2 * p; k < 2 * p + 2; ++k)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) { q = fmaxf(q, t.v[k][e]); bad |= !(t.v[k][e] <= FLT_MAX); }      // NaN or +Inf
+    half[p] = wave_max_f32(q);
+  }
+  m = fmaxf(half[0], half[1]);
+  const double ref = m == -INFINITY ? 0.0 : (double)m;     // (a tile masked whole adds 0)
+  double sum[4] = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+  for (int k = 0; k < 4; ++k)
+#pragma unroll
+    for (int e = 0; e < 4; ++e) sum[e] += dsbd_exp_nonpos((double)t.v[k][e] - ref, tab);
+  s = wave_sum((sum[0] + sum[1]) + (sum[2] + sum[3]));
+}
+
+// SINGLE: a chunk is one tile (rows of up to 131072 logits); else several, merged as they go.  A chunk per wave and as many
+// waves as there are chunks: those that wait for their logits and those that work on theirs mix by themselves (four resident
+// waves per SIMD that take chunk after chunk, the next two on their way: 2 us slower on 54 MB).
+template <bool SINGLE>
+__global__ __launch_bounds__(VR_BLOCK) void verify_chunk_kernel(RowsArgs a, int rows) {
+  __shared__ double tab[64];
+  const int lane = threadIdx.x & 63;
+  const long long item = (long long)blockIdx.x * (VR_BLOCK / 64) + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const bool live = item < (long long)rows * a.nchunk;
+  const unsigned int at = live ? (unsigned int)item : 0u;      // (below 2^32: the grid holds four items per workgroup)
+  const int row = (int)(at / (unsigned int)a.nchunk), c = (int)(at % (unsigned int)a.nchunk);
+  const float* const z = row_logits(a, row);
+  const int x_lo = c * a.chunk, x_hi = min(a.V, x_lo + a.chunk);
+  const Tile first = load_tile(z, x_lo, x_hi);
+  if (threadIdx.x < 64) tab[threadIdx.x] = c_rows_exp2_tab[threadIdx.x];
+  __syncthreads();
+  if (!live) return;
+  bool bad = false;
+  float sub[VR_SUBS], M;
+  double S;
+  take_tile(first, tab, bad, sub, M, S);
+  if constexpr (!SINGLE) {
+    float part[VR_SUBS] = {M, -INFINITY};                  // (a part is half of the chunk: whole tiles)
+    for (int x0 = x_lo + VR_TILE; x0 < x_hi; x0 += VR_TILE) {
+      float m;
+      double s;
+      take_tile(load_tile(z, x0, x_hi), tab, bad, sub, m, s);
+      if (x0 - x_lo < a.chunk / VR_SUBS) part[0] = fmaxf(part[0], m); else part[1] = fmaxf(part[1], m);
+      if (m > -INFINITY) {
+        const float Mn = fmaxf(M, m);
+        S = (M > -INFINITY ? S * dsbd_exp_nonpos((double)M - (double)Mn, tab) : 0.0) + s * dsbd_exp_nonpos((double)m - (double)Mn, tab);
+        M = Mn;
+      }
+    }
+    sub[0] = part[0]; sub[1] = part[1];
+  }
+  if (lane == 0) {
+    if (a.part) a.part[item] = make_double2((double)M, S);
+    else { RowHead h; h.sum = S; h.max = M; h.n = 0; *reinterpret_cast<RowHead*>(a.rec + item * a.rec_stride) = h; }
+  }
+  if (a.sub && lane < VR_SUBS) a.sub[item * VR_SUBS + lane] = lane == 0 ? sub[0] : sub[1];
+  if (__ballot(bad) != 0ull && lane == 0) atomicOr(a.fault, DSBD_FAULT_NONFINITE);
+}
+
+// Entry (z, x) comes before entry (z2, x2) of the same row.
+__device__ __forceinline__ bool entry_before(float z, int x, float z2, int x2) { return (z > z2) | ((z == z2) & (x < x2)); }
+
+__global__ __launch_bounds__(VR_ROW_BLOCK) void verify_row_kernel(RowsArgs a) {
+  __shared__ double tab[64];
+  __shared__ __attribute__((aligned(16))) float part_max[VR_MAX_CHUNKS * VR_SUBS];
+  __shared__ int list[VR_MAX_CHUNKS * VR_SUBS];
+  __shared__ float cz[VR_CAND];
+  __shared__ int cx[VR_CAND];
+  __shared__ float bound_s;
+  __shared__ int n_list, n_cand;
+  __shared__ float best_z[VR_ROW_WAVES];
+  __shared__ int best_x[VR_ROW_WAVES];
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int row = blockIdx.x, K = a.K, V = a.V;
+  const bool second = !a.alias && (row & 1);
+  const int node = a.alias ? row : row >> 1;
+  const float* const z = row_logits(a, row);
+  const int nsub = a.nchunk * VR_SUBS, sub_len = a.chunk / VR_SUBS;
+  // everything that is read from memory first is requested together
+  double2 ms[VR_MAX_CHUNKS / 64];
+#pragma unroll
+  for (int k = 0; k < VR_MAX_CHUNKS / 64; ++k) {
+    ms[k] = make_double2(-INFINITY, 0.0);
+    if (lane + 64 * k < a.nchunk) {
+      if (a.part) ms[k] = a.part[(long long)row * a.nchunk + lane + 64 * k];
+      else { const RowHead h = *reinterpret_cast<const RowHead*>(a.rec + (long long)row * a.rec_stride); ms[k] = make_double2((double)h.max, h.sum); }
+    }
+  }
+  // (parts whose maxima were not kept: all of them are looked at, without a bound)
+  if (tid < VR_MAX_CHUNKS * VR_SUBS) part_max[tid] = tid >= nsub ? -INFINITY : a.sub ? a.sub[(long long)row * nsub + tid] : INFINITY;
+  // children: nodes of the same tree, behind this one, no further than a tree is long
+  const int child_n = min(node + tid, a.n_nodes - 1);
+  int child_par = -1, ct = -1, par = -1, tok = -1;
+  if (tid < DSBD_MAX_TREE_NODES) {
+    child_par = a.parent[child_n]; ct = a.token[child_n];
+    par = a.parent[node]; tok = a.token[node];
+  }
+  if (tid < 64) tab[tid] = c_rows_exp2_tab[tid];
+  if (tid == 0) { bound_s = -INFINITY; n_list = 0; n_cand = 0; }
+  __syncthreads();
+  const bool child = tid >= 1 && tid < DSBD_MAX_TREE_NODES && node + tid < a.n_nodes && child_par == node && ct >= 0 && ct < V;
+  const float zt = child ? z[ct] : 0.f;
+  // the row's maximum and sum, every wave for itself, in a fixed order
+  static_assert(VR_MAX_CHUNKS == 128, "two chunks per lane");
+  const double M = wave_max_f64(fmax(ms[0].x, ms[1].x));
+  const double S = wave_sum((ms[0].x > -INFINITY ? ms[0].y * dsbd_exp_nonpos(ms[0].x - M, tab) : 0.0) +
+                            (ms[1].x > -INFINITY ? ms[1].y * dsbd_exp_nonpos(ms[1].x - M, tab) : 0.0));
+  // the bound: the K-th largest of the maxima of 64 groups of parts (K entries reach it; fewer groups: none), one group per
+  // lane, the same in every wave, each of which ranks four of them
+  {
+    static_assert(VR_MAX_CHUNKS * VR_SUBS == 4 * 64 && VR_ROW_WAVES == 16, "four parts per lane, four groups per wave");
+    const float gm = fmaxf(fmaxf(part_max[lane], part_max[lane + 64]), fmaxf(part_max[lane + 128], part_max[lane + 192]));
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      const int i = 4 * wave + k;
+      const float v = __shfl(gm, i);
+      const int ahead = __popcll(__ballot((gm > v) | ((gm == v) & (lane < i))));
+      if (ahead == K - 1 && lane == 0) bound_s = v;
+    }
+  }
+  __syncthreads();
+  const float bound = a.sub ? bound_s : -INFINITY;
+  if (tid < nsub && part_max[tid] >= bound && part_max[tid] > -INFINITY) list[atomicAdd(&n_list, 1)] = tid;
+  __syncthreads();
+  const int nl = n_list;
+  // the entries at or above the bound
+  for (int i = wave; i < nl; i += VR_ROW_WAVES) {
+    const int x_lo = list[i] * sub_len, x_hi = min(V, x_lo + sub_len);
+    for (int x0 = x_lo; x0 < x_hi; x0 += 512) {
+      float v[8];
+#pragma unroll
+      for (int k = 0; k < 8; ++k) v[k] = z[min(x0 + k * 64 + lane, x_hi - 1)];
+#pragma unroll
+      for (int k = 0; k < 8; ++k) {
+        const int x = x0 + k * 64 + lane;
+        if (x < x_hi && v[k] >= bound && v[k] > -INFINITY) {
+          const int at = atomicAdd(&n_cand, 1);
+          if (at < VR_CAND) { cz[at] = v[k]; cx[at] = x; }
+        }
+      }
+    }
+  }
+  __syncthreads();
+  char* const rec = a.rec + (long long)row * a.rec_stride;
+  auto put = [&](int r, float v, int x) {
+    if (a.compact == 1) { reinterpret_cast<uint8_t*>(rec + sizeof(RowHead))[r] = (uint8_t)x; return; }
+    if (a.compact == 2) { reinterpret_cast<uint16_t*>(rec + sizeof(RowHead))[r] = (uint16_t)x; return; }
+    RowEntry e;
+    e.z = v; e.x = x;
+    reinterpret_cast<RowEntry*>(rec + sizeof(RowHead))[r] = e;
+  };
+  const int nc = n_cand;
+  if (nc <= min(a.direct, VR_CAND)) {
+    for (int t = tid; t < nc; t += VR_ROW_BLOCK) {
+      const float v = cz[t];
+      const int x = cx[t];
+      int rank = 0;
+#pragma unroll 4
+      for (int o = 0; o < nc; ++o) rank += entry_before(cz[o], cx[o], v, x) ? 1 : 0;
+      if (rank < K) put(rank, v, x);
+    }
+  } else {
+    // Entries crowd at the bound (equal logits): rank after rank, every thread offers its first entry behind the last one
+    // taken, and only the thread whose offer was taken looks for its next.
+    auto next = [&](float z_prev, int x_prev, float& bz, int& bx) {
+      bz = -INFINITY; bx = INT_MAX;
+      for (int i = 0; i < nl; ++i) {
+        const int x_lo = list[i] * sub_len, x_hi = min(V, x_lo + sub_len);
+        for (int x = x_lo + tid; x < x_hi; x += VR_ROW_BLOCK) {
+          const float v = z[x];
+          if (v > -INFINITY && entry_before(z_prev, x_prev, v, x) && entry_before(v, x, bz, bx)) { bz = v; bx = x; }
+        }
+      }
+    };
+    float bz;
+    int bx;
+    next(INFINITY, -1, bz, bx);
+    for (int r = 0; r < K; ++r) {
+      float wz = bz;
+      int wx = bx;
+#pragma unroll
+      for (int off = 32; off >= 1; off >>= 1) {
+        const float oz = __shfl_xor(wz, off);
+        const int ox = __shfl_xor(wx, off);
+        if (entry_before(oz, ox, wz, wx)) { wz = oz; wx = ox; }
+      }
+      __syncthreads();
+      if (lane == 0) { best_z[wave] = wz; best_x[wave] = wx; }
+      __syncthreads();
+#pragma unroll
+      for (int w = 0; w < VR_ROW_WAVES; ++w)
+        if (entry_before(best_z[w], best_x[w], wz, wx)) { wz = best_z[w]; wx = best_x[w]; }
+      if (wx == INT_MAX) break;                                  // (no more entries; uniform)
+      if (tid == 0) put(r, wz, wx);
+      if (bx == wx) next(wz, wx, bz, bx);
+    }
+  }
+  // ---- head and per-node outputs
+  const double lse64 = M + log(S);
+  const float lse = (float)lse64;
+  float* const o_lse = second ? a.lse_q : a.lse_p;
+  float* const o_logp = second ? a.logp_q : a.logp_p;
+  int fault = 0;
+  if (tid == 0) {
+    RowHead h;
+    h.sum = S; h.max = (float)M; h.n = min(nc, K);
+    *reinterpret_cast<RowHead*>(rec) = h;
+    if (o_lse) o_lse[node] = lse;
+    if (a.alias && a.lse_q) a.lse_q[node] = lse;
+    if (!(S > 0.0)) fault = DSBD_FAULT_NONFINITE;              // a row without a finite logit (NaN and +Inf: the chunks report them)
+    if (!(par >= 0 && par < node && node - par < DSBD_MAX_TREE_NODES && tok >= 0 && tok < V)) {      // a root (or a node reported elsewhere)
+      if (o_logp) o_logp[node] = 0.f;
+      if (a.alias && a.logp_q) a.logp_q[node] = 0.f;
+    }
+  }
+  if (child) {
+    if (zt == -INFINITY) fault = DSBD_FAULT_NONFINITE;         // a drafted token masked in its parent's row
+    const float lp = (float)((double)zt - lse64);
+    if (o_logp) o_logp[child_n] = lp;
+    if (a.alias && a.logp_q) a.logp_q[child_n] = lp;
+  }
+  if (fault) atomicOr(a.fault, fault);
+}
+
+}  // namespace
+
+hipError_t launch_verify_rows(const RowsArgs& a, hipStream_t stream) {
+  const int rows = a.n_nodes * (a.alias ? 1 : 2);
+  const long long items = (long long)rows * a.nchunk;
+  const dim3 grid((unsigned)((items + VR_BLOCK / 64 - 1) / (VR_BLOCK / 64)));
+  if (a.chunk == VR_TILE) hipLaunchKernelGGL(verify_chunk_kernel<true>, grid, dim3(VR_BLOCK), 0, stream, a, rows);
+  else hipLaunchKernelGGL(verify_chunk_kernel<false>, grid, dim3(VR_BLOCK), 0, stream, a, rows);
+  hipLaunchKernelGGL(verify_row_kernel, dim3((unsigned)rows), dim3(VR_ROW_BLOCK), 0, stream, a);
+  return hipGetLastError();
+}

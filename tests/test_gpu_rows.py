@@ -1,0 +1,115 @@
+"""The row records behind warped verifications, where their cuts can go wrong: rows shorter than a tile, ragged last tiles
+and chunks, rows of several tiles per chunk, as many entries as there are tokens, crowds of equal logits, one model in both
+roles.  Against the oracle, bit for bit but for near ties; the fp32 row outputs against 64 bits."""
+import dataclasses
+
+import numpy as np
+import pytest
+
+from dsbd_synth import make_workload
+
+pytestmark = pytest.mark.gpu
+
+
+def _check(w, top_k, top_p, t):
+    import gpu_util as gu
+    d = gu.DeviceWorkload(w)
+    res, _ = d.verify_select(t=t, top_k=top_k, top_p=top_p)
+    assert int(res.fault.item()) == 0
+    gu.compare_verify(res, gu.oracle_verify(w, t=t, top_k=top_k, top_p=top_p), w)
+    for z, lse, logp in ((w.logits_p, res.lse_target, res.node_logp_target), (w.logits_q, res.lse_draft, res.node_logp_draft)):
+        z = z.astype(np.float64)
+        m = z.max(axis=1, keepdims=True)
+        want = m[:, 0] + np.log(np.exp(z - m).sum(axis=1))
+        # (one rounding to fp32 of a value computed in fp64: half an ulp, 6e-8 relative)
+        np.testing.assert_allclose(lse.cpu().numpy(), want, rtol=6.5e-8, atol=1e-12)
+        child = np.nonzero(w.parent >= 0)[0]
+        want = z[w.parent[child], w.token[child]] - want[w.parent[child]]
+        np.testing.assert_allclose(logp.cpu().numpy()[child], want, rtol=6.5e-8, atol=1e-9)
+
+
+@pytest.mark.parametrize("fast", [1, 0])
+@pytest.mark.parametrize("V,top_k,top_p", [
+    (1, 1, 1.0), (3, 32, 0.9), (63, 10, 0.8), (1023, 32, 1.0), (1024, 5, 0.8), (1025, 10, 0.8), (2049, 32, 0.95),
+    (4099, 2, 0.8), (32001, 10, 0.8),
+])
+def test_rows_of_any_length(V, top_k, top_p, fast, knobs):
+    knobs.set("DSBD_WARP_FAST", fast)
+    w = make_workload("c2", L=8, V=V, Hq=4, Hkv=4, draft_top_k=min(4, V))
+    for t in (-1.0, 0.7):
+        _check(w, top_k, top_p, t)
+
+
+@pytest.mark.parametrize("fast", [1, 0])
+@pytest.mark.parametrize("V", [131073, 270001])            # two and three tiles of 1024 in the last chunks, ragged ends
+def test_rows_of_several_tiles_per_chunk(V, fast, knobs):
+    knobs.set("DSBD_WARP_FAST", fast)
+    w = make_workload("c1", L=8, V=V, draft_top_k=4)
+    # the leading entries also where a chunk's second half, a row's last tile and its last token are
+    lead = np.array([0, 1023, 1024, 2047, 2048, 3071, V - 1025, V - 1])
+    w.logits_p[:, lead] += 12.0
+    w.logits_q[:, lead] += 12.0
+    _check(w, 16, 0.9, -1.0)
+
+
+@pytest.mark.parametrize("fast", [1, 0])
+@pytest.mark.parametrize("V", [300, 5000, 40000])
+def test_rows_with_crowds_of_equal_logits(V, fast, knobs):
+    """More entries at the bound than are ranked directly (5000, 40000), masked tokens among them."""
+    knobs.set("DSBD_WARP_FAST", fast)
+    w = make_workload("c1", L=8, V=V, draft_top_k=4)
+    zp, zq = np.round(w.logits_p / 8) * 8, np.zeros_like(w.logits_q)
+    keep = w.token[w.token >= 0]
+    mask = np.zeros(V, dtype=bool)
+    mask[::3] = True
+    mask[keep] = False
+    zp[:, mask] = -np.inf
+    zq[:, mask] = -np.inf
+    w = dataclasses.replace(w, logits_p=zp.astype(np.float32), logits_q=zq.astype(np.float32))
+    _check(w, 10, 0.8, -1.0)
+    _check(w, 32, 1.0, 0.5)
+
+
+def test_one_model_in_both_roles():
+    import gpu_util as gu
+    w = make_workload("c2", L=8, V=3001, Hq=4, Hkv=4, draft_top_k=4)
+    w = dataclasses.replace(w, logits_q=w.logits_p, beam_logp_q=w.beam_logp_p)
+    d = gu.DeviceWorkload(w)
+    d.logits_q, d.blq = d.logits_p, d.blp
+    res, _ = d.verify_select(t=-1.0, top_k=10, top_p=0.8)
+    assert int(res.fault.item()) == 0
+    gu.compare_verify(res, gu.oracle_verify(w, top_k=10, top_p=0.8), w)
+
+
+@pytest.mark.parametrize("V,top_k,n_prompts", [(200, 32, 600), (1000, 32, 600), (1500, 32, 600)])
+def test_compact_records_of_large_batches(V, top_k, n_prompts):
+    """Batches whose records with logits would outgrow 32 MiB keep 8- or 16-bit tokens instead."""
+    import gpu_util as gu
+    import paper_2409_16560_amd as dsbd
+    base = make_workload("c4", n_prompts=n_prompts, W=(8, 8), tree_nodes=(12, 16), L=1, Hq=1, Hkv=1, D=64, V=4, seed=5)
+    N, rng = len(base.parent), np.random.default_rng(3)
+    zp = rng.standard_normal((N, V), dtype=np.float32) * 3
+    zq = zp + rng.standard_normal((N, V), dtype=np.float32) * np.float32(0.5)
+    par = np.maximum(base.parent, 0)
+    token = np.argpartition(-zq[par], 3, axis=1)[np.arange(N), rng.integers(0, 4, N)].astype(np.int32)
+    w = dataclasses.replace(base, logits_p=zp, logits_q=zq, token=token)
+    d = gu.DeviceWorkload(w)
+    assert N * 2 * (16 + 8 * top_k) > 32 << 20                      # what the records with logits would take
+    assert dsbd.dsbd_verify_forest_workspace_bytes(d.forest, V, 0, 1, w.W_cap, -1.0, top_k, 0.9) <= 32 << 20
+    res, _ = d.verify_select(t=0.6, top_k=top_k, top_p=0.9)
+    assert int(res.fault.item()) == 0
+    # (the first prompts only: the oracle takes milliseconds for each)
+    P, T = 12, int(np.searchsorted(w.tree_prompt, 12))
+    n = int(w.tree_off[T])
+    first = dataclasses.replace(
+        w, n_prompts=P, n_trees=T, n_nodes=n, tree_prompt=w.tree_prompt[:T], tree_off=w.tree_off[:T + 1], parent=w.parent[:n], token=token[:n], logits_p=zp[:n],
+        logits_q=zq[:n], beam_logp_p=w.beam_logp_p[:T], beam_logp_q=w.beam_logp_q[:T], u_accept=w.u_accept[:n],
+        u_resid=w.u_resid[:P], u_fill=w.u_fill[:P])
+    ref = gu.oracle_verify(first, t=0.6, top_k=top_k, top_p=0.9)
+    for k in ("l_last", "n_out"):
+        assert np.array_equal(getattr(res, k).cpu().numpy()[:P], ref[k])
+    assert np.array_equal(res.node_status.cpu().numpy()[:n], ref["node_status"])
+    for p in range(P):
+        m = int(ref["n_out"][p])
+        assert np.array_equal(res.out_token.cpu().numpy()[p, :m], ref["out_token"][p, :m])
+        assert np.array_equal(res.out_parent.cpu().numpy()[p, :m], ref["out_parent"][p, :m])
