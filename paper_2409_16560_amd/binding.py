@@ -145,6 +145,19 @@ def load_library():
     return lib
 
 
+_host = None
+
+
+def _native():
+    """The binding's native part (csrc/host.cpp), built along with the library; there is no fallback."""
+    global _host
+    if _host is None:
+        load_library()
+        from . import _dsbd_host
+        _host = _dsbd_host
+    return _host
+
+
 def dsbd_version():
     return load_library().dsbd_version().decode()
 
@@ -520,30 +533,15 @@ def dsbd_draft_layer(beam_off, logits_draft, beam_logp_draft, u, W_S, *, max_pro
     """One beam-sampling step of the small model.  beam_off i32[P+1] (device), logits_draft f32[n_beams,V],
     beam_logp_draft f64[n_beams], u f32[P,W_S].  Returns (parent i32[P,W_S] rows of the input, token i32[P,W_S],
     logp f64[P,W_S], fault i32[1])."""
-    lib = load_library()
-    n_beams, V = logits_draft.shape
-    P = beam_off.numel() - 1
-    dev = logits_draft.device
-    assert beam_off.dtype == torch.int32 and logits_draft.dtype == torch.float32 and logits_draft.is_contiguous()
-    assert beam_logp_draft.dtype == torch.float64 and u.dtype == torch.float32 and u.is_contiguous()
-    assert u.numel() == P * W_S and beam_logp_draft.numel() == n_beams
-    din = _DraftIn(int(P), int(n_beams), int(max_prompt_beams), int(V), _ptr(beam_off), _ptr(logits_draft),
-                   _ptr(beam_logp_draft), _ptr(u))
-    parent = torch.empty((P, W_S), dtype=torch.int32, device=dev)
-    token = torch.empty_like(parent)
-    logp = torch.empty((P, W_S), dtype=torch.float64, device=dev)
-    dout = _DraftOut(_ptr(parent), _ptr(token), _ptr(logp))
     if fault is None:
-        fault = _fault_word(dev, stream)
-    if workspace is None:
-        nbytes = int(lib.dsbd_draft_layer_workspace_bytes(C.byref(din), int(W_S), int(top_k), float(top_p)))
-        if nbytes == 0:
-            raise DsbdError(-2, "dsbd_draft_layer_workspace_bytes")
-        workspace = torch.empty(max(nbytes, 256), dtype=torch.uint8, device=dev)
-    rc = lib.dsbd_draft_layer(C.byref(din), int(W_S), int(top_k), float(top_p), C.byref(dout), _ptr(workspace),
-                              workspace.numel(), _ptr(fault), _stream(stream))
-    _check(rc, "dsbd_draft_layer")
-    return parent, token, logp, fault
+        fault = _fault_word(logits_draft.device, stream)
+    out = (_host or _native()).draft_layer(beam_off, logits_draft, beam_logp_draft, u, W_S, max_prompt_beams, top_k, top_p,
+                                           workspace, fault, _stream(stream))
+    if type(out) is int:
+        raise DsbdError(out, "dsbd_draft_layer")
+    if not out:
+        raise DsbdError(-2, "dsbd_draft_layer_workspace_bytes")
+    return out[0], out[1], out[2], fault
 
 
 def dsbd_build_forest(root_off, layer_parent, layer_token, root_token=None, *, n_roots, max_prompt_trees,
@@ -552,33 +550,16 @@ def dsbd_build_forest(root_off, layer_parent, layer_token, root_token=None, *, n
     i32[gamma, P*W_S] (device), root_token i32[n_roots] or None.  Returns (Forest, node_of_root i32[n_roots],
     node_of i32[gamma, P*W_S], max_tree_nodes i32[1] (device), fault i32[1]); the Forest carries the bound of 64
     nodes per tree, the device value says what the largest tree really holds."""
-    lib = load_library()
     dev = root_off.device
-    P = root_off.numel() - 1
-    gamma = int(layer_parent.shape[0]) if layer_parent is not None and layer_parent.numel() > 0 else 0
-    W_S = int(layer_parent.shape[1]) // P if gamma else 0
-    N = int(n_roots) + gamma * P * W_S
-    # one allocation, cut into the arrays (their places are passed as numbers: an array of no entries has no pointer)
-    n_roots, D = int(n_roots), gamma * P * W_S
-    sizes = (n_roots, n_roots + 1, N, N, N, n_roots, D, 1)
-    buf = torch.empty(sum(sizes), dtype=torch.int32, device=dev)
-    tree_prompt, tree_off, parent, token, rank, node_of_root, node_of, mx = buf.split_with_sizes(sizes)
-    at, places = buf.data_ptr(), []
-    for n in sizes:
-        places.append(at)
-        at += 4 * n
-    fo = _ForestOut(*places)
     if fault is None:
         fault = _fault_word(dev, stream)
-    for t_ in (root_off, layer_parent, layer_token, root_token):
-        assert t_ is None or (t_.dtype == torch.int32 and t_.is_contiguous())
-    rc = lib.dsbd_build_forest(int(P), int(n_roots), gamma, W_S, _ptr(root_off), _ptr(root_token),
-                               _ptr(layer_parent) if gamma else None, _ptr(layer_token) if gamma else None,
-                               C.byref(fo), _ptr(fault), _stream(stream))
-    _check(rc, "dsbd_build_forest")
-    f = Forest(tree_prompt, tree_off, parent, token, rank, n_prompts=P,
+    out = (_host or _native()).build_forest(root_off, layer_parent, layer_token, root_token, n_roots, fault, _stream(stream))
+    if type(out) is int:
+        raise DsbdError(out, "dsbd_build_forest")
+    gamma, tree_prompt, tree_off, parent, token, rank, node_of_root, node_of, mx = out
+    f = Forest(tree_prompt, tree_off, parent, token, rank, n_prompts=root_off.numel() - 1,
                max_tree_nodes=64, max_depth=gamma, max_prompt_trees=int(max_prompt_trees), device=dev)
-    return f, node_of_root, node_of.view(gamma, P * W_S) if gamma else node_of, mx, fault
+    return f, node_of_root, node_of, mx, fault
 
 
 def dsbd_stream_read_probe(buf: torch.Tensor, reps: int = 10, stream=None) -> float:

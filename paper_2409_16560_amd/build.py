@@ -1,4 +1,4 @@
-"""Builds libdsbd.so (HIP, gfx950) in-tree with hipcc."""
+"""Builds libdsbd.so (HIP, gfx950) and the binding's native part in-tree."""
 import os
 import subprocess
 import sys
@@ -7,6 +7,7 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libdsbd.so")
+HOST = os.path.join(HERE, "_dsbd_host.so")      # the binding's native part (csrc/host.cpp), on top of libdsbd.so and torch
 SOURCES = ["attention.hip", "verify.hip", "verify_rows.hip", "select.hip", "commit.hip", "draft.hip", "timing.hip", "knobs.hip"]
 # Per-file flags.  attention.hip: scores come out of the matrix units and go through max / exp2 only; without
 # -fno-honor-nans every fmaxf operand is first canonicalised (v_max x, x), which triples the instructions of the
@@ -29,6 +30,21 @@ def hipcc():
         if c and (os.path.isabs(c) and os.path.exists(c) or not os.path.isabs(c)):
             return c
     return "hipcc"
+
+
+def host_commands():
+    """Compile and link commands of the binding's native part (host code only)."""
+    import sysconfig
+    import torch
+    from torch.utils import cpp_extension
+    obj = os.path.join(CSRC, "host.o")
+    inc = cpp_extension.include_paths() + [sysconfig.get_paths()["include"], os.path.join(ROOT, "include")]
+    compile_ = (["g++", "-O2", "-std=c++17", "-fPIC", "-D_GLIBCXX_USE_CXX11_ABI=%d" % int(torch._C._GLIBCXX_USE_CXX11_ABI)]
+                + ["-I" + i for i in inc] + ["-c", os.path.join(CSRC, "host.cpp"), "-o", obj])
+    torch_lib = os.path.join(os.path.dirname(torch.__file__), "lib")
+    link = ["g++", "-shared", "-o", HOST, obj, "-L" + HERE, "-ldsbd", "-L" + torch_lib, "-ltorch_python", "-ltorch_cpu", "-lc10",
+            "-Wl,-rpath,$ORIGIN"]
+    return compile_, link
 
 
 def check_registers(report, verbose):
@@ -65,11 +81,13 @@ def build(verbose=True):
         cmd = [hipcc()] + flags + FILE_FLAGS.get(src, []) + ["-c", os.path.join(CSRC, src), "-o", obj]
         procs.append((src, subprocess.Popen(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)))
         objs.append(obj)
+    host_compile, host_link = host_commands()
+    procs.append(("host.cpp", subprocess.Popen(host_compile, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)))
     for src, p in procs:
         out, _ = p.communicate()
         out = "\n".join(l for l in out.splitlines() if "packed-fp32-ops" not in l)
         if p.returncode != 0:
-            raise RuntimeError("hipcc failed on %s:\n%s" % (src, out))
+            raise RuntimeError("compiler failed on %s:\n%s" % (src, out))
         if "-Rpass-analysis=kernel-resource-usage" in FILE_FLAGS.get(src, []):
             out = check_registers(out, verbose)
         if verbose and out.strip():
@@ -78,6 +96,9 @@ def build(verbose=True):
     r = subprocess.run(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)
     if r.returncode != 0:
         raise RuntimeError("link failed:\n" + r.stdout)
+    r = subprocess.run(host_link, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)
+    if r.returncode != 0:
+        raise RuntimeError("link of the binding's native part failed:\n" + r.stdout)
     if verbose:
         print("built", LIB)
     return LIB
