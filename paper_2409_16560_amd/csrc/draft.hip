@@ -595,6 +595,7 @@ struct BuildShared {
   int par_local[BF_NODE_CAP];   // prompt-local index (layer-major) of the parent, -1 for roots
   int pos[BF_NODE_CAP];         // position of the node in the prompt's part of the forest
   int tree_n[64];
+  int largest;
   int bad;
 };
 
@@ -611,7 +612,7 @@ __global__ __launch_bounds__(BF_BLOCK) void build_forest_kernel(BuildArgs a) {
   int n_p = W > 0 ? W + a.gamma * a.W_S : 0;            // nodes of the prompt; local index: roots, then layer-major
   if (n_p > BF_NODE_CAP) { bad |= DSBD_FAULT_BOUNDS; n_p = 0; W = 0; }
   const long long base = (long long)r0 + (long long)p * a.gamma * a.W_S;     // first forest node of the prompt
-  if (tid == 0) sh.bad = 0;
+  if (tid == 0) { sh.bad = 0; sh.largest = 0; }
   if (tid < 64) sh.tree_n[tid] = 0;
   __syncthreads();
   // every node: its parent (prompt-local) and, walking up, its input beam
@@ -658,7 +659,7 @@ __global__ __launch_bounds__(BF_BLOCK) void build_forest_kernel(BuildArgs a) {
       a.out.tree_off[r0 + tid] = (int)n;
       a.out.node_of_root[r0 + tid] = (int)n;
       if (sh.tree_n[tid] > DSBD_MAX_TREE_NODES) atomicOr(&sh.bad, DSBD_FAULT_BOUNDS);
-      atomicMax(a.out.max_tree_nodes, sh.tree_n[tid]);
+      atomicMax(&sh.largest, sh.tree_n[tid]);
     } else {
       const int l = 1 + (tid - W) / a.W_S, j = (tid - W) % a.W_S;
       const long long li = (long long)(l - 1) * rows + p * a.W_S + j;
@@ -676,7 +677,11 @@ __global__ __launch_bounds__(BF_BLOCK) void build_forest_kernel(BuildArgs a) {
   }
   if (p == a.n_prompts - 1 && tid == 0) a.out.tree_off[a.n_roots] = a.n_roots + a.gamma * rows;
   __syncthreads();
-  if (tid == 0 && (bad | sh.bad)) atomicOr(a.fault, bad | sh.bad);
+  if (tid == 0) {
+    if (bad | sh.bad) atomicOr(a.fault, bad | sh.bad);
+    if (a.n_prompts == 1) *a.out.max_tree_nodes = sh.largest;      // (a lone prompt needs no cleared word: a launch less)
+    else atomicMax(a.out.max_tree_nodes, sh.largest);
+  }
 }
 
 __global__ void build_forest_init_kernel(int32_t* max_tree_nodes) { *max_tree_nodes = 0; }
@@ -701,7 +706,7 @@ extern "C" int32_t dsbd_build_forest(int32_t n_prompts, int32_t n_roots, int32_t
   a.n_prompts = n_prompts; a.n_roots = n_roots; a.gamma = gamma; a.W_S = gamma > 0 ? W_S : 0;
   a.root_off = root_off; a.root_token = root_token; a.layer_parent = layer_parent; a.layer_token = layer_token;
   a.out = *out; a.fault = fault;
-  hipLaunchKernelGGL(build_forest_init_kernel, dim3(1), dim3(1), 0, stream, out->max_tree_nodes);
+  if (n_prompts > 1) hipLaunchKernelGGL(build_forest_init_kernel, dim3(1), dim3(1), 0, stream, out->max_tree_nodes);
   hipLaunchKernelGGL(build_forest_kernel, dim3((unsigned)n_prompts), dim3(BF_BLOCK), 0, stream, a);
   DSBD_HIP_LAUNCH_CHECK();
   return DSBD_OK;
