@@ -60,6 +60,7 @@ struct AttnArgs {
   int nsplit, n_rowblocks;      // row blocks: of the largest tree the caller announces
   int rows_block;               // query rows per workgroup
   int wg_slots;                 // by_tree: workgroups to spread the work over
+  int waves;                    // waves per workgroup of the wave-private kernel
   // Partial results, one of two layouts (the plan takes the smaller): by split, the row of split s behind those of all
   // rows of the splits before it; or a slot of part_pitch rows per workgroup, a unit's splits in consecutive slots.
   int by_split;
@@ -137,9 +138,9 @@ __device__ __forceinline__ const __bf16* lane_pointer(const void* p, int l) {
 // units of 23 steps 15.3 / 14.3 / 13.2 / 13.1 / 11.7 / 11.7).  Tile kernel: four 64-token tiles, and as little as two tiles for
 // up to four splits (at 2 / 4 / 6 / 8 / 16 splits: 32 units of 33 tiles 30.4 / 22.2 / 20.9 / 21.1 / 26.3; of 9 tiles 17.4 / 15.5 /
 // 16.8 / 16.5).
-__host__ __device__ __forceinline__ int split_limit(int steps, bool tiles) {
+__host__ __device__ __forceinline__ int split_limit(int steps, bool tiles, int waves) {
   const int four = steps / 4, two = steps / 2;
-  const int most = !tiles ? four : (four >= 4 ? four : (two < 4 ? two : 4));
+  const int most = !tiles ? (waves == 8 ? (steps + 7) / 8 : four) : (four >= 4 ? four : (two < 4 ? two : 4));
   return most < 1 ? 1 : (most > AT_MAX_SPLIT ? AT_MAX_SPLIT : most);
 }
 
@@ -150,7 +151,7 @@ __host__ __device__ __forceinline__ int split_limit(int steps, bool tiles) {
 __device__ __forceinline__ int splits_of(const AttnArgs& a, int steps, float total, float units, bool tiles) {
   const float left = fmaxf((float)a.wg_slots - units, 0.f);
   const int ns = 1 + (int)((float)steps * left / total + 1e-3f);
-  return max(1, min(min(ns, split_limit(steps, tiles)), a.nsplit));
+  return max(1, min(min(ns, split_limit(steps, tiles, a.waves)), a.nsplit));
 }
 
 // False: nothing to do for this workgroup.
@@ -267,9 +268,9 @@ __device__ __forceinline__ void write_row_part(const AttnArgs& a, long long row,
   if (a.lse && part == 0) a.lse[row] = (M + log2f(L)) * 0.6931471805599453f;
 }
 
-template <int D, int NRT>
-__global__ __launch_bounds__(AT_BLOCK) void forest_attention_kernel(AttnArgs a) {
-  constexpr int TW = 4;             // waves, each with steps of its own
+// TW: waves, each with steps of its own.
+template <int D, int NRT, int TW>
+__global__ __launch_bounds__(64 * TW) void forest_attention_kernel(AttnArgs a) {
   constexpr int DS = D / 32;        // MFMA k-steps over the head dimension for S^T
   constexpr int DT = D / 16;        // 16-row output tiles over the head dimension for O^T
   constexpr int ROWS_B = 16 * NRT;  // query rows
@@ -556,7 +557,7 @@ __global__ __launch_bounds__(AT_BLOCK) void forest_attention_kernel(AttnArgs a) 
   constexpr int QPR = D / 4;
   const PartPlace place = part_place(a, split, nsplit, min(R - row0, ROWS_B));
 #pragma unroll
-  for (int c = threadIdx.x; c < ROWS_B * QPR; c += AT_BLOCK) {
+  for (int c = threadIdx.x; c < ROWS_B * QPR; c += 64 * TW) {
     const int rl = c / QPR, part = c % QPR, r = row0 + rl;
     if (rl >= place.rows) break;       // (rows rise with c)
     float m[TW], M = NEG_BIG, L = 0.f;
@@ -1050,6 +1051,7 @@ namespace {
 
 struct AttnPlan {
   int nrt;                    // 16-row tiles per wave
+  int waves;                  // waves per workgroup of the wave-private kernel
   bool shared;                // tiles shared by the waves (many rows per stream) instead of wave-private streams
   int rows_block, n_rowblocks;
   bool by_tree;
@@ -1084,16 +1086,31 @@ AttnPlan make_plan(const dsbd_forest* f, const dsbd_kv* kv, int Hq, int Hkv, int
   // at 256 / 512 workgroups or the next fewer that come out even: 64 units of 36 steps 16.1 / 16.5, 80 units of 36 steps, 24
   // rows, 20.6 / 32.7, 128 units of 65 steps 29.8 / 28.7).
   p.slots = 512;
-  if (!p.shared && ((D == 128 && p.nrt == 2) || units * most_steps < 16LL * 512)) p.slots = 256;
+  p.waves = 4;
+  // Workgroups of eight waves, one per compute unit, where all units fit the device at once: the same waves as two workgroups
+  // of four, but no or half the splits, and twice the loads in flight where a unit is not worth splitting.  Not for few
+  // units of middling length, which more workgroups serve better, nor for long ones that leave units idle.  Measured, call in
+  // us with four / eight waves: 128 units of 18 steps 15.7 / 13.4, 256 units of 36 steps 32.3 / 27.5, 160 units of 36 steps 26.0
+  // / 21.8, 32 units of 130 steps 20.0 / 18.4, of 9 steps 11.3 / 10.0; 32 units of 36 steps (64 channels) 11.4 / 12.3, 12 units of
+  // 49 steps 12.3 / 13.2, 8 units of 64 steps 12.0 / 12.8, 128 units of 130 steps (64 channels) 31.4 / 33.8.
+  const long long work = units * most_steps;
+  const bool unsplit = most_steps < (units <= 16 ? 12 : 24);
+  if (!p.shared && f->n_trees <= 64 && units <= 256 && (p.nrt == 1 || D == 64) &&
+      (units > 192 || unsplit || (units > 64 ? work <= 8448 : work >= (units > 32 ? 2048 : 4096)))) { p.waves = 8; p.slots = 256; }
+  else if (!p.shared && ((D == 128 && p.nrt == 2) || units * most_steps < 16LL * 512)) p.slots = 256;
   // Short units stay whole: what splitting takes off them is less than the merge's launch, the less so the more units there
   // are (us unsplit / in two / three / four: 8 units of 8 steps 12.7 / 13.0 / 12.9 / 12.9, of 11 steps 14.3 / 15.1 / 13.0 / 12.8;
   // 64 units of 11 steps 11.5 / 12.7 / 11.2 / 11.2; 96 units of 15 steps 13.0 / 13.6, of 17 steps 14.3 / 14.0; 128 units of 17
   // steps 14.5 / 15.1, of 23 steps 16.5 / 16.4; 32 units of 5 tiles 15.1 / 15.5 / - / 14.7, of 3 tiles 12.9 / 14.3 / - / 14.1).  And
   // with two rounds of workgroups none is split (a tree much longer than the others could still gain by it; not measured).
-  const int worth = p.shared ? 7 : (units <= 64 ? 12 : (units < 128 ? 18 : 24));
-  int most_split = split_limit(most_steps, p.shared);
+  const int worth = p.shared ? 7 : p.waves == 8 ? 24 : (units <= 64 ? 12 : (units < 128 ? 18 : 24));
+  int most_split = split_limit(most_steps, p.shared, p.waves);
   if (most_steps < worth || (long long)f->n_trees * Hkv >= 2 * 512) most_split = 1;
   if (p.by_tree) {
+    // (a tree's units are at least its KV heads, so its share of what the units leave is at most this; with no split there
+    // is nothing to merge: 256 units of 36 steps 29.3 -> 27.4 us)
+    const long long spare = p.slots - (long long)f->n_trees * Hkv;
+    if (const long long share = 1 + (spare > 0 ? spare / Hkv : 0); most_split > share) most_split = (int)share;
     p.nsplit = most_split;
     p.grid = p.nsplit > 1 && units < p.slots ? p.slots : units;
   } else {
@@ -1115,7 +1132,7 @@ AttnPlan make_plan(const dsbd_forest* f, const dsbd_kv* kv, int Hq, int Hkv, int
   // not, so that a buffer for a caller's largest call serves the others too.
   auto room = [&](bool tiles) -> long long {       // (smaller trees may take the other kernel)
     const int steps = (kv->max_len + (tiles ? 64 : STEP) - 1) / (tiles ? 64 : STEP) + 2;
-    const int splits = steps < (tiles ? 7 : 12) ? 1 : split_limit(steps, tiles), pitch = tiles ? p.part_pitch : (p.part_pitch < 32 ? p.part_pitch : 32);
+    const int splits = steps < (tiles ? 7 : 12) ? 1 : split_limit(steps, tiles, 4), pitch = tiles ? p.part_pitch : (p.part_pitch < 32 ? p.part_pitch : 32);
     const long long by_slot = (f->n_trees > AT_BLOCK ? 1024LL : 512LL) * pitch;
     return splits < 2 ? 0 : (rows * splits < by_slot ? rows * splits : by_slot);
   };
@@ -1156,11 +1173,16 @@ template <int D>
 void launch_attention(const AttnPlan& p, const AttnArgs& a, hipStream_t stream) {
   const dim3 grid((unsigned)p.grid), block(AT_BLOCK);
   if (p.shared) dsbd_launch(DSBD_KERNEL_ATTENTION, forest_attention_dma_kernel<D, D == 128 ? 2 : 3>, grid, block, 0, stream, a);
-  else if (p.nrt == 1) dsbd_launch(DSBD_KERNEL_ATTENTION, forest_attention_kernel<D, 1>, grid, block, 0, stream, a);
-  else dsbd_launch(DSBD_KERNEL_ATTENTION, forest_attention_kernel<D, 2>, grid, block, 0, stream, a);
+  else if (p.waves == 8) {
+    const dim3 wide(512);
+    if (p.nrt == 1) dsbd_launch(DSBD_KERNEL_ATTENTION, forest_attention_kernel<D, 1, 8>, grid, wide, 0, stream, a);
+    else if constexpr (D == 64) dsbd_launch(DSBD_KERNEL_ATTENTION, forest_attention_kernel<D, 2, 8>, grid, wide, 0, stream, a);
+  }
+  else if (p.nrt == 1) dsbd_launch(DSBD_KERNEL_ATTENTION, forest_attention_kernel<D, 1, 4>, grid, block, 0, stream, a);
+  else dsbd_launch(DSBD_KERNEL_ATTENTION, forest_attention_kernel<D, 2, 4>, grid, block, 0, stream, a);
   if (p.merge) {
     const long long rows = (long long)a.n_nodes * a.Hq, wgs = (rows * (D / 4) + AT_BLOCK - 1) / AT_BLOCK;
-    if (wgs < 256 && p.nsplit > 8) {          // fewer workgroups than compute units
+    if (wgs < 256 && p.nsplit >= 8) {         // fewer workgroups than compute units
       hipLaunchKernelGGL((forest_attention_combine_kernel<D, 4>), dim3((unsigned)((rows * D + AT_BLOCK - 1) / AT_BLOCK)), block, 0, stream, a);
     } else {
       hipLaunchKernelGGL((forest_attention_combine_kernel<D, 1>), dim3((unsigned)wgs), block, 0, stream, a);
@@ -1216,7 +1238,7 @@ extern "C" int32_t dsbd_forest_attention(const dsbd_forest* f, const dsbd_kv* kv
   a.scale_log2 = sc * 1.4426950408889634f;
   a.max_len = kv->max_len;
   a.by_tree = p.by_tree ? 1 : 0; a.nsplit = p.nsplit; a.n_rowblocks = p.n_rowblocks; a.rows_block = p.rows_block;
-  a.wg_slots = p.slots;
+  a.wg_slots = p.slots; a.waves = p.waves;
   a.by_split = p.by_split ? 1 : 0; a.part_pitch = p.part_pitch; a.part_stride = p.part_stride; a.part_rows = p.part_rows;
   a.out = static_cast<__bf16*>(out); a.lse = lse; a.fault = fault;
   if (D == 128) launch_attention<128>(p, a, stream);
