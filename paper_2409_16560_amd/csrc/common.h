@@ -40,10 +40,16 @@ struct DsbdKnobs {
   int verify_mute_wg;          // DSBD_VERIFY_TEST_MUTE_WG: test hook, this workgroup withholds its first post; -1 = none
   int verify_lds_slice;        // DSBD_VERIFY_LDS_SLICE: largest joint slice kept in the LDS; -1 = the plan's choice
   int warp_fast;               // DSBD_WARP_FAST: 0 = the warped rows' entries are always selected one by one, as where they crowd
+  int draft_wait_us;           // DSBD_DRAFT_WAIT_US: how long a draft step's drawing workgroups wait for a chunk before they take it
+                               // themselves (0: they always do); -1 = default
   int event_fence;             // DSBD_EVENT_FENCE: 1 = the library's cross-stream events keep HIP's system-scope fence; 0 = they order
                                // device work only (no cache write-back for the host's sake at every one)
 };
 const DsbdKnobs& dsbd_knobs();
+
+// The base of a launch's exchange tags: a number of its own for every launch of the process, with 24 bits below it for the
+// launch's exchanges (knobs.hip).
+unsigned long long dsbd_launch_nonce();
 
 // Measurement hook (timing.hip).  When timing is enabled for `kernel_id`, the launch goes through HIP's extended
 // launch call, which stamps a pair of events with the kernel's own start and end on the device (what a profiler's

@@ -2,23 +2,22 @@
 // the sampled layers as a draft forest.
 //
 // dsbd_draft_layer: W_S independent draws from q_beam = T o q/Q over (beams of the current layer) x V, by inverse CDF
-// in flat order.  Two dependent passes, two kernels that know nothing of each other's residency:
-//   1. draft_chunk_kernel: every row is cut into chunks, a workgroup per chunk; its maximum and its fp64 sum of
-//      exponentials against that maximum;
-//   2. draft_draw_kernel (a workgroup per draw) or, with warping, draft_warp_kernel (a workgroup per prompt): the row
-//      totals and beam weights out of the chunks' pairs, which every workgroup folds for itself in the same order, and
-//      then only the chunks that matter are read again: the one that holds the draw, or those that can hold one of
-//      the top_k leading entries.
-// What bounds a step is the chain of dependent memory round trips (8 MB of logits are 1.6 us at HBM rate); no
-// exchange between running workgroups is left in it.  Measured, 16 beams x 128256 tokens, 16 draws, top_k 10 / top_p
-// 0.8: chunk kernel 5.7 us and warp kernel 11.4 us, where the persistent layer kernel of the verification, which served
-// the draws before with a set-up kernel in front (its exchanges among 256 workgroups), took 42.6 + 3.2 us; 64 beams of
-// eight prompts x 32000, 8 draws each, no warping: 5.8 + 6.6 us against 27.9 + 3.4 us.
+// in flat order.  Two dependent passes:
+//   1. take_chunks: every row is cut into chunks; a chunk's maximum and its fp64 sum of exponentials against that maximum;
+//   2. draw_one (a workgroup per draw) or, with warping, draw_warped (a workgroup per prompt): the row totals and beam weights
+//      out of the chunks' pairs, which every workgroup folds for itself in the same order, and then only the chunks that
+//      matter are read again: the one that holds the draw, or those that can hold one of the top_k leading entries.
+// One launch: the second pass's workgroups stand behind the first's and wait for the pairs in tagged slots (two launches
+// under capture, and for more than DR_WAITING of them).
+// What bounds a step is the chain of dependent memory round trips (8 MB of logits are 1.6 us at HBM rate).  Measured, 16
+// beams x 128256 tokens, 16 draws, top_k 10 / top_p 0.8: 5.7 + 11.4 us in two kernels, 16.1 in one; 64 beams of eight prompts x
+// 32000, 8 draws each, no warping: 6.0 + 6.6 and 12.0 us.  The rest of the gain is the host's: a launch less is 3 us.
 //
 // dsbd_build_forest: one workgroup per prompt turns the layers' (parent row, token) lists into the
 // tree-contiguous layout the other calls expect.
 #include "common.h"
 #include "exp_nonpos.h"
+#include "slots.h"
 #include "wave_f64.h"
 #include <float.h>
 #include <limits.h>
@@ -29,6 +28,8 @@
 #define DW_WAVES (DW_BLOCK / 64)
 #define DR_MAX_CHUNKS 64       // chunks per row: one per lane
 #define DR_K_MAX 32
+#define DR_WAITING 256         // most workgroups that wait behind the chunks in one launch
+#define DR_WAIT_TICKS 20000    // 200 us of the 100 MHz wall clock: how long a wave waits for a chunk before it takes it itself
 #define DW_CAND 1024           // candidates the warped kernel ranks directly
 #define DW_DIGIT 11            // bits per pass of its radix selection
 #define BF_BLOCK 512
@@ -45,7 +46,11 @@ struct DraftArgs {
   const float* z;
   const double* cum;
   const float* u;
-  double2* part;               // [n_beams][nchunk]: maximum of the chunk, sum of exp(z - maximum)
+  double2* part;               // [n_beams][nchunk]: maximum of the chunk, sum of exp(z - maximum) ...
+  Slot* slots;                 // ... or, in one launch, [n_beams][nchunk][2]: the two in tagged slots
+  unsigned long long tag;
+  long long wait_limit;        // of every wait for a slot, in ticks of the 100 MHz wall clock
+  int chunk_wgs;               // one launch: the workgroups that take chunks; those behind them draw
   int top_k;
   float top_p;
   int32_t *out_parent, *out_token;
@@ -57,20 +62,26 @@ struct DraftArgs {
 // give 1008 workgroups, 4.4 us at best): NPT logits per thread and tile stay in registers between the maximum and the exponentials; chunks of
 // more than one tile (vocabularies above 262144 tokens) merge their tiles as they go.  Loads of 4 bytes per lane: a
 // row of an odd vocabulary starts anywhere, and 8 MB do not ask for more.
-template <int NPT>
-__global__ __launch_bounds__(DC_BLOCK) void draft_chunk_kernel(DraftArgs a) {
+// A workgroup of BLOCK threads takes BLOCK / DC_BLOCK chunks; ONE: their results go into slots for workgroups that wait.
+template <int NPT, int BLOCK, bool ONE>
+__device__ __forceinline__ void take_chunks(const DraftArgs& a, int wg) {
+  constexpr int W = DC_BLOCK / 64;
   __shared__ double tab[64];
-  __shared__ float wmax[DC_BLOCK / 64];
-  __shared__ double wsum[DC_BLOCK / 64];
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int row = blockIdx.x / a.nchunk, c = blockIdx.x - row * a.nchunk;
+  __shared__ float wmax[BLOCK / 64];
+  __shared__ double wsum[BLOCK / 64];
+  const int group = BLOCK == DC_BLOCK ? 0 : __builtin_amdgcn_readfirstlane(threadIdx.x / DC_BLOCK);
+  const int tid = threadIdx.x % DC_BLOCK, lane = threadIdx.x & 63, wave = threadIdx.x >> 6, first = group * W;
+  const long long n_items = (long long)a.n_beams * a.nchunk, item_raw = (long long)wg * (BLOCK / DC_BLOCK) + group;
+  const long long item = item_raw < n_items ? item_raw : n_items - 1;      // (the last workgroup may have threads left over)
+  const int row = (int)(item / a.nchunk), c = (int)(item - (long long)row * a.nchunk);
   const float* const z = a.z + (long long)row * a.V;
-  const int x_end = min(a.V, (c + 1) * a.chunk);
-  if (tid < 64) tab[tid] = c_draft_exp2_tab[tid];
+  const int x_lo = c * a.chunk, x_end = min(a.V, x_lo + a.chunk);
+  if (threadIdx.x < 64) tab[threadIdx.x] = c_draft_exp2_tab[threadIdx.x];
   float M = -INFINITY;
   double S = 0.0;
   bool bad = false;
-  for (int x0 = c * a.chunk; x0 < x_end; x0 += NPT * DC_BLOCK) {
+  for (int i = 0; i < a.chunk; i += NPT * DC_BLOCK) {       // (as often in every chunk: there are barriers inside)
+    const int x0 = min(x_lo + i, x_end);
     float v[NPT];
 #pragma unroll
     for (int k = 0; k < NPT; ++k) v[k] = z[min(x0 + k * DC_BLOCK + tid, x_end - 1)];     // (clamped repeats leave a maximum alone)
@@ -84,7 +95,7 @@ __global__ __launch_bounds__(DC_BLOCK) void draft_chunk_kernel(DraftArgs a) {
     __syncthreads();                                 // (the table; and the tile before has read its totals)
     if (lane == 0) wmax[wave] = m;
     __syncthreads();
-    m = fmaxf(fmaxf(wmax[0], wmax[1]), fmaxf(wmax[2], wmax[3]));
+    m = fmaxf(fmaxf(wmax[first], wmax[first + 1]), fmaxf(wmax[first + 2], wmax[first + 3]));
     const double ref = m == -INFINITY ? 0.0 : (double)m;       // a tile masked whole adds 0
     double s = 0.0;
 #pragma unroll
@@ -95,7 +106,7 @@ __global__ __launch_bounds__(DC_BLOCK) void draft_chunk_kernel(DraftArgs a) {
     s = wave_sum(s);
     if (lane == 0) wsum[wave] = s;
     __syncthreads();
-    s = (wsum[0] + wsum[1]) + (wsum[2] + wsum[3]);
+    s = (wsum[first] + wsum[first + 1]) + (wsum[first + 2] + wsum[first + 3]);
     if (m > -INFINITY) {
       const float Mn = fmaxf(M, m);
       S = (M > -INFINITY ? S * dsbd_exp_nonpos((double)M - (double)Mn, tab) : 0.0) + s * dsbd_exp_nonpos((double)m - (double)Mn, tab);
@@ -103,8 +114,16 @@ __global__ __launch_bounds__(DC_BLOCK) void draft_chunk_kernel(DraftArgs a) {
     }
   }
   if (bad) atomicOr(a.fault, DSBD_FAULT_NONFINITE);
-  if (tid == 0) a.part[(long long)row * a.nchunk + c] = make_double2((double)M, S);
+  if (item_raw >= n_items) return;
+  if constexpr (ONE) {
+    if (tid < 2) slot_post(a.slots + item * 2 + tid, tid ? S : (double)M, a.tag);
+  } else {
+    if (tid == 0) a.part[item] = make_double2((double)M, S);
+  }
 }
+
+template <int NPT>
+__global__ __launch_bounds__(DC_BLOCK) void draft_chunk_kernel(DraftArgs a) { take_chunks<NPT, DC_BLOCK, false>(a, blockIdx.x); }
 
 // A prompt's rows.  False: no usable beams (out of range or none); `bad` gets the fault bits.
 __device__ __forceinline__ bool prompt_rows(const DraftArgs& a, int p, int& r0, int& n, int& bad) {
@@ -118,16 +137,65 @@ __device__ __forceinline__ bool prompt_rows(const DraftArgs& a, int p, int& r0, 
   return n > 0;
 }
 
+// A chunk by one wave, the same sums in the same order as take_chunks forms them with four: for a wave that has waited long
+// enough for the chunk's own workgroup.
+__device__ double2 chunk_alone(const DraftArgs& a, int row, int c, const double* tab) {
+  const int lane = threadIdx.x & 63, npt = a.chunk >= 4096 ? 16 : a.chunk / DC_BLOCK;
+  const float* const z = a.z + (long long)row * a.V;
+  const int x_lo = c * a.chunk, x_end = min(a.V, x_lo + a.chunk);
+  float M = -INFINITY;
+  double S = 0.0;
+  for (int x0 = x_lo; x0 < x_end; x0 += npt * DC_BLOCK) {
+    float m = -INFINITY;
+    for (int k = 0; k < npt * (DC_BLOCK / 64); ++k) m = fmaxf(m, z[min(x0 + k * 64 + lane, x_end - 1)]);
+    m = wave_max_f32(m);
+    const double ref = m == -INFINITY ? 0.0 : (double)m;
+    double part[DC_BLOCK / 64];
+#pragma unroll
+    for (int w = 0; w < DC_BLOCK / 64; ++w) {
+      double s = 0.0;
+      for (int k = 0; k < npt; ++k) {
+        const int x = x0 + k * DC_BLOCK + w * 64 + lane;
+        const double e = dsbd_exp_nonpos((double)z[min(x, x_end - 1)] - ref, tab);
+        s += x < x_end ? e : 0.0;
+      }
+      part[w] = wave_sum(s);
+    }
+    const double s = (part[0] + part[1]) + (part[2] + part[3]);
+    if (m > -INFINITY) {
+      const float Mn = fmaxf(M, m);
+      S = (M > -INFINITY ? S * dsbd_exp_nonpos((double)M - (double)Mn, tab) : 0.0) + s * dsbd_exp_nonpos((double)m - (double)Mn, tab);
+      M = Mn;
+    }
+  }
+  return make_double2((double)M, S);
+}
+
 // What the chunks' pairs say about a prompt: every row's maximum, sum and scale (beam weight / sum, Section 2.1: the
 // joint entry of token x is exp(z - max) * scale), folded by one wave per row, a chunk per lane, in a fixed order
 // (equal rows give equal bits).  `each(row, lane's chunk maximum, its sum, row maximum, scale)` sees every chunk.
-template <int WAVES, class Each>
+template <int WAVES, bool ONE, class Each>
 __device__ __forceinline__ void fold_rows(const DraftArgs& a, int r0, int n, const double* tab, double* row_max,
                                           double* row_sum, double* row_scale, int& bad, Each&& each) {
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  auto pair = [&](int r) -> double2 {
+    double2 ms = make_double2(-INFINITY, 0.0);
+    const long long at = (long long)(r0 + r) * a.nchunk + lane;
+    if constexpr (!ONE) {
+      if (lane < a.nchunk) ms = a.part[at];
+    } else {
+      const bool have = lane >= a.nchunk || (a.wait_limit > 0 && slot_wait2(a.slots + at * 2, a.slots + at * 2 + 1, a.tag, ms.x, ms.y, a.wait_limit));
+      for (unsigned long long missing = __ballot(!have); missing; missing &= missing - 1) {
+        const int c = (int)__ffsll((long long)missing) - 1;
+        const double2 own = chunk_alone(a, r0 + r, c, tab);
+        if (lane == c) ms = own;
+      }
+    }
+    return ms;
+  };
   // the first rows' pairs are requested before anything else: their round trip runs beside the weights
   double2 first = make_double2(-INFINITY, 0.0);
-  if (wave < n && lane < a.nchunk) first = a.part[(long long)(r0 + wave) * a.nchunk + lane];
+  if (!ONE && wave < n) first = pair(wave);
   // beam weights = softmax of the stored likelihoods (Section 2.1), every wave for itself
   const double cm = lane < n ? a.cum[r0 + lane] : -INFINITY;
   const double top = wave_max_f64(cm);
@@ -136,11 +204,7 @@ __device__ __forceinline__ void fold_rows(const DraftArgs& a, int r0, int n, con
   const double e = lane < n ? dsbd_exp_nonpos(cm - top, tab) : 0.0;
   const double w = e / wave_sum(e);
   for (int r = wave; r < n; r += WAVES) {
-    double2 ms = first;
-    if (r != wave) {
-      ms = make_double2(-INFINITY, 0.0);
-      if (lane < a.nchunk) ms = a.part[(long long)(r0 + r) * a.nchunk + lane];
-    }
+    const double2 ms = ONE || r != wave ? pair(r) : first;
     const double M = wave_max_f64(ms.x);
     double share = ms.x > -INFINITY ? ms.y * dsbd_exp_nonpos(ms.x - M, tab) : 0.0;
     const double S = wave_sum(share);
@@ -178,13 +242,14 @@ __device__ __forceinline__ int first_above(double incl, double mass, double targ
 
 // ---- pass 2, no warping: one draw per workgroup, so that the draws' dependent round trips (pairs, chunk, group) run side
 // by side; 6.6 us whatever the number of draws.
-__global__ __launch_bounds__(DD_BLOCK) void draft_draw_kernel(DraftArgs a) {
+template <bool ONE>
+__device__ __forceinline__ void draw_one(const DraftArgs& a, int wg) {
   __shared__ double tab[64];
   __shared__ double row_max[64], row_sum[64], row_scale[64], row_mass[64];
   __shared__ double pre[64 * DR_MAX_CHUNKS];       // inclusive prefixes of the chunks' masses inside their row
   __shared__ double group[64];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int p = blockIdx.x / a.W_S, j = blockIdx.x - p * a.W_S;
+  const int p = wg / a.W_S, j = wg - p * a.W_S;
   int r0, n, bad = 0;
   const bool any = prompt_rows(a, p, r0, n, bad);
   if (!any) {
@@ -194,7 +259,7 @@ __global__ __launch_bounds__(DD_BLOCK) void draft_draw_kernel(DraftArgs a) {
   const double u = (double)a.u[(long long)p * a.W_S + j];
   if (tid < 64) tab[tid] = c_draft_exp2_tab[tid];
   __syncthreads();
-  fold_rows<DD_BLOCK / 64>(a, r0, n, tab, row_max, row_sum, row_scale, bad,
+  fold_rows<DD_BLOCK / 64, ONE>(a, r0, n, tab, row_max, row_sum, row_scale, bad,
                            [&](int r, double, double share, double, double scale) {
     const double incl = wave_inclusive_scan(share * scale);
     pre[r * DR_MAX_CHUNKS + lane] = incl;
@@ -245,6 +310,14 @@ __global__ __launch_bounds__(DD_BLOCK) void draft_draw_kernel(DraftArgs a) {
   if (lane == 0) write_draw(a, p, j, r0 + r, pick, M, row_sum[r]);
 }
 
+__global__ __launch_bounds__(DD_BLOCK) void draft_draw_kernel(DraftArgs a) { draw_one<false>(a, blockIdx.x); }
+
+template <int NPT>
+__global__ __launch_bounds__(DD_BLOCK) void draft_one_kernel(DraftArgs a) {
+  if ((int)blockIdx.x < a.chunk_wgs) take_chunks<NPT, DD_BLOCK, true>(a, blockIdx.x);
+  else draw_one<true>(a, (int)blockIdx.x - a.chunk_wgs);
+}
+
 // ---- pass 2 with warping T (Section 2.1): the top_k first joint entries (by value, equal values by flat index), of
 // those the shortest leading part whose share exceeds top_p, renormalised; all of a prompt's draws from that list.
 struct WarpShared {
@@ -278,10 +351,11 @@ __device__ __forceinline__ void bound_of_groups(WarpShared& sh, double g, int K)
   }
 }
 
-__global__ __launch_bounds__(DW_BLOCK) void draft_warp_kernel(DraftArgs a) {
+template <bool ONE>
+__device__ __forceinline__ void draw_warped(const DraftArgs& a, int p) {
   __shared__ WarpShared sh;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int p = blockIdx.x, K = a.top_k, V = a.V;
+  const int K = a.top_k, V = a.V;
   int r0, n, bad = 0;
   const bool any = prompt_rows(a, p, r0, n, bad);
   if (!any) {
@@ -293,7 +367,7 @@ __global__ __launch_bounds__(DW_BLOCK) void draft_warp_kernel(DraftArgs a) {
   if (tid < 64) sh.tab[tid] = c_draft_exp2_tab[tid];
   if (tid == 0) { sh.n_list = 0; sh.n_cand = 0; sh.bound = -1.0; }
   __syncthreads();
-  fold_rows<DW_WAVES>(a, r0, n, sh.tab, sh.row_max, sh.row_sum, sh.row_scale, bad,
+  fold_rows<DW_WAVES, ONE>(a, r0, n, sh.tab, sh.row_max, sh.row_sum, sh.row_scale, bad,
                       [&](int r, double m, double, double M, double scale) {
     if (lane < a.nchunk) sh.cmax[r * a.nchunk + lane] = m > -INFINITY ? dsbd_exp_nonpos(m - M, sh.tab) * scale : -1.0;
   });
@@ -507,6 +581,14 @@ __global__ __launch_bounds__(DW_BLOCK) void draft_warp_kernel(DraftArgs a) {
   }
 }
 
+__global__ __launch_bounds__(DW_BLOCK) void draft_warp_kernel(DraftArgs a) { draw_warped<false>(a, blockIdx.x); }
+
+template <int NPT>
+__global__ __launch_bounds__(DW_BLOCK) void draft_warp_one_kernel(DraftArgs a) {
+  if ((int)blockIdx.x < a.chunk_wgs) take_chunks<NPT, DW_BLOCK, true>(a, blockIdx.x);
+  else draw_warped<true>(a, (int)blockIdx.x - a.chunk_wgs);
+}
+
 int32_t check_draft(const dsbd_draft_in* in, int32_t W_S) {
   if (!in) return DSBD_ERR_INVALID;
   if (in->n_prompts < 0 || in->n_beams < 0 || in->max_prompt_beams < 0) return DSBD_ERR_INVALID;
@@ -544,7 +626,7 @@ extern "C" size_t dsbd_draft_layer_workspace_bytes(const dsbd_draft_in* in, int3
   int chunk, nchunk;
   draft_chunks(in, &chunk, &nchunk);
   WorkspaceCarver ws(nullptr);
-  ws.take<double2>((size_t)in->n_beams * nchunk);
+  ws.take<Slot>((size_t)in->n_beams * nchunk * 2);
   return ws.total() + 256;
 }
 
@@ -564,17 +646,44 @@ extern "C" int32_t dsbd_draft_layer(const dsbd_draft_in* in, int32_t W_S, int32_
   DraftArgs a;
   draft_chunks(in, &a.chunk, &a.nchunk);
   WorkspaceCarver ws(reinterpret_cast<char*>(dsbd_align_up(reinterpret_cast<uintptr_t>(workspace), 256)));
-  a.part = ws.take<double2>((size_t)in->n_beams * a.nchunk);
+  a.slots = ws.take<Slot>((size_t)in->n_beams * a.nchunk * 2);
+  a.part = reinterpret_cast<double2*>(a.slots);
   a.n_prompts = in->n_prompts; a.n_beams = in->n_beams; a.max_prompt_beams = in->max_prompt_beams; a.V = in->V; a.W_S = W_S;
   a.beam_off = in->beam_off; a.z = in->logits_draft; a.cum = in->beam_logp_draft; a.u = in->u;
   a.top_k = top_k; a.top_p = (top_p > 0.0f && top_p < 1.0f) ? top_p : 1.0f;
   a.out_parent = out->parent; a.out_token = out->token; a.out_logp = out->logp_draft; a.fault = fault;
-  const dim3 grid((unsigned)in->n_beams * (unsigned)a.nchunk);
-  if (a.chunk == 1024) hipLaunchKernelGGL(draft_chunk_kernel<4>, grid, dim3(DC_BLOCK), 0, stream, a);
-  else if (a.chunk == 2048) hipLaunchKernelGGL(draft_chunk_kernel<8>, grid, dim3(DC_BLOCK), 0, stream, a);
-  else hipLaunchKernelGGL(draft_chunk_kernel<16>, grid, dim3(DC_BLOCK), 0, stream, a);
-  if (top_k > 0) hipLaunchKernelGGL(draft_warp_kernel, dim3((unsigned)in->n_prompts), dim3(DW_BLOCK), 0, stream, a);
-  else hipLaunchKernelGGL(draft_draw_kernel, dim3((unsigned)in->n_prompts * (unsigned)W_S), dim3(DD_BLOCK), 0, stream, a);
+  const long long n_chunks = (long long)in->n_beams * a.nchunk;
+  const long long draws = top_k > 0 ? in->n_prompts : (long long)in->n_prompts * W_S;
+  // One launch: the drawing workgroups stand behind those that take the chunks and wait for their results.  The workgroups in
+  // front wait for nobody, and a wait that lasts (other streams' work can keep them from starting) ends with the waiting wave
+  // taking the chunk itself, so nothing depends on what runs beside it.  Not under capture, where a replay would repeat the
+  // tags.  Measured, us per step: 8 to 16 beams x 128256, warped, 17.1 on the device in two kernels, 16.1 in one; 6 us of host
+  // time in two launches, 2.9 in one.
+  hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
+  const bool capturing = hipStreamIsCapturing(stream, &cs) != hipSuccess || cs != hipStreamCaptureStatusNone;
+  if (!capturing && draws <= DR_WAITING) {
+    const DsbdKnobs& knobs = dsbd_knobs();
+    a.tag = exchange_tag(dsbd_launch_nonce());
+    a.wait_limit = knobs.draft_wait_us >= 0 ? knobs.draft_wait_us * 100LL : DR_WAIT_TICKS;
+    const int block = top_k > 0 ? DW_BLOCK : DD_BLOCK, per_wg = block / DC_BLOCK;
+    a.chunk_wgs = (int)((n_chunks + per_wg - 1) / per_wg);
+    const dim3 grid((unsigned)(a.chunk_wgs + draws));
+    auto launch = [&](auto warped, auto plain) {
+      if (top_k > 0) hipLaunchKernelGGL(warped, grid, dim3(DW_BLOCK), 0, stream, a);
+      else hipLaunchKernelGGL(plain, grid, dim3(DD_BLOCK), 0, stream, a);
+    };
+    if (a.chunk == 1024) launch(draft_warp_one_kernel<4>, draft_one_kernel<4>);
+    else if (a.chunk == 2048) launch(draft_warp_one_kernel<8>, draft_one_kernel<8>);
+    else launch(draft_warp_one_kernel<16>, draft_one_kernel<16>);
+  } else {
+    if (capturing) (void)hipGetLastError();
+    const dim3 grid((unsigned)n_chunks);
+    if (a.chunk == 1024) hipLaunchKernelGGL(draft_chunk_kernel<4>, grid, dim3(DC_BLOCK), 0, stream, a);
+    else if (a.chunk == 2048) hipLaunchKernelGGL(draft_chunk_kernel<8>, grid, dim3(DC_BLOCK), 0, stream, a);
+    else hipLaunchKernelGGL(draft_chunk_kernel<16>, grid, dim3(DC_BLOCK), 0, stream, a);
+    if (top_k > 0) hipLaunchKernelGGL(draft_warp_kernel, dim3((unsigned)draws), dim3(DW_BLOCK), 0, stream, a);
+    else hipLaunchKernelGGL(draft_draw_kernel, dim3((unsigned)draws), dim3(DD_BLOCK), 0, stream, a);
+  }
   DSBD_HIP_LAUNCH_CHECK();
   return DSBD_OK;
 }

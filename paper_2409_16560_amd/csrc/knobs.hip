@@ -26,6 +26,7 @@ void load(DsbdKnobs& k) {
   k.verify_mute_wg = env_int("DSBD_VERIFY_TEST_MUTE_WG", -1);
   k.verify_lds_slice = env_int("DSBD_VERIFY_LDS_SLICE", -1);
   k.warp_fast = env_int("DSBD_WARP_FAST", 1);
+  k.draft_wait_us = env_int("DSBD_DRAFT_WAIT_US", -1);
   k.event_fence = env_int("DSBD_EVENT_FENCE", 0);
 }
 }  // namespace
@@ -39,6 +40,11 @@ const DsbdKnobs& dsbd_knobs() {
     }
   }
   return g_knobs;
+}
+
+unsigned long long dsbd_launch_nonce() {
+  static std::atomic<unsigned long long> launches{0};
+  return (launches.fetch_add(1, std::memory_order_relaxed) + 1) << 24;
 }
 
 extern "C" void dsbd_reload_knobs(void) {

@@ -30,6 +30,7 @@
 #include "common.h"
 #include "topology_device.h"
 #include "exp_nonpos.h"
+#include "slots.h"
 #include "verify_rows.h"
 #include "wave_f64.h"
 #include <type_traits>
@@ -259,48 +260,6 @@ __device__ __forceinline__ void lds_barrier() {
 //  * the three hops of the warping merge (every workgroup -> its group's first -> the prompt's first -> every
 //    workgroup) have a bank each: nobody posts a hop of the next layer before having received the result of
 //    this one, which exists only after every reader of the earlier hops is done.
-struct Slot { unsigned long long w0, w1; };
-
-__device__ __forceinline__ unsigned long long exchange_tag(unsigned long long epoch) {
-  return epoch * 0x9E3779B97F4A7C15ull;
-}
-
-__device__ __forceinline__ void slot_post(Slot* s, double v, unsigned long long tag) {
-  const unsigned long long b = (unsigned long long)__double_as_longlong(v);
-  __hip_atomic_store(&s->w0, b, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-  __hip_atomic_store(&s->w1, b ^ tag, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
-
-// Waits until the slot carries the tag; gives up after `limit` ticks of the wall clock (returns false).
-__device__ __forceinline__ bool slot_wait(Slot* s, unsigned long long tag, double& v, long long limit) {
-  long long t0 = 0;
-  for (int spin = 0;; ++spin) {
-    const unsigned long long w0 = __hip_atomic_load(&s->w0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    const unsigned long long w1 = __hip_atomic_load(&s->w1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    if ((w0 ^ w1) == tag) { v = __longlong_as_double((long long)w0); return true; }
-    if (spin == 0) t0 = wall_clock64();
-    else if ((spin & 15) == 0 && wall_clock64() - t0 > limit) return false;
-    __builtin_amdgcn_s_sleep(1);
-  }
-}
-
-// The same for two slots at once (their loads in flight together).
-__device__ __forceinline__ bool slot_wait2(Slot* s0, Slot* s1, unsigned long long tag, double& v0, double& v1, long long limit) {
-  long long t0 = 0;
-  bool h0 = false, h1 = false;
-  for (int spin = 0;; ++spin) {
-    unsigned long long a0 = 0, a1 = 0, b0 = 0, b1 = 0;
-    if (!h0) { a0 = __hip_atomic_load(&s0->w0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); a1 = __hip_atomic_load(&s0->w1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
-    if (!h1) { b0 = __hip_atomic_load(&s1->w0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); b1 = __hip_atomic_load(&s1->w1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
-    if (!h0 && (a0 ^ a1) == tag) { v0 = __longlong_as_double((long long)a0); h0 = true; }
-    if (!h1 && (b0 ^ b1) == tag) { v1 = __longlong_as_double((long long)b0); h1 = true; }
-    if (h0 && h1) return true;
-    if (spin == 0) t0 = wall_clock64();
-    else if ((spin & 15) == 0 && wall_clock64() - t0 > limit) return false;
-    __builtin_amdgcn_s_sleep(1);
-  }
-}
-
 // Single-value exchanges: workgroup w owns the slot at the start of its own 128-byte line of the bank (slot index
 // w * LINE_SLOTS), so that no two workgroups ever write the same cache line.  Measured with a microbenchmark
 // on this chip, all-to-all among 256 workgroups: 2.3 us with a line per workgroup, 3.1 us with the words packed
@@ -2412,8 +2371,6 @@ int statistics_threads(const dsbd_forest* f, const VerifyPlan& pl, unsigned rows
   return threads;
 }
 
-std::atomic<unsigned long long> g_launch_counter{0};
-
 // In front of a layer kernel that is recorded into a graph: every replay repeats the launch's arguments, so what tells
 // its exchange slots from those of the replay before is this count (whatever the word held to begin with).
 __global__ void bump_replay_count_kernel(unsigned long long* count) { *count += 1; }
@@ -2502,7 +2459,7 @@ int32_t verify_impl(const dsbd_forest* f, const dsbd_verify_in* in, const dsbd_p
   la.mute_wg = knobs.verify_mute_wg;   // error-path test hook
   // Exchange slots carry a tag made of this number and the exchange's index: nothing an earlier launch left in the
   // workspace can pass for a value of this one, so the slots need no clearing.
-  la.nonce = (g_launch_counter.fetch_add(1, std::memory_order_relaxed) + 1) << 24;
+  la.nonce = dsbd_launch_nonce();
   la.replay = nullptr;
   la.rec = nullptr; la.rec_stride = 0; la.rec_compact = 0;
   if (capturing && !warped) {
