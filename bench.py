@@ -182,7 +182,7 @@ def commit_measurement(dsbd, torch, case, reps=10):
     nx = o["nx"]
     torch.cuda.synchronize()
     n_next, src_tree, path_len = nx.n_next.cpu().numpy(), nx.src_tree.cpu().numpy(), nx.path_len.cpu().numpy()
-    dst_k, dst_v, taken, moved = [], [], set(), 0
+    dst_k, dst_v, taken, read, moved = [], [], set(), set(), 0
     row = w.Hkv * w.D * 2
     for p in range(w.n_prompts):
         for s_ in range(w.W_cap):
@@ -192,7 +192,8 @@ def commit_measurement(dsbd, torch, case, reps=10):
                 moved += int(path_len[p, s_]) * row * 2 * 2
             elif b >= 0:
                 dst_k.append(mk()); dst_v.append(mk())
-                moved += (L[b] + int(path_len[p, s_])) * row * 2 * 2
+                moved += (L[b] * (1 if b in read else 2) + 2 * int(path_len[p, s_])) * row * 2      # (a source is read once)
+                read.add(b)
             else:
                 dst_k.append(None); dst_v.append(None)
     dst = dsbd.KVDst(dst_k, dst_v, kv)
@@ -209,7 +210,7 @@ def commit_measurement(dsbd, torch, case, reps=10):
     return {"ms": med, "next_beams": int(n_next.sum()), "continued_in_place": len(taken),
             "bytes_read_plus_written": moved, "achieved": moved / (med * 1e-3) / 1e9 if med > 0 else 0.0,
             "peak": HBM_PEAK_GBS, "unit": "GB/s", "frac": (moved / (med * 1e-3) / 1e9 / HBM_PEAK_GBS) if med > 0 else 0.0,
-            "note": "copies count read + write; not included in value / ms_per_step"}
+            "note": "every source read once, every copy written; not included in value / ms_per_step"}
 
 
 def main():

@@ -115,4 +115,4 @@ extern "C" int32_t dsbd_select_beams(const dsbd_forest* f, const dsbd_verify_out
   return DSBD_OK;
 }
 
-extern "C" const char* dsbd_version(void) { return "dsbd 0.8 (gfx950)"; }
+extern "C" const char* dsbd_version(void) { return "dsbd 0.9 (gfx950)"; }

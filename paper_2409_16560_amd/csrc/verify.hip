@@ -213,6 +213,8 @@ struct LayerShared {
   int U_idx[64];
   double U_p[64], U_q[64];
   int nU;
+  unsigned long long warp_bound[2];  // bits of a lower bound of the K-th entry of either joint ...
+  int warp_kept[2];                  // ... and the entries that reach it
   int last_mass[2];                  // draws: the last workgroup that holds any mass, of either kind of weights
   int state[2];                      // outcome of the decision rounds, alternating entries
   int kmax, counter, abort, found, sbad, sgamma;
@@ -1216,11 +1218,10 @@ void verify_layers_kernel(LayersArgs a) {
       // equal values), then their ranks by counting.
       const int K = a.top_k, n_cand = nI * K;            // at most 64 x 32 per model
       typedef __attribute__((address_space(3))) int lds_i32;
-      typedef double f64x2 __attribute__((ext_vector_type(2)));
-      typedef __attribute__((address_space(3))) f64x2 lds_f64x2;
-      const int stride = (n_cand + 1) & ~1;
+      const int stride = n_cand;
       lds_f64* const cv = (lds_f64*)dyn_lds;             // [2][stride] values of p_beam's and q_beam's entries, row by row, then
-      lds_i32* const ci = (lds_i32*)(dyn_lds + 2 * stride);      // their flat indices
+      lds_i32* const ci = (lds_i32*)(dyn_lds + 2 * stride);      // their flat indices, and
+      lds_i32* const kept = ci + 2 * stride;                     // the numbers of those that can be among the K first
       lds_f64* const lv = (lds_f64*)sh.Pa; lds_i32* const li = (lds_i32*)sh.Pb;      // the K first of either, in rank order
       lds_barrier();                                     // the beam weights are there
       for (int t = tid; t < 2 * n_cand; t += VL_BLOCK) {
@@ -1237,37 +1238,55 @@ void verify_layers_kernel(LayersArgs a) {
         ci[m * stride + e] = real ? i * V + x.x : INT_MAX;
       }
       if (tid < 2 * K) { lv[tid] = -1.0; li[tid] = INT_MAX; }      // ("none", which sorts last)
-      if (tid < 2 && stride > n_cand) cv[tid * stride + n_cand] = -1.0;
+      if (tid < 2) { sh.warp_bound[tid] = 0ull; sh.warp_kept[tid] = 0; }
       __syncthreads();
       stamp(60);
-      // Ranks by counting the entries ahead, PT threads each (of equal values the one in front has the lower index: rows are in
-      // index order, and so are equal logits of a row).  A single row's list has the ranks already.  (Merging the rows' lists
-      // entry by entry, a row per lane, took 0.24 us an entry.)
+      // Ranks by counting the entries ahead (of equal values the one in front has the lower index: rows are in index order, and
+      // so are equal logits of a row).  A single row's list has the ranks already.
       if (nI == 1) {
         for (int t = tid; t < 2 * K; t += VL_BLOCK) {
           const int m = t >= K ? 1 : 0, r = t - m * K;
           if (cv[m * stride + r] >= 0.0) { lv[t] = cv[m * stride + r]; li[t] = ci[m * stride + r]; }
         }
       } else {
-        int PT = 16;
-        while (PT > 1 && PT * 2 * n_cand > VL_BLOCK) PT >>= 1;
-        const int part = tid & (PT - 1);
-        for (int t0 = 0; t0 < 2 * n_cand; t0 += VL_BLOCK / PT) {
-          const int t = t0 + tid / PT;
-          const bool has = t < 2 * n_cand;
-          const int m = has && t >= n_cand ? 1 : 0, e = has ? t - m * n_cand : 0;
+        // First a lower bound of the K-th entry: in column c of the rows' lists, the ceil(K / (c + 1))-th largest entry has
+        // c + 1 entries of each of so many rows at or above it.  The best of these bounds leaves little more than K entries.
+        // (Counting among all, 8 rows: K = 10 2.2 us, K = 20 7.1, K = 32 12.7.)
+        for (int t = tid; t < 2 * n_cand; t += VL_BLOCK) {
+          const int m = t >= n_cand ? 1 : 0, e = t - m * n_cand, i = e / K, c = e - i * K;
+          const lds_f64* const all = cv + m * stride;
+          const double v = all[e];
+          int ahead = 0;
+#pragma unroll 4
+          for (int o = 0; o < nI; ++o) { const double w = all[o * K + c]; ahead += (w > v) | ((w == v) & (o < i)); }
+          if (v >= 0.0 && ahead == (K + c) / (c + 1) - 1) atomicMax(&sh.warp_bound[m], (unsigned long long)__double_as_longlong(v));
+        }
+        __syncthreads();
+        for (int t = tid; t < 2 * n_cand; t += VL_BLOCK) {
+          const int m = t >= n_cand ? 1 : 0, e = t - m * n_cand;
+          const double v = cv[m * stride + e];
+          if (v >= 0.0 && v >= __longlong_as_double((long long)sh.warp_bound[m])) kept[m * stride + atomicAdd(&sh.warp_kept[m], 1)] = e;
+        }
+        __syncthreads();
+        const int n_p = sh.warp_kept[0], n_all = n_p + sh.warp_kept[1];
+        for (int t0 = 0; t0 < n_all; t0 += VL_BLOCK / 8) {      // eight threads an entry
+          const int t = t0 + (tid >> 3);
+          const bool has = t < n_all;
+          const int m = has && t >= n_p ? 1 : 0;
+          const lds_i32* const mine = kept + m * stride;
+          const int e = has ? mine[t - m * n_p] : 0, n_m = has ? (m ? n_all - n_p : n_p) : 0;
           const double v = cv[m * stride + e];
           int rank = 0;
-          if (has && v >= 0.0) {
-            const lds_f64x2* const all = (const lds_f64x2*)(cv + m * stride);
-#pragma unroll 8
-            for (int c = part; c < stride / 2; c += PT) {
-              const f64x2 o = all[c];
-              rank += ((o.x > v) | ((o.x == v) & (2 * c < e))) + ((o.y > v) | ((o.y == v) & (2 * c + 1 < e)));
-            }
+#pragma unroll 4
+          for (int c = tid & 7; c < n_m; c += 8) {
+            const int oe = mine[c];
+            const double o = cv[m * stride + oe];
+            rank += (o > v) | ((o == v) & (oe < e));
           }
-          for (int off = 1; off < PT; off <<= 1) rank += __shfl_xor(rank, off);
-          if (has && v >= 0.0 && part == 0 && rank < K) { lv[m * K + rank] = v; li[m * K + rank] = ci[m * stride + e]; }
+          rank += __shfl_xor(rank, 1);
+          rank += __shfl_xor(rank, 2);
+          rank += __shfl_xor(rank, 4);
+          if (has && (tid & 7) == 0 && rank < K) { lv[m * K + rank] = v; li[m * K + rank] = ci[m * stride + e]; }
         }
       }
       __syncthreads();
@@ -1287,6 +1306,7 @@ void verify_layers_kernel(LayersArgs a) {
           // (the lists are read from the LDS, every lane of a half the same word: one read serves 32 lanes; lane
           // reads of the other lanes' registers cost a scalar round trip each)
           const int own = is_q ? K : 0, oth = is_q ? 0 : K;
+#pragma unroll 8
           for (int c = 0; c < K; ++c) {
             const int i_own = li[own + c], i_oth = li[oth + c];
             const double v_own = i_own != INT_MAX ? lv[own + c] : 0.0;
@@ -1319,6 +1339,7 @@ void verify_layers_kernel(LayersArgs a) {
           lds_i32* const vx = (lds_i32*)sh.A_idx;
           vx[lane] = valid ? ix : INT_MAX;
           wave_lds_fence();
+#pragma unroll 8
           for (int c = 0; c < K; ++c) rank += (vx[c] < ix ? 1 : 0) + (vx[32 + c] < ix ? 1 : 0);
         }
         if (valid) { sh.U_idx[rank] = ix; sh.U_p[rank] = is_q ? 0.0 : w; sh.U_q[rank] = is_q ? w : other; }
@@ -2275,7 +2296,7 @@ VerifyPlan warped_plan(const dsbd_forest* f, const dsbd_params* p) {
   pl.I_cap = p->W_cap > f->max_prompt_trees ? p->W_cap : f->max_prompt_trees;
   pl.G = 1;
   pl.group = f->n_prompts;
-  pl.lds_bytes = dsbd_align_up((size_t)2 * (pl.I_cap * p->top_k + 1) * (sizeof(double) + sizeof(int)), 16);     // a layer's candidates
+  pl.lds_bytes = dsbd_align_up((size_t)2 * pl.I_cap * p->top_k * (sizeof(double) + 2 * sizeof(int)), 16);     // a layer's candidates
   return pl;
 }
 
@@ -2285,8 +2306,7 @@ size_t carve_warped(WorkspaceCarver& ws, const dsbd_forest* f, const RowsPlan& r
   const bool in_records = rp.compact && rp.nchunk == 1;
   ra->part = ws.take<double2>(in_records ? 0 : rows * rp.nchunk);
   if (in_records) ra->part = nullptr;
-  ra->sub = ws.take<float>(in_records ? 0 : rows * rp.nchunk * VR_SUBS);
-  if (in_records) ra->sub = nullptr;
+  ra->sub = ws.take<float>(rows * rp.nchunk * rp.parts);
   ra->rec = ws.take<char>(rows * (size_t)rp.rec_stride);
   return ws.total();
 }
@@ -2487,7 +2507,7 @@ int32_t verify_impl(const dsbd_forest* f, const dsbd_verify_in* in, const dsbd_p
     }
   }
   if (warped) {
-    ra.n_nodes = f->n_nodes; ra.V = in->V; ra.K = p->top_k; ra.chunk = rp.chunk; ra.nchunk = rp.nchunk;
+    ra.n_nodes = f->n_nodes; ra.V = in->V; ra.K = p->top_k; ra.chunk = rp.chunk; ra.nchunk = rp.nchunk; ra.parts = rp.parts;
     ra.alias = la.alias; ra.zp = in->logits_target; ra.zq = in->logits_draft;
     ra.parent = f->parent; ra.token = f->token; ra.rec_stride = rp.rec_stride; ra.compact = rp.compact;
     ra.lse_p = out->lse_target; ra.lse_q = out->lse_draft; ra.logp_p = out->node_logp_target; ra.logp_q = out->node_logp_draft;

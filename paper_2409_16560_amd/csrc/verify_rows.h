@@ -4,7 +4,7 @@
 #include "common.h"
 
 #define VR_MAX_CHUNKS 128      // chunks per row: two per lane where they are folded
-#define VR_SUBS 2              // parts of a chunk whose maxima are kept
+#define VR_WHOLE 4096          // rows of up to so many logits are read whole where their entries are selected
 #define VR_K_MAX 32
 
 // A row's record: `sum` (of exp(z - max)), `max`, the number of entries, then the entries (logit, token) by descending
@@ -14,6 +14,7 @@ struct RowEntry { float z; int x; };
 
 struct RowsPlan {
   int chunk, nchunk;           // logits per chunk (a power of two), chunks per row
+  int parts;                   // parts of a chunk whose maxima are kept (0: none; rows of up to VR_WHOLE logits)
   int compact;                 // > 0: the entries are tokens of so many bytes (1 or 2), whose logits are looked up again
   long long rec_stride;        // bytes from record to record
 };
@@ -24,6 +25,8 @@ inline RowsPlan rows_plan(int V, int K, int compact) {
   while ((V + c - 1) / c > VR_MAX_CHUNKS) c *= 2;
   r.chunk = (int)c;
   r.nchunk = (int)((V + c - 1) / c);
+  // parts so short that a row has more of them than entries are ever asked for, and no more than 256
+  r.parts = V <= VR_WHOLE ? 0 : V <= 16384 ? 16 : V <= 65536 ? 4 : 2;
   r.compact = compact;
   const size_t entries = (size_t)(K < V ? K : V);
   r.rec_stride = compact ? (long long)dsbd_align_up(sizeof(RowHead) + entries * compact, 8)
@@ -32,12 +35,12 @@ inline RowsPlan rows_plan(int V, int K, int compact) {
 }
 
 struct RowsArgs {
-  int n_nodes, V, K, chunk, nchunk;
+  int n_nodes, V, K, chunk, nchunk, parts;
   int alias;                   // one model in both roles: one row per node, whose outputs serve both
   const float *zp, *zq;
   const int32_t *parent, *token;
   double2* part;               // [rows][nchunk]: maximum of the chunk, sum of exp(z - maximum); null (rows of one chunk): in the records
-  float* sub;                  // [rows][nchunk * VR_SUBS]: maxima of the chunk's parts; null (rows of one chunk): not kept
+  float* sub;                  // [rows][nchunk * parts]: maxima of the chunk's parts
   char* rec;                   // [rows] records, `rec_stride` bytes apart
   int compact;
   long long rec_stride;

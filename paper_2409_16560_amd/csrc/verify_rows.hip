@@ -25,6 +25,7 @@
 #define VR_BLOCK 256           // chunk kernel
 #define VR_ROW_BLOCK 1024      // row kernel
 #define VR_ROW_WAVES (VR_ROW_BLOCK / 64)
+#define VR_PARTS 256            // most parts of a row
 #define VR_CAND 1024           // candidates that are ranked directly
 
 namespace {
@@ -60,18 +61,27 @@ __device__ __forceinline__ Tile load_tile(const float* __restrict__ z, int x0, i
   return t;
 }
 
-// The maxima of a tile's halves, its maximum and its sum of exponentials against that.
-__device__ __forceinline__ void take_tile(const Tile& t, const double* tab, bool& bad, float (&half)[VR_SUBS], float& m, double& s) {
+// The maxima of a tile's parts (PARTS 2 or 4: in every lane; 16: of four lanes' rows and four loads, lane l's row's in
+// part[k]), its maximum and its sum of exponentials against that.
+template <int PARTS>
+__device__ __forceinline__ void take_tile(const Tile& t, const double* tab, bool& bad, float (&part)[4], float& m, double& s) {
+  float q[4];
 #pragma unroll
-  for (int p = 0; p < VR_SUBS; ++p) {
-    float q = -INFINITY;
+  for (int k = 0; k < 4; ++k) {
+    q[k] = fmaxf(fmaxf(t.v[k][0], t.v[k][1]), fmaxf(t.v[k][2], t.v[k][3]));
 #pragma unroll
-    for (int k = 2 * p; k < 2 * p + 2; ++k)
-#pragma unroll
-      for (int e = 0; e < 4; ++e) { q = fmaxf(q, t.v[k][e]); bad |= !(t.v[k][e] <= FLT_MAX); }      // NaN or +Inf
-    half[p] = wave_max_f32(q);
+    for (int e = 0; e < 4; ++e) bad |= !(t.v[k][e] <= FLT_MAX);      // NaN or +Inf
   }
-  m = fmaxf(half[0], half[1]);
+  if constexpr (PARTS == 2 || PARTS == 0) {
+    part[0] = wave_max_f32(fmaxf(q[0], q[1]));
+    part[1] = wave_max_f32(fmaxf(q[2], q[3]));
+    m = fmaxf(part[0], part[1]);
+  } else {
+#pragma unroll
+    for (int k = 0; k < 4; ++k) part[k] = PARTS == 4 ? wave_max_f32(q[k]) : row16_max_f32(q[k]);
+    m = fmaxf(fmaxf(part[0], part[1]), fmaxf(part[2], part[3]));
+    if constexpr (PARTS == 16) m = wave_max_f32(m);
+  }
   const double ref = m == -INFINITY ? 0.0 : (double)m;     // (a tile masked whole adds 0)
   double sum[4] = {0.0, 0.0, 0.0, 0.0};
 #pragma unroll
@@ -84,7 +94,7 @@ __device__ __forceinline__ void take_tile(const Tile& t, const double* tab, bool
 // SINGLE: a chunk is one tile (rows of up to 131072 logits); else several, merged as they go.  A chunk per wave and as many
 // waves as there are chunks: those that wait for their logits and those that work on theirs mix by themselves (four resident
 // waves per SIMD that take chunk after chunk, the next two on their way: 2 us slower on 54 MB).
-template <bool SINGLE>
+template <bool SINGLE, int PARTS>
 __global__ __launch_bounds__(VR_BLOCK) void verify_chunk_kernel(RowsArgs a, int rows) {
   __shared__ double tab[64];
   const int lane = threadIdx.x & 63;
@@ -99,16 +109,16 @@ __global__ __launch_bounds__(VR_BLOCK) void verify_chunk_kernel(RowsArgs a, int 
   __syncthreads();
   if (!live) return;
   bool bad = false;
-  float sub[VR_SUBS], M;
+  float sub[4], M;
   double S;
-  take_tile(first, tab, bad, sub, M, S);
+  take_tile<PARTS>(first, tab, bad, sub, M, S);
   if constexpr (!SINGLE) {
-    float part[VR_SUBS] = {M, -INFINITY};                  // (a part is half of the chunk: whole tiles)
+    float part[2] = {M, -INFINITY};                        // (a part is half of the chunk: whole tiles)
     for (int x0 = x_lo + VR_TILE; x0 < x_hi; x0 += VR_TILE) {
       float m;
       double s;
-      take_tile(load_tile(z, x0, x_hi), tab, bad, sub, m, s);
-      if (x0 - x_lo < a.chunk / VR_SUBS) part[0] = fmaxf(part[0], m); else part[1] = fmaxf(part[1], m);
+      take_tile<2>(load_tile(z, x0, x_hi), tab, bad, sub, m, s);
+      if (x0 - x_lo < a.chunk / 2) part[0] = fmaxf(part[0], m); else part[1] = fmaxf(part[1], m);
       if (m > -INFINITY) {
         const float Mn = fmaxf(M, m);
         S = (M > -INFINITY ? S * dsbd_exp_nonpos((double)M - (double)Mn, tab) : 0.0) + s * dsbd_exp_nonpos((double)m - (double)Mn, tab);
@@ -121,7 +131,14 @@ __global__ __launch_bounds__(VR_BLOCK) void verify_chunk_kernel(RowsArgs a, int 
     if (a.part) a.part[item] = make_double2((double)M, S);
     else { RowHead h; h.sum = S; h.max = M; h.n = 0; *reinterpret_cast<RowHead*>(a.rec + item * a.rec_stride) = h; }
   }
-  if (a.sub && lane < VR_SUBS) a.sub[item * VR_SUBS + lane] = lane == 0 ? sub[0] : sub[1];
+  if constexpr (PARTS == 16) {
+    if ((lane & 15) == 0) {
+#pragma unroll
+      for (int k = 0; k < 4; ++k) a.sub[item * 16 + 4 * k + (lane >> 4)] = sub[k];
+    }
+  } else if constexpr (PARTS > 0) {
+    if (lane < PARTS) a.sub[item * PARTS + lane] = lane == 0 ? sub[0] : lane == 1 ? sub[1] : lane == 2 ? sub[2] : sub[3];
+  }
   if (__ballot(bad) != 0ull && lane == 0) atomicOr(a.fault, DSBD_FAULT_NONFINITE);
 }
 
@@ -130,8 +147,8 @@ __device__ __forceinline__ bool entry_before(float z, int x, float z2, int x2) {
 
 __global__ __launch_bounds__(VR_ROW_BLOCK) void verify_row_kernel(RowsArgs a) {
   __shared__ double tab[64];
-  __shared__ __attribute__((aligned(16))) float part_max[VR_MAX_CHUNKS * VR_SUBS];
-  __shared__ int list[VR_MAX_CHUNKS * VR_SUBS];
+  __shared__ __attribute__((aligned(16))) float part_max[VR_PARTS];
+  __shared__ int list[VR_PARTS];
   __shared__ float cz[VR_CAND];
   __shared__ int cx[VR_CAND];
   __shared__ float bound_s;
@@ -143,7 +160,8 @@ __global__ __launch_bounds__(VR_ROW_BLOCK) void verify_row_kernel(RowsArgs a) {
   const bool second = !a.alias && (row & 1);
   const int node = a.alias ? row : row >> 1;
   const float* const z = row_logits(a, row);
-  const int nsub = a.nchunk * VR_SUBS, sub_len = a.chunk / VR_SUBS;
+  const int nsub = a.nchunk * a.parts, sub_len = a.parts > 0 ? a.chunk / a.parts : 0;
+  const bool whole = a.parts == 0;            // a short row: its logits are in the threads' registers
   // everything that is read from memory first is requested together
   double2 ms[VR_MAX_CHUNKS / 64];
 #pragma unroll
@@ -154,14 +172,26 @@ __global__ __launch_bounds__(VR_ROW_BLOCK) void verify_row_kernel(RowsArgs a) {
       else { const RowHead h = *reinterpret_cast<const RowHead*>(a.rec + (long long)row * a.rec_stride); ms[k] = make_double2((double)h.max, h.sum); }
     }
   }
-  // (parts whose maxima were not kept: all of them are looked at, without a bound)
-  if (tid < VR_MAX_CHUNKS * VR_SUBS) part_max[tid] = tid >= nsub ? -INFINITY : a.sub ? a.sub[(long long)row * nsub + tid] : INFINITY;
+  float mine[VR_WHOLE / VR_ROW_BLOCK];
+  if (whole) {
+#pragma unroll
+    for (int k = 0; k < VR_WHOLE / VR_ROW_BLOCK; ++k) {
+      const float v = z[min(tid + k * VR_ROW_BLOCK, V - 1)];
+      mine[k] = tid + k * VR_ROW_BLOCK < V ? v : -INFINITY;
+    }
+  } else if (tid < VR_PARTS) {
+    part_max[tid] = tid < nsub ? a.sub[(long long)row * nsub + tid] : -INFINITY;
+  }
   // children: nodes of the same tree, behind this one, no further than a tree is long
   const int child_n = min(node + tid, a.n_nodes - 1);
   int child_par = -1, ct = -1, par = -1, tok = -1;
   if (tid < DSBD_MAX_TREE_NODES) {
     child_par = a.parent[child_n]; ct = a.token[child_n];
     par = a.parent[node]; tok = a.token[node];
+  }
+  if (whole) {                                // groups of 16 threads, in place of four parts each
+    const float gm = row16_max_f32(fmaxf(fmaxf(mine[0], mine[1]), fmaxf(mine[2], mine[3])));
+    if ((lane & 15) == 0) part_max[tid >> 4] = gm;
   }
   if (tid < 64) tab[tid] = c_rows_exp2_tab[tid];
   if (tid == 0) { bound_s = -INFINITY; n_list = 0; n_cand = 0; }
@@ -176,8 +206,10 @@ __global__ __launch_bounds__(VR_ROW_BLOCK) void verify_row_kernel(RowsArgs a) {
   // the bound: the K-th largest of the maxima of 64 groups of parts (K entries reach it; fewer groups: none), one group per
   // lane, the same in every wave, each of which ranks four of them
   {
-    static_assert(VR_MAX_CHUNKS * VR_SUBS == 4 * 64 && VR_ROW_WAVES == 16, "four parts per lane, four groups per wave");
-    const float gm = fmaxf(fmaxf(part_max[lane], part_max[lane + 64]), fmaxf(part_max[lane + 128], part_max[lane + 192]));
+    static_assert(VR_PARTS == 4 * 64 && VR_ROW_WAVES == 16, "four parts per lane, four groups per wave");
+    static_assert(VR_ROW_BLOCK == 64 * 16 && VR_WHOLE == 4 * VR_ROW_BLOCK, "64 groups of threads, four logits each");
+    float gm = part_max[lane];
+    if (!whole) gm = fmaxf(fmaxf(gm, part_max[lane + 64]), fmaxf(part_max[lane + 128], part_max[lane + 192]));
 #pragma unroll
     for (int k = 0; k < 4; ++k) {
       const int i = 4 * wave + k;
@@ -187,11 +219,21 @@ __global__ __launch_bounds__(VR_ROW_BLOCK) void verify_row_kernel(RowsArgs a) {
     }
   }
   __syncthreads();
-  const float bound = a.sub ? bound_s : -INFINITY;
-  if (tid < nsub && part_max[tid] >= bound && part_max[tid] > -INFINITY) list[atomicAdd(&n_list, 1)] = tid;
+  const float bound = bound_s;
+  auto offer = [&](float v, int x) {                         // an entry at or above the bound is a candidate
+    if (v >= bound && v > -INFINITY) {
+      const int at = atomicAdd(&n_cand, 1);
+      if (at < VR_CAND) { cz[at] = v; cx[at] = x; }
+    }
+  };
+  if (whole) {
+#pragma unroll
+    for (int k = 0; k < VR_WHOLE / VR_ROW_BLOCK; ++k) offer(mine[k], tid + k * VR_ROW_BLOCK);
+  } else if (tid < nsub && part_max[tid] >= bound && part_max[tid] > -INFINITY) {
+    list[atomicAdd(&n_list, 1)] = tid;
+  }
   __syncthreads();
   const int nl = n_list;
-  // the entries at or above the bound
   for (int i = wave; i < nl; i += VR_ROW_WAVES) {
     const int x_lo = list[i] * sub_len, x_hi = min(V, x_lo + sub_len);
     for (int x0 = x_lo; x0 < x_hi; x0 += 512) {
@@ -199,13 +241,8 @@ __global__ __launch_bounds__(VR_ROW_BLOCK) void verify_row_kernel(RowsArgs a) {
 #pragma unroll
       for (int k = 0; k < 8; ++k) v[k] = z[min(x0 + k * 64 + lane, x_hi - 1)];
 #pragma unroll
-      for (int k = 0; k < 8; ++k) {
-        const int x = x0 + k * 64 + lane;
-        if (x < x_hi && v[k] >= bound && v[k] > -INFINITY) {
-          const int at = atomicAdd(&n_cand, 1);
-          if (at < VR_CAND) { cz[at] = v[k]; cx[at] = x; }
-        }
-      }
+      for (int k = 0; k < 8; ++k)
+        if (x0 + k * 64 + lane < x_hi) offer(v[k], x0 + k * 64 + lane);
     }
   }
   __syncthreads();
@@ -232,8 +269,8 @@ __global__ __launch_bounds__(VR_ROW_BLOCK) void verify_row_kernel(RowsArgs a) {
     // taken, and only the thread whose offer was taken looks for its next.
     auto next = [&](float z_prev, int x_prev, float& bz, int& bx) {
       bz = -INFINITY; bx = INT_MAX;
-      for (int i = 0; i < nl; ++i) {
-        const int x_lo = list[i] * sub_len, x_hi = min(V, x_lo + sub_len);
+      for (int i = 0; i < (whole ? 1 : nl); ++i) {
+        const int x_lo = whole ? 0 : list[i] * sub_len, x_hi = whole ? V : min(V, x_lo + sub_len);
         for (int x = x_lo + tid; x < x_hi; x += VR_ROW_BLOCK) {
           const float v = z[x];
           if (v > -INFINITY && entry_before(z_prev, x_prev, v, x) && entry_before(v, x, bz, bx)) { bz = v; bx = x; }
@@ -296,8 +333,11 @@ hipError_t launch_verify_rows(const RowsArgs& a, hipStream_t stream) {
   const int rows = a.n_nodes * (a.alias ? 1 : 2);
   const long long items = (long long)rows * a.nchunk;
   const dim3 grid((unsigned)((items + VR_BLOCK / 64 - 1) / (VR_BLOCK / 64)));
-  if (a.chunk == VR_TILE) hipLaunchKernelGGL(verify_chunk_kernel<true>, grid, dim3(VR_BLOCK), 0, stream, a, rows);
-  else hipLaunchKernelGGL(verify_chunk_kernel<false>, grid, dim3(VR_BLOCK), 0, stream, a, rows);
+  if (a.chunk > VR_TILE) hipLaunchKernelGGL((verify_chunk_kernel<false, 2>), grid, dim3(VR_BLOCK), 0, stream, a, rows);
+  else if (a.parts == 0) hipLaunchKernelGGL((verify_chunk_kernel<true, 0>), grid, dim3(VR_BLOCK), 0, stream, a, rows);
+  else if (a.parts == 16) hipLaunchKernelGGL((verify_chunk_kernel<true, 16>), grid, dim3(VR_BLOCK), 0, stream, a, rows);
+  else if (a.parts == 4) hipLaunchKernelGGL((verify_chunk_kernel<true, 4>), grid, dim3(VR_BLOCK), 0, stream, a, rows);
+  else hipLaunchKernelGGL((verify_chunk_kernel<true, 2>), grid, dim3(VR_BLOCK), 0, stream, a, rows);
   hipLaunchKernelGGL(verify_row_kernel, dim3((unsigned)rows), dim3(VR_ROW_BLOCK), 0, stream, a);
   return hipGetLastError();
 }

@@ -32,6 +32,8 @@ def _check(w, top_k, top_p, t):
 @pytest.mark.parametrize("V,top_k,top_p", [
     (1, 1, 1.0), (3, 32, 0.9), (63, 10, 0.8), (1023, 32, 1.0), (1024, 5, 0.8), (1025, 10, 0.8), (2049, 32, 0.95),
     (4099, 2, 0.8), (32001, 10, 0.8),
+    # around the lengths where the parts of a row change
+    (4096, 32, 0.95), (4097, 32, 0.95), (16384, 32, 0.95), (16385, 32, 0.95), (65536, 32, 0.95), (65537, 32, 0.95),
 ])
 def test_rows_of_any_length(V, top_k, top_p, fast, knobs):
     knobs.set("DSBD_WARP_FAST", fast)
