@@ -23,8 +23,11 @@
 #include <limits.h>
 
 #define VR_BLOCK 256           // chunk kernel
-#define VR_ROW_BLOCK 1024      // row kernel
-#define VR_ROW_WAVES (VR_ROW_BLOCK / 64)
+#define VR_ROW_BLOCK 1024      // row kernel, few rows: short chains of round trips ...
+#define VR_ROW_BLOCK_MANY 256  // ... and many: workgroups side by side
+#define VR_ROWS_MANY 512       // rows up to which the large ones are all resident at once, two on every compute unit (verification, us
+                               // at 1024 / 256 threads per row: 106 rows x 128256 47.3 / 49.3, 240 x 32000 top_k 32 65.5 / 73.3, 496 x
+                               // 32000 73.5 / 74.3, 1154 x 32000 105 / 98, 5642 x 1000 119 / 86, 72000 x 300 788 / 367)
 #define VR_PARTS 256            // most parts of a row
 #define VR_CAND 1024           // candidates that are ranked directly
 
@@ -145,7 +148,9 @@ __global__ __launch_bounds__(VR_BLOCK) void verify_chunk_kernel(RowsArgs a, int 
 // Entry (z, x) comes before entry (z2, x2) of the same row.
 __device__ __forceinline__ bool entry_before(float z, int x, float z2, int x2) { return (z > z2) | ((z == z2) & (x < x2)); }
 
-__global__ __launch_bounds__(VR_ROW_BLOCK) void verify_row_kernel(RowsArgs a) {
+template <int RB>
+__global__ __launch_bounds__(RB) void verify_row_kernel(RowsArgs a) {
+  constexpr int WAVES = RB / 64, PT = VR_WHOLE / RB;      // logits per thread of a row read whole
   __shared__ double tab[64];
   __shared__ __attribute__((aligned(16))) float part_max[VR_PARTS];
   __shared__ int list[VR_PARTS];
@@ -153,8 +158,8 @@ __global__ __launch_bounds__(VR_ROW_BLOCK) void verify_row_kernel(RowsArgs a) {
   __shared__ int cx[VR_CAND];
   __shared__ float bound_s;
   __shared__ int n_list, n_cand;
-  __shared__ float best_z[VR_ROW_WAVES];
-  __shared__ int best_x[VR_ROW_WAVES];
+  __shared__ float best_z[WAVES];
+  __shared__ int best_x[WAVES];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int row = blockIdx.x, K = a.K, V = a.V;
   const bool second = !a.alias && (row & 1);
@@ -172,12 +177,12 @@ __global__ __launch_bounds__(VR_ROW_BLOCK) void verify_row_kernel(RowsArgs a) {
       else { const RowHead h = *reinterpret_cast<const RowHead*>(a.rec + (long long)row * a.rec_stride); ms[k] = make_double2((double)h.max, h.sum); }
     }
   }
-  float mine[VR_WHOLE / VR_ROW_BLOCK];
+  float mine[PT];
   if (whole) {
 #pragma unroll
-    for (int k = 0; k < VR_WHOLE / VR_ROW_BLOCK; ++k) {
-      const float v = z[min(tid + k * VR_ROW_BLOCK, V - 1)];
-      mine[k] = tid + k * VR_ROW_BLOCK < V ? v : -INFINITY;
+    for (int k = 0; k < PT; ++k) {
+      const float v = z[min(tid + k * RB, V - 1)];
+      mine[k] = tid + k * RB < V ? v : -INFINITY;
     }
   } else if (tid < VR_PARTS) {
     part_max[tid] = tid < nsub ? a.sub[(long long)row * nsub + tid] : -INFINITY;
@@ -189,9 +194,12 @@ __global__ __launch_bounds__(VR_ROW_BLOCK) void verify_row_kernel(RowsArgs a) {
     child_par = a.parent[child_n]; ct = a.token[child_n];
     par = a.parent[node]; tok = a.token[node];
   }
-  if (whole) {                                // groups of 16 threads, in place of four parts each
-    const float gm = row16_max_f32(fmaxf(fmaxf(mine[0], mine[1]), fmaxf(mine[2], mine[3])));
-    if ((lane & 15) == 0) part_max[tid >> 4] = gm;
+  if (whole) {                                // 64 groups of threads, in place of four parts each
+    float gm = mine[0];
+#pragma unroll
+    for (int k = 1; k < PT; ++k) gm = fmaxf(gm, mine[k]);
+    gm = RB == 1024 ? row16_max_f32(gm) : quad_max_f32(gm);
+    if (tid % (RB / 64) == 0) part_max[tid / (RB / 64)] = gm;
   }
   if (tid < 64) tab[tid] = c_rows_exp2_tab[tid];
   if (tid == 0) { bound_s = -INFINITY; n_list = 0; n_cand = 0; }
@@ -206,13 +214,13 @@ __global__ __launch_bounds__(VR_ROW_BLOCK) void verify_row_kernel(RowsArgs a) {
   // the bound: the K-th largest of the maxima of 64 groups of parts (K entries reach it; fewer groups: none), one group per
   // lane, the same in every wave, each of which ranks four of them
   {
-    static_assert(VR_PARTS == 4 * 64 && VR_ROW_WAVES == 16, "four parts per lane, four groups per wave");
-    static_assert(VR_ROW_BLOCK == 64 * 16 && VR_WHOLE == 4 * VR_ROW_BLOCK, "64 groups of threads, four logits each");
+    static_assert(VR_PARTS == 4 * 64, "four parts per lane");
+    static_assert(RB == 64 * 16 || RB == 64 * 4, "groups of 16 or four threads");
     float gm = part_max[lane];
     if (!whole) gm = fmaxf(fmaxf(gm, part_max[lane + 64]), fmaxf(part_max[lane + 128], part_max[lane + 192]));
 #pragma unroll
-    for (int k = 0; k < 4; ++k) {
-      const int i = 4 * wave + k;
+    for (int k = 0; k < 64 / WAVES; ++k) {
+      const int i = 64 / WAVES * wave + k;
       const float v = __shfl(gm, i);
       const int ahead = __popcll(__ballot((gm > v) | ((gm == v) & (lane < i))));
       if (ahead == K - 1 && lane == 0) bound_s = v;
@@ -228,13 +236,13 @@ __global__ __launch_bounds__(VR_ROW_BLOCK) void verify_row_kernel(RowsArgs a) {
   };
   if (whole) {
 #pragma unroll
-    for (int k = 0; k < VR_WHOLE / VR_ROW_BLOCK; ++k) offer(mine[k], tid + k * VR_ROW_BLOCK);
+    for (int k = 0; k < PT; ++k) offer(mine[k], tid + k * RB);
   } else if (tid < nsub && part_max[tid] >= bound && part_max[tid] > -INFINITY) {
     list[atomicAdd(&n_list, 1)] = tid;
   }
   __syncthreads();
   const int nl = n_list;
-  for (int i = wave; i < nl; i += VR_ROW_WAVES) {
+  for (int i = wave; i < nl; i += WAVES) {
     const int x_lo = list[i] * sub_len, x_hi = min(V, x_lo + sub_len);
     for (int x0 = x_lo; x0 < x_hi; x0 += 512) {
       float v[8];
@@ -256,7 +264,7 @@ __global__ __launch_bounds__(VR_ROW_BLOCK) void verify_row_kernel(RowsArgs a) {
   };
   const int nc = n_cand;
   if (nc <= min(a.direct, VR_CAND)) {
-    for (int t = tid; t < nc; t += VR_ROW_BLOCK) {
+    for (int t = tid; t < nc; t += RB) {
       const float v = cz[t];
       const int x = cx[t];
       int rank = 0;
@@ -271,7 +279,7 @@ __global__ __launch_bounds__(VR_ROW_BLOCK) void verify_row_kernel(RowsArgs a) {
       bz = -INFINITY; bx = INT_MAX;
       for (int i = 0; i < (whole ? 1 : nl); ++i) {
         const int x_lo = whole ? 0 : list[i] * sub_len, x_hi = whole ? V : min(V, x_lo + sub_len);
-        for (int x = x_lo + tid; x < x_hi; x += VR_ROW_BLOCK) {
+        for (int x = x_lo + tid; x < x_hi; x += RB) {
           const float v = z[x];
           if (v > -INFINITY && entry_before(z_prev, x_prev, v, x) && entry_before(v, x, bz, bx)) { bz = v; bx = x; }
         }
@@ -293,7 +301,7 @@ __global__ __launch_bounds__(VR_ROW_BLOCK) void verify_row_kernel(RowsArgs a) {
       if (lane == 0) { best_z[wave] = wz; best_x[wave] = wx; }
       __syncthreads();
 #pragma unroll
-      for (int w = 0; w < VR_ROW_WAVES; ++w)
+      for (int w = 0; w < WAVES; ++w)
         if (entry_before(best_z[w], best_x[w], wz, wx)) { wz = best_z[w]; wx = best_x[w]; }
       if (wx == INT_MAX) break;                                  // (no more entries; uniform)
       if (tid == 0) put(r, wz, wx);
@@ -338,6 +346,7 @@ hipError_t launch_verify_rows(const RowsArgs& a, hipStream_t stream) {
   else if (a.parts == 16) hipLaunchKernelGGL((verify_chunk_kernel<true, 16>), grid, dim3(VR_BLOCK), 0, stream, a, rows);
   else if (a.parts == 4) hipLaunchKernelGGL((verify_chunk_kernel<true, 4>), grid, dim3(VR_BLOCK), 0, stream, a, rows);
   else hipLaunchKernelGGL((verify_chunk_kernel<true, 2>), grid, dim3(VR_BLOCK), 0, stream, a, rows);
-  hipLaunchKernelGGL(verify_row_kernel, dim3((unsigned)rows), dim3(VR_ROW_BLOCK), 0, stream, a);
+  if (rows <= VR_ROWS_MANY) hipLaunchKernelGGL(verify_row_kernel<VR_ROW_BLOCK>, dim3((unsigned)rows), dim3(VR_ROW_BLOCK), 0, stream, a);
+  else hipLaunchKernelGGL(verify_row_kernel<VR_ROW_BLOCK_MANY>, dim3((unsigned)rows), dim3(VR_ROW_BLOCK_MANY), 0, stream, a);
   return hipGetLastError();
 }

@@ -45,10 +45,13 @@ __device__ __forceinline__ float wave_max_f32(float v) {
   return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), 63));
 }
 
-// The largest of a value over each row of 16 lanes, in every lane of the row.
-__device__ __forceinline__ float row16_max_f32(float v) {
+// The largest of a value over each quad of lanes, or row of 16, in every lane of it.
+__device__ __forceinline__ float quad_max_f32(float v) {
   v = fmaxf(v, dpp_other_f32<0xB1, 0xf>(v));    // quad_perm [1,0,3,2]
-  v = fmaxf(v, dpp_other_f32<0x4E, 0xf>(v));    // quad_perm [2,3,0,1]
+  return fmaxf(v, dpp_other_f32<0x4E, 0xf>(v));    // quad_perm [2,3,0,1]
+}
+__device__ __forceinline__ float row16_max_f32(float v) {
+  v = quad_max_f32(v);
   v = fmaxf(v, dpp_other_f32<0x141, 0xf>(v));   // row_half_mirror
   return fmaxf(v, dpp_other_f32<0x140, 0xf>(v));   // row_mirror
 }
