@@ -8,7 +8,7 @@
 //      out of the chunks' pairs, which every workgroup folds for itself in the same order, and then only the chunks that
 //      matter are read again: the one that holds the draw, or those that can hold one of the top_k leading entries.
 // One launch: the second pass's workgroups stand behind the first's and wait for the pairs in tagged slots (two launches
-// under capture, and for more than DR_WAITING of them).
+// under capture, for more than DR_WAITING of them, and where the chunks are long to stream: DR_ONE_*).
 // What bounds a step is the chain of dependent memory round trips (8 MB of logits are 1.6 us at HBM rate).  Measured, 16
 // beams x 128256 tokens, 16 draws, top_k 10 / top_p 0.8: 5.7 + 11.4 us in two kernels, 16.1 in one; 64 beams of eight prompts x
 // 32000, 8 draws each, no warping: 6.0 + 6.6 and 12.0 us.  The rest of the gain is the host's: a launch less is 3 us.
@@ -29,6 +29,8 @@
 #define DR_MAX_CHUNKS 64       // chunks per row: one per lane
 #define DR_K_MAX 32
 #define DR_WAITING 256         // most workgroups that wait behind the chunks in one launch
+#define DR_ONE_WARPED (3LL << 20)    // most logits of a step in one launch, with warping ...
+#define DR_ONE_PLAIN (12LL << 20)    // ... and without
 #define DR_WAIT_TICKS 20000    // 200 us of the 100 MHz wall clock: how long a wave waits for a chunk before it takes it itself
 #define DW_CAND 1024           // candidates the warped kernel ranks directly
 #define DW_DIGIT 11            // bits per pass of its radix selection
@@ -659,9 +661,15 @@ extern "C" int32_t dsbd_draft_layer(const dsbd_draft_in* in, int32_t W_S, int32_
   // taking the chunk itself, so nothing depends on what runs beside it.  Not under capture, where a replay would repeat the
   // tags.  Measured, us per step: 8 to 16 beams x 128256, warped, 17.1 on the device in two kernels, 16.1 in one; 6 us of host
   // time in two launches, 2.9 in one.
+  // Only up to a size: the chunks then run in the drawing kernel's workgroups, of which a compute unit holds two (warped, 74 KB
+  // of LDS) or four, not eight as of the chunk kernel's, and a step of many chunks is bound by their stream.  Measured, us on
+  // the device in two kernels -> one: warped, 8.2 MB of logits 17.3 -> 15.4, 15.6 -> 13.9 and 15.4 -> 15.5; 16.4 MB 19.9 -> 19.3
+  // and 18.7 -> 19.3; 24.6 MB 23.7 -> 24.7; 67.7 MB 33.3 -> 42.4.  Not warped, 32.8 MB 20.8 -> 19.9, 49.3 MB 24.6 -> 24.0, 65.5 MB
+  // 31.0 -> 31.7.
+  const bool streams = (long long)in->n_beams * in->V > (top_k > 0 ? DR_ONE_WARPED : DR_ONE_PLAIN);
   hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
   const bool capturing = hipStreamIsCapturing(stream, &cs) != hipSuccess || cs != hipStreamCaptureStatusNone;
-  if (!capturing && draws <= DR_WAITING) {
+  if (!capturing && !streams && draws <= DR_WAITING) {
     const DsbdKnobs& knobs = dsbd_knobs();
     a.tag = exchange_tag(dsbd_launch_nonce());
     a.wait_limit = knobs.draft_wait_us >= 0 ? knobs.draft_wait_us * 100LL : DR_WAIT_TICKS;

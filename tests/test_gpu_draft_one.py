@@ -22,6 +22,8 @@ SHAPES = [
     ([2], 300001, 8),                      # chunks of several tiles, a ragged last one
     ([2, 0, 3, 1], 5000, 8),               # a prompt without beams
     ([1] * 40, 3001, 6),                   # 240 drawing workgroups, and 40 warped ones
+    ([8, 3], 285975, 4),                   # 3145725 logits, the most of a warped step in one launch ...
+    ([16], 196609, 4),                     # ... and 3145744, in two
 ]
 
 
