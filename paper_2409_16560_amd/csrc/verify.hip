@@ -2344,10 +2344,13 @@ VerifyPlan make_verify_plan(const dsbd_forest* f, int V, const dsbd_params* p, b
 // the other one's keep out.  The library therefore orders its layer launches itself once it has seen calls on more
 // than one stream: the first change of stream waits for the device to drain, and from then on layers_done is recorded
 // behind every layer launch and a launch on another stream than the last one waits for it.  (Recording from the start
-// would cost every single-stream caller 6 us per call, measured.)  One per device; the event is created on first use
-// and kept until the process ends.  enqueue makes one call's records and waits a unit among host threads.
+// would cost every single-stream caller 6 us per call, measured.)  Warped calls wait for nobody and take part only where
+// their workspace is the static array, which they share with every other static call.  One per device; the event is
+// created on first use and kept until the process ends.  enqueue makes one call's launches, records and waits a unit among
+// host threads, with or without the event: the kernels of a warped call follow each other on one workspace.
 struct LaunchOrder {
-  bool tried = false, ok = false;
+  bool tried = false;
+  std::atomic<bool> ok{false};       // the event exists
   hipEvent_t layers_done = nullptr;
   hipStream_t last_stream = nullptr;
   bool have_last = false, several_streams = false;
@@ -2366,7 +2369,7 @@ LaunchOrder* launch_order_of_current_device(bool may_create) {
     s.ok = hipEventCreateWithFlags(&s.layers_done, ev) == hipSuccess;
     if (!s.ok) (void)hipGetLastError();
   }
-  return s.ok ? &s : nullptr;
+  return &s;
 }
 
 // Threads per row of the row statistics.  A wave with a row of its own streams without a break between its loads and waits
@@ -2408,14 +2411,13 @@ extern "C" size_t dsbd_verify_forest_workspace_bytes(const dsbd_forest* f, int32
 }
 
 namespace {
-// may_create: the event that orders launches across streams may be created by this call (an ordinary call); false for
-// the entry point that must not allocate, which takes part in the ordering only if an earlier call or dsbd_init() has
-// made it.
+// static_scratch: the workspace is the device array that all such calls share, and the call must not allocate: it takes
+// part in the ordering across streams only if an earlier ordinary call or dsbd_init() has made the event.
 // next: the next-beam plan to be written along with the output beams (nullptr: none).  With keep_one == 0 the layer
 // kernel writes it itself; the single surviving beam of keep_one != 0 needs all of a prompt's output beams side by
 // side, which sit in several workgroups' hands: there the selection kernel is launched behind the verification.
 int32_t verify_impl(const dsbd_forest* f, const dsbd_verify_in* in, const dsbd_params* p, const dsbd_verify_out* out,
-                    void* workspace, size_t workspace_bytes, int32_t* fault, void* stream_, bool may_create,
+                    void* workspace, size_t workspace_bytes, int32_t* fault, void* stream_, bool static_scratch,
                     const dsbd_next_beams* next = nullptr, int keep_one = 0) {
   if (!in || !out || !fault) return DSBD_ERR_INVALID;
   int32_t rc = check_verify(f, in->V, p);
@@ -2448,10 +2450,10 @@ int32_t verify_impl(const dsbd_forest* f, const dsbd_verify_in* in, const dsbd_p
   if (warped) carve_warped(ws, f, rp, &ra); else carve_verify(ws, f, pl, &pb, &qb, &red);
 
   const bool want_stats = out->lse_target || out->lse_draft || out->node_logp_target || out->node_logp_draft;
-  // (the workgroups of warped layers wait for nobody: they need no order among launches)
-  LaunchOrder* const state = warped ? nullptr : launch_order_of_current_device(may_create);
+  LaunchOrder* state = launch_order_of_current_device(!static_scratch);
   std::unique_lock<std::mutex> enqueue_lock;
   if (state) enqueue_lock = std::unique_lock<std::mutex>(state->enqueue);
+  if (state && (!state->ok || (warped && !static_scratch))) state = nullptr;      // (no part in the order)
   // a stream under capture takes no part in the ordering of layer launches (an event recorded into a capture cannot
   // be waited for from outside it): replays of such a graph are the caller's to keep apart from other verifications
   bool capturing = false;
@@ -2506,6 +2508,7 @@ int32_t verify_impl(const dsbd_forest* f, const dsbd_verify_in* in, const dsbd_p
       return DSBD_ERR_HIP;
     }
   }
+  hipError_t le;
   if (warped) {
     ra.n_nodes = f->n_nodes; ra.V = in->V; ra.K = p->top_k; ra.chunk = rp.chunk; ra.nchunk = rp.nchunk; ra.parts = rp.parts;
     ra.alias = la.alias; ra.zp = in->logits_target; ra.zq = in->logits_draft;
@@ -2513,32 +2516,33 @@ int32_t verify_impl(const dsbd_forest* f, const dsbd_verify_in* in, const dsbd_p
     ra.lse_p = out->lse_target; ra.lse_q = out->lse_draft; ra.logp_p = out->node_logp_target; ra.logp_q = out->node_logp_draft;
     ra.fault = fault;
     ra.direct = knobs.warp_fast ? INT_MAX : 0;
-    if (launch_verify_rows(ra, stream) != hipSuccess) return DSBD_ERR_HIP;
+    le = launch_verify_rows(ra, stream);
     la.rec = ra.rec; la.rec_stride = rp.rec_stride; la.rec_compact = rp.compact;
     la.layer_wgs = f->n_prompts; la.prompt0 = 0;
-    dsbd_launch(DSBD_KERNEL_VERIFY_LAYERS, verify_layers_kernel<true, NODE_CAP>, dim3((unsigned)f->n_prompts), dim3(VL_BLOCK),
-                (unsigned int)pl.lds_bytes, stream, la);
-    DSBD_HIP_LAUNCH_CHECK();
-    if (next && keep_one) return dsbd_select_beams(f, out, p->W_cap, keep_one, next, fault, stream_);
-    return DSBD_OK;
-  }
-  const unsigned rows = (unsigned)f->n_nodes * (alias ? 1u : 2u);
-  la.stats_threads = statistics_threads(f, pl, rows);
-  const unsigned rows_per_wg = VL_BLOCK / la.stats_threads;
-  for (int p0 = 0; p0 < f->n_prompts; p0 += pl.group) {
-    la.prompt0 = p0;
-    const int np = f->n_prompts - p0 < pl.group ? f->n_prompts - p0 : pl.group;
-    unsigned grid3 = (unsigned)np * (unsigned)pl.G;
-    la.layer_wgs = (int)grid3;
-    if (want_stats && p0 + np == f->n_prompts) grid3 += (rows + rows_per_wg - 1) / rows_per_wg;     // behind the (last) layers
-    if (pl.small_nodes)
-      dsbd_launch(DSBD_KERNEL_VERIFY_LAYERS, verify_layers_kernel<false, NODE_CAP_SMALL>, dim3(grid3), dim3(VL_BLOCK),
+    if (le == hipSuccess) {
+      dsbd_launch(DSBD_KERNEL_VERIFY_LAYERS, verify_layers_kernel<true, NODE_CAP>, dim3((unsigned)f->n_prompts), dim3(VL_BLOCK),
                   (unsigned int)pl.lds_bytes, stream, la);
-    else
-      dsbd_launch(DSBD_KERNEL_VERIFY_LAYERS, verify_layers_kernel<false, NODE_CAP>, dim3(grid3), dim3(VL_BLOCK),
-                  (unsigned int)pl.lds_bytes, stream, la);
+      le = hipGetLastError();
+    }
+  } else {
+    const unsigned rows = (unsigned)f->n_nodes * (alias ? 1u : 2u);
+    la.stats_threads = statistics_threads(f, pl, rows);
+    const unsigned rows_per_wg = VL_BLOCK / la.stats_threads;
+    for (int p0 = 0; p0 < f->n_prompts; p0 += pl.group) {
+      la.prompt0 = p0;
+      const int np = f->n_prompts - p0 < pl.group ? f->n_prompts - p0 : pl.group;
+      unsigned grid3 = (unsigned)np * (unsigned)pl.G;
+      la.layer_wgs = (int)grid3;
+      if (want_stats && p0 + np == f->n_prompts) grid3 += (rows + rows_per_wg - 1) / rows_per_wg;     // behind the (last) layers
+      if (pl.small_nodes)
+        dsbd_launch(DSBD_KERNEL_VERIFY_LAYERS, verify_layers_kernel<false, NODE_CAP_SMALL>, dim3(grid3), dim3(VL_BLOCK),
+                    (unsigned int)pl.lds_bytes, stream, la);
+      else
+        dsbd_launch(DSBD_KERNEL_VERIFY_LAYERS, verify_layers_kernel<false, NODE_CAP>, dim3(grid3), dim3(VL_BLOCK),
+                    (unsigned int)pl.lds_bytes, stream, la);
+    }
+    le = hipGetLastError();
   }
-  hipError_t le = hipGetLastError();
   if (state && !capturing) {
     if (state->several_streams && hipEventRecord(state->layers_done, stream) != hipSuccess) le = hipErrorUnknown;
     state->last_stream = stream;
@@ -2553,14 +2557,14 @@ int32_t verify_impl(const dsbd_forest* f, const dsbd_verify_in* in, const dsbd_p
 extern "C" int32_t dsbd_verify_forest(const dsbd_forest* f, const dsbd_verify_in* in, const dsbd_params* p,
                                       const dsbd_verify_out* out, void* workspace, size_t workspace_bytes,
                                       int32_t* fault, void* stream_) {
-  return verify_impl(f, in, p, out, workspace, workspace_bytes, fault, stream_, true);
+  return verify_impl(f, in, p, out, workspace, workspace_bytes, fault, stream_, false);
 }
 
 extern "C" int32_t dsbd_verify_forest_select(const dsbd_forest* f, const dsbd_verify_in* in, const dsbd_params* p,
                                              const dsbd_verify_out* out, int32_t keep_one, const dsbd_next_beams* next,
                                              void* workspace, size_t workspace_bytes, int32_t* fault, void* stream_) {
   if (!next) return DSBD_ERR_INVALID;
-  return verify_impl(f, in, p, out, workspace, workspace_bytes, fault, stream_, true, next, keep_one != 0);
+  return verify_impl(f, in, p, out, workspace, workspace_bytes, fault, stream_, false, next, keep_one != 0);
 }
 
 // ---- the same call for callers that cannot allocate device memory (code under HIP graph capture, serving loops,
@@ -2592,7 +2596,8 @@ extern "C" int32_t dsbd_init(void) {
   if (!static_scratch_of_current_device()) return DSBD_ERR_HIP;
   (void)device_limits();
   (void)dsbd_knobs();
-  return launch_order_of_current_device(true) ? DSBD_OK : DSBD_ERR_HIP;
+  const LaunchOrder* const order = launch_order_of_current_device(true);
+  return order && order->ok ? DSBD_OK : DSBD_ERR_HIP;
 }
 
 extern "C" size_t dsbd_verify_forest_static_capacity(void) { return DSBD_STATIC_SCRATCH_BYTES; }
@@ -2606,5 +2611,5 @@ extern "C" int32_t dsbd_verify_forest_static(const dsbd_forest* f, const dsbd_ve
   if (dsbd_verify_forest_workspace_bytes(f, in->V, p) > (size_t)DSBD_STATIC_SCRATCH_BYTES) return DSBD_ERR_WORKSPACE;
   void* ptr = static_scratch_of_current_device();
   if (!ptr) return DSBD_ERR_HIP;
-  return verify_impl(f, in, p, out, ptr, DSBD_STATIC_SCRATCH_BYTES, fault, stream_, false);
+  return verify_impl(f, in, p, out, ptr, DSBD_STATIC_SCRATCH_BYTES, fault, stream_, true);
 }
