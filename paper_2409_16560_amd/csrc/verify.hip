@@ -861,7 +861,7 @@ void verify_layers_kernel(LayersArgs a) {
       const char* const at = a.rec + (a.alias ? (long long)node : 2LL * node + m) * a.rec_stride;
       h = *reinterpret_cast<const RowHead*>(at);
       if (a.rec_compact) {
-        if (r >= h.n) e.x = 0;
+        if (r >= h.n % VR_ROW_BAD) e.x = 0;
         else if (a.rec_compact == 1) e.x = reinterpret_cast<const uint8_t*>(at + sizeof(RowHead))[r];
         else e.x = reinterpret_cast<const uint16_t*>(at + sizeof(RowHead))[r];
         e.z = (m ? a.zq : a.zp)[(long long)node * V + e.x];
@@ -1232,8 +1232,9 @@ void verify_layers_kernel(LayersArgs a) {
         const double scale = (m ? sh.bw_q[i] : sh.bw_p[i]) / h.sum, top = (double)h.max;
         if (r == 0) {
           (m ? sh.max_q : sh.max_p)[i] = top; (m ? sh.sq : sh.sp)[i] = scale; (m ? sh.lse_q : sh.lse_p)[i] = h.sum;
+          if (h.n >= VR_ROW_BAD) atomicOr(a.fault, DSBD_FAULT_NONFINITE);
         }
-        const bool real = r < h.n;
+        const bool real = r < h.n % VR_ROW_BAD;
         cv[m * stride + e] = real ? exp_nonpos((double)x.z - top, sh.exp_tab) * scale : -1.0;
         ci[m * stride + e] = real ? i * V + x.x : INT_MAX;
       }
@@ -2514,7 +2515,7 @@ int32_t verify_impl(const dsbd_forest* f, const dsbd_verify_in* in, const dsbd_p
     ra.alias = la.alias; ra.zp = in->logits_target; ra.zq = in->logits_draft;
     ra.parent = f->parent; ra.token = f->token; ra.rec_stride = rp.rec_stride; ra.compact = rp.compact;
     ra.lse_p = out->lse_target; ra.lse_q = out->lse_draft; ra.logp_p = out->node_logp_target; ra.logp_q = out->node_logp_draft;
-    ra.fault = fault;
+    ra.fault = fault; ra.report = want_stats ? 1 : 0;
     ra.direct = knobs.warp_fast ? INT_MAX : 0;
     le = launch_verify_rows(ra, stream);
     la.rec = ra.rec; la.rec_stride = rp.rec_stride; la.rec_compact = rp.compact;

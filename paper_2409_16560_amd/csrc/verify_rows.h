@@ -7,8 +7,9 @@
 #define VR_WHOLE 4096          // rows of up to so many logits are read whole where their entries are selected
 #define VR_K_MAX 32
 
-// A row's record: `sum` (of exp(z - max)), `max`, the number of entries, then the entries (logit, token) by descending
-// logit, equal ones by ascending token; masked tokens (-Inf) are no entries.
+// A row's record: `sum` (of exp(z - max)), `max`, the number of entries (VR_ROW_BAD added where the row holds NaN or +Inf),
+// then the entries (logit, token) by descending logit, equal ones by ascending token; masked tokens (-Inf) are no entries.
+#define VR_ROW_BAD 256
 struct RowHead { double sum; float max; int n; };
 struct RowEntry { float z; int x; };
 
@@ -39,12 +40,14 @@ struct RowsArgs {
   int alias;                   // one model in both roles: one row per node, whose outputs serve both
   const float *zp, *zq;
   const int32_t *parent, *token;
-  double2* part;               // [rows][nchunk]: maximum of the chunk, sum of exp(z - maximum); null (rows of one chunk): in the records
+  double2* part;               // [rows][nchunk]: maximum of the chunk, sum of exp(z - maximum), its sign set where the chunk holds NaN or
+                               // +Inf; null (rows of one chunk): in the records
   float* sub;                  // [rows][nchunk * parts]: maxima of the chunk's parts
   char* rec;                   // [rows] records, `rec_stride` bytes apart
   int compact;
   long long rec_stride;
   float *lse_p, *lse_q, *logp_p, *logp_q;     // per-node outputs (any may be null)
+  int report;                  // faults of all rows are reported here (some output is wanted); else the layers report the rows they use
   int32_t* fault;
   int direct;                  // candidates that are ranked directly (fewer: a test hook for the other form)
 };

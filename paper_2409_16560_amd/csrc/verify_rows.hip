@@ -130,6 +130,8 @@ __global__ __launch_bounds__(VR_BLOCK) void verify_chunk_kernel(RowsArgs a, int 
     }
     sub[0] = part[0]; sub[1] = part[1];
   }
+  bad = __ballot(bad) != 0ull;
+  if (bad) S = -S;                                         // (sums are never negative)
   if (lane == 0) {
     if (a.part) a.part[item] = make_double2((double)M, S);
     else { RowHead h; h.sum = S; h.max = M; h.n = 0; *reinterpret_cast<RowHead*>(a.rec + item * a.rec_stride) = h; }
@@ -142,7 +144,7 @@ __global__ __launch_bounds__(VR_BLOCK) void verify_chunk_kernel(RowsArgs a, int 
   } else if constexpr (PARTS > 0) {
     if (lane < PARTS) a.sub[item * PARTS + lane] = lane == 0 ? sub[0] : lane == 1 ? sub[1] : lane == 2 ? sub[2] : sub[3];
   }
-  if (__ballot(bad) != 0ull && lane == 0) atomicOr(a.fault, DSBD_FAULT_NONFINITE);
+  if (bad && a.report && lane == 0) atomicOr(a.fault, DSBD_FAULT_NONFINITE);
 }
 
 // Entry (z, x) comes before entry (z2, x2) of the same row.
@@ -208,6 +210,8 @@ __global__ __launch_bounds__(RB) void verify_row_kernel(RowsArgs a) {
   const float zt = child ? z[ct] : 0.f;
   // the row's maximum and sum, every wave for itself, in a fixed order
   static_assert(VR_MAX_CHUNKS == 128, "two chunks per lane");
+  const bool bad = __ballot((__double2hiint(ms[0].y) | __double2hiint(ms[1].y)) < 0) != 0ull;
+  ms[0].y = fabs(ms[0].y); ms[1].y = fabs(ms[1].y);
   const double M = wave_max_f64(fmax(ms[0].x, ms[1].x));
   const double S = wave_sum((ms[0].x > -INFINITY ? ms[0].y * dsbd_exp_nonpos(ms[0].x - M, tab) : 0.0) +
                             (ms[1].x > -INFINITY ? ms[1].y * dsbd_exp_nonpos(ms[1].x - M, tab) : 0.0));
@@ -316,7 +320,7 @@ __global__ __launch_bounds__(RB) void verify_row_kernel(RowsArgs a) {
   int fault = 0;
   if (tid == 0) {
     RowHead h;
-    h.sum = S; h.max = (float)M; h.n = min(nc, K);
+    h.sum = S; h.max = (float)M; h.n = min(nc, K) + (bad ? VR_ROW_BAD : 0);
     *reinterpret_cast<RowHead*>(rec) = h;
     if (o_lse) o_lse[node] = lse;
     if (a.alias && a.lse_q) a.lse_q[node] = lse;
@@ -332,7 +336,7 @@ __global__ __launch_bounds__(RB) void verify_row_kernel(RowsArgs a) {
     if (o_logp) o_logp[child_n] = lp;
     if (a.alias && a.logp_q) a.logp_q[child_n] = lp;
   }
-  if (fault) atomicOr(a.fault, fault);
+  if (fault && a.report) atomicOr(a.fault, fault);
 }
 
 }  // namespace

@@ -115,3 +115,49 @@ def test_compact_records_of_large_batches(V, top_k, n_prompts):
         m = int(ref["n_out"][p])
         assert np.array_equal(res.out_token.cpu().numpy()[p, :m], ref["out_token"][p, :m])
         assert np.array_equal(res.out_parent.cpu().numpy()[p, :m], ref["out_parent"][p, :m])
+
+
+@pytest.mark.parametrize("V", [300, 5000, 140000])
+@pytest.mark.parametrize("top_k", [0, 10])
+def test_without_row_outputs_only_the_layers_rows_are_reported(V, top_k):
+    """All four per-node outputs left out: NaN and +Inf are reported for the rows of beams that enter a layer alone, rows of
+    nothing but -Inf and masked drafted tokens not at all; with an output, every row's are."""
+    import torch
+    import gpu_util as gu
+    import paper_2409_16560_amd as dsbd
+    w = make_workload("c2", L=8, V=V, Hq=4, Hkv=4, draft_top_k=4)
+    d = gu.DeviceWorkload(w)
+    kw = dict(t=-1.0, top_k=top_k, top_p=0.9 if top_k else 1.0)
+    names = ("lse_target", "lse_draft", "node_logp_target", "node_logp_draft")
+    whole = ("node_status", "l_last", "layer_width", "n_out", "out_parent", "out_token", "out_node")
+
+    def call(outputs):
+        res = dsbd.VerifyResult.allocate(d.forest, w.W_cap)
+        kept = {n: getattr(res, n) for n in names}
+        for n in names:
+            if n not in outputs:
+                setattr(res, n, None)
+        d.verify(result=res, **kw)
+        torch.cuda.synchronize()
+        del kept
+        return res
+    clean = call(())
+    assert int(clean.fault.item()) == 0
+    status = clean.node_status.cpu().numpy()
+    unused = [n for n in range(w.n_nodes) if status[n] not in (dsbd.DSBD_ROOT, dsbd.DSBD_ACCEPTED)]
+    assert unused                                                    # (nodes that are not accepted enter no layer)
+    first_child = int(np.nonzero(np.asarray(w.parent) >= 0)[0][0])
+    masked = (int(w.parent[first_child]), int(w.token[first_child]))
+    for bad, used in (((unused[-1], 7, float("nan")), False), ((unused[0], V - 1, float("inf")), False),
+                      ((unused[0], slice(None), -float("inf")), False), ((masked[0], masked[1], -float("inf")), False),
+                      ((0, V // 2, float("nan")), True), ((0, V - 1, float("inf")), True)):
+        for z in (d.logits_p, d.logits_q):
+            row = z[bad[0]].clone()
+            z[bad[0], bad[1]] = bad[2]
+            res = call(())
+            assert int(res.fault.item()) == (dsbd.DSBD_FAULT_NONFINITE if used else 0), (bad, used)
+            if not used and bad[0] in unused:
+                for n in whole:
+                    assert torch.equal(getattr(res, n), getattr(clean, n)), (bad, n)
+            assert int(call(names).fault.item()) & dsbd.DSBD_FAULT_NONFINITE, bad
+            z[bad[0]] = row
