@@ -2293,6 +2293,7 @@ size_t carve_verify(WorkspaceCarver& ws, const dsbd_forest* f, const VerifyPlan&
 
 // Warped joints: one workgroup walks a prompt's layers from the rows' records.
 VerifyPlan warped_plan(const dsbd_forest* f, const dsbd_params* p) {
+  (void)device_limits();                   // (the kernel's dynamic LDS is set up there)
   VerifyPlan pl = {};
   pl.I_cap = p->W_cap > f->max_prompt_trees ? p->W_cap : f->max_prompt_trees;
   pl.G = 1;

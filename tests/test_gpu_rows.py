@@ -161,3 +161,24 @@ def test_without_row_outputs_only_the_layers_rows_are_reported(V, top_k):
                     assert torch.equal(getattr(res, n), getattr(clean, n)), (bad, n)
             assert int(call(names).fault.item()) & dsbd.DSBD_FAULT_NONFINITE, bad
             z[bad[0]] = row
+
+
+def test_a_warped_verification_as_a_process_s_first_call():
+    """The most dynamic LDS a warped call asks for (64 beams, 32 entries each) without any other call in front."""
+    import subprocess
+    import sys
+    import gpu_util as gu
+    w = make_workload("c2", W_cap=64, L=8, V=300, Hq=4, Hkv=4, draft_top_k=4)
+    code = ("import conftest, json, torch\n"
+            "from dsbd_synth import make_workload\n"
+            "from dsbd_synth.device import DeviceWorkload\n"
+            "w = make_workload('c2', W_cap=64, L=8, V=300, Hq=4, Hkv=4, draft_top_k=4)\n"
+            "r = DeviceWorkload(w).verify(t=-1.0, top_k=32, top_p=0.9)\n"
+            "print(json.dumps([int(r.fault.item()), r.n_out.tolist(), r.out_token.tolist(), r.node_status.tolist()]))\n")
+    out = subprocess.run([sys.executable, "-c", code], cwd=__file__.rsplit("/", 1)[0], capture_output=True, text=True, timeout=100)
+    assert out.returncode == 0, out.stderr[-2000:]
+    import json
+    fault, n_out, token, status = json.loads(out.stdout.strip().splitlines()[-1])
+    ref = gu.oracle_verify(w, t=-1.0, top_k=32, top_p=0.9)
+    assert fault == 0 and n_out == ref["n_out"].tolist() and status == ref["node_status"].tolist()
+    assert [r[:n] for r, n in zip(token, n_out)] == [r[:n] for r, n in zip(ref["out_token"].tolist(), n_out)]
