@@ -499,7 +499,9 @@ __device__ __forceinline__ void row_statistics(const LayersArgs& a, Shared& sh) 
 // the compiler doubles the number it is given.  Without it the allocator takes whatever two waves per SIMD leave it, up
 // to 256, whether it needs them or not.)
 #define VL_MAX_VGPRS 240
-template <bool WARP, int NC>
+// BARE: the rows' records hold no entries (RowsPlan::compact < 0); a build of its own, whose registers the other's place for two
+// workgroups on a compute unit would not survive.
+template <bool WARP, int NC, bool BARE = false>
 __global__ __launch_bounds__(VL_BLOCK) __attribute__((amdgpu_num_vgpr(VL_MAX_VGPRS / 2)))
 void verify_layers_kernel(LayersArgs a) {
   __shared__ LayerShared<NC> sh;
@@ -871,7 +873,7 @@ void verify_layers_kernel(LayersArgs a) {
     };
     if constexpr (WARP) {
       const int n_cand = nI * a.top_k;
-      if (tid < 2 * n_cand) {
+      if (!BARE && tid < 2 * n_cand) {
         const int m = tid >= n_cand ? 1 : 0, e = tid - m * n_cand;
         row_record(sh.I_node[e / a.top_k], m, e % a.top_k, rec_head, rec_entry);
       }
@@ -1223,12 +1225,56 @@ void verify_layers_kernel(LayersArgs a) {
       lds_i32* const ci = (lds_i32*)(dyn_lds + 2 * stride);      // their flat indices, and
       lds_i32* const kept = ci + 2 * stride;                     // the numbers of those that can be among the K first
       lds_f64* const lv = (lds_f64*)sh.Pa; lds_i32* const li = (lds_i32*)sh.Pb;      // the K first of either, in rank order
+      if constexpr (BARE) {
+        // a wave per row takes its K first entries one after the other out of its registers
+        for (int t = wave; t < 2 * nI; t += VL_WAVES) {
+          const int m = t >= nI ? 1 : 0, i = t - m * nI, node = sh.I_node[i];
+          const float* const mine = (m ? a.zq : a.zp) + (long long)node * V + lane;
+          float z[VR_BARE / 64];
+#pragma unroll
+          for (int k = 0; k < VR_BARE / 64; ++k) {
+            z[k] = -INFINITY;
+            if (64 * k + lane < V) z[k] = mine[64 * k];
+            if (!(z[k] > -INFINITY)) z[k] = -INFINITY;                      // (NaN is no entry)
+          }
+          for (int r = 0; r < K; ++r) {
+            float best = -INFINITY;
+            int at = INT_MAX;
+#pragma unroll
+            for (int k = 0; k < VR_BARE / 64; ++k)
+              if (z[k] > best) { best = z[k]; at = lane + 64 * k; }
+            float wz = best;
+            int wx = at;
+#pragma unroll
+            for (int off = 32; off >= 1; off >>= 1) {
+              const float oz = __shfl_xor(wz, off);
+              const int ox = __shfl_xor(wx, off);
+              if ((oz > wz) | ((oz == wz) & (ox < wx))) { wz = oz; wx = ox; }
+            }
+#pragma unroll
+            for (int k = 0; k < VR_BARE / 64; ++k)
+              if (lane + 64 * k == wx) z[k] = -INFINITY;
+            if (lane == 0) {
+              ci[m * stride + i * K + r] = wx;
+              kept[m * stride + i * K + r] = __float_as_int(wz);
+              if (r == 0) (m ? sh.max_q : sh.max_p)[i] = (double)wz;
+            }
+          }
+        }
+      }
       lds_barrier();                                     // the beam weights are there
       for (int t = tid; t < 2 * n_cand; t += VL_BLOCK) {
         const int m = t >= n_cand ? 1 : 0, e = t - m * n_cand, i = e / K, r = e - i * K;
         RowHead h = rec_head;
         RowEntry x = rec_entry;
-        if (t != tid) row_record(sh.I_node[i], m, r, h, x);
+        if constexpr (BARE) {
+          const double s = *reinterpret_cast<const double*>(a.rec + (a.alias ? (long long)sh.I_node[i] : 2LL * sh.I_node[i] + m) * a.rec_stride);
+          x.z = __int_as_float(kept[m * stride + e]); x.x = ci[m * stride + e];
+          h.sum = fabs(s); h.max = (float)(m ? sh.max_q : sh.max_p)[i];
+          h.n = (x.x != INT_MAX ? r + 1 : 0) + (__double2hiint(s) < 0 ? VR_ROW_BAD : 0);
+        } else {
+          if (t != tid) row_record(sh.I_node[i], m, r, h, x);
+        }
         const double scale = (m ? sh.bw_q[i] : sh.bw_p[i]) / h.sum, top = (double)h.max;
         if (r == 0) {
           (m ? sh.max_q : sh.max_p)[i] = top; (m ? sh.sq : sh.sp)[i] = scale; (m ? sh.lse_q : sh.lse_p)[i] = h.sum;
@@ -2166,6 +2212,8 @@ const DeviceLimits& device_limits() {
                               hipFuncAttributeMaxDynamicSharedMemorySize, VL_DYN_LDS_BYTES);
     (void)hipFuncSetAttribute(reinterpret_cast<const void*>(verify_layers_kernel<true, NODE_CAP>),
                               hipFuncAttributeMaxDynamicSharedMemorySize, VL_DYN_LDS_BYTES);
+    (void)hipFuncSetAttribute(reinterpret_cast<const void*>(verify_layers_kernel<true, NODE_CAP, true>),
+                              hipFuncAttributeMaxDynamicSharedMemorySize, VL_DYN_LDS_BYTES);
     (void)hipFuncSetAttribute(reinterpret_cast<const void*>(verify_layers_kernel<false, NODE_CAP_SMALL>),
                               hipFuncAttributeMaxDynamicSharedMemorySize, VL_DYN_LDS_BYTES_SMALL);
     int nb = 0, nb3 = 0;
@@ -2314,12 +2362,20 @@ size_t carve_warped(WorkspaceCarver& ws, const dsbd_forest* f, const RowsPlan& r
 }
 
 // Records with logits, unless they would push the workspace above the 32 MiB of dsbd_verify_forest_static and the tokens fit
-// 16 bits (large batches over vocabularies of a few hundred tokens): a dependent load per layer more.
-RowsPlan warped_rows(const dsbd_forest* f, int V, int K) {
-  WorkspaceCarver ws(nullptr);
-  RowsArgs ra;
+// 16 bits (large batches over vocabularies of a few hundred tokens): a dependent load per layer more, or no entries at all.
+// `bytes`: what the call asks for.
+RowsPlan warped_rows(const dsbd_forest* f, int V, int K, size_t* bytes = nullptr) {
+  auto size = [&](const RowsPlan& rp) { WorkspaceCarver ws(nullptr); RowsArgs ra; return carve_warped(ws, f, rp, &ra) + 256; };
+  const size_t most = DSBD_STATIC_SCRATCH_BYTES;
   const RowsPlan plain = rows_plan(V, K, 0);
-  return V <= 65536 && carve_warped(ws, f, plain, &ra) + 256 > (size_t)DSBD_STATIC_SCRATCH_BYTES ? rows_plan(V, K, V <= 256 ? 1 : 2) : plain;
+  const size_t n = size(plain);
+  RowsPlan rp = plain;
+  if (n > most && V <= 65536) {
+    rp = rows_plan(V, K, V <= 256 ? 1 : 2);
+    if (size(rp) > most && V <= VR_BARE) rp = rows_plan(V, K, -1);
+  }
+  if (bytes) *bytes = size(rp);
+  return rp;
 }
 
 size_t verify_workspace(const dsbd_forest* f, const VerifyPlan& pl) {
@@ -2405,9 +2461,9 @@ __global__ void bump_replay_count_kernel(unsigned long long* count) { *count += 
 extern "C" size_t dsbd_verify_forest_workspace_bytes(const dsbd_forest* f, int32_t V, const dsbd_params* p) {
   if (check_verify(f, V, p) != DSBD_OK) return 0;
   if (p->top_k > 0) {
-    WorkspaceCarver ws(nullptr);
-    RowsArgs ra;
-    return carve_warped(ws, f, warped_rows(f, V, p->top_k), &ra) + 256;
+    size_t bytes;
+    (void)warped_rows(f, V, p->top_k, &bytes);
+    return bytes;
   }
   return verify_workspace(f, make_verify_plan(f, V, p));
 }
@@ -2522,8 +2578,9 @@ int32_t verify_impl(const dsbd_forest* f, const dsbd_verify_in* in, const dsbd_p
     la.rec = ra.rec; la.rec_stride = rp.rec_stride; la.rec_compact = rp.compact;
     la.layer_wgs = f->n_prompts; la.prompt0 = 0;
     if (le == hipSuccess) {
-      dsbd_launch(DSBD_KERNEL_VERIFY_LAYERS, verify_layers_kernel<true, NODE_CAP>, dim3((unsigned)f->n_prompts), dim3(VL_BLOCK),
-                  (unsigned int)pl.lds_bytes, stream, la);
+      const dim3 grid((unsigned)f->n_prompts), block(VL_BLOCK);
+      if (rp.compact < 0) dsbd_launch(DSBD_KERNEL_VERIFY_LAYERS, verify_layers_kernel<true, NODE_CAP, true>, grid, block, (unsigned int)pl.lds_bytes, stream, la);
+      else dsbd_launch(DSBD_KERNEL_VERIFY_LAYERS, verify_layers_kernel<true, NODE_CAP>, grid, block, (unsigned int)pl.lds_bytes, stream, la);
       le = hipGetLastError();
     }
   } else {

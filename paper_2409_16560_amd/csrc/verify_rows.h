@@ -6,6 +6,7 @@
 #define VR_MAX_CHUNKS 128      // chunks per row: two per lane where they are folded
 #define VR_WHOLE 4096          // rows of up to so many logits are read whole where their entries are selected
 #define VR_K_MAX 32
+#define VR_BARE 1024           // rows of up to so many logits can do with records of a sum alone
 
 // A row's record: `sum` (of exp(z - max)), `max`, the number of entries (VR_ROW_BAD added where the row holds NaN or +Inf),
 // then the entries (logit, token) by descending logit, equal ones by ascending token; masked tokens (-Inf) are no entries.
@@ -16,7 +17,8 @@ struct RowEntry { float z; int x; };
 struct RowsPlan {
   int chunk, nchunk;           // logits per chunk (a power of two), chunks per row
   int parts;                   // parts of a chunk whose maxima are kept (0: none; rows of up to VR_WHOLE logits)
-  int compact;                 // > 0: the entries are tokens of so many bytes (1 or 2), whose logits are looked up again
+  int compact;                 // > 0: the entries are tokens of so many bytes (1 or 2), whose logits are looked up again; < 0: a
+                               // record is the row's sum alone (sign set: the row is bad), the layers select from the logits
   long long rec_stride;        // bytes from record to record
 };
 // Chunks depend on the row's length alone, so that equal rows are summed in the same order and get the same bits.
@@ -30,7 +32,7 @@ inline RowsPlan rows_plan(int V, int K, int compact) {
   r.parts = V <= VR_WHOLE ? 0 : V <= 16384 ? 16 : V <= 65536 ? 4 : 2;
   r.compact = compact;
   const size_t entries = (size_t)(K < V ? K : V);
-  r.rec_stride = compact ? (long long)dsbd_align_up(sizeof(RowHead) + entries * compact, 8)
+  r.rec_stride = compact < 0 ? (long long)sizeof(double) : compact ? (long long)dsbd_align_up(sizeof(RowHead) + entries * compact, 8)
                          : (long long)dsbd_align_up(sizeof(RowHead) + entries * sizeof(RowEntry), 16);
   return r;
 }
@@ -41,7 +43,7 @@ struct RowsArgs {
   const float *zp, *zq;
   const int32_t *parent, *token;
   double2* part;               // [rows][nchunk]: maximum of the chunk, sum of exp(z - maximum), its sign set where the chunk holds NaN or
-                               // +Inf; null (rows of one chunk): in the records
+                               // +Inf; null (rows of one chunk): in the records (without the maximum where they hold a sum alone)
   float* sub;                  // [rows][nchunk * parts]: maxima of the chunk's parts
   char* rec;                   // [rows] records, `rec_stride` bytes apart
   int compact;

@@ -134,6 +134,7 @@ __global__ __launch_bounds__(VR_BLOCK) void verify_chunk_kernel(RowsArgs a, int 
   if (bad) S = -S;                                         // (sums are never negative)
   if (lane == 0) {
     if (a.part) a.part[item] = make_double2((double)M, S);
+    else if (a.compact < 0) *reinterpret_cast<double*>(a.rec + item * a.rec_stride) = S;
     else { RowHead h; h.sum = S; h.max = M; h.n = 0; *reinterpret_cast<RowHead*>(a.rec + item * a.rec_stride) = h; }
   }
   if constexpr (PARTS == 16) {
@@ -176,6 +177,7 @@ __global__ __launch_bounds__(RB) void verify_row_kernel(RowsArgs a) {
     ms[k] = make_double2(-INFINITY, 0.0);
     if (lane + 64 * k < a.nchunk) {
       if (a.part) ms[k] = a.part[(long long)row * a.nchunk + lane + 64 * k];
+      else if (a.compact < 0) ms[k].y = *reinterpret_cast<const double*>(a.rec + (long long)row * a.rec_stride);
       else { const RowHead h = *reinterpret_cast<const RowHead*>(a.rec + (long long)row * a.rec_stride); ms[k] = make_double2((double)h.max, h.sum); }
     }
   }
@@ -210,6 +212,7 @@ __global__ __launch_bounds__(RB) void verify_row_kernel(RowsArgs a) {
   const float zt = child ? z[ct] : 0.f;
   // the row's maximum and sum, every wave for itself, in a fixed order
   static_assert(VR_MAX_CHUNKS == 128, "two chunks per lane");
+  if (a.compact < 0) ms[0].x = lane == 0 ? (double)wave_max_f32(part_max[lane]) : -INFINITY;      // (one chunk, read whole)
   const bool bad = __ballot((__double2hiint(ms[0].y) | __double2hiint(ms[1].y)) < 0) != 0ull;
   ms[0].y = fabs(ms[0].y); ms[1].y = fabs(ms[1].y);
   const double M = wave_max_f64(fmax(ms[0].x, ms[1].x));
@@ -260,6 +263,7 @@ __global__ __launch_bounds__(RB) void verify_row_kernel(RowsArgs a) {
   __syncthreads();
   char* const rec = a.rec + (long long)row * a.rec_stride;
   auto put = [&](int r, float v, int x) {
+    if (a.compact < 0) return;
     if (a.compact == 1) { reinterpret_cast<uint8_t*>(rec + sizeof(RowHead))[r] = (uint8_t)x; return; }
     if (a.compact == 2) { reinterpret_cast<uint16_t*>(rec + sizeof(RowHead))[r] = (uint16_t)x; return; }
     RowEntry e;
@@ -321,7 +325,7 @@ __global__ __launch_bounds__(RB) void verify_row_kernel(RowsArgs a) {
   if (tid == 0) {
     RowHead h;
     h.sum = S; h.max = (float)M; h.n = min(nc, K) + (bad ? VR_ROW_BAD : 0);
-    *reinterpret_cast<RowHead*>(rec) = h;
+    if (a.compact >= 0) *reinterpret_cast<RowHead*>(rec) = h;
     if (o_lse) o_lse[node] = lse;
     if (a.alias && a.lse_q) a.lse_q[node] = lse;
     if (!(S > 0.0)) fault = DSBD_FAULT_NONFINITE;              // a row without a finite logit (NaN and +Inf: the chunks report them)

@@ -83,20 +83,25 @@ def test_one_model_in_both_roles():
     gu.compare_verify(res, gu.oracle_verify(w, top_k=10, top_p=0.8), w)
 
 
-@pytest.mark.parametrize("V,top_k,n_prompts", [(200, 32, 600), (1000, 32, 600), (1500, 32, 600)])
-def test_compact_records_of_large_batches(V, top_k, n_prompts):
-    """Batches whose records with logits would outgrow 32 MiB keep 8- or 16-bit tokens instead."""
+@pytest.mark.parametrize("V,top_k,n_prompts,nodes,entry_bytes", [
+    (200, 32, 600, (12, 16), 8), (1000, 32, 600, (12, 16), 8), (1500, 32, 600, (12, 16), 8),
+    # ... nor would records with tokens alone fit: records without entries
+    (24, 10, 1134, (60, 64), 1), (300, 14, 900, (60, 64), 2), (3, 32, 1600, (60, 64), 1),
+])
+def test_compact_records_of_large_batches(V, top_k, n_prompts, nodes, entry_bytes):
+    """Batches whose records with logits would outgrow 32 MiB keep 8- or 16-bit tokens instead, or no entries."""
     import gpu_util as gu
     import paper_2409_16560_amd as dsbd
-    base = make_workload("c4", n_prompts=n_prompts, W=(8, 8), tree_nodes=(12, 16), L=1, Hq=1, Hkv=1, D=64, V=4, seed=5)
+    base = make_workload("c4", n_prompts=n_prompts, W=(8, 8), tree_nodes=nodes, L=1, Hq=1, Hkv=1, D=64, V=4, seed=5)
     N, rng = len(base.parent), np.random.default_rng(3)
     zp = rng.standard_normal((N, V), dtype=np.float32) * 3
     zq = zp + rng.standard_normal((N, V), dtype=np.float32) * np.float32(0.5)
     par = np.maximum(base.parent, 0)
-    token = np.argpartition(-zq[par], 3, axis=1)[np.arange(N), rng.integers(0, 4, N)].astype(np.int32)
+    kth = min(3, V - 1)
+    token = np.argpartition(-zq[par], kth, axis=1)[np.arange(N), rng.integers(0, kth + 1, N)].astype(np.int32)
     w = dataclasses.replace(base, logits_p=zp, logits_q=zq, token=token)
     d = gu.DeviceWorkload(w)
-    assert N * 2 * (16 + 8 * top_k) > 32 << 20                      # what the records with logits would take
+    assert N * 2 * ((16 + entry_bytes * min(top_k, V) + 7) // 8 * 8) > 32 << 20    # what the records would take
     assert dsbd.dsbd_verify_forest_workspace_bytes(d.forest, V, 0, 1, w.W_cap, -1.0, top_k, 0.9) <= 32 << 20
     res, _ = d.verify_select(t=0.6, top_k=top_k, top_p=0.9)
     assert int(res.fault.item()) == 0
