@@ -2361,9 +2361,10 @@ size_t carve_warped(WorkspaceCarver& ws, const dsbd_forest* f, const RowsPlan& r
   return ws.total();
 }
 
-// Records with logits, unless they would push the workspace above the 32 MiB of dsbd_verify_forest_static and the tokens fit
-// 16 bits (large batches over vocabularies of a few hundred tokens): a dependent load per layer more, or no entries at all.
-// `bytes`: what the call asks for.
+// Records with logits, unless smaller ones bring the workspace down to the 32 MiB of dsbd_verify_forest_static where those do
+// not (large batches over vocabularies of a few hundred tokens): tokens of 8 or 16 bits, a dependent load per layer more, or no
+// entries at all.  `bytes`: what the call asks for.  A call with smaller records asks for the whole 32 MiB, so that the sizes
+// rise with the batch: a buffer for the largest call serves the others, records with logits or not.
 RowsPlan warped_rows(const dsbd_forest* f, int V, int K, size_t* bytes = nullptr) {
   auto size = [&](const RowsPlan& rp) { WorkspaceCarver ws(nullptr); RowsArgs ra; return carve_warped(ws, f, rp, &ra) + 256; };
   const size_t most = DSBD_STATIC_SCRATCH_BYTES;
@@ -2373,8 +2374,9 @@ RowsPlan warped_rows(const dsbd_forest* f, int V, int K, size_t* bytes = nullptr
   if (n > most && V <= 65536) {
     rp = rows_plan(V, K, V <= 256 ? 1 : 2);
     if (size(rp) > most && V <= VR_BARE) rp = rows_plan(V, K, -1);
+    if (size(rp) > most) rp = plain;
   }
-  if (bytes) *bytes = size(rp);
+  if (bytes) *bytes = rp.compact ? most : n;
   return rp;
 }
 
