@@ -1237,28 +1237,33 @@ void verify_layers_kernel(LayersArgs a) {
             if (64 * k + lane < V) z[k] = mine[64 * k];
             if (!(z[k] > -INFINITY)) z[k] = -INFINITY;                      // (NaN is no entry)
           }
+          float top = z[0];
+#pragma unroll
+          for (int k = 1; k < VR_BARE / 64; ++k) top = fmaxf(top, z[k]);
+          const double M = (double)wave_max_f32(top);
+          if (lane == 0) (m ? sh.max_q : sh.max_p)[i] = M;
+          double v[VR_BARE / 64];
+#pragma unroll
+          for (int k = 0; k < VR_BARE / 64; ++k) {
+            v[k] = -1.0;
+            if (64 * k < V && z[k] > -INFINITY) v[k] = exp_nonpos((double)z[k] - M, sh.exp_tab);
+          }
           for (int r = 0; r < K; ++r) {
-            float best = -INFINITY;
-            int at = INT_MAX;
+            double wv = -1.0;
+            int wx = INT_MAX;
 #pragma unroll
             for (int k = 0; k < VR_BARE / 64; ++k)
-              if (z[k] > best) { best = z[k]; at = lane + 64 * k; }
-            float wz = best;
-            int wx = at;
+              if (v[k] > wv) { wv = v[k]; wx = lane + 64 * k; }
 #pragma unroll
             for (int off = 32; off >= 1; off >>= 1) {
-              const float oz = __shfl_xor(wz, off);
+              const double ov = __shfl_xor(wv, off);
               const int ox = __shfl_xor(wx, off);
-              if ((oz > wz) | ((oz == wz) & (ox < wx))) { wz = oz; wx = ox; }
+              if ((ov > wv) | ((ov == wv) & (ox < wx))) { wv = ov; wx = ox; }
             }
 #pragma unroll
             for (int k = 0; k < VR_BARE / 64; ++k)
-              if (lane + 64 * k == wx) z[k] = -INFINITY;
-            if (lane == 0) {
-              ci[m * stride + i * K + r] = wx;
-              kept[m * stride + i * K + r] = __float_as_int(wz);
-              if (r == 0) (m ? sh.max_q : sh.max_p)[i] = (double)wz;
-            }
+              if (lane + 64 * k == wx) { v[k] = -1.0; kept[m * stride + i * K + r] = __float_as_int(z[k]); }
+            if (lane == 0) ci[m * stride + i * K + r] = wx;
           }
         }
       }

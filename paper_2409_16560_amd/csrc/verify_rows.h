@@ -9,7 +9,8 @@
 #define VR_BARE 1024           // rows of up to so many logits can do with records of a sum alone
 
 // A row's record: `sum` (of exp(z - max)), `max`, the number of entries (VR_ROW_BAD added where the row holds NaN or +Inf),
-// then the entries (logit, token) by descending logit, equal ones by ascending token; masked tokens (-Inf) are no entries.
+// then the entries (logit, token) by descending exp(logit - max) in fp64, equal ones by ascending token (logits around zero
+// differ by less than that resolves); masked tokens (-Inf) are no entries.
 #define VR_ROW_BAD 256
 struct RowHead { double sum; float max; int n; };
 struct RowEntry { float z; int x; };

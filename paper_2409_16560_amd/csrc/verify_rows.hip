@@ -148,8 +148,9 @@ __global__ __launch_bounds__(VR_BLOCK) void verify_chunk_kernel(RowsArgs a, int 
   if (bad && a.report && lane == 0) atomicOr(a.fault, DSBD_FAULT_NONFINITE);
 }
 
-// Entry (z, x) comes before entry (z2, x2) of the same row.
-__device__ __forceinline__ bool entry_before(float z, int x, float z2, int x2) { return (z > z2) | ((z == z2) & (x < x2)); }
+// The entry of value v and token x comes before the one of value v2 and token x2 of the same row.
+template <class T>
+__device__ __forceinline__ bool entry_before(T v, int x, T v2, int x2) { return (v > v2) | ((v == v2) & (x < x2)); }
 
 template <int RB>
 __global__ __launch_bounds__(RB) void verify_row_kernel(RowsArgs a) {
@@ -160,8 +161,8 @@ __global__ __launch_bounds__(RB) void verify_row_kernel(RowsArgs a) {
   __shared__ float cz[VR_CAND];
   __shared__ int cx[VR_CAND];
   __shared__ float bound_s;
-  __shared__ int n_list, n_cand;
-  __shared__ float best_z[WAVES];
+  __shared__ int n_list, n_cand, close;
+  __shared__ double best_v[WAVES];
   __shared__ int best_x[WAVES];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int row = blockIdx.x, K = a.K, V = a.V;
@@ -206,7 +207,7 @@ __global__ __launch_bounds__(RB) void verify_row_kernel(RowsArgs a) {
     if (tid % (RB / 64) == 0) part_max[tid / (RB / 64)] = gm;
   }
   if (tid < 64) tab[tid] = c_rows_exp2_tab[tid];
-  if (tid == 0) { bound_s = -INFINITY; n_list = 0; n_cand = 0; }
+  if (tid == 0) { bound_s = -INFINITY; n_list = 0; n_cand = 0; close = 0; }
   __syncthreads();
   const bool child = tid >= 1 && tid < DSBD_MAX_TREE_NODES && node + tid < a.n_nodes && child_par == node && ct >= 0 && ct < V;
   const float zt = child ? z[ct] : 0.f;
@@ -218,6 +219,7 @@ __global__ __launch_bounds__(RB) void verify_row_kernel(RowsArgs a) {
   const double M = wave_max_f64(fmax(ms[0].x, ms[1].x));
   const double S = wave_sum((ms[0].x > -INFINITY ? ms[0].y * dsbd_exp_nonpos(ms[0].x - M, tab) : 0.0) +
                             (ms[1].x > -INFINITY ? ms[1].y * dsbd_exp_nonpos(ms[1].x - M, tab) : 0.0));
+  float top;                                  // the row's maximum
   // the bound: the K-th largest of the maxima of 64 groups of parts (K entries reach it; fewer groups: none), one group per
   // lane, the same in every wave, each of which ranks four of them
   {
@@ -232,13 +234,19 @@ __global__ __launch_bounds__(RB) void verify_row_kernel(RowsArgs a) {
       const int ahead = __popcll(__ballot((gm > v) | ((gm == v) & (lane < i))));
       if (ahead == K - 1 && lane == 0) bound_s = v;
     }
+    top = wave_max_f32(gm);
   }
   __syncthreads();
-  const float bound = bound_s;
+  // (lowered by the distance that logits of equal entries can have, eight times over: the roundings of z - max and of exp)
+  const float bound = bound_s - 1e-15f * (4.f + (top - bound_s));
+  // Different logits can have equal entries only where they differ by no more than the bound was lowered by: both around zero
+  // (neighbours are |z| 2^-24 apart).
+  const float near = 4e-8f * (4.f + fabsf(top));
   auto offer = [&](float v, int x) {                         // an entry at or above the bound is a candidate
     if (v >= bound && v > -INFINITY) {
       const int at = atomicAdd(&n_cand, 1);
       if (at < VR_CAND) { cz[at] = v; cx[at] = x; }
+      if (fabsf(v) <= near) close = 1;
     }
   };
   if (whole) {
@@ -271,8 +279,8 @@ __global__ __launch_bounds__(RB) void verify_row_kernel(RowsArgs a) {
     reinterpret_cast<RowEntry*>(rec + sizeof(RowHead))[r] = e;
   };
   const int nc = n_cand;
-  if (nc <= min(a.direct, VR_CAND)) {
-    for (int t = tid; t < nc; t += RB) {
+  if (nc <= min(a.direct, VR_CAND) && close == 0) {
+    for (int t = tid; t < nc; t += RB) {                     // (the entries' order is that of their logits)
       const float v = cz[t];
       const int x = cx[t];
       int rank = 0;
@@ -281,39 +289,43 @@ __global__ __launch_bounds__(RB) void verify_row_kernel(RowsArgs a) {
       if (rank < K) put(rank, v, x);
     }
   } else {
-    // Entries crowd at the bound (equal logits): rank after rank, every thread offers its first entry behind the last one
+    // Entries crowd at the bound (equal logits), or some may be equal though their logits are not: rank after rank, every thread offers its first entry behind the last one
     // taken, and only the thread whose offer was taken looks for its next.
-    auto next = [&](float z_prev, int x_prev, float& bz, int& bx) {
-      bz = -INFINITY; bx = INT_MAX;
-      for (int i = 0; i < (whole ? 1 : nl); ++i) {
-        const int x_lo = whole ? 0 : list[i] * sub_len, x_hi = whole ? V : min(V, x_lo + sub_len);
-        for (int x = x_lo + tid; x < x_hi; x += RB) {
-          const float v = z[x];
-          if (v > -INFINITY && entry_before(z_prev, x_prev, v, x) && entry_before(v, x, bz, bx)) { bz = v; bx = x; }
+    double bv = -1.0, pv = INFINITY;                             // the thread's offer; the last entry taken
+    float bz = 0.f;
+    int bx = -1, px = -1;
+    for (int r = 0; r < K; ++r) {
+      if (bx == px) {
+        bv = -1.0; bx = INT_MAX;
+        float same = NAN;                                        // (crowds: an exponential for each change of the logit)
+        double v = 0.0;
+        for (int i = 0; i < (whole ? 1 : nl); ++i) {
+          const int x_lo = whole ? 0 : list[i] * sub_len, x_hi = whole ? V : min(V, x_lo + sub_len);
+          for (int x = x_lo + tid; x < x_hi; x += RB) {
+            const float w = z[x];
+            if (!(w >= bound && w > -INFINITY)) continue;
+            if (w != same) { same = w; v = dsbd_exp_nonpos((double)w - M, tab); }
+            if (entry_before(pv, px, v, x) && entry_before(v, x, bv, bx)) { bv = v; bz = w; bx = x; }
+          }
         }
       }
-    };
-    float bz;
-    int bx;
-    next(INFINITY, -1, bz, bx);
-    for (int r = 0; r < K; ++r) {
-      float wz = bz;
+      double wv = bv;
       int wx = bx;
 #pragma unroll
       for (int off = 32; off >= 1; off >>= 1) {
-        const float oz = __shfl_xor(wz, off);
+        const double ov = __shfl_xor(wv, off);
         const int ox = __shfl_xor(wx, off);
-        if (entry_before(oz, ox, wz, wx)) { wz = oz; wx = ox; }
+        if (entry_before(ov, ox, wv, wx)) { wv = ov; wx = ox; }
       }
       __syncthreads();
-      if (lane == 0) { best_z[wave] = wz; best_x[wave] = wx; }
+      if (lane == 0) { best_v[wave] = wv; best_x[wave] = wx; }
       __syncthreads();
 #pragma unroll
       for (int w = 0; w < WAVES; ++w)
-        if (entry_before(best_z[w], best_x[w], wz, wx)) { wz = best_z[w]; wx = best_x[w]; }
+        if (entry_before(best_v[w], best_x[w], wv, wx)) { wv = best_v[w]; wx = best_x[w]; }
       if (wx == INT_MAX) break;                                  // (no more entries; uniform)
-      if (tid == 0) put(r, wz, wx);
-      if (bx == wx) next(wz, wx, bz, bx);
+      if (bx == wx) put(r, bz, wx);
+      pv = wv; px = wx;
     }
   }
   // ---- head and per-node outputs

@@ -72,6 +72,27 @@ def test_rows_with_crowds_of_equal_logits(V, fast, knobs):
     _check(w, 32, 1.0, 0.5)
 
 
+@pytest.mark.parametrize("fast", [1, 0])
+@pytest.mark.parametrize("V", [300, 4097, 40000, 140000])
+def test_different_logits_with_equal_joint_entries(V, fast, knobs):
+    """Logits around zero that differ by less than fp64 resolves in exp(z - max): equal entries, ordered by token.  (Magnitude
+    1e-18 against maxima of 0.5 and 2.)"""
+    import gpu_util as gu
+    knobs.set("DSBD_WARP_FAST", fast)
+    w = make_workload("c2", L=1, V=4, Hq=1, Hkv=1, D=64)
+    rng, N = np.random.default_rng(1), len(w.parent)
+    token = np.array([5, V - 1], dtype=np.int32)[rng.integers(0, 2, N)]
+    zp, zq = (rng.standard_normal((2, N, V)) * 1e-18).astype(np.float32)
+    for z, top in ((zp, 0.5), (zq, 2.0)):
+        z[:, [5, V - 1]] = top
+    w = dataclasses.replace(w, logits_p=zp, logits_q=zq, token=token)
+    for top_k, top_p in ((32, 1.0), (32, 0.95), (20, 1.0)):
+        d = gu.DeviceWorkload(w)
+        res, _ = d.verify_select(t=-1.0, top_k=top_k, top_p=top_p)
+        assert int(res.fault.item()) == 0
+        gu.compare_verify(res, gu.oracle_verify(w, t=-1.0, top_k=top_k, top_p=top_p), w)
+
+
 def test_one_model_in_both_roles():
     import gpu_util as gu
     w = make_workload("c2", L=8, V=3001, Hq=4, Hkv=4, draft_top_k=4)
@@ -96,6 +117,10 @@ def test_compact_records_of_large_batches(V, top_k, n_prompts, nodes, entry_byte
     N, rng = len(base.parent), np.random.default_rng(3)
     zp = rng.standard_normal((N, V), dtype=np.float32) * 3
     zq = zp + rng.standard_normal((N, V), dtype=np.float32) * np.float32(0.5)
+    if V > 4:          # (every third row: all but a few logits so close to zero that their entries are equal)
+        zp[::3, 4:] *= np.float32(1e-19)
+        zq[::3, 4:] *= np.float32(1e-19)
+        zp[::3, :4] = zq[::3, :4] = (0.25, 0.5, 0.375, 0.125)
     par = np.maximum(base.parent, 0)
     kth = min(3, V - 1)
     token = np.argpartition(-zq[par], kth, axis=1)[np.arange(N), rng.integers(0, kth + 1, N)].astype(np.int32)
