@@ -14,6 +14,7 @@
 
 #define CM_BLOCK 256
 #define CM_TOKENS 16           // tokens per workgroup (8: 43.7 us, 24: 45.7, 32: 49.1 on the plan above)
+#define CM_CHUNKS (1LL << 20)  // most chunks of a launch: beyond, a workgroup takes several (a far bound on the lengths costs little)
 #define CM_LOADS 8             // 16-byte loads in flight per thread (4: 46.8 us; 512 threads with 4: 45.3)
 #define CM_GRID 2048           // workgroups that the device holds at once (grids of twice that: 47.4 us)
 
@@ -78,8 +79,10 @@ __global__ __launch_bounds__(CM_BLOCK) void commit_kv_kernel(CommitArgs a) {
   };
 
   // ---- the sources' tokens
-  const int t0 = chunk * CM_TOKENS;
+  for (long long at = (long long)chunk * CM_TOKENS; at < a.max_len; at += (long long)(gridDim.x >> 1) * CM_TOKENS) {
+  const int t0 = (int)at;
   unsigned long long left = __builtin_amdgcn_ballot_w64(good && t0 < L && dst != src);
+  if (!left) break;
   for (int n = 0; left; ++n) {
     const int q0 = (int)__ffsll((long long)left) - 1;
     const unsigned long long takers = left & __builtin_amdgcn_ballot_w64(b == __builtin_amdgcn_readlane(b, q0));
@@ -103,6 +106,7 @@ __global__ __launch_bounds__(CM_BLOCK) void commit_kv_kernel(CommitArgs a) {
           if (i0 + k * CM_BLOCK < n_piece) __builtin_nontemporal_store(v[k], (cm_gvec*)(to + off[k]));
       }
     }
+  }
   }
 
   // ---- the destinations' path rows, handed out over the workgroups of the prompt
@@ -145,9 +149,9 @@ extern "C" int32_t dsbd_commit_kv(const dsbd_forest* f, const dsbd_kv* src, cons
   a.n_next = next->n_next; a.src_tree = next->src_tree; a.path_len = next->path_len; a.path = next->path;
   a.dst_k = dst->k_ptr; a.dst_v = dst->v_ptr; a.dst_len = dst->len; a.capacity = dst->capacity; a.max_len = src->max_len;
   a.fault = fault;
-  const long long chunks = std::max(1LL, ((long long)src->max_len + CM_TOKENS - 1) / CM_TOKENS);
+  const long long chunks = std::min(std::max(1LL, ((long long)src->max_len + CM_TOKENS - 1) / CM_TOKENS), CM_CHUNKS);
   const long long slots = (long long)f->n_prompts * W_cap;
-  if (chunks > 0x3fffffffLL || slots > 65535) return DSBD_ERR_UNSUPPORTED;
+  if (slots > 65535) return DSBD_ERR_UNSUPPORTED;
   // a prompt's sources side by side where its chunks leave compute units idle
   a.shares = (int)std::max(1LL, std::min((long long)W_cap, CM_GRID / (chunks * 2 * f->n_prompts)));
   hipStream_t stream = static_cast<hipStream_t>(stream_);

@@ -78,3 +78,24 @@ def test_commit_plans_with_shared_sources(P, trees, W_cap, L, Hkv, D, head_major
             t = pool[plane][j]
             rest = t[:, int(rlen.reshape(-1)[j]):] if head_major else t[int(rlen.reshape(-1)[j]):]
             assert bool((rest == -1.0).all())
+
+
+def test_commit_with_a_far_bound_on_the_lengths():
+    """A caller's bound on the cache lengths may be far above them: as many chunks as one dimension of a launch holds."""
+    import paper_2409_16560_amd as dsbd
+    gen = torch.Generator().manual_seed(3)
+    src = [torch.randn((20, 1, 8), generator=gen).to(torch.bfloat16).cuda() for _ in range(2)]
+    tree = [torch.randn((1, 1, 8), generator=gen).to(torch.bfloat16).cuda() for _ in range(2)]
+    i32 = lambda *a: torch.tensor(a, dtype=torch.int32, device="cuda")      # noqa: E731
+    forest = dsbd.Forest(np.zeros(1, np.int32), np.array([0, 1], np.int32), np.array([-1], np.int32), None, n_prompts=1,
+                         max_tree_nodes=1, max_depth=0, max_prompt_trees=1, device="cuda")
+    kv = dsbd.PrefixKV([src[0][:19]], [src[1][:19]])
+    kv.max_len = (1 << 27) + 1
+    plan = dsbd.NextBeams.allocate(forest, 1)
+    plan.n_next, plan.src_tree, plan.path_len, plan.path = i32(1), i32([0]), i32([1]), i32([[0]])
+    dst = [torch.full((20, 1, 8), -1.0, dtype=torch.bfloat16, device="cuda") for _ in range(2)]
+    n, fault = dsbd.dsbd_commit_kv(forest, kv, tree[0], tree[1], plan, 1, dsbd.KVDst([dst[0]], [dst[1]], kv))
+    torch.cuda.synchronize()
+    assert int(fault.item()) == 0 and int(n.item()) == 20
+    for plane in range(2):
+        assert torch.equal(dst[plane][:19], src[plane][:19]) and torch.equal(dst[plane][19], tree[plane][0])
