@@ -6,20 +6,29 @@
 // dsbd_select_beams).  A pure copy, bound by HBM bandwidth.  A destination that IS its source buffer (the beam continues
 // in place) only gets the tree rows appended.
 //
-// A workgroup takes 16 tokens of K or of V of one prompt and works through the prompt's sources: 16-byte pieces, eight
+// A workgroup takes up to 16 tokens of K or of V of one prompt and works through the prompt's sources: 16-byte pieces, eight
 // loads in flight per thread, and every piece goes to all the destinations that continue this source, so a source is read
-// once however many next beams share it.
+// once however many next beams share it.  The path rows are handed out over the prompt's workgroups in units of four tokens,
+// to those first that are left over by the sources.
+//
+// Measured, a call in us: 8 beams of 8192 tokens x 8 heads x 128, their caches copied along a plan (33.7 MB read, 235 MB
+// written) 42.0; 7 prompts of 8 beams, 40 heads, prefixes of 40 tokens 12.2 (27.7 with 16 tokens per workgroup whatever their
+// length: too few workgroups); eight chains of 64 nodes x 40 heads behind prefixes of 32 tokens 9.7 (57.6 with all of a
+// destination's path rows in one workgroup).
 #include "common.h"
 #include <algorithm>
 
 #define CM_BLOCK 256
-#define CM_TOKENS 16           // tokens per workgroup (8: 43.7 us, 24: 45.7, 32: 49.1 on the plan above)
+#define CM_TOKENS 16           // most tokens per workgroup (8: 43.7 us, 24: 45.7, 32: 49.1 on the first plan above, at 43.0 for 16); fewer
+                               // where a round of loads takes fewer (more than 8 heads of 128)
 #define CM_CHUNKS (1LL << 20)  // most chunks of a launch: beyond, a workgroup takes several (a far bound on the lengths costs little)
-#define CM_LOADS 8             // 16-byte loads in flight per thread (4: 46.8 us; 512 threads with 4: 45.3)
-#define CM_GRID 2048           // workgroups that the device holds at once (grids of twice that: 47.4 us)
+#define CM_PATH_TOKENS 4       // path rows per unit (8 with eight loads in flight: 13.6 us on the last plan above)
+#define CM_LOADS 8             // 16-byte loads in flight per thread (4: 46.8 us; 512 threads with 4: 45.3, at 43.0 for 8)
+#define CM_GRID 2048           // workgroups that the device holds at once (grids of twice that: 47.4 us, at 43.0)
 
 struct CommitArgs {
   int n_prompts, n_trees, n_nodes, W_cap, plen, Hkv, D, shares;
+  int tokens;                  // per chunk
   const void* const* src_k; const void* const* src_v; const int32_t* src_len;
   long long token_stride, head_stride;      // elements; the same layout for sources and destinations
   const __bf16 *k_tree, *v_tree;            // [n_nodes, Hkv, D]
@@ -78,52 +87,69 @@ __global__ __launch_bounds__(CM_BLOCK) void commit_kv_kernel(CommitArgs a) {
     return ((long long)t * a.token_stride + (long long)(r / CG) * a.head_stride + r % CG * 8) * 2;
   };
 
-  // ---- the sources' tokens
-  for (long long at = (long long)chunk * CM_TOKENS; at < a.max_len; at += (long long)(gridDim.x >> 1) * CM_TOKENS) {
-  const int t0 = (int)at;
-  unsigned long long left = __builtin_amdgcn_ballot_w64(good && t0 < L && dst != src);
-  if (!left) break;
-  for (int n = 0; left; ++n) {
-    const int q0 = (int)__ffsll((long long)left) - 1;
-    const unsigned long long takers = left & __builtin_amdgcn_ballot_w64(b == __builtin_amdgcn_readlane(b, q0));
-    left &= ~takers;
-    if (n % a.shares != share) continue;
-    const char* const from = reinterpret_cast<const char*>(cm_lane(src, q0));
-    const int n_piece = (min(__builtin_amdgcn_readlane(L, q0), t0 + CM_TOKENS) - t0) * per_tok;
-    for (int i0 = tid; i0 < n_piece; i0 += CM_LOADS * CM_BLOCK) {
-      cm_u32x4 v[CM_LOADS];
-      long long off[CM_LOADS];
+  // ---- the destinations' path rows, CM_PATH_TOKENS at a time, over the workgroups of the prompt: the last shares first, which
+  // have no source where there are fewer sources than shares
+  const __bf16* const rows = is_v ? a.v_tree : a.k_tree;
+  const unsigned long long with_path = __builtin_amdgcn_ballot_w64(good && pl > 0);
+  const int parts = (a.plen + CM_PATH_TOKENS - 1) / CM_PATH_TOKENS, n_unit = nn * parts;
+  for (long long at = (long long)(a.shares - 1 - share) * (gridDim.x >> 1) + chunk; at < n_unit; at += (long long)(gridDim.x >> 1) * a.shares) {
+    const int unit = (int)at;
+    const int q = unit / parts, k0 = (unit - q * parts) * CM_PATH_TOKENS;
+    if (!((with_path >> q) & 1)) continue;
+    const int qL = __builtin_amdgcn_readlane(L, q), n_piece = (min(__builtin_amdgcn_readlane(pl, q), k0 + CM_PATH_TOKENS) - k0) * per_tok;
+    char* const to = reinterpret_cast<char*>(cm_lane(dst, q));
+    const int32_t* const path = a.path + (long long)(j0 + q) * a.plen + k0;
+    for (int i0 = tid; i0 < n_piece; i0 += 2 * CM_BLOCK) {
+      cm_u32x4 v[2];
+      long long off[2];
+      bool have[2];
 #pragma unroll
-      for (int k = 0; k < CM_LOADS; ++k) {
-        const int i = min(i0 + k * CM_BLOCK, n_piece - 1);
-        off[k] = place(t0 + i / per_tok, i % per_tok);
-        v[k] = __builtin_nontemporal_load((const cm_gvec*)(from + off[k]));
+      for (int l = 0; l < 2; ++l) {
+        const int i = i0 + l * CM_BLOCK, k = i / per_tok, r = i % per_tok;
+        have[l] = false;
+        if (i >= n_piece) continue;
+        const int node = path[k];
+        if (node < 0 || node >= a.n_nodes) { atomicOr(a.fault, DSBD_FAULT_TOPOLOGY); continue; }
+        v[l] = *(const cm_gvec*)(rows + ((long long)node * per_tok + r) * 8);
+        off[l] = place(qL + k0 + k, r);
+        have[l] = true;
       }
-      for (unsigned long long m = takers; m; m &= m - 1) {
-        char* const to = reinterpret_cast<char*>(cm_lane(dst, (int)__ffsll((long long)m) - 1));
 #pragma unroll
-        for (int k = 0; k < CM_LOADS; ++k)
-          if (i0 + k * CM_BLOCK < n_piece) __builtin_nontemporal_store(v[k], (cm_gvec*)(to + off[k]));
-      }
+      for (int l = 0; l < 2; ++l)
+        if (have[l]) __builtin_nontemporal_store(v[l], (cm_gvec*)(to + off[l]));
     }
   }
+  // ---- the sources' tokens
+  for (long long at = (long long)chunk * a.tokens; at < a.max_len; at += (long long)(gridDim.x >> 1) * a.tokens) {
+    const int t0 = (int)at;
+    unsigned long long left = __builtin_amdgcn_ballot_w64(good && t0 < L && dst != src);
+    if (!left) break;
+    for (int n = 0; left; ++n) {
+      const int q0 = (int)__ffsll((long long)left) - 1;
+      const unsigned long long takers = left & __builtin_amdgcn_ballot_w64(b == __builtin_amdgcn_readlane(b, q0));
+      left &= ~takers;
+      if (n % a.shares != share) continue;
+      const char* const from = reinterpret_cast<const char*>(cm_lane(src, q0));
+      const int n_piece = (min(__builtin_amdgcn_readlane(L, q0), t0 + a.tokens) - t0) * per_tok;
+      for (int i0 = tid; i0 < n_piece; i0 += CM_LOADS * CM_BLOCK) {
+        cm_u32x4 v[CM_LOADS];
+        long long off[CM_LOADS];
+#pragma unroll
+        for (int k = 0; k < CM_LOADS; ++k) {
+          const int i = min(i0 + k * CM_BLOCK, n_piece - 1);
+          off[k] = place(t0 + i / per_tok, i % per_tok);
+          v[k] = __builtin_nontemporal_load((const cm_gvec*)(from + off[k]));
+        }
+        for (unsigned long long m = takers; m; m &= m - 1) {
+          char* const to = reinterpret_cast<char*>(cm_lane(dst, (int)__ffsll((long long)m) - 1));
+#pragma unroll
+          for (int k = 0; k < CM_LOADS; ++k)
+            if (i0 + k * CM_BLOCK < n_piece) __builtin_nontemporal_store(v[k], (cm_gvec*)(to + off[k]));
+        }
+      }
+    }
   }
 
-  // ---- the destinations' path rows, handed out over the workgroups of the prompt
-  const __bf16* const rows = is_v ? a.v_tree : a.k_tree;
-  const unsigned long long mine = __builtin_amdgcn_ballot_w64(good && pl > 0 && (unsigned)lane % ((gridDim.x >> 1) * gridDim.y) == chunk * gridDim.y + share);
-  for (unsigned long long m = mine; m; m &= m - 1) {
-    const int q = (int)__ffsll((long long)m) - 1;
-    const int qL = __builtin_amdgcn_readlane(L, q), n_piece = __builtin_amdgcn_readlane(pl, q) * per_tok;
-    char* const to = reinterpret_cast<char*>(cm_lane(dst, q));
-    for (int i = tid; i < n_piece; i += CM_BLOCK) {
-      const int k = i / per_tok, r = i % per_tok;
-      const int node = a.path[(long long)(j0 + q) * a.plen + k];
-      if (node < 0 || node >= a.n_nodes) { atomicOr(a.fault, DSBD_FAULT_TOPOLOGY); continue; }
-      const cm_u32x4 v = *(const cm_gvec*)(rows + ((long long)node * per_tok + r) * 8);
-      __builtin_nontemporal_store(v, (cm_gvec*)(to + place(qL + k, r)));
-    }
-  }
 }
 
 extern "C" int32_t dsbd_commit_kv(const dsbd_forest* f, const dsbd_kv* src, const void* k_tree, const void* v_tree,
@@ -149,11 +175,13 @@ extern "C" int32_t dsbd_commit_kv(const dsbd_forest* f, const dsbd_kv* src, cons
   a.n_next = next->n_next; a.src_tree = next->src_tree; a.path_len = next->path_len; a.path = next->path;
   a.dst_k = dst->k_ptr; a.dst_v = dst->v_ptr; a.dst_len = dst->len; a.capacity = dst->capacity; a.max_len = src->max_len;
   a.fault = fault;
-  const long long chunks = std::min(std::max(1LL, ((long long)src->max_len + CM_TOKENS - 1) / CM_TOKENS), CM_CHUNKS);
   const long long slots = (long long)f->n_prompts * W_cap;
   if (slots > 65535) return DSBD_ERR_UNSUPPORTED;
-  // a prompt's sources side by side where its chunks leave compute units idle
-  a.shares = (int)std::max(1LL, std::min((long long)W_cap, CM_GRID / (chunks * 2 * f->n_prompts)));
+  a.tokens = (int)std::max(1LL, std::min((long long)CM_TOKENS, CM_LOADS * CM_BLOCK / ((long long)Hkv * (D / 8))));
+  const long long chunks = std::min(std::max(1LL, ((long long)src->max_len + a.tokens - 1) / a.tokens), CM_CHUNKS);
+  // a prompt's sources, and the units of its path rows, side by side where its chunks leave compute units idle
+  const long long units = (long long)W_cap * ((a.plen + CM_PATH_TOKENS - 1) / CM_PATH_TOKENS);
+  a.shares = (int)std::max(1LL, std::min(std::max((long long)W_cap, (units + chunks - 1) / chunks), CM_GRID / (chunks * 2 * f->n_prompts)));
   hipStream_t stream = static_cast<hipStream_t>(stream_);
   dsbd_launch(DSBD_KERNEL_KV_COMMIT, commit_kv_kernel, dim3(2 * (unsigned)chunks, (unsigned)a.shares, (unsigned)f->n_prompts), dim3(CM_BLOCK), 0, stream, a);
   DSBD_HIP_LAUNCH_CHECK();

@@ -6,19 +6,22 @@ import torch
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("P,trees,W_cap,L,Hkv,D,head_major", [
-    (1, 1, 64, 33, 1, 8, False),        # one source for every slot; pieces that fill no load round; a chunk of one token
-    (1, 8, 16, 256, 8, 128, False),     # whole chunks
-    (3, 3, 5, 17, 3, 40, True),         # odd piece counts, a token behind a chunk, several prompts
-    (40, 2, 4, 7, 2, 16, False),        # fewer tokens than a chunk
-    (2, 2, 3, 0, 2, 16, False),         # empty caches: path rows alone
-    (1, 2, 4, 40, 40, 128, True),       # more pieces than one round of loads takes
+@pytest.mark.parametrize("P,trees,W_cap,L,Hkv,D,head_major,per", [
+    (1, 1, 64, 33, 1, 8, False, 3),        # one source for every slot; pieces that fill no load round; a chunk of one token
+    (1, 8, 16, 256, 8, 128, False, 3),     # whole chunks
+    (3, 3, 5, 17, 3, 40, True, 3),         # odd piece counts, a token behind a chunk, several prompts
+    (40, 2, 4, 7, 2, 16, False, 3),        # fewer tokens than a chunk
+    (2, 2, 3, 0, 2, 16, False, 3),         # empty caches: path rows alone
+    (1, 2, 4, 40, 40, 128, True, 3),       # more pieces than one round of loads takes
+    (1, 8, 16, 32, 40, 128, False, 64),    # long paths: several units each, fewer and ...
+    (3, 2, 64, 5, 3, 40, True, 61),        # ... more of them than a prompt has workgroups; units cut short
+    (2, 3, 7, 0, 2, 16, False, 9),         # a unit of one token
 ])
-def test_commit_plans_with_shared_sources(P, trees, W_cap, L, Hkv, D, head_major):
+def test_commit_plans_with_shared_sources(P, trees, W_cap, L, Hkv, D, head_major, per):
     import paper_2409_16560_amd as dsbd
     from oracle import commit as o_commit
     rng = np.random.default_rng(P * 1000 + L)
-    T, per, depth = P * trees, 3, 2
+    T, depth = P * trees, per - 1
     N = T * per
     cap = L + depth + 1
     gen = torch.Generator().manual_seed(7)
