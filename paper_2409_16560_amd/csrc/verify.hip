@@ -53,6 +53,7 @@
 #define VL_DYN_LDS_BYTES (84 * 1024)   // dynamic LDS of the layer kernel (its static LDS takes most of the rest) ...
 #define VL_DYN_LDS_BYTES_SMALL (112 * 1024)   // ... and of its variant for prompts of at most NODE_CAP_SMALL nodes
 #define NODE_CAP_SMALL 128
+#define VL_LAUNCH_PROMPTS (1 << 22)    // most prompts of a launch with a workgroup each (2^32 threads are the limit)
 
 // ------------------------------------------------------------------------------------------------ row statistics, fp32
 // 2^x by the hardware instruction alone: results below 2^-126 come out as zero instead of denormal, which a sum
@@ -2583,9 +2584,9 @@ int32_t verify_impl(const dsbd_forest* f, const dsbd_verify_in* in, const dsbd_p
     ra.direct = knobs.warp_fast ? INT_MAX : 0;
     le = launch_verify_rows(ra, stream);
     la.rec = ra.rec; la.rec_stride = rp.rec_stride; la.rec_compact = rp.compact;
-    la.layer_wgs = f->n_prompts; la.prompt0 = 0;
-    if (le == hipSuccess) {
-      const dim3 grid((unsigned)f->n_prompts), block(VL_BLOCK);
+    for (la.prompt0 = 0; le == hipSuccess && la.prompt0 < f->n_prompts; la.prompt0 += la.layer_wgs) {
+      la.layer_wgs = std::min(f->n_prompts - la.prompt0, VL_LAUNCH_PROMPTS);
+      const dim3 grid((unsigned)la.layer_wgs), block(VL_BLOCK);
       if (rp.compact < 0) dsbd_launch(DSBD_KERNEL_VERIFY_LAYERS, verify_layers_kernel<true, NODE_CAP, true>, grid, block, (unsigned int)pl.lds_bytes, stream, la);
       else dsbd_launch(DSBD_KERNEL_VERIFY_LAYERS, verify_layers_kernel<true, NODE_CAP>, grid, block, (unsigned int)pl.lds_bytes, stream, la);
       le = hipGetLastError();

@@ -21,6 +21,7 @@
 #include "wave_f64.h"
 #include <float.h>
 #include <limits.h>
+#include <algorithm>
 
 #define VR_BLOCK 256           // chunk kernel
 #define VR_ROW_BLOCK 1024      // row kernel, few rows: short chains of round trips ...
@@ -29,6 +30,7 @@
                                // at 1024 / 256 threads per row: 106 rows x 128256 47.3 / 49.3, 240 x 32000 top_k 32 65.5 / 73.3, 496 x
                                // 32000 73.5 / 74.3, 1154 x 32000 105 / 98, 5642 x 1000 119 / 86, 72000 x 300 788 / 367)
 #define VR_PARTS 256            // most parts of a row
+#define VR_LAUNCH_CHUNKS (1 << 23)     // most chunks, and so rows, of a launch (2^32 threads are the limit)
 #define VR_CAND 1024           // candidates that are ranked directly
 
 namespace {
@@ -98,13 +100,14 @@ __device__ __forceinline__ void take_tile(const Tile& t, const double* tab, bool
 // waves as there are chunks: those that wait for their logits and those that work on theirs mix by themselves (four resident
 // waves per SIMD that take chunk after chunk, the next two on their way: 2 us slower on 54 MB).
 template <bool SINGLE, int PARTS>
-__global__ __launch_bounds__(VR_BLOCK) void verify_chunk_kernel(RowsArgs a, int rows) {
+__global__ __launch_bounds__(VR_BLOCK) void verify_chunk_kernel(RowsArgs a, int row0, int rows) {
   __shared__ double tab[64];
   const int lane = threadIdx.x & 63;
-  const long long item = (long long)blockIdx.x * (VR_BLOCK / 64) + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const bool live = item < (long long)rows * a.nchunk;
-  const unsigned int at = live ? (unsigned int)item : 0u;      // (below 2^32: the grid holds four items per workgroup)
-  const int row = (int)(at / (unsigned int)a.nchunk), c = (int)(at % (unsigned int)a.nchunk);
+  const unsigned int mine = blockIdx.x * (VR_BLOCK / 64) + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const bool live = mine < (unsigned int)rows * (unsigned int)a.nchunk;      // (below VR_LAUNCH_CHUNKS)
+  const unsigned int at = live ? mine : 0u;
+  const int row = row0 + (int)(at / (unsigned int)a.nchunk), c = (int)(at % (unsigned int)a.nchunk);
+  const long long item = (long long)row * a.nchunk + c;
   const float* const z = row_logits(a, row);
   const int x_lo = c * a.chunk, x_hi = min(a.V, x_lo + a.chunk);
   const Tile first = load_tile(z, x_lo, x_hi);
@@ -153,7 +156,7 @@ template <class T>
 __device__ __forceinline__ bool entry_before(T v, int x, T v2, int x2) { return (v > v2) | ((v == v2) & (x < x2)); }
 
 template <int RB>
-__global__ __launch_bounds__(RB) void verify_row_kernel(RowsArgs a) {
+__global__ __launch_bounds__(RB) void verify_row_kernel(RowsArgs a, int row0) {
   constexpr int WAVES = RB / 64, PT = VR_WHOLE / RB;      // logits per thread of a row read whole
   __shared__ double tab[64];
   __shared__ __attribute__((aligned(16))) float part_max[VR_PARTS];
@@ -165,7 +168,7 @@ __global__ __launch_bounds__(RB) void verify_row_kernel(RowsArgs a) {
   __shared__ double best_v[WAVES];
   __shared__ int best_x[WAVES];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int row = blockIdx.x, K = a.K, V = a.V;
+  const int row = row0 + blockIdx.x, K = a.K, V = a.V;
   const bool second = !a.alias && (row & 1);
   const int node = a.alias ? row : row >> 1;
   const float* const z = row_logits(a, row);
@@ -359,14 +362,16 @@ __global__ __launch_bounds__(RB) void verify_row_kernel(RowsArgs a) {
 
 hipError_t launch_verify_rows(const RowsArgs& a, hipStream_t stream) {
   const int rows = a.n_nodes * (a.alias ? 1 : 2);
-  const long long items = (long long)rows * a.nchunk;
-  const dim3 grid((unsigned)((items + VR_BLOCK / 64 - 1) / (VR_BLOCK / 64)));
-  if (a.chunk > VR_TILE) hipLaunchKernelGGL((verify_chunk_kernel<false, 2>), grid, dim3(VR_BLOCK), 0, stream, a, rows);
-  else if (a.parts == 0) hipLaunchKernelGGL((verify_chunk_kernel<true, 0>), grid, dim3(VR_BLOCK), 0, stream, a, rows);
-  else if (a.parts == 16) hipLaunchKernelGGL((verify_chunk_kernel<true, 16>), grid, dim3(VR_BLOCK), 0, stream, a, rows);
-  else if (a.parts == 4) hipLaunchKernelGGL((verify_chunk_kernel<true, 4>), grid, dim3(VR_BLOCK), 0, stream, a, rows);
-  else hipLaunchKernelGGL((verify_chunk_kernel<true, 2>), grid, dim3(VR_BLOCK), 0, stream, a, rows);
-  if (rows <= VR_ROWS_MANY) hipLaunchKernelGGL(verify_row_kernel<VR_ROW_BLOCK>, dim3((unsigned)rows), dim3(VR_ROW_BLOCK), 0, stream, a);
-  else hipLaunchKernelGGL(verify_row_kernel<VR_ROW_BLOCK_MANY>, dim3((unsigned)rows), dim3(VR_ROW_BLOCK_MANY), 0, stream, a);
+  for (int row0 = 0, most = std::max(1, VR_LAUNCH_CHUNKS / a.nchunk); row0 < rows; row0 += std::min(most, rows - row0)) {
+    const int n = std::min(most, rows - row0);
+    const dim3 grid(((unsigned)n * (unsigned)a.nchunk + VR_BLOCK / 64 - 1) / (VR_BLOCK / 64));
+    if (a.chunk > VR_TILE) hipLaunchKernelGGL((verify_chunk_kernel<false, 2>), grid, dim3(VR_BLOCK), 0, stream, a, row0, n);
+    else if (a.parts == 0) hipLaunchKernelGGL((verify_chunk_kernel<true, 0>), grid, dim3(VR_BLOCK), 0, stream, a, row0, n);
+    else if (a.parts == 16) hipLaunchKernelGGL((verify_chunk_kernel<true, 16>), grid, dim3(VR_BLOCK), 0, stream, a, row0, n);
+    else if (a.parts == 4) hipLaunchKernelGGL((verify_chunk_kernel<true, 4>), grid, dim3(VR_BLOCK), 0, stream, a, row0, n);
+    else hipLaunchKernelGGL((verify_chunk_kernel<true, 2>), grid, dim3(VR_BLOCK), 0, stream, a, row0, n);
+    if (rows <= VR_ROWS_MANY) hipLaunchKernelGGL(verify_row_kernel<VR_ROW_BLOCK>, dim3((unsigned)n), dim3(VR_ROW_BLOCK), 0, stream, a, row0);
+    else hipLaunchKernelGGL(verify_row_kernel<VR_ROW_BLOCK_MANY>, dim3((unsigned)n), dim3(VR_ROW_BLOCK_MANY), 0, stream, a, row0);
+  }
   return hipGetLastError();
 }

@@ -212,3 +212,40 @@ def test_a_warped_verification_as_a_process_s_first_call():
     ref = gu.oracle_verify(w, t=-1.0, top_k=32, top_p=0.9)
     assert fault == 0 and n_out == ref["n_out"].tolist() and status == ref["node_status"].tolist()
     assert [r[:n] for r, n in zip(token, n_out)] == [r[:n] for r, n in zip(ref["out_token"].tolist(), n_out)]
+
+
+def test_more_rows_than_a_launch_takes():
+    """16.8 million rows (with 256 threads each more than the 2^32 of a launch): the first and the last prompts as if alone."""
+    import torch
+    import paper_2409_16560_amd as dsbd
+    P, W, n, V, W_cap = 16400, 8, 64, 4, 8
+    T, N = P * W, P * W * n
+    assert 2 * N * 256 > 1 << 32
+    gen = torch.Generator(device="cuda").manual_seed(1)
+    rand = lambda *s, dt=torch.float32: torch.rand(*s, generator=gen, device="cuda", dtype=dt)      # noqa: E731
+    token = torch.randint(0, V, (N,), generator=gen, device="cuda", dtype=torch.int32)
+    zp = rand(N, V) * 4
+    arrays = [(zp, W * n), (zp + rand(N, V), W * n), (-rand(T, dt=torch.float64), W), (-rand(T, dt=torch.float64), W), (rand(N), W * n),
+              (rand(P, n + 1), 1), (rand(P, n + 1, W_cap), 1)]
+
+    def call(p0, p1):
+        m = p1 - p0
+        forest = dsbd.Forest(np.repeat(np.arange(m), W).astype(np.int32), (np.arange(m * W + 1) * n).astype(np.int32),
+                             np.where(np.arange(m * W * n) % n == 0, -1, np.arange(m * W * n) - 1).astype(np.int32),
+                             token[p0 * W * n:p1 * W * n].contiguous(), n_prompts=m, max_tree_nodes=n, max_depth=n - 1,
+                             max_prompt_trees=W, device="cuda")
+        res = dsbd.dsbd_verify_forest(forest, *[x[p0 * k:p1 * k].contiguous() for x, k in arrays], W_cap=W_cap, top_k=3, top_p=0.9)
+        torch.cuda.synchronize()
+        assert int(res.fault.item()) == 0
+        return res
+    whole = call(0, P)
+    for p0, p1 in ((0, 3), (P - 3, P)):
+        part = call(p0, p1)
+        for name in ("l_last", "n_out", "layer_width"):
+            assert torch.equal(getattr(whole, name)[p0:p1], getattr(part, name)), name
+        for name in ("node_status", "lse_target", "lse_draft", "node_logp_target", "node_logp_draft"):
+            assert torch.equal(getattr(whole, name)[p0 * W * n:p1 * W * n], getattr(part, name)), name
+        for p in range(p1 - p0):
+            k = int(part.n_out[p])
+            for name in ("out_token", "out_logp_target"):
+                assert torch.equal(getattr(whole, name)[p0 + p, :k], getattr(part, name)[p, :k]), name
