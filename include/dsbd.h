@@ -197,12 +197,13 @@ size_t dsbd_verify_forest_workspace_bytes(const dsbd_forest* forest, int32_t V, 
  *   - Limits: at most 64 input beams, 512 forest nodes and W_cap <= 64 per prompt.  Any number of prompts: when
  *     they need more workgroups than the device holds at once, the layer kernel is launched for one group of
  *     prompts after the other (Algorithm 1 runs per prompt).
- *   - One kernel: its first workgroups walk the layers, those behind them produce the per-node outputs (lse_*,
- *     node_logp_*) from the rows of logits, on the compute units the layers leave free.  If all four per-node outputs are
- *     NULL that part is left out; NaN and +Inf logits are then reported only for the rows of beams that enter a layer,
+ *   - Unwarped, one kernel: its first workgroups walk the layers, those behind them produce the per-node outputs (lse_*,
+ *     node_logp_*) from the rows of logits, on the compute units the layers leave free.  Warped (top_k > 0), three: two
+ *     take the rows of both models, all of them, the third walks the layers from their records.  If all four per-node
+ *     outputs are NULL they are not written; NaN and +Inf logits are then reported only for the rows of beams that enter a layer,
  *     and the two misuses of -Inf (a row of nothing else, a masked drafted token) not at all.
- *   - The layer kernel's workgroups wait for each other, so it needs its share of the device while it runs.
- *     Verifications on DIFFERENT streams are kept apart by the library: the first call that arrives on another
+ *   - The unwarped layer kernel's workgroups wait for each other, so it needs its share of the device while it runs.
+ *     (Warped calls wait for nobody: with a workspace of the caller's they are not ordered.)  Other verifications on DIFFERENT streams are kept apart by the library: the first call that arrives on another
  *     stream than the one before waits for the device to drain (once per device and process), and from then on
  *     every layer kernel is ordered behind the previous one by an event (6 us per call, which callers that stay on
  *     one stream never pay).  A stream under graph capture: the call can be recorded (a one-thread kernel

@@ -12,8 +12,8 @@ SOURCES = ["attention.hip", "verify.hip", "verify_rows.hip", "select.hip", "comm
 # Per-file flags.  attention.hip: scores come out of the matrix units and go through max / exp2 only; without
 # -fno-honor-nans every fmaxf operand is first canonicalised (v_max x, x), which triples the instructions of the
 # row-maximum checks.  (verify.hip must keep NaN semantics: it detects non-finite logits.)
-# verify.hip: the layer kernel is held to 240 registers (an attribute in the source) and its warped build uses them
-# all; hoisting loop-invariant address arithmetic out of its layer loop (machine LICM) made it spill 84-120 bytes per
+# verify.hip: the layer kernel is held to 240 registers (an attribute in the source; 215 plain, 127 warped, 172 where
+# warped records are sums alone); hoisting loop-invariant address arithmetic out of its layer loop (machine LICM) made it spill 84-120 bytes per
 # lane, with reloads in front of stores on the critical path.
 # (-Rpass-analysis: the compiler's per-kernel register report, checked below)
 FILE_FLAGS = {"attention.hip": os.environ.get("DSBD_ATTN_FLAGS", "-fno-honor-nans").split(),

@@ -1093,6 +1093,9 @@ AttnPlan make_plan(const dsbd_forest* f, const dsbd_kv* kv, int Hq, int Hkv, int
   // us with four / eight waves: 128 units of 18 steps 15.7 / 13.4, 256 units of 36 steps 32.3 / 27.5, 160 units of 36 steps 26.0
   // / 21.8, 32 units of 130 steps 20.0 / 18.4, of 9 steps 11.3 / 10.0; 32 units of 36 steps (64 channels) 11.4 / 12.3, 12 units of
   // 49 steps 12.3 / 13.2, 8 units of 64 steps 12.0 / 12.8, 128 units of 130 steps (64 channels) 31.4 / 33.8.
+  // The bounds where a unit is worth splitting: more than 64 units, 8448 = 128 units x 66 steps, just above the 65 at which eight
+  // waves still won (the next point, 128 x 130 = 16640, lost; nothing was measured between); up to 32 units, 4096, just below the
+  // 32 x 130 that won (32 x 36 lost); 33 to 64 units have no point of their own, 2048 lies between these two.
   const long long work = units * most_steps;
   const bool unsplit = most_steps < (units <= 16 ? 12 : 24);
   if (!p.shared && f->n_trees <= 64 && units <= 256 && (p.nrt == 1 || D == 64) &&

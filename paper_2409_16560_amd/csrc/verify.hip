@@ -254,15 +254,12 @@ __device__ __forceinline__ void lds_barrier() {
 // workgroup polls exactly the slots it needs.  The tag changes with every exchange, so a slot is valid
 // only once both words of the current exchange have landed.  A bank of slots is never overwritten while
 // somebody may still read it:
-//  * exchanges that every workgroup posts and then collects at once from all the others (chain entries,
-//    sampling prefixes, warping candidates) alternate between banks 0 and 1: whoever posts exchange n + 2 has
-//    collected n + 1, so everybody had posted n + 1 and was therefore done collecting n;
-//  * the row-sum exchange (collected only from the workgroups that share a row) and the early post of the
-//    chain's second entry (collected later, or never) give no such guarantee, so each layer has a bank of its
-//    own for either of them, written once per launch;
-//  * the three hops of the warping merge (every workgroup -> its group's first -> the prompt's first -> every
-//    workgroup) have a bank each: nobody posts a hop of the next layer before having received the result of
-//    this one, which exists only after every reader of the earlier hops is done.
+//  * the row-sum exchange is collected only from the workgroups that share a row, so each layer has a bank of its own
+//    for it, written once per launch;
+//  * the accumulator words' values at launch have a bank, written once per launch;
+//  * the two sampling prefixes (banks 0 and 1) are the prompt's last exchanges, written once per launch.
+// Chain entries travel in the accumulator words below.  Warped layers are walked by one workgroup per prompt and
+// exchange nothing.
 // Single-value exchanges: workgroup w owns the slot at the start of its own 128-byte line of the bank (slot index
 // w * LINE_SLOTS), so that no two workgroups ever write the same cache line.  Measured with a microbenchmark
 // on this chip, all-to-all among 256 workgroups: 2.3 us with a line per workgroup, 3.1 us with the words packed
@@ -315,7 +312,8 @@ __device__ __forceinline__ bool wave_collect4(Slot* bank, int G, int g, double o
 // which every workgroup knows (the value it read at the end of the word's previous exchange; the values at launch are
 // read by the prompt's first workgroup before anybody adds and handed round with the first layer's row sums).  The
 // difference decodes as (members << 54) + sum as long as the sum stays below 2^54 units and there are fewer than 1024
-// members per word.  Two banks alternate as for the slot exchanges.  Measured among 256 workgroups: 1.8 us against
+// members per word.  Two banks alternate: whoever posts exchange
+// n + 2 has collected n + 1, so everybody had posted n + 1 and was therefore done collecting n.  Measured among 256 workgroups: 1.8 us against
 // 2.45 us for a two-hop slot exchange (a microbenchmark of both on the same box).
 // Posting and collecting are separate, so that an exchange can travel beside other work; every workgroup collects what it
 // posted before it posts again (only then has nobody left the bank before the last to be collected).
@@ -520,7 +518,6 @@ void verify_layers_kernel(LayersArgs a) {
   const int lane = tid & 63, wave = tid >> 6;
   const int V = a.V;
   unsigned int epoch = 0;      // exchanges so far (sets the tag); identical in every workgroup of the prompt
-  unsigned int xchg = 0;       // of those, the ones on the two alternating banks
   Slot* const slots = WARP ? nullptr : prompt_slots(a, prompt);      // (one workgroup walks a prompt's warped layers: no exchanges)
   // (a replayed launch: the replay count, which the kernel in front of this one has just raised, sets the tags apart
   // from those of the graph's earlier replays)
@@ -528,7 +525,6 @@ void verify_layers_kernel(LayersArgs a) {
       a.nonce + (a.replay ? (__hip_atomic_load(a.replay, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) << 40) : 0ull);
   // (selected, not indexed: a run-time index into the kernel's argument block would move the whole block into scratch memory)
   const int slx0 = a.sl.x[0], slx1 = a.sl.x[1];
-  auto bank_x = [&](unsigned int n) { return (n & 1) ? slx1 : slx0; };
   unsigned int wsum_round = 0; // alternates the two wsum buffers
   unsigned int decide_round = 0;
   int trace_n = 0;
@@ -1455,7 +1451,7 @@ void verify_layers_kernel(LayersArgs a) {
     auto slice_sum = [&](double c, int t0, int nt) -> double {
       double s0 = 0.0, s1 = 0.0, s2 = 0.0, s3 = 0.0;
       if (tid < t0) return 0.0;
-      if constexpr (WARP) {       // the whole (warped) joint is the short list every workgroup holds
+      if constexpr (WARP) {       // the whole (warped) joint is the prompt's workgroup's short list
         const int c2 = tid - t0;
         return c2 < sh.nU ? fmax(sh.U_p[c2] - c * sh.U_q[c2], 0.0) : 0.0;
       }
@@ -1626,7 +1622,7 @@ void verify_layers_kernel(LayersArgs a) {
     // second wave exchanges the partial sums.  All threads leave through one barrier; false = a wait gave up.
     auto extend_chain = [&]() -> bool {
       const int k = sh.kmax;
-      if constexpr (WARP) {          // every workgroup holds the whole warped joint: the total is F itself
+      if constexpr (WARP) {          // the workgroup holds the whole warped joint: the total is F itself
         const double c = sh.cc[k] + sh.FF[k];
         const double tot = wg_total(slice_sum(c, 0, VL_BLOCK));
         if (tid == 0) { sh.cc[k + 1] = c; sh.FF[k + 1] = tot; sh.kmax = k + 1; }
@@ -1658,7 +1654,7 @@ void verify_layers_kernel(LayersArgs a) {
     if (dynamic) {
       // alpha_j for j = 1..M (Eq. 3) from the chain; stop early if the residual mass vanishes
       if constexpr (WARP) {
-        // The warped joints are the short list every workgroup holds, an entry per lane: the first wave runs the
+        // The warped joints are the workgroup's short list, an entry per lane: the first wave runs the
         // whole chain by itself (c_{k+1} = c_k + F(c_k), F a sum over its lanes), no barrier per entry.  The same
         // sums as extend_chain forms (there the other waves add zeros).
         if (wave == 0) {
@@ -1898,8 +1894,7 @@ void verify_layers_kernel(LayersArgs a) {
       emit_next(d_base + j, node, x, lp_o, lq_o);
     };
     if constexpr (WARP) {
-      // the weights live on the short list (ascending flat index) that every workgroup holds: one wave scans it, the
-      // first workgroup writes the samples
+      // the weights live on the short list (ascending flat index): one wave scans it and writes the samples
       __syncthreads();           // the rows' log-sum-exps (another wave's work since the fold) are in place
       if (wave == 0 && g == 0) {
         const int nU = sh.nU;
@@ -2045,7 +2040,7 @@ void verify_layers_kernel(LayersArgs a) {
       double v[4];
       if (!known_totals) {
         const unsigned long long tag = exchange_tag(nonce + epoch + 1 + wave);
-        Slot* const bank = slots + bank_x(xchg + wave);
+        Slot* const bank = slots + (wave == 0 ? slx0 : slx1);
         double mine = 0.0;
         for (int w = 0; w < VL_WAVES; ++w) mine += wave == 0 ? sh.scan_w[w] : sh.scan_w2[w];
         if (lane == 0) dense_post(bank, a.G, g, mine, tag);

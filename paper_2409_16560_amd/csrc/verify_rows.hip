@@ -8,14 +8,14 @@
 // joint over I x V on up to 256 workgroups and selected from it by exchanges: 15 us of a layer's 22; now 4 of 11.)
 //
 // Two kernels:
-//  1. verify_chunk_kernel: a wave per chunk of a row, no barrier: maximum, sum, and the maxima of the chunk's halves.
+//  1. verify_chunk_kernel: a wave per chunk of a row, no barrier: maximum, sum, and the maxima of the chunk's parts.
 //     Bound by fp64 exponentials as soon as there are many: both models' rows of 53 nodes x 128256 (54 MB) take 15 us, of 248
 //     nodes (254 MB) 60; without the exponentials 13 and 36 (7.1 TB/s).  Fewer instructions per exponential (rounding by an
 //     addition, the power of two put into the table entry's exponent) changed nothing, a table of 256 entries with a
 //     polynomial of degree 4 took 5 us off 248 nodes and nothing off 53.
 //  2. verify_row_kernel: a workgroup per row folds the chunks, bounds the row's K-th entry by the K-th largest of the
-//     maxima of groups of halves (K entries reach it) and reads again only the halves that reach the bound.  A chain of round
-//     trips: 6 us for 106 rows, 9 for 496 (with 256 threads per row, which take the halves three after the other: 14).
+//     maxima of groups of parts (K entries reach it) and reads again only the parts that reach the bound.  A chain of round
+//     trips: 6 us for 106 rows, 9 for 496 (with 256 threads per row, which take the parts three after the other: 14).
 #include "verify_rows.h"
 #include "exp_nonpos.h"
 #include "wave_f64.h"
